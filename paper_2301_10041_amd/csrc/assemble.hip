@@ -177,6 +177,72 @@ void stencil_tables(int n, double nu, double rdt, StencilTable<double> &t64, Ste
   }
 }
 
+// The values of AfCoef from nu and M = (rho/dt) h^2 / 720; every entry of the stencil table above,
+// summed from the element matrices, has to be the value cell_products takes for it.
+void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f) {
+  const double h = 1.0 / n, k = nu / 24.0, m = rdt * h * h / 720.0;
+  c.cv = 72 * k + 72 * m;
+  c.ce = 96 * k + 128 * m;
+  c.k2 = 2 * k;
+  c.k8 = 8 * k;
+  c.k12 = 12 * k;
+  c.k16 = 16 * k;
+  c.k32 = 32 * k;
+  c.v2p = 8 * k - 4 * m;
+  c.v2n = 4 * k - 4 * m;
+  c.e1p = -32 * k + 32 * m;
+  c.e1n = -16 * k + 32 * m;
+  c.m4 = -4 * m;
+  c.m8 = -8 * m;
+  c.m32 = 32 * m;
+  const double dv = c.cv * c.cv - c.k12 * c.k12, de = c.ce * c.ce - c.k16 * c.k16;
+  c.dvd = c.cv / dv;
+  c.dvo = c.k12 / dv;
+  c.ded = c.ce / de;
+  c.deo = c.k16 / de;
+  const double *p = &c.cv;
+  float *q = &f.cv;
+  static_assert(sizeof(AfCoef<double>) == 18 * sizeof(double) && sizeof(AfCoef<float>) == 18 * sizeof(float),
+                "coefficients only");
+  for (int i = 0; i < 18; ++i) q[i] = (float)p[i];
+  StencilTable<double> t;
+  StencilTable<float> tf;
+  stencil_tables(n, nu, rdt, t, tf);
+  // entry (class, offset): along and across the x component, and the cross coupling
+  struct E { double xx, yy, xy; };
+  auto entry = [&](int cls, int I, int J) -> E {
+    if (I < 0 || (I == 0 && J < 0)) { I = -I; J = -J; }   // opposite neighbours are alike
+    const int key = 10 * I + J;
+    if (key == 0) return cls == 0 ? E{c.cv, c.cv, -c.k12} : E{c.ce, c.ce, -c.k16};
+    if (cls == 0) switch (key) {
+      case 10: return E{-c.k32, -c.k16, c.k8};
+      case 1: return E{-c.k16, -c.k32, c.k8};
+      case 20: return E{c.v2p, c.v2n, -c.k2};
+      case 2: return E{c.v2n, c.v2p, -c.k2};
+      case 11: return E{0, 0, -c.k8};
+      case 22: return E{c.m4, c.m4, c.k2};
+      default: return E{c.m8, c.m8, 0};                   // (1, 2), (2, 1), (1, -1)
+    }
+    if (key == 10) return cls == 1 ? E{-c.k32, -c.k16, c.k8} : E{c.e1p, c.e1n, c.k8};
+    if (key == 1) return cls == 2 ? E{-c.k16, -c.k32, c.k8} : E{c.e1n, c.e1p, c.k8};
+    if (key == 11) return cls == 3 ? E{0, 0, -c.k8} : E{c.m32, c.m32, -c.k8};
+    return E{c.m8, c.m8, 0};
+  };
+  for (int cls = 0; cls < 4; ++cls) {
+    for (int q2 = 0; q2 < t.count[cls]; ++q2) {
+      const E e = entry(cls, t.off[cls][q2][0], t.off[cls][q2][1]);
+      const double *v = t.coef[cls][q2], tol = 1e-13 * c.ce;
+      FSI_REQUIRE(std::abs(v[0] - e.xx) <= tol && std::abs(v[3] - e.yy) <= tol && std::abs(v[1] - e.xy) <= tol &&
+                      std::abs(v[2] - e.xy) <= tol,
+                  FSI_E_STATE, "an entry of A_f differs from its closed form");
+    }
+    const double *d = t.dinv[cls], dd = cls ? c.ded : c.dvd, od = cls ? c.deo : c.dvo;
+    FSI_REQUIRE(std::abs(d[0] - dd) <= 1e-12 * dd && std::abs(d[3] - dd) <= 1e-12 * dd &&
+                    std::abs(d[1] - od) <= 1e-12 * dd && std::abs(d[2] - od) <= 1e-12 * dd,
+                FSI_E_STATE, "an inverse diagonal block of A_f differs from its closed form");
+  }
+}
+
 // Host: B^T rows of the four interior P2 node classes and the B row of an interior P1
 // node, summed over the triangles around the node from the element blocks
 // B_alpha(k, i) = int d_alpha phi_i lam_k.
@@ -1246,6 +1312,7 @@ void build_multigrid(Ctx &c) {
       StencilTable<double> t64;
       StencilTable<float> t32;
       stencil_tables(m, c.nu, c.rho / c.dt, t64, t32);
+      af_coefs(m, c.nu, c.rho / c.dt, U.af64, U.af32);
       U.stab64.alloc(sizeof(t64));
       U.stab32.alloc(sizeof(t32));
       FSI_HIP(hipMemcpyAsync(U.stab64.p, &t64, sizeof(t64), hipMemcpyHostToDevice, s));

@@ -5,6 +5,7 @@
 #include <string>
 #include <vector>
 
+#include "afcell.h"
 #include "common.h"
 
 namespace fsi {
@@ -57,6 +58,8 @@ struct MgLevel {
   DevBuf<double> w64[5];   // x, b, r, d, x2 work vectors
   DevBuf<float> w32[5];
   DevBuf<unsigned char> stab64, stab32;   // StencilTable<double/float> (velocity levels)
+  AfCoef<double> af64{};                  // the level's A_f entries (velocity levels)
+  AfCoef<float> af32{};
   DevBuf<unsigned char> p1tab64, p1tab32; // P1Table<double/float> of L_p (pressure levels)
   DevBuf<unsigned char> q2tab64, q2tab32; // Q2Table<double/float> (velocity levels of the Q2 pair)
 };

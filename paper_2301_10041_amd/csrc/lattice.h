@@ -115,12 +115,7 @@ void p1_launch(int n, const P1Table<T> *tab, LP<const T> x, LP<const T> b, LP<T>
 // d = x = scale D^{-1} b (first Chebyshev step from zero), class-wise diagonal
 template <typename T>
 void p1_first(int n, const P1Table<T> *tab, LP<const T> b, T scale, LP<T> d, LP<T> x, hipStream_t s, int K = 1);
-template <typename T>
-void p2_first(int n, const StencilTable<T> *tab, LP<const T> b, T scale, LP<T> d, LP<T> x, hipStream_t s,
-              int K = 1);
-// y += P xc (fine grid nf; coarse vector on the nf / 2 grid); P2 has two components
-template <typename T>
-void p2_prolong_add(int nf, LP<const T> xc, LP<T> y, hipStream_t s, int K = 1);
+// y += P xc (fine grid nf; coarse vector on the nf / 2 grid)
 template <typename T>
 void p1_prolong_add(int nf, LP<const T> xc, LP<T> y, hipStream_t s, int K = 1);
 // bc = R r (pressure levels; the velocity levels restrict in resid_restrict)
@@ -222,7 +217,6 @@ template <typename T>
 void p1_tail(const PTailArgs<T> &a, hipStream_t s, int K = 1);
 // bc = R (b - A_f x) in one launch (stencil.hip): the residual lives only in LDS
 template <typename T>
-void resid_restrict(int nf, const StencilTable<T> *tab, const P2RestrTable<T> *rtab, LP<const T> x,
-                    LP<const T> b, LP<T> bc, hipStream_t s, int K = 1);
+void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K = 1);
 
 }  // namespace fsi

@@ -1,14 +1,14 @@
 // Matrix-free multigrid pieces on the structured grid: P1 pressure operators, the first
-// Chebyshev step with class-wise diagonal inverses, and P2 / P1 grid transfers.  Each
+// Chebyshev step with class-wise diagonal inverses, and P1 grid transfers.  Each
 // equals the corresponding assembled (CSR) product up to the order of the sums; the CSR
 // path stays available and serves as the reference in the tests.
 //
 // Bytes per node (scalar values of width w per component):
 //   P1 Chebyshev step   x, b, d read; d, y written           5 w
-//   first step          b read; d, x written                 3 w per component
-//   P2 prolongation-add fine y read and written, coarse x    (2 + 1/4) w per component
-//   (the P2 restriction runs with the residual in resid_restrict, stencil.hip; the P2
-//   restriction weights are built here)
+//   first step          b read; d, x written                 3 w
+//   (the P2 transfers run with the residual and the post-smoothing, stencil.hip; the P2
+//   restriction weights of the coarse tail are built here)
+#include <cstdlib>
 #include <cstring>
 
 #include "kernels.h"
@@ -90,150 +90,7 @@ void p1_first(int n, const P1Table<T> *tab, LP<const T> b, T scale, LP<T> d, LP<
   FSI_CHECK_LAUNCH();
 }
 
-// ---------------------------------------------------------------- P2 first Chebyshev step
-template <typename T>
-__global__ void k_p2_first(int n, const StencilTable<T> *__restrict__ tabp, LP<const T> bl, T scale, LP<T> dl,
-                           LP<T> xl) {
-  const T *__restrict__ b = bl.at(blockIdx.y);
-  T *d = dl.at(blockIdx.y), *x = xl.at(blockIdx.y);
-  const int L = 2 * n + 1;
-  const int64_t N = (int64_t)L * L;
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= N) return;
-  const int I = (int)(r % L), J = (int)(r / L);
-  const T b0 = b[r], b1 = b[N + r];
-  T z0, z1;
-  if (I == 0 || J == 0 || I == 2 * n || J == 2 * n) {
-    z0 = scale * b0;                           // identity rows (Dirichlet nodes)
-    z1 = scale * b1;
-  } else {
-    const T *di = tabp->dinv[(I & 1) | ((J & 1) << 1)];
-    z0 = scale * (di[0] * b0 + di[1] * b1);
-    z1 = scale * (di[2] * b0 + di[3] * b1);
-  }
-  d[r] = z0;
-  x[r] = z0;
-  d[N + r] = z1;
-  x[N + r] = z1;
-}
-
-template <typename T>
-void p2_first(int n, const StencilTable<T> *tab, LP<const T> b, T scale, LP<T> d, LP<T> x, hipStream_t s,
-              int K) {
-  const int64_t nodes = (int64_t)(2 * n + 1) * (2 * n + 1);
-  hipLaunchKernelGGL(k_p2_first<T>, dim3(grid_for(nodes, 256), K), dim3(256), 0, s, n, tab, b, scale, d, x);
-  FSI_CHECK_LAUNCH();
-}
-
-// ---------------------------------------------------------------- P2 transfers
-__device__ __forceinline__ bool on_p2_boundary(int I, int J, int n) {
-  return I == 0 || J == 0 || I == 2 * n || J == 2 * n;
-}
-
-// y += P xc: coarse quadratic evaluated at the fine node; Dirichlet nodes (fine rows and
-// coarse columns) take no part.  An interior fine node (I, J) lies in coarse cell
-// (I >> 2, J >> 2) at the local position (I mod 4, J mod 4): one of 16 classes, each a fixed
-// set of at most six coarse nodes and weights (prolong_classes).
-struct ProlongClass {
-  int cnt;
-  int d[6][2];    // coarse lattice offsets from (2 ci, 2 cj)
-  double w[6];    // basis values (exact binary fractions)
-};
-struct ProlongClasses {
-  ProlongClass c[16];   // index 4 (J mod 4) + (I mod 4)
-};
-__host__ __device__ constexpr ProlongClasses prolong_classes() {
-  ProlongClasses t{};
-  const int vx[2][3] = {{0, 2, 2}, {0, 2, 0}};
-  const int vy[2][3] = {{0, 0, 2}, {0, 2, 2}};
-  for (int B = 0; B < 4; ++B)
-    for (int A = 0; A < 4; ++A) {
-      ProlongClass &p = t.c[4 * B + A];
-      const double xi = 0.25 * A, eta = 0.25 * B;
-      const int tr = xi >= eta ? 0 : 1;
-      const double l0 = tr == 0 ? 1.0 - xi : 1.0 - eta, l1 = tr == 0 ? xi - eta : xi,
-                   l2 = tr == 0 ? eta : eta - xi;
-      const double phi[6] = {l0 * (2 * l0 - 1), l1 * (2 * l1 - 1), l2 * (2 * l2 - 1),
-                             4 * l0 * l1,       4 * l1 * l2,       4 * l2 * l0};
-      p.cnt = 0;
-      for (int b = 0; b < 6; ++b) {
-        if (phi[b] == 0.0) continue;
-        int dI = 0, dJ = 0;
-        if (b < 3) {
-          dI = vx[tr][b];
-          dJ = vy[tr][b];
-        } else {
-          const int e = b - 3, f = (e + 1) % 3;
-          dI = (vx[tr][e] + vx[tr][f]) / 2;
-          dJ = (vy[tr][e] + vy[tr][f]) / 2;
-        }
-        p.d[p.cnt][0] = dI;
-        p.d[p.cnt][1] = dJ;
-        p.w[p.cnt] = phi[b];
-        ++p.cnt;
-      }
-    }
-  return t;
-}
-
-// One fine row segment per block, one node per thread (lanes on consecutive nodes: coalesced
-// reads and writes of y).  The row's J mod 4 = B is uniform over the block; the node's
-// I mod 4 varies with the lane, so each of the six (offset, weight) entries is selected from
-// the four compile-time classes of the row (unused entries: weight 0 at the cell's first
-// node).  Coarse Dirichlet nodes read as 0.  Sums in the order of prolong_classes.
-template <typename T, int B>
-__device__ __forceinline__ void prolong_row(int I, int J, int nc, int Lc, int64_t Nc, const T *__restrict__ xc, T &s0,
-                                            T &s1) {
-  constexpr ProlongClasses pcs = prolong_classes();
-  const int A = I & 3, ci = I >> 2, cj = J >> 2;
-  s0 = 0;
-  s1 = 0;
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    auto pick_i = [&](int a) { return q < pcs.c[4 * B + a].cnt ? pcs.c[4 * B + a].d[q][0] : 0; };
-    auto pick_j = [&](int a) { return q < pcs.c[4 * B + a].cnt ? pcs.c[4 * B + a].d[q][1] : 0; };
-    auto pick_w = [&](int a) { return q < pcs.c[4 * B + a].cnt ? pcs.c[4 * B + a].w[q] : 0.0; };
-    const int dI = A == 0 ? pick_i(0) : A == 1 ? pick_i(1) : A == 2 ? pick_i(2) : pick_i(3);
-    const int dJ = A == 0 ? pick_j(0) : A == 1 ? pick_j(1) : A == 2 ? pick_j(2) : pick_j(3);
-    const T w = (T)(A == 0 ? pick_w(0) : A == 1 ? pick_w(1) : A == 2 ? pick_w(2) : pick_w(3));
-    const int Ic = 2 * ci + dI, Jc = 2 * cj + dJ;
-    const bool in = Ic > 0 && Jc > 0 && Ic < 2 * nc && Jc < 2 * nc;
-    const int64_t k = in ? (int64_t)Jc * Lc + Ic : 0;
-    const T v0 = in ? xc[k] : T(0), v1 = in ? xc[Nc + k] : T(0);
-    s0 += w * v0;
-    s1 += w * v1;
-  }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_p2_prolong_add(int nf, LP<const T> xcl, LP<T> yl, int segs) {
-  const T *__restrict__ xc = xcl.at(blockIdx.y);
-  T *y = yl.at(blockIdx.y);
-  const int L = 2 * nf + 1, nc = nf / 2, Lc = 2 * nc + 1;
-  const int64_t Nf = (int64_t)L * L, Nc = (int64_t)Lc * Lc;
-  const int J = blockIdx.x / segs, seg = blockIdx.x % segs;
-  const int I = seg * 256 + (int)threadIdx.x;
-  if (I >= L || I == 0 || J == 0 || I == 2 * nf || J == 2 * nf) return;
-  T s0, s1;
-  switch (J & 3) {
-    case 0: prolong_row<T, 0>(I, J, nc, Lc, Nc, xc, s0, s1); break;
-    case 1: prolong_row<T, 1>(I, J, nc, Lc, Nc, xc, s0, s1); break;
-    case 2: prolong_row<T, 2>(I, J, nc, Lc, Nc, xc, s0, s1); break;
-    default: prolong_row<T, 3>(I, J, nc, Lc, Nc, xc, s0, s1); break;
-  }
-  const int64_t r = (int64_t)J * L + I;
-  y[r] += s0;
-  y[Nf + r] += s1;
-}
-
-template <typename T>
-void p2_prolong_add(int nf, LP<const T> xc, LP<T> y, hipStream_t s, int K) {
-  const int L = 2 * nf + 1;
-  const int segs = (L + 255) / 256;
-  hipLaunchKernelGGL(k_p2_prolong_add<T>, dim3((unsigned)(L * segs), K), dim3(256), 0, s, nf, xc, y, segs);
-  FSI_CHECK_LAUNCH();
-}
-
+// ---------------------------------------------------------------- P2 restriction weights
 // Host: the restriction weights do not depend on the level (nested uniform refinement),
 // so they are read off at interior coarse nodes of a 16 x 16 fine grid.
 void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32) {
@@ -265,17 +122,29 @@ void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32) {
       FSI_REQUIRE(t64.off[cls][k][0] == ro.d[cls][k][0] && t64.off[cls][k][1] == ro.d[cls][k][1], FSI_E_ARG,
                   "restriction offsets differ from the compiled pattern");
   }
-  // the compiled prolongation classes against the interpolation they stand for
-  constexpr ProlongClasses pcs = prolong_classes();
-  for (int c = 0; c < 16; ++c) {
-    const int ci = 3, cj = 3, I = 4 * ci + (c & 3), J = 4 * cj + (c >> 2);
-    int ic[6], jc[6];
-    double w[6];
-    const int m = p2_prolong_weights(I, J, nf, ic, jc, w);
-    FSI_REQUIRE(m == pcs.c[c].cnt, FSI_E_ARG, "prolongation class width differs from the interpolation");
-    for (int q = 0; q < m; ++q)
-      FSI_REQUIRE(ic[q] == 2 * ci + pcs.c[c].d[q][0] && jc[q] == 2 * cj + pcs.c[c].d[q][1] && w[q] == pcs.c[c].w[q],
-                  FSI_E_ARG, "prolongation class differs from the interpolation");
+  // the compiled transfer weights (afcell.h) against the interpolation they stand for
+  for (int B = 0; B < 4; ++B)
+    for (int A = 0; A < 4; ++A) {
+      int ic[6], jc[6];
+      double w[6], v[9] = {};
+      const int m = p2_prolong_weights(4 + A, 4 + B, nf, ic, jc, w);
+      for (int q = 0; q < m; ++q) v[3 * (jc[q] - 2) + ic[q] - 2] = w[q];
+      for (int q = 0; q < 9; ++q)
+        FSI_REQUIRE(v[q] == prolong_weight(A, B, q % 3, q / 3), FSI_E_ARG,
+                    "the compiled prolongation weights differ from the interpolation");
+    }
+  for (int cls = 0; cls < 4; ++cls) {
+    double sum = 0.0;
+    for (int k = 0; k < t64.count[cls]; ++k) {
+      const int *o = t64.off[cls][k];
+      sum += t64.w[cls][k];
+      FSI_REQUIRE(std::abs(o[0]) <= 3 && std::abs(o[1]) <= 3 &&
+                      t64.w[cls][k] == restrict_weight(cls & 1, cls >> 1, o[0], o[1]),
+                  FSI_E_ARG, "the compiled restriction weights differ from the transposed interpolation");
+    }
+    for (int dJ = -3; dJ <= 3; ++dJ)
+      for (int dI = -3; dI <= 3; ++dI) sum -= restrict_weight(cls & 1, cls >> 1, dI, dJ);
+    FSI_REQUIRE(sum == 0.0, FSI_E_ARG, "a compiled restriction weight has no entry in the table");
   }
 }
 
@@ -477,8 +346,6 @@ void p1_multi(const P1MultiArgs<T, TZ> &a, hipStream_t s, int K) {
   template void p1_launch<T, SP_CHEB>(int, const P1Table<T> *, LP<const T>, LP<const T>, LP<T>, LP<T>, T, T,  \
                                       hipStream_t, int);                                                    \
   template void p1_first<T>(int, const P1Table<T> *, LP<const T>, T, LP<T>, LP<T>, hipStream_t, int);        \
-  template void p2_first<T>(int, const StencilTable<T> *, LP<const T>, T, LP<T>, LP<T>, hipStream_t, int);   \
-  template void p2_prolong_add<T>(int, LP<const T>, LP<T>, hipStream_t, int);                               \
   template void p1_prolong_add<T>(int, LP<const T>, LP<T>, hipStream_t, int);                               \
   template void p1_restrict<T>(int, LP<const T>, LP<T>, hipStream_t, int);                                  \
   template void p1_multi<T, T, 2, true, P1_OUT_X>(const P1MultiArgs<T, T> &, hipStream_t, int);              \

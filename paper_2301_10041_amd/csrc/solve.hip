@@ -349,97 +349,23 @@ static T *chebyshev_mf(First first, Step step, double lmin, double lmax, int ste
   return x;
 }
 
-// Chebyshev on A_f (stencil) with right-hand side b and direction buffer d: the first three
-// steps from zero (pre-smoothing) or the first three (else two) from x (post-smoothing) as
-// one temporally blocked launch, further steps one launch each (same recurrence as
-// chebyshev_mf; the profile brackets the post-smoothing launches, the largest single
-// kernel of a step).
-// out (optional, not zero_init): the last launch writes the result there instead of into a
-// ping-pong buffer (returned); used to write a V-cycle's result into the caller's vector.
-// out64 (optional, FP32 arithmetic, three steps from x): the result goes to that FP64 vector
-// and the function returns nullptr.
-// xc (optional, at least three steps from x): the steps start from x + P xc, the coarse
-// correction of lattice n / 2 (lane stride lc) added by the fused launch.
+// The level's A_f entries in the arithmetic of the cycle
+template <typename T> static const AfCoef<T> &afc(const MgLevel &L);
+template <> const AfCoef<double> &afc<double>(const MgLevel &L) { return L.af64; }
+template <> const AfCoef<float> &afc<float>(const MgLevel &L) { return L.af32; }
+
+// The Chebyshev coefficients of chebyshev_mf for three steps: s = 1 / theta, then (c1, c2) of
+// the two later steps
 template <typename T>
-static T *chebyshev_stencil(int n, const StencilTable<T> *tab, double lmin, double lmax, int steps,
-                            const T *b, T *x, T *x2, T *d, bool zero_init, hipStream_t s, Prof *prof,
-                            int K = 1, int64_t ls = 0, T *out = nullptr, double *out64 = nullptr,
-                            const T *xc = nullptr, int64_t lc = 0, LP<double> dot = LP<double>(),
-                            LP<const double> b64 = LP<const double>()) {
-  FSI_REQUIRE(!xc || (!zero_init && steps >= 3), FSI_E_STATE, "the coarse correction rides on the fused steps");
-  FSI_REQUIRE(!dot.p || (!zero_init && steps == 3), FSI_E_STATE, "the tile sums ride on the last fused launch");
-  const LP<const T> lxc(xc, lc);
-  const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
-  const double sigma = theta / delta;
-  double rho = 1.0 / sigma;
-  auto next = [&](T &c1, T &c2) {
-    const double rho1 = 1.0 / (2.0 * sigma - rho);
-    c1 = (T)(rho1 * rho);
-    c2 = (T)(2.0 * rho1 / delta);
-    rho = rho1;
-  };
-  const LP<const T> lb(b, ls);
-  const LP<T> ld(d, ls);
-  // the fused launches store their last direction only for the single steps that follow
-  const LP<T> ld3 = steps > 3 ? ld : LP<T>();
-  int done = 0;
-  if (zero_init && steps >= 3) {
-    T c1a, c2a, c1b, c2b;
-    next(c1a, c2a);
-    next(c1b, c2b);
-    cheb2_pre<T>(n, tab, lb, ld3, LP<T>(x, ls), (T)(1.0 / theta), c1a, c2a, c1b, c2b, s, K);
-    done = 3;
-  } else if (!zero_init && steps == 3 && out64) {
-    T c1b, c2b, c1c, c2c;
-    next(c1b, c2b);
-    next(c1c, c2c);
-    if (prof) prof->begin(s);
-    cheb3_post<T, double>(n, tab, LP<const T>(x, ls), lb, LP<T>(), LP<double>(out64, ls), (T)(1.0 / theta), c1b, c2b,
-                          c1c, c2c, s, K, lxc, dot, b64);
-    if (prof) prof->end(s);
-    return nullptr;
-  } else if (!zero_init && steps >= 3) {
-    T c1b, c2b, c1c, c2c;
-    next(c1b, c2b);
-    next(c1c, c2c);
-    T *dst = (out && steps == 3) ? out : x2;
-    if (prof) prof->begin(s);
-    cheb3_post<T>(n, tab, LP<const T>(x, ls), lb, ld3, LP<T>(dst, ls), (T)(1.0 / theta), c1b, c2b, c1c, c2c, s, K,
-                  lxc, dot, b64);
-    if (prof) prof->end(s);
-    x2 = x;
-    x = dst;
-    done = 3;
-  } else if (!zero_init && steps >= 2) {
-    T c1b, c2b;
-    next(c1b, c2b);
-    T *dst = (out && steps == 2) ? out : x2;
-    if (prof) prof->begin(s);
-    cheb2_post<T>(n, tab, LP<const T>(x, ls), lb, steps > 2 ? ld : LP<T>(), LP<T>(dst, ls), (T)(1.0 / theta), c1b,
-                  c2b, s, K);
-    if (prof) prof->end(s);
-    x2 = x;
-    x = dst;
-    done = 2;
-  } else if (zero_init) {
-    p2_first<T>(n, tab, lb, (T)(1.0 / theta), ld, LP<T>(x, ls), s, K);
-    done = 1;
-  } else {
-    T *dst = (out && steps == 1) ? out : x2;
-    stencil_launch<T, SP_CHEB>(n, tab, LP<const T>(x, ls), lb, ld, LP<T>(dst, ls), (T)0, (T)(1.0 / theta), s, K);
-    x2 = x;
-    x = dst;
-    done = 1;
-  }
-  for (int k = done; k < steps; ++k) {
-    T c1, c2;
-    next(c1, c2);
-    T *dst = (out && k == steps - 1) ? out : x2;
-    stencil_launch<T, SP_CHEB>(n, tab, LP<const T>(x, ls), lb, ld, LP<T>(dst, ls), c1, c2, s, K);
-    x2 = x;
-    x = dst;
-  }
-  return x;
+struct Cheb3Coef {
+  T s, c1a, c2a, c1b, c2b;
+};
+template <typename T>
+static Cheb3Coef<T> cheb3_coefs(double lmin, double lmax) {
+  const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin), sigma = theta / delta;
+  const double rho = 1.0 / sigma, rho1 = 1.0 / (2.0 * sigma - rho), rho2 = 1.0 / (2.0 * sigma - rho1);
+  return Cheb3Coef<T>{(T)(1.0 / theta), (T)(rho1 * rho), (T)(2.0 * rho1 / delta), (T)(rho2 * rho1),
+                      (T)(2.0 * rho2 / delta)};
 }
 
 template <typename T>
@@ -530,7 +456,7 @@ static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, T
     t.off = off;
     off += 4 * tail_plane_entries(L.n);
     t.tab = stab<T>(L);
-    // the coefficients of chebyshev_stencil on [lmax / 15, lmax]
+    // the coefficients of cheb3_coefs on [lmax / 15, lmax]
     const double lmax = L.lmax, lmin = L.lmax / 15.0;
     const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin), sigma = theta / delta;
     double rho = 1.0 / sigma;
@@ -620,7 +546,7 @@ static bool p1_tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls
 // pointer); otherwise a level work vector.  out64 (optional, FP32 cycle): an FP64 vector the
 // result goes to when the last smoothing launch can store it there (then nullptr is returned).
 // dot (optional, level 0 of a velocity cycle with tile_dot_ok): the last launch stores the
-// per-tile sums of b . result (cheb3_dot_count(n) per lane), with b64 (FP32 cycle) in place
+// per-tile sums of b . result (post3_dot_count(n) per lane), with b64 (FP32 cycle) in place
 // of b.
 template <typename T, int W, int NC>
 static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr, int K = 1, T *out = nullptr,
@@ -662,36 +588,44 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
     }
   }
   if (mg.stencil) {   // matrix-free smoothing, residual and transfers
-    // velocity levels with three or more post-smoothing steps: the fused launch adds the
-    // coarse correction while it stages x (no separate prolongation pass)
-    const bool fuse = W == 4 && degree >= 3;
-    auto smooth = [&](T *x0, T *x1, bool zero, const T *xcor) -> T * {
-      if constexpr (W == 4)
-        return chebyshev_stencil<T>(L.n, stab<T>(L), lmin, lmax, degree, b, x0, x1, d, zero, s, pl, K, ls,
-                                    zero ? nullptr : out, zero ? nullptr : out64, xcor, lc,
-                                    zero ? LP<double>() : dot, zero ? LP<const double>() : b64);
-      else if (p1_cheb_fused<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, zero ? x0 : x1, zero, s, K, ls))
-        return (void)xcor, zero ? x0 : x1;
-      else
-        return (void)xcor, chebyshev_p1<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, x1, d, zero, s, K, ls);
-    };
-    T *xs = smooth(x, x2, true, nullptr);
-    T *xo = (xs == x) ? x2 : x;
-    if constexpr (W == 4) {   // the fine residual stays in LDS
+    if constexpr (W == 4) {
+      // three launches per level: pre-smoothing; residual with the restriction (the residual stays
+      // in LDS); post-smoothing, which adds the coarse correction while it stages x (the profile
+      // brackets this one, the largest single kernel of a step)
+      FSI_REQUIRE(degree == 3, FSI_E_STATE, "the matrix-free velocity cycle takes three steps");
       (void)r;
-      resid_restrict<T>(L.n, stab<T>(L), rtab<T>(mg), LP<const T>(xs, ls), LP<const T>(b, ls), LP<T>(bc, lc), s, K);
+      (void)d;
+      const AfCoef<T> &cf = afc<T>(L);
+      const Cheb3Coef<T> cc = cheb3_coefs<T>(lmin, lmax);
+      const LP<const T> lb(b, ls), lx(x, ls);
+      pre3<T>(L.n, cf, lb, LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K);
+      resid_restrict<T>(L.n, cf, lx, lb, LP<T>(bc, lc), s, K);
+      T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s, nullptr, K);
+      const LP<const T> lxc(xc, lc);
+      T *y = out ? out : x2;
+      if (pl) pl->begin(s);
+      if (out64)
+        post3<T, double>(L.n, cf, lx, lb, LP<double>(out64, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot,
+                         b64);
+      else
+        post3<T, T>(L.n, cf, lx, lb, LP<T>(y, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot, b64);
+      if (pl) pl->end(s);
+      return out64 ? nullptr : y;
     } else {
+      auto smooth = [&](T *x0, T *x1, bool zero) -> T * {
+        if (p1_cheb_fused<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, zero ? x0 : x1, zero, s, K, ls))
+          return zero ? x0 : x1;
+        return chebyshev_p1<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, x1, d, zero, s, K, ls);
+      };
+      T *xs = smooth(x, x2, true);
+      T *xo = (xs == x) ? x2 : x;
       p1_launch<T, SP_RESID>(L.n, p1tab<T>(L), LP<const T>(xs, ls), LP<const T>(b, ls), LP<T>(), LP<T>(r, ls),
                              (T)0, (T)0, s, K);
       p1_restrict<T>(L.n, LP<const T>(r, ls), LP<T>(bc, lc), s, K);
-    }
-    T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s, nullptr, K);
-    if constexpr (W == 4) {
-      if (!fuse) p2_prolong_add<T>(L.n, LP<const T>(xc, lc), LP<T>(xs, ls), s, K);
-    } else {
+      T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s, nullptr, K);
       p1_prolong_add<T>(L.n, LP<const T>(xc, lc), LP<T>(xs, ls), s, K);
+      return smooth(xs, xo, false);
     }
-    return smooth(xs, xo, false, fuse ? xc : nullptr);
   }
   // the Q2 pair's velocity levels: class stencils for the smoothing steps and the residual
   const Q2Table<T> *q2 = nullptr;
@@ -732,7 +666,7 @@ constexpr int kMpSteps = 3;
 // r64, z64 (FP32 arithmetic, one system): the results are stored straight into the FP64 vector
 // z64 (z unused) and the pressure residual is read from r64 (r holds the velocity part).
 // dot (FP64 form, tile_dot_ok): the launches that write z also store per-tile / per-block
-// parts of r . z: cheb3_dot_count(n) velocity tile sums, then kPresDotBlocks pressure
+// parts of r . z: post3_dot_count(n) velocity tile sums, then kPresDotBlocks pressure
 // block sums, per lane (lane stride dot.s).
 // part: PC_BOTH, or only the velocity cycle (PC_VEL) or only the pressure part (PC_PRES); the
 // other part of z is left as it is.
@@ -798,7 +732,7 @@ static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 =
     // with the pinned entry and the parts of r . z, in one launch
     static_assert(kMpSteps == 3, "the fused mass solve takes three steps");
     const P1Table<T> *mtab = (const P1Table<T> *)(std::is_same<T, double>::value ? c.mptab64.p : c.mptab32.p);
-    double *part = dot.p ? dot.p + cheb3_dot_count(c.n) : nullptr;
+    double *part = dot.p ? dot.p + post3_dot_count(c.n) : nullptr;
     if (z64) {
       P1MultiArgs<T, double> a{};
       a.n = c.n;
@@ -851,14 +785,14 @@ static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 =
   if (z64 && dot.p) {
     hipLaunchKernelGGL((k_pres_out_dot<double, T>), dim3(kPresDotBlocks, 1), dim3(kRedBlock), 0, sp, z64 + 2 * N2,
                        r64 + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, nf, Np,
-                       dot.p + cheb3_dot_count(c.n), dot.s, nullptr);
+                       dot.p + post3_dot_count(c.n), dot.s, nullptr);
   } else if (z64) {
     lincomb_to<double, T>(z64 + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
     hipLaunchKernelGGL((k_set_pinned_to<double, T>), dim3(1), dim3(1), 0, sp, z64 + 2 * N2, r64 + 2 * N2);
   } else if (dot.p) {
     hipLaunchKernelGGL((k_pres_out_dot<T, T>), dim3(kPresDotBlocks, K), dim3(kRedBlock), 0, sp, z + 2 * N2,
                        r + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, nf, Np,
-                       dot.p + cheb3_dot_count(c.n), dot.s, r64 ? r64 + 2 * N2 : nullptr);
+                       dot.p + post3_dot_count(c.n), dot.s, r64 ? r64 + 2 * N2 : nullptr);
   } else {
     lincomb_l(LP<T>(z + 2 * N2, nf), LP<const T>(mres, Np), LP<const T>(xp, Np), (T)c.nu, (T)(c.rho / c.dt), Np,
               sp, K);
@@ -1289,7 +1223,7 @@ static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) 
   else
     hipLaunchKernelGGL(k_ms_axpy, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, 1, nf);
   if (dot_ok) {   // beta^2 = r . z from the launches that write z
-    const int nu = cheb3_dot_count(c.n), np = pres_dot_count(c);
+    const int nu = post3_dot_count(c.n), np = pres_dot_count(c);
     const int64_t ld = nu + pres_dot_slots(c.n);
     const LP<double> dot(c.ms_dot.p, ld);
     if constexpr (f32) {   // the same arithmetic as a11_precond_on64<float>, sums on FP64 r
@@ -1751,7 +1685,7 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
     c.ms_state.alloc(nl * kMsDoubles);
     c.ms_red.alloc(nl * red_blocks(nf));   // dot products of one system per lane: never regrown
     c.ms_part.alloc(nl * stencil_tile_count(c.n));
-    c.ms_dot.alloc(nl * (cheb3_dot_count(c.n) + pres_dot_slots(c.n)));
+    c.ms_dot.alloc(nl * (post3_dot_count(c.n) + pres_dot_slots(c.n)));
   }
   if (!c.pc_in.p) {
     c.pc_in.alloc(nl * nf);

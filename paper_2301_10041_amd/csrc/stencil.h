@@ -1,6 +1,7 @@
 // Coefficient tables of the matrix-free A_f products (see stencil.hip).
 #pragma once
 
+#include "afcell.h"
 #include "common.h"
 
 namespace fsi {
@@ -95,9 +96,6 @@ struct DivTable {
 
 // Launchers run K independent systems (lane = blockIdx.y) over per-lane views (LP); the
 // vector views of one launch share one lane stride.  K = 1: one system.
-template <typename T, int MODE>
-void stencil_launch(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<T> y, T c1,
-                    T c2, hipStream_t s, int K = 1);
 
 // Fluid rows of the operator on [u_x | u_y | p] in one tiled launch:
 //   y_u = A_f x_u - B^T x_p (+ C_f^T x_lam when cft_rp is given; lam_x at xl, lam_y at xl + Ns)
@@ -107,27 +105,21 @@ void stencil_fluid_rows(int n, const StencilTable<T> *tab, const DivTable<T> *dv
                         const int *cft_rp, const int *cft_col, const T *cft_val, const T *xl, int64_t Ns,
                         hipStream_t s);
 
-// Two Chebyshev steps per launch on the A_f stencil (temporal blocking):
-// cheb2_pre : x = d = s D^{-1} b, then two steps (c1a, c2a), (c1b, c2b); writes x, d
-// cheb2_post: from x, a step with c1 = 0 (c2a) and a step (c1b, c2b); writes y, d
-// (all three: a null d skips the store of the last direction when no later step reads it)
+// Chebyshev smoothing of a velocity level, three steps per launch:
+// pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x
+// post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and
+//        the steps (c1b, c2b), (c1c, c2c); writes y (stored as TY: double or T; x is not
+//        written).  With dot, tile t of lane k stores the sum over its nodes of b . y (FP64, y as
+//        stored) at dot.at(k)[t] (post3_dot_count(n) tiles); with b64 the sums take that FP64
+//        right-hand side in place of b (the FP32 cycle of the mixed form).
 template <typename T>
-void cheb2_pre(int n, const StencilTable<T> *tab, LP<const T> b, LP<T> d, LP<T> x, T s, T c1a, T c2a, T c1b,
-               T c2b, hipStream_t st, int K = 1);
-template <typename T>
-void cheb2_post(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<T> y, T c2a, T c1b,
-                T c2b, hipStream_t st, int K = 1);
-// cheb3_post: from x, a step with c1 = 0 (c2a) and steps (c1b, c2b), (c1c, c2c); writes y
-// (stored as TY: double or T) and d.  With xc (coarse lattice n / 2, same lane count) the
-// steps start from x + P xc (the V-cycle's coarse correction; x itself is not written).
-// With dot, tile t of lane k stores the sum over its nodes of b . y (FP64, y as stored) at
-// dot.at(k)[t] (cheb3_dot_count(n) tiles); with b64 the sums take that FP64 right-hand side
-// in place of b (the FP32 cycle of the mixed form).
-template <typename T, typename TY = T>
-void cheb3_post(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<TY> y, T c2a, T c1b,
-                T c2b, T c1c, T c2c, hipStream_t st, int K = 1, LP<const T> xc = LP<const T>(),
-                LP<double> dot = LP<double>(), LP<const double> b64 = LP<const double>());
-int cheb3_dot_count(int n);
+void pre3(int n, const AfCoef<T> &cf, LP<const T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st,
+          int K = 1);
+template <typename T, typename TY>
+void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
+           hipStream_t st, int K, LP<const T> xc, LP<double> dot = LP<double>(),
+           LP<const double> b64 = LP<const double>());
+int post3_dot_count(int n);
 
 // The same launch inside the inner MINRES (FP64): v = s x, y = s (A11 x) + c r1 written over
 // r1, and one partial sum of v . y per tile in part[] (s, c read from device memory;

@@ -12,6 +12,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "afcell.h"
 #include "ctx.h"
 #include "kernels.h"
 #include "lattice.h"
@@ -435,893 +436,570 @@ template void stencil_fluid_rows<float>(int, const StencilTable<float> *, const 
                                         float *, const int *, const int *, const float *, const float *, int64_t,
                                         hipStream_t);
 
-// ---------------------------------------------------------------- two steps per launch
-// Temporal blocking of the Chebyshev smoother: two steps on a tile of kC2R x kC2W nodes.
-// x is staged with a halo of four nodes (X0), the first step is computed on the tile plus
-// a halo of two (X1, and its direction D1 on the tile), the second on the tile.  Dirichlet
-// and out-of-lattice values are stored as 0 in X0 and X1 (zero columns); Dirichlet rows
-// (identity) are stepped pointwise from global memory.  b and d are read where needed
-// (pointwise).  Modes:
-//   C2_PRE : the first step from x = 0 (x = d = s D^{-1} b) and two more: the whole
-//            pre-smoothing of a degree-3 smoother; reads b, writes x and d.
-//   C2_POST: two steps from x with the first direction coefficient c1 = 0 (no d read):
-//            the start of the post-smoothing; reads x and b, writes y and d.
-// Bytes per node: C2_PRE 6 w for three steps, C2_POST 8 w for two (w = value size,
-// two components).
-constexpr int kC2W = 124, kC2R = 8;                 // output tile (kC2W + 4 = 2 x 64 lanes)
-constexpr int kC2W0 = kC2W + 8;                     // width of x with a halo of 4
-constexpr int kC2W1 = kC2W + 4;                     // width of the first step (halo of 2)
-static_assert(kC2W1 == 2 * kWave && kC2W0 == kTW, "lane layout and LDS offsets of the tables");
+// ---------------------------------------------------------------- smoothing, cell by cell
+// The Chebyshev steps of a velocity level and its residual with one thread per cell
+// (cell_products, afcell.h).  A block of 8 waves owns 8 rows of 64 cells: wave w is cell row w of
+// the region, lane l cell column l, in every pass, so a thread's right-hand side, directions and
+// values stay in its registers from one step to the next.  x is staged in LDS as two planes of
+// even and odd lattice columns, [parity][row][column / 2], with both components of a node side
+// by side, so that the lanes of a wave read consecutive 16-byte (FP32: 8-byte) words; each step
+// writes its values over the ones before it between two barriers.  Dirichlet and out-of-lattice
+// nodes are staged as 0 (zero columns); Dirichlet rows are the identity, stepped pointwise from
+// device memory.
+//
+// On coarse levels a launch is bound by the latency of its dependent passes, on fine ones by
+// memory (pre3: 134 MB at 1024^2, 3.6 TB/s of the 4.3 that a copy reaches) and, in post3, by the
+// FP64 issue of the steps it recomputes on the halo.  Against one thread per node with the
+// coefficients loaded through the scalar cache in every pass (kernel times in a step, FP64):
+//   1024^2  pre-smoothing 79.7 -> 37.6 us, residual and restriction 51.2 -> 32.7, post-smoothing
+//           139 -> 118 (beside the pressure part on the other stream)
+//   512^2   28.5 -> 15.2, 18.4 -> 11.5, 41.5 -> 24.4
+//   32^2    8.6 -> 6.2, 7.9 -> 4.8, 12.0 -> 8.1
+constexpr int kCellWaves = 8;
+constexpr int kCellHW = kWave + 2;                    // plane width: a halo of one cell
+constexpr int kCellH = 2 * kCellWaves + 3;            // staged rows of 8 cell rows
+constexpr int kCellPL = kCellH * kCellHW;             // plane stride
+
+// device-memory nodes (2 i, J), (2 i + 1, J) of one component of a vector
+template <typename T>
+__device__ __forceinline__ NodePair<T> ld_pair(const T *v, int64_t r) {
+  return *reinterpret_cast<const NodePair<T> *>(v + r);
+}
+
+// The four nodes of cell (i, j) of a vector (component stride N, lattice side L = 2n + 1) in the
+// order of cell_products; zero outside the lattice
+template <typename T>
+__device__ __forceinline__ void load_cell(const T *v, int64_t N, int L, int n, int i, int j, V2<T> (&q)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) q[k] = V2<T>{T(0), T(0)};
+  if (i < 0 || j < 0 || i > n || j > n) return;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && j == n) continue;
+    const int64_t r = (int64_t)(2 * j + h) * L + 2 * i;
+    if (i < n) {
+      const NodePair<T> a = ld_pair(v, r), b = ld_pair(v, N + r);
+      q[2 * h] = V2<T>{a.a, b.a};
+      q[2 * h + 1] = V2<T>{a.b, b.b};
+    } else {
+      q[2 * h] = V2<T>{v[r], v[N + r]};
+    }
+  }
+}
+
+// v = q at the four nodes of cell (i, j), those in the lattice
+template <typename T, typename TY>
+__device__ __forceinline__ void store_cell(TY *v, int64_t N, int L, int n, int i, int j, const V2<T> (&q)[4]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && j == n) continue;
+    const int64_t r = (int64_t)(2 * j + h) * L + 2 * i;
+    if (i < n) {
+      *reinterpret_cast<NodePair<TY> *>(v + r) = NodePair<TY>{(TY)q[2 * h].x, (TY)q[2 * h + 1].x};
+      *reinterpret_cast<NodePair<TY> *>(v + N + r) = NodePair<TY>{(TY)q[2 * h].y, (TY)q[2 * h + 1].y};
+    } else {
+      v[r] = (TY)q[2 * h].x;
+      v[N + r] = (TY)q[2 * h].y;
+    }
+  }
+}
+
+// the thread's four values at its place in the staged planes (vertex at row r, column h)
+template <typename T, int PL, int HW>
+__device__ __forceinline__ void put_cell(V2<T> *X, int r, int h, const V2<T> (&q)[4]) {
+  V2<T> *p = X + r * HW + h;
+  p[0] = q[0];
+  p[PL] = q[1];
+  p[HW] = q[2];
+  p[PL + HW] = q[3];
+}
+
+// x (a pair of nodes of each staged row, interior nodes only) of the region whose first cell is
+// (i0, j0), with the halo of one cell; f maps a node's value before it is stored (row parity,
+// column parity, value)
+template <typename T, int ROWS, typename F>
+__device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int L, int n, int i0, int j0, F f) {
+  constexpr int NT = kWave * kCellWaves, NE = ROWS * kCellHW, IT = (NE + NT - 1) / NT, PL = ROWS * kCellHW;
+  NodePair<T> a[IT], b[IT];
+#pragma unroll
+  for (int q = 0; q < IT; ++q) {
+    const int e = threadIdx.x + NT * q, lr = e / kCellHW, i = i0 - 1 + e % kCellHW, J = 2 * (j0 - 1) + lr;
+    a[q] = b[q] = NodePair<T>{T(0), T(0)};
+    if (e < NE && i >= 0 && i < n && J > 0 && J < 2 * n) {
+      const int64_t r = (int64_t)J * L + 2 * i;
+      a[q] = ld_pair(v, r);
+      b[q] = ld_pair(v, N + r);
+      if (i == 0) a[q].a = b[q].a = T(0);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < IT; ++q) {
+    const int e = threadIdx.x + NT * q, lr = e / kCellHW;
+    if (e < NE) {
+      X[e] = f(lr & 1, 0, V2<T>{a[q].a, b[q].a});
+      X[PL + e] = f(lr & 1, 1, V2<T>{a[q].b, b[q].b});
+    }
+  }
+}
 
 template <typename T>
-struct Cheb2Args {
+struct PreArgs {
   int n;
-  const StencilTable<T> *tab;
-  const T *x, *b;
-  T *d, *y;
-  int L2;
-  T s;                   // C2_PRE: scale of the first step
-  T c1a, c2a, c1b, c2b;  // the two stencil steps
-  int64_t lv;            // lane stride of x, b, d, y (lane = blockIdx.y)
+  AfCoef<T> cf;
+  const T *b;
+  T *y;
+  T s, c1a, c2a, c1b, c2b;   // the first step's scale, the two stencil steps
+  int64_t lv;                // lane stride of b and y (lane = blockIdx.y)
 };
 
-// The staged tiles are stored as two planes of even and odd lattice columns
-// (X[component][parity][row][column / 2]), so a half-wave pass over nodes of one parity
-// reads consecutive words (no LDS bank conflicts).  Node at plane column h of parity PAR
-// (= CLS & 1), neighbour (dI, dJ): parity (PAR + dI) & 1, plane column h + ((PAR + dI) >> 1).
-template <typename T, int CLS, int ROWS, int HW, int NR>
-__device__ __forceinline__ void split_products(const StencilTable<T> &tb, const T *X, const int (&row)[NR], int h,
-                                               T (&s)[NR][2]) {
-  constexpr int PAR = CLS & 1;
-  constexpr int COMP = 2 * ROWS * HW;   // offset of the second component
-  constexpr StencilOffsets so = stencil_offsets();
-  constexpr CrossZero cz = cross_zero();
-#pragma unroll
-  for (int q = 0; q < NR; ++q) s[q][0] = s[q][1] = 0;
-#pragma unroll
-  for (int k = 0; k < kStencilCount[CLS]; ++k) {
-    const int dI = so.d[CLS][k][0], dJ = so.d[CLS][k][1];
-    const int off = (((PAR + dI) & 1) * ROWS + dJ) * HW + ((PAR + dI) >> 1);
-    const T c0 = tb.coef[CLS][k][0], c1 = tb.coef[CLS][k][1], c2 = tb.coef[CLS][k][2], c3 = tb.coef[CLS][k][3];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {   // FMA chains: two FMAs per coefficient pair
-      const int o = row[q] * HW + h + off;
-      const T y0 = X[o], y1 = X[COMP + o];
-      if (cz.z[CLS][k]) {   // xy = yx = 0 (fma with a zero coefficient adds nothing)
-        s[q][0] = fma(c0, y0, s[q][0]);
-        s[q][1] = fma(c3, y1, s[q][1]);
-      } else {
-        s[q][0] = fma(c1, y1, fma(c0, y0, s[q][0]));
-        s[q][1] = fma(c3, y1, fma(c2, y0, s[q][1]));
-      }
-    }
-  }
-}
-
-// rows of one parity class (the class is uniform over the wave: jodd is wave-uniform)
-template <typename T, int PAR, int ROWS, int HW, int NR>
-__device__ __forceinline__ void class_products(const StencilTable<T> &tb, int jodd, const T *X,
-                                               const int (&row)[NR], int h, T (&s)[NR][2]) {
-  if (jodd) split_products<T, PAR | 2, ROWS, HW, NR>(tb, X, row, h, s);
-  else split_products<T, PAR, ROWS, HW, NR>(tb, X, row, h, s);
-}
-
-enum { C2_PRE = 0, C2_POST = 1 };
-
-// A block of 64 RR threads owns a tile of RR rows.  Wave w owns region-1 row w + 2 (tile
-// row w) and, for w < 4, one halo row (0, 1, RR + 2 or RR + 3) of the same parity; its
-// lanes hold the nodes i = 2 lane + par of those rows (region-1 column i = tile column
-// i - 2), so the tile row's b and first-step direction stay in registers for the second
-// step.  All b loads are issued before x is staged.
-template <typename T, int M, int RR>
-__global__ void __launch_bounds__(64 * RR, 4) k_cheb2(Cheb2Args<T> a0, int tiles_x, int tiles, int band) {
-  constexpr int NT = 64 * RR;                       // threads
-  constexpr int kC2H0 = RR + 8, kC2H1 = RR + 4;     // rows of the staged x and the first step
-  static_assert(RR >= 4 && RR % 2 == 0, "four halo rows go to the first four waves");
-  constexpr int HW0 = kC2W0 / 2, HW1 = kC2W1 / 2;   // plane widths
-  static_assert(kC2H1 * HW1 <= kC2H0 * HW0, "the first-step tile fits in the staged x");
-  __shared__ T X0[2 * 2 * kC2H0 * HW0];             // [component][parity][row][column / 2]
-  T *const X1 = X0;   // the first-step tile replaces x once every wave has read it
+// The pre-smoothing of a degree-3 smoother: x = d = s D^{-1} b, then two steps; reads b, writes x
+// (4 w per node).  The first stencil step runs on 8 x 64 cells, the second on the inner 6 x 62,
+// which are the block's tile.
+constexpr int kPreW = kWave - 2, kPreR = kCellWaves - 2;
+template <typename T>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T> a, int tiles_x, int tiles, int band) {
+  __shared__ V2<T> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
-  Cheb2Args<T> a = a0;
-  lane_shift(a.x, a.lv);
-  lane_shift(a.b, a.lv);
-  lane_shift(a.d, a.lv);
-  lane_shift(a.y, a.lv);
-  const int n2 = 2 * a.n, L = n2 + 1;
-  const int64_t N = a.L2;
-  const int I0 = (t % tiles_x) * kC2W, J0 = (t / tiles_x) * RR;
-  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-  const StencilTable<T> &tb = *a.tab;
-  const bool halo = w < 4;                          // wave-uniform
-  const int rows[2] = {w < 2 ? w : RR + w, w + 2};  // halo row (w < 4), tile row (region-1 rows)
-  auto inside = [&](int I, int J) { return I > 0 && J > 0 && I < n2 && J < n2; };
-  // b at the wave's region-1 nodes (0 outside the lattice)
-  T bv[2][2][2];
+  const T *bg = a.b + (int64_t)blockIdx.y * a.lv;
+  T *yg = a.y + (int64_t)blockIdx.y * a.lv;
+  const int n = a.n, L = 2 * n + 1;
+  const int64_t N = (int64_t)L * L;
+  const int i0 = (t % tiles_x) * kPreW - 1, j0 = (t / tiles_x) * kPreR - 1;   // first cell of the region
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i = i0 + lane, j = j0 + w;
+  const AfCoef<T> &cf = a.cf;
+  V2<T> b[4];
+  load_cell(bg, N, L, n, i, j, b);
+  stage_pairs<T, kCellH>(X, bg, N, L, n, i0, j0, [&](int pj, int pi, V2<T> v) -> V2<T> {
+    const V2<T> z = cell_dinv(cf, pi | pj, v);
+    return V2<T>{a.s * z.x, a.s * z.y};
+  });
+  const CellIn in = cell_inside(i, j, n);
+  const int row = 2 * w + 2, h = lane + 1;
+  const V2<T> *p = X + row * kCellHW + h;
+  V2<T> x[4], s[4], d[4];
+  __syncthreads();
+  cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int J = J0 - 2 + rows[q];
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int I = I0 - 2 + 2 * lane + par;
-      bv[q][par][0] = 0;
-      bv[q][par][1] = 0;
-      if ((q == 1 || halo) && I >= 0 && J >= 0 && I <= n2 && J <= n2) {
-        const int64_t r = (int64_t)J * L + I;
-        bv[q][par][0] = a.b[r];
-        bv[q][par][1] = a.b[N + r];
-      }
-    }
-  }
-  // phase A: x (or, from zero, the first step s D^{-1} b) with a halo of 4; all loads are
-  // issued before the first LDS store
-  constexpr int NE = kC2H0 * kC2W0, IT = (NE + NT - 1) / NT;
-  T v[IT][2];
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / kC2W0, tc = e % kC2W0;
-    const int I = I0 - 4 + tc, J = J0 - 4 + tr;
-    v[q][0] = 0;
-    v[q][1] = 0;
-    if (e < NE && inside(I, J)) {
-      const int64_t r = (int64_t)J * L + I;
-      v[q][0] = M == C2_PRE ? a.b[r] : a.x[r];
-      v[q][1] = M == C2_PRE ? a.b[N + r] : a.x[N + r];
-    }
-  }
-  if constexpr (M == C2_PRE) {
-    // class-wise D^{-1} (scalar loads) picked per node: parity of I = parity of tc, of J = of tr
-    T dv[4][4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) dv[c][k] = tb.dinv[c][k];
-#pragma unroll
-    for (int q = 0; q < IT; ++q) {
-      const int e = tid + NT * q, tr = e / kC2W0, tc = e % kC2W0;
-      const int c = (tc & 1) | ((tr & 1) << 1);
-      T di[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        di[k] = c == 0 ? dv[0][k] : c == 1 ? dv[1][k] : c == 2 ? dv[2][k] : dv[3][k];
-      const T b0 = v[q][0], b1 = v[q][1];
-      v[q][0] = a.s * (di[0] * b0 + di[1] * b1);
-      v[q][1] = a.s * (di[2] * b0 + di[3] * b1);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / kC2W0, tc = e % kC2W0;
-    if (e < NE) {
-      const int o = ((tc & 1) * kC2H0 + tr) * HW0 + (tc >> 1);
-      X0[o] = v[q][0];
-      X0[2 * kC2H0 * HW0 + o] = v[q][1];
-    }
+  for (int q = 0; q < 4; ++q) {   // the direction of the first step is x itself
+    const V2<T> z = cell_dinv(cf, q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+    d[q] = V2<T>{fma(a.c2a, z.x, a.c1a * x[q].x), fma(a.c2a, z.y, a.c1a * x[q].y)};
+    x[q] = in.q[q] ? V2<T>{x[q].x + d[q].x, x[q].y + d[q].y} : V2<T>{T(0), T(0)};
   }
   __syncthreads();
-  // phase B: first stencil step on the tile plus a halo of 2; a wave's rows have the same
-  // parity, so one pass per column parity covers them with one set of coefficients
-  T d1[2][2] = {{0, 0}, {0, 0}};   // tile row
-  T x1v[2][2][2] = {};             // first-step values of the wave's rows
-  const int jodd = __builtin_amdgcn_readfirstlane((J0 - 2 + rows[1]) & 1);
-  auto phase_b = [&](auto q0_tag) {
-    constexpr int Q0 = decltype(q0_tag)::value, NR = 2 - Q0;   // rows Q0..1
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int i = 2 * lane + par, I = I0 - 2 + i;   // I0 is even: I has the parity of i
-      const int cls = par | (jodd << 1);
-      int xr[NR];                                      // X0 rows; X0 column i + 2 = 2 (lane + 1) + par
-#pragma unroll
-      for (int k = 0; k < NR; ++k) xr[k] = rows[Q0 + k] + 2;
-      T sp[NR][2];
-      if (par) class_products<T, 1, kC2H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-      else class_products<T, 0, kC2H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-      const T *di = tb.dinv[cls];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        const int q = Q0 + k, row = rows[q], J = J0 - 2 + row;
-        T &x10 = x1v[q][par][0], &x11 = x1v[q][par][1];
-        x10 = 0;
-        x11 = 0;
-        if (inside(I, J)) {
-          const int c0 = (par * kC2H0 + row + 2) * HW0 + lane + 1;
-          const T x00 = X0[c0], x01 = X0[2 * kC2H0 * HW0 + c0];
-          const T r0 = bv[q][par][0] - sp[k][0], r1 = bv[q][par][1] - sp[k][1];
-          const T z0 = di[0] * r0 + di[1] * r1, z1 = di[2] * r0 + di[3] * r1;
-          T e0, e1;
-          if constexpr (M == C2_PRE) {   // d = x after the first step from zero
-            e0 = a.c1a * x00 + a.c2a * z0;
-            e1 = a.c1a * x01 + a.c2a * z1;
-          } else {
-            e0 = a.c2a * z0;
-            e1 = a.c2a * z1;
-          }
-          x10 = x00 + e0;
-          x11 = x01 + e1;
-          if (q == 1) {
-            d1[par][0] = e0;
-            d1[par][1] = e1;
-          }
-        }
-      }
-    }
-  };
-  if (halo) phase_b(std::integral_constant<int, 0>{});
-  else phase_b(std::integral_constant<int, 1>{});
-  __syncthreads();   // every wave has read x: the first-step tile goes over it
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      if (q == 0 && !halo) continue;
-      const int o1 = (par * kC2H1 + rows[q]) * HW1 + lane;   // column i = 2 lane + par
-      X1[o1] = x1v[q][par][0];
-      X1[2 * kC2H1 * HW1 + o1] = x1v[q][par][1];
-    }
+  put_cell<T, kCellPL, kCellHW>(X, row, h, x);
   __syncthreads();
-  // phase C: second step on the tile row
-  {
-    const int row = rows[1], J = J0 - 2 + row;
-    if (J <= n2) {
+  if (w < 1 || w > kPreR || j > n) return;
+  cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
+  if (lane < 1 || lane > kPreW || i > n) return;
 #pragma unroll
-      for (int par = 0; par < 2; ++par) {
-        const int i = 2 * lane + par, I = I0 - 2 + i;
-        if (i < 2 || i >= 2 + kC2W || I > n2) continue;
-        const int64_t r = (int64_t)J * L + I;
-        const T b0 = bv[1][par][0], b1 = bv[1][par][1];
-        T x20, x21, d20, d21;
-        if (inside(I, J)) {
-          const int cls = par | (jodd << 1);
-          const int xr[1] = {row};
-          T sp[1][2];
-          if (par) class_products<T, 1, kC2H1, HW1, 1>(tb, jodd, X1, xr, lane, sp);
-          else class_products<T, 0, kC2H1, HW1, 1>(tb, jodd, X1, xr, lane, sp);
-          const T s0 = sp[0][0], s1 = sp[0][1];
-          const int c1 = (par * kC2H1 + row) * HW1 + lane;
-          const T r0 = b0 - s0, r1 = b1 - s1;
-          const T *di = tb.dinv[cls];
-          const T z0 = di[0] * r0 + di[1] * r1, z1 = di[2] * r0 + di[3] * r1;
-          d20 = a.c1b * d1[par][0] + a.c2b * z0;
-          d21 = a.c1b * d1[par][1] + a.c2b * z1;
-          x20 = X1[c1] + d20;
-          x21 = X1[2 * kC2H1 * HW1 + c1] + d21;
-        } else {   // Dirichlet row: the identity, stepped pointwise
-          T x00, x01, d00, d01;
-          if constexpr (M == C2_PRE) {
-            x00 = a.s * b0;
-            x01 = a.s * b1;
-            d00 = x00;
-            d01 = x01;
-          } else {
-            x00 = a.x[r];
-            x01 = a.x[N + r];
-            d00 = 0;
-            d01 = 0;
-          }
-          const T e0 = a.c1a * d00 + a.c2a * (b0 - x00), e1 = a.c1a * d01 + a.c2a * (b1 - x01);
-          const T x10 = x00 + e0, x11 = x01 + e1;
-          d20 = a.c1b * e0 + a.c2b * (b0 - x10);
-          d21 = a.c1b * e1 + a.c2b * (b1 - x11);
-          x20 = x10 + d20;
-          x21 = x11 + d21;
-        }
-        if (a.d) {   // null when no later step reads the direction
-          a.d[r] = d20;
-          a.d[N + r] = d21;
-        }
-        a.y[r] = x20;
-        a.y[N + r] = x21;
-      }
+  for (int q = 0; q < 4; ++q) {
+    if (in.q[q]) {
+      const V2<T> z = cell_dinv(cf, q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+      x[q].x += fma(a.c2b, z.x, a.c1b * d[q].x);
+      x[q].y += fma(a.c2b, z.y, a.c1b * d[q].y);
+    } else {   // Dirichlet row: the identity, stepped pointwise
+      auto steps = [&](T bv) -> T {
+        const T x0 = a.s * bv, e = a.c1a * x0 + a.c2a * (bv - x0), x1 = x0 + e;
+        return x1 + (a.c1b * e + a.c2b * (bv - x1));
+      };
+      x[q] = V2<T>{steps(b[q].x), steps(b[q].y)};
     }
   }
+  store_cell<T, T>(yg, N, L, n, i, j, x);
 }
 
-// ---------------------------------------------------------------- three steps per launch
-// The whole post-smoothing of a degree-3 smoother: from x, a step with c1 = 0 (c2a) and two
-// steps (c1b, c2b), (c1c, c2c); reads x and b, writes y and d (8 w per node, as C2_POST).
-// Tile of kC3R rows x kC3W nodes; x staged with a halo of 6 (X0), the first step on the tile
-// plus a halo of 4 (region 1: kC3R + 8 rows x 128 nodes, X1 over X0), the second on the tile
-// plus a halo of 2 (stored in region-1 coordinates, X2 over X1), the third on the tile.
-// Every phase uses the lane layout of region 1 (lane holds columns i = 2 lane + par), so a
-// thread's b and directions stay in registers from one step to the next.  Waves: wave w owns
-// tile row w + 4 of region 1 in every phase and, for w < 8, one halo row: the inner halo rows
-// 2, 3, R + 4, R + 5 (steps 1 and 2) go to waves 0-3, the outer halo rows 0, 1, R + 6, R + 7
-// (step 1 only) to waves 4-7.
-// With a coarse correction xc (the V-cycle's post-smoothing), the smoothing starts from
-// x + P xc: the coarse nodes under the staged region go to LDS first and every staged
-// interior node adds the coarse quadratic evaluated there (Sec. 4 multigrid transfer: the
-// P2 interpolation of the coarse lattice, the same sums as the separate prolongation).
-constexpr int kC3W = 120, kC3R = 8;
-static_assert(kC3W + 8 == 2 * kWave && kC3W + 12 == kC2W0, "region-1 lane layout and staged width");
+// The coarse correction and the whole post-smoothing of a degree-3 smoother: x + P xc staged,
+// then a step with c1 = 0 and two more; reads x, b and xc, writes y (stored as TY: the mixed
+// form writes FP32 results into an FP64 vector), and with DOT the tile's sum of b . y.  The first
+// step runs on 8 x 64 cells, the second on the inner 6 x 62, the third on 4 x 60, the tile.
+// x is staged by coarse cells (4 x 4 fine nodes; one thread takes two of its rows), so that the
+// interpolation weights are compile-time constants and no coarse value goes through LDS.
+constexpr int kPostW = kWave - 4, kPostR = kCellWaves - 4;
+static_assert(kPostW % 2 == 0 && kPostR % 2 == 0, "tile origins on coarse cell corners");
 
 template <typename T, typename TY>
-struct Cheb3Args {   // y stored as TY (the mixed form writes FP32 results into an FP64 vector)
+struct PostArgs {
   int n;
-  const StencilTable<T> *tab;
+  AfCoef<T> cf;
   const T *x, *b;
-  T *d;
   TY *y;
-  int L2;
   T c2a, c1b, c2b, c1c, c2c;
-  int64_t lv;    // lane stride of x, b, d, y (lane = blockIdx.y)
-  const T *xc;   // coarse correction (lattice n / 2, two components) or null
-  int64_t lc;    // its lane stride
-  double *dot;   // per-tile sums of b . y over the tile's nodes (FP64), or null
-  int64_t ldot;  // their lane stride
+  int64_t lv;          // lane stride of x, b, y (lane = blockIdx.y)
+  const T *xc;         // coarse correction (lattice n / 2, two components)
+  int64_t lc;          // its lane stride
+  double *dot;         // per-tile sums of b . y (FP64), or null
+  int64_t ldot;        // their lane stride
   const double *b64;   // with dot: the FP64 right-hand side the sums use instead of b, or null
   int64_t lb64;        // its lane stride
 };
 
-// Coarse P2 interpolation at an interior fine node (I, J) of the cell (I >> 2, J >> 2) at
-// local position (A, B) = (I mod 4, J mod 4): the six P2 basis functions of the cell's
-// triangle (lower right when A >= B, upper left otherwise) at (A / 4, B / 4); basis values
-// are multiples of 1/8, exact in float.  XC holds the coarse nodes of the staged region
-// ([row][column][component], row stride CW, origin (Ic0, Jc0) in coarse coordinates; 0 at
-// Dirichlet nodes).  Sums in the order vertices 0, 1, 2, then edges 01, 12, 20.
-template <typename T, int CW>
-__device__ __forceinline__ void prolong_lds(const T *XC, int I, int J, int Ic0, int Jc0, T &s0, T &s1) {
-  const int A = I & 3, B = J & 3;
-  const int base = (2 * (J >> 2) - Jc0) * CW + 2 * (I >> 2) - Ic0;
-  const bool lo = A >= B;
-  const float xi = 0.25f * (float)A, eta = 0.25f * (float)B;
-  const float l0 = lo ? 1.0f - xi : 1.0f - eta, l1 = lo ? xi - eta : xi, l2 = lo ? eta : eta - xi;
-  const float phi[6] = {l0 * (2.0f * l0 - 1.0f), l1 * (2.0f * l1 - 1.0f), l2 * (2.0f * l2 - 1.0f),
-                        4.0f * l0 * l1,         4.0f * l1 * l2,         4.0f * l2 * l0};
-  const int off[6] = {0,
-                      lo ? 2 : 2 * CW + 2,
-                      lo ? 2 * CW + 2 : 2 * CW,
-                      lo ? 1 : CW + 1,
-                      lo ? CW + 2 : 2 * CW + 1,
-                      CW + (lo ? 1 : 0)};
-  s0 = 0;
-  s1 = 0;
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    const T w = (T)phi[q];
-    const int o = 2 * (base + off[q]);
-    s0 = fma(w, XC[o], s0);
-    s1 = fma(w, XC[o + 1], s1);
-  }
-}
-
-template <typename T, int RR, typename TY, bool PROL, bool DOT>
-__global__ void __launch_bounds__(64 * RR, 4) k_cheb3(Cheb3Args<T, TY> a0, int tiles_x, int tiles, int band) {
-  constexpr int NT = 64 * RR;
-  constexpr int H0 = RR + 12, H1 = RR + 8;           // rows of the staged x and of region 1
-  constexpr int W0 = kC3W + 12, HW0 = W0 / 2, HW1 = kWave;
-  static_assert(RR >= 8 && RR % 2 == 0, "eight halo rows go to the first eight waves");
-  static_assert(2 * H1 * HW1 <= 2 * H0 * HW0, "region 1 fits in the staged x");
-  __shared__ T X0[2 * 2 * H0 * HW0];                 // [component][parity][row][column / 2]
-  T *const X1 = X0;                                  // region-1 layout, rows H1, width 128
+template <typename T, typename TY, bool DOT>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY> a, int tiles_x, int tiles, int band) {
+  __shared__ V2<T> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
-  Cheb3Args<T, TY> a = a0;
-  lane_shift(a.x, a.lv);
-  lane_shift(a.b, a.lv);
-  lane_shift(a.d, a.lv);
-  lane_shift(a.y, a.lv);
-  lane_shift(a.xc, a.lc);
-  lane_shift(a.dot, a.ldot);
-  lane_shift(a.b64, a.lb64);
-  const int n2 = 2 * a.n, L = n2 + 1;
-  const int64_t N = a.L2;
-  const int I0 = (t % tiles_x) * kC3W, J0 = (t / tiles_x) * RR;
-  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-  const StencilTable<T> &tb = *a.tab;
-  const bool inner = w < 4, has_h = w < 8;          // wave-uniform
-  // region-1 rows (origin J0 - 4): tile row, halo row
-  const int rows[2] = {w + 4, inner ? (w < 2 ? 2 + w : RR + 2 + w) : (w < 6 ? w - 4 : RR + w)};
-  auto inside = [&](int I, int J) { return I > 0 && J > 0 && I < n2 && J < n2; };
-  // b at the wave's nodes (0 outside the lattice)
-  T bv[2][2][2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int J = J0 - 4 + rows[q];
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int I = I0 - 4 + 2 * lane + par;
-      bv[q][par][0] = 0;
-      bv[q][par][1] = 0;
-      if ((q == 0 || has_h) && I >= 0 && J >= 0 && I <= n2 && J <= n2) {
-        const int64_t r = (int64_t)J * L + I;
-        bv[q][par][0] = a.b[r];
-        bv[q][par][1] = a.b[N + r];
-      }
-    }
-  }
-  // coarse nodes under the staged region: coarse columns I0 / 2 - 4 .. I0 / 2 + W0 / 2 + 2,
-  // rows J0 / 2 - 4 .. J0 / 2 + RR + 4 (the cells of fine columns I0 - 6 .. I0 + W0 - 7)
-  constexpr int CW = 2 * ((W0 - 7) / 4) + 7, CH = 2 * ((RR + 5) / 4) + 7;
-  static_assert(RR % 4 == 0 && kC3W % 4 == 0, "tile origins on coarse cell corners");
-  __shared__ T XC[PROL ? 2 * CH * CW : 1];
-  const int Ic0 = I0 / 2 - 4, Jc0 = J0 / 2 - 4;
-  constexpr int NC = CH * CW, ITC = PROL ? (NC + NT - 1) / NT : 0;
-  T cv[ITC > 0 ? ITC : 1][2];
-  if constexpr (PROL) {   // loads issued before those of x; stored once they are in flight
-    const int Lc = a.n + 1, nc2 = a.n;   // coarse lattice: 2 (n / 2) + 1 nodes a side
+  const T *xg = a.x + (int64_t)blockIdx.y * a.lv, *bg = a.b + (int64_t)blockIdx.y * a.lv;
+  const T *xcg = a.xc + (int64_t)blockIdx.y * a.lc;
+  TY *yg = a.y + (int64_t)blockIdx.y * a.lv;
+  const int n = a.n, L = 2 * n + 1;
+  const int64_t N = (int64_t)L * L;
+  const int i0 = (t % tiles_x) * kPostW - 2, j0 = (t / tiles_x) * kPostR - 2;   // first cell of the region
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i = i0 + lane, j = j0 + w;
+  const AfCoef<T> &cf = a.cf;
+  {   // stage x + P xc: coarse cell (ci, cj), its fine rows 0, 1 (first four waves) or 2, 3
+    constexpr int CX = (kCellHW + 2) / 2, CY = (kCellH + 4) / 4 + 1;
+    static_assert(CX * CY <= kWave * kCellWaves / 2, "two threads per coarse cell");
+    const int c = threadIdx.x % (kWave * kCellWaves / 2), half = w / (kCellWaves / 2);
+    const int kx = c % CX, ky = c / CX;
+    const int ci = i0 / 2 - 1 + kx, cj = j0 / 2 - 1 + ky;   // i0 and j0 are even
+    const int nc = n / 2, Lc = n + 1;
     const int64_t Nc = (int64_t)Lc * Lc;
+    V2<T> v[2][4], k9[9];
 #pragma unroll
-    for (int q = 0; q < ITC; ++q) {
-      const int e = tid + NT * q, Ic = Ic0 + e % CW, Jc = Jc0 + e / CW;
-      cv[q][0] = 0;
-      cv[q][1] = 0;
-      if (e < NC && Ic > 0 && Jc > 0 && Ic < nc2 && Jc < nc2) {
-        const int64_t k = (int64_t)Jc * Lc + Ic;
-        cv[q][0] = a.xc[k];
-        cv[q][1] = a.xc[Nc + k];
-      }
-    }
-  }
-  // stage x with a halo of 6 (0 at Dirichlet nodes and outside the lattice)
-  constexpr int NE = H0 * W0, IT = (NE + NT - 1) / NT;
-  T v[IT][2];
+    for (int q = 0; q < 9; ++q) k9[q] = V2<T>{T(0), T(0)};
 #pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / W0, tc = e % W0;
-    const int I = I0 - 6 + tc, J = J0 - 6 + tr;
-    v[q][0] = 0;
-    v[q][1] = 0;
-    if (e < NE && inside(I, J)) {
-      const int64_t r = (int64_t)J * L + I;
-      v[q][0] = a.x[r];
-      v[q][1] = a.x[N + r];
-    }
-  }
-  if constexpr (PROL) {
+    for (int B = 0; B < 2; ++B)
 #pragma unroll
-    for (int q = 0; q < ITC; ++q) {
-      const int e = tid + NT * q;
-      if (e < NC) {
-        XC[2 * e] = cv[q][0];
-        XC[2 * e + 1] = cv[q][1];
-      }
-    }
-    __syncthreads();   // the coarse nodes are in XC
-  }
+      for (int A = 0; A < 4; ++A) v[B][A] = V2<T>{T(0), T(0)};
+    const bool live = ky < CY && ci >= 0 && cj >= 0 && ci < nc && cj < nc;
+    if (live) {
 #pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / W0, tc = e % W0;
-    if (e < NE) {
-      if constexpr (PROL) {
-        const int I = I0 - 6 + tc, J = J0 - 6 + tr;
-        if (inside(I, J)) {
-          T s0, s1;
-          prolong_lds<T, CW>(XC, I, J, Ic0, Jc0, s0, s1);
-          v[q][0] += s0;
-          v[q][1] += s1;
+      for (int B = 0; B < 2; ++B) {
+        const int64_t r = (int64_t)(4 * cj + 2 * half + B) * L + 4 * ci;
+#pragma unroll
+        for (int A = 0; A < 4; A += 2) {
+          const NodePair<T> px = ld_pair(xg, r + A), py = ld_pair(xg, N + r + A);
+          v[B][A] = V2<T>{px.a, py.a};
+          v[B][A + 1] = V2<T>{px.b, py.b};
         }
       }
-      const int o = ((tc & 1) * H0 + tr) * HW0 + (tc >> 1);
-      X0[o] = v[q][0];
-      X0[2 * H0 * HW0 + o] = v[q][1];
+#pragma unroll
+      for (int bq = 0; bq < 3; ++bq) {
+        const int64_t r = (int64_t)(2 * cj + bq) * Lc + 2 * ci;
+        const NodePair<T> px = ld_pair(xcg, r), py = ld_pair(xcg, Nc + r);
+        k9[3 * bq] = V2<T>{px.a, py.a};
+        k9[3 * bq + 1] = V2<T>{px.b, py.b};
+        k9[3 * bq + 2] = V2<T>{xcg[r + 2], xcg[Nc + r + 2]};
+      }
+      // Dirichlet coarse nodes are read as 0
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        const int Ic = 2 * ci + q % 3, Jc = 2 * cj + q / 3;
+        if (Ic == 0 || Jc == 0 || Ic == n || Jc == n) k9[q] = V2<T>{T(0), T(0)};
+      }
+      auto addp = [&](auto h_tag) {
+        constexpr int H = decltype(h_tag)::value;
+        auto node = [&](auto a_tag, auto b_tag) {
+          constexpr int A = decltype(a_tag)::value, B = decltype(b_tag)::value;
+          const V2<T> p = prolong_node<A, 2 * H + B, T>(k9);
+          v[B][A].x += p.x;
+          v[B][A].y += p.y;
+        };
+        using std::integral_constant;
+        node(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+        node(integral_constant<int, 1>{}, integral_constant<int, 0>{});
+        node(integral_constant<int, 2>{}, integral_constant<int, 0>{});
+        node(integral_constant<int, 3>{}, integral_constant<int, 0>{});
+        node(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+        node(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+        node(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+        node(integral_constant<int, 3>{}, integral_constant<int, 1>{});
+      };
+      if (half) addp(std::integral_constant<int, 1>{});
+      else addp(std::integral_constant<int, 0>{});
     }
-  }
-  __syncthreads();
-  // a wave's rows have one parity: the class is wave-uniform per column parity
-  const int jodd = __builtin_amdgcn_readfirstlane((J0 - 4 + rows[0]) & 1);
-  // step 1 on region 1 (from X0), c1 = 0
-  T d1[2][2][2] = {};   // [row][par][component]
-  T xs[2][2][2] = {};   // values of the step, stored after the barrier
-  auto step1 = [&](auto nr_tag) {
-    constexpr int NR = decltype(nr_tag)::value;
 #pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int I = I0 - 4 + 2 * lane + par;
-      const int cls = par | (jodd << 1);
-      int xr[NR];
+    for (int B = 0; B < 2; ++B) {
+      const int lr = 4 * ky - 2 + 2 * half + B;          // staged row: lattice row - 2 (j0 - 1)
+      const bool wall = cj == 0 && half == 0 && B == 0;  // lattice row 0: Dirichlet
+      if (ky < CY && lr >= 0 && lr < kCellH) {
 #pragma unroll
-      for (int k = 0; k < NR; ++k) xr[k] = rows[k] + 2;
-      T sp[NR][2];
-      if (par) class_products<T, 1, H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-      else class_products<T, 0, H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-      const T *di = tb.dinv[cls];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        const int J = J0 - 4 + rows[k];
-        if (inside(I, J)) {
-          const int c0 = (par * H0 + rows[k] + 2) * HW0 + lane + 1;
-          const T x00 = X0[c0], x01 = X0[2 * H0 * HW0 + c0];
-          const T r0 = bv[k][par][0] - sp[k][0], r1 = bv[k][par][1] - sp[k][1];
-          const T e0 = a.c2a * (di[0] * r0 + di[1] * r1), e1 = a.c2a * (di[2] * r0 + di[3] * r1);
-          d1[k][par][0] = e0;
-          d1[k][par][1] = e1;
-          xs[k][par][0] = x00 + e0;
-          xs[k][par][1] = x01 + e1;
+        for (int A = 0; A < 4; ++A) {
+          const int h = 2 * kx - 1 + A / 2;
+          if (h >= 0 && h < kCellHW)
+            X[(A & 1) * kCellPL + lr * kCellHW + h] = (wall || (A == 0 && ci == 0)) ? V2<T>{T(0), T(0)} : v[B][A];
         }
       }
     }
-  };
-  if (has_h) step1(std::integral_constant<int, 2>{});
-  else step1(std::integral_constant<int, 1>{});
-  __syncthreads();   // every wave has read X0
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      if (q == 1 && !has_h) continue;
-      const int o1 = (par * H1 + rows[q]) * HW1 + lane;
-      X1[o1] = xs[q][par][0];
-      X1[2 * H1 * HW1 + o1] = xs[q][par][1];
-    }
+  }
+  // b after the staging, whose registers it takes over: its latency runs behind the barrier
+  V2<T> b[4];
+  load_cell(bg, N, L, n, i, j, b);
+  const CellIn in = cell_inside(i, j, n);
+  const int row = 2 * w + 2, h = lane + 1;
+  const V2<T> *p = X + row * kCellHW + h;
+  V2<T> x[4], s[4], d[4];
   __syncthreads();
-  // step 2 on region 2 (region-1 columns 2..125, rows 2..R+5): tile row, inner halo row
-  T d2[2][2] = {};      // tile row only
-  auto step2 = [&](auto nr_tag) {
-    constexpr int NR = decltype(nr_tag)::value;
+  cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
 #pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int i = 2 * lane + par, I = I0 - 4 + i;
-      const int cls = par | (jodd << 1);
-      int xr[NR];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) xr[k] = rows[k];
-      // lanes 0 and 63 hold no region-2 node: their (discarded) products read in-row columns
-      const int h = lane < 1 ? 1 : lane > 62 ? 62 : lane;
-      T sp[NR][2];
-      if (par) class_products<T, 1, H1, HW1, NR>(tb, jodd, X1, xr, h, sp);
-      else class_products<T, 0, H1, HW1, NR>(tb, jodd, X1, xr, h, sp);
-      const T *di = tb.dinv[cls];
-#pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        const int J = J0 - 4 + rows[k];
-        T x0 = 0, x1 = 0;
-        if (i >= 2 && i < 2 + kC3W + 4 && inside(I, J)) {
-          const int c1 = (par * H1 + rows[k]) * HW1 + lane;
-          const T r0 = bv[k][par][0] - sp[k][0], r1 = bv[k][par][1] - sp[k][1];
-          const T z0 = di[0] * r0 + di[1] * r1, z1 = di[2] * r0 + di[3] * r1;
-          const T e0 = a.c1b * d1[k][par][0] + a.c2b * z0, e1 = a.c1b * d1[k][par][1] + a.c2b * z1;
-          x0 = X1[c1] + e0;
-          x1 = X1[2 * H1 * HW1 + c1] + e1;
-          if (k == 0) {
-            d2[par][0] = e0;
-            d2[par][1] = e1;
-          }
-        }
-        xs[k][par][0] = x0;
-        xs[k][par][1] = x1;
-      }
-    }
-  };
-  if (inner) step2(std::integral_constant<int, 2>{});
-  else step2(std::integral_constant<int, 1>{});
-  __syncthreads();   // every wave has read X1
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      if (q == 1 && !inner) continue;
-      const int o1 = (par * H1 + rows[q]) * HW1 + lane;
-      X1[o1] = xs[q][par][0];
-      X1[2 * H1 * HW1 + o1] = xs[q][par][1];
-    }
+  for (int q = 0; q < 4; ++q) {
+    const V2<T> z = cell_dinv(cf, q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+    d[q] = V2<T>{a.c2a * z.x, a.c2a * z.y};
+    x[q] = in.q[q] ? V2<T>{x[q].x + d[q].x, x[q].y + d[q].y} : V2<T>{T(0), T(0)};
+  }
   __syncthreads();
-  // step 3 on the tile row (region-1 columns 4..R+3 of the tile: i in [4, 4 + kC3W))
+  put_cell<T, kCellPL, kCellHW>(X, row, h, x);
+  __syncthreads();
+  const bool in2 = w >= 1 && w <= kCellWaves - 2;
+  if (in2) {
+    cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const V2<T> z = cell_dinv(cf, q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+      d[q] = V2<T>{fma(a.c2b, z.x, a.c1b * d[q].x), fma(a.c2b, z.y, a.c1b * d[q].y)};
+      x[q] = in.q[q] ? V2<T>{x[q].x + d[q].x, x[q].y + d[q].y} : V2<T>{T(0), T(0)};
+    }
+  }
+  __syncthreads();
+  if (in2 && lane >= 1 && lane <= kWave - 2) put_cell<T, kCellPL, kCellHW>(X, row, h, x);
+  __syncthreads();
   double by = 0.0;   // the thread's part of b . y
-  {
-    const int row = rows[0], J = J0 - 4 + row;
-    if (J <= n2) {
+  if (w >= 2 && w < 2 + kPostR && j <= n) {
+    cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
+    if (lane >= 2 && lane < 2 + kPostW && i <= n) {
+      V2<T> xb[4];
+      if (i == 0 || j == 0 || i == n || j == n) load_cell(xg, N, L, n, i, j, xb);
 #pragma unroll
-      for (int par = 0; par < 2; ++par) {
-        const int i = 2 * lane + par, I = I0 - 4 + i;
-        if (i < 4 || i >= 4 + kC3W || I > n2) continue;
-        const int64_t r = (int64_t)J * L + I;
-        const T b0 = bv[0][par][0], b1 = bv[0][par][1];
-        T y0, y1, e0, e1;
-        if (inside(I, J)) {
-          const int cls = par | (jodd << 1);
-          const int xr[1] = {row};
-          T sp[1][2];
-          if (par) class_products<T, 1, H1, HW1, 1>(tb, jodd, X1, xr, lane, sp);
-          else class_products<T, 0, H1, HW1, 1>(tb, jodd, X1, xr, lane, sp);
-          const int c1 = (par * H1 + row) * HW1 + lane;
-          const T r0 = b0 - sp[0][0], r1 = b1 - sp[0][1];
-          const T *di = tb.dinv[cls];
-          const T z0 = di[0] * r0 + di[1] * r1, z1 = di[2] * r0 + di[3] * r1;
-          e0 = a.c1c * d2[par][0] + a.c2c * z0;
-          e1 = a.c1c * d2[par][1] + a.c2c * z1;
-          y0 = X1[c1] + e0;
-          y1 = X1[2 * H1 * HW1 + c1] + e1;
+      for (int q = 0; q < 4; ++q) {
+        if (in.q[q]) {
+          const V2<T> z = cell_dinv(cf, q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+          x[q].x += fma(a.c2c, z.x, a.c1c * d[q].x);
+          x[q].y += fma(a.c2c, z.y, a.c1c * d[q].y);
         } else {   // Dirichlet row: the identity, stepped pointwise
-          const T x00 = a.x[r], x01 = a.x[N + r];
-          const T f0 = a.c2a * (b0 - x00), f1 = a.c2a * (b1 - x01);
-          const T x10 = x00 + f0, x11 = x01 + f1;
-          const T g0 = a.c1b * f0 + a.c2b * (b0 - x10), g1 = a.c1b * f1 + a.c2b * (b1 - x11);
-          const T x20 = x10 + g0, x21 = x11 + g1;
-          e0 = a.c1c * g0 + a.c2c * (b0 - x20);
-          e1 = a.c1c * g1 + a.c2c * (b1 - x21);
-          y0 = x20 + e0;
-          y1 = x21 + e1;
+          auto steps = [&](T bv, T x0) -> T {
+            const T f = a.c2a * (bv - x0), x1 = x0 + f, e = a.c1b * f + a.c2b * (bv - x1), x2 = x1 + e;
+            return x2 + (a.c1c * e + a.c2c * (bv - x2));
+          };
+          x[q] = V2<T>{steps(b[q].x, xb[q].x), steps(b[q].y, xb[q].y)};
         }
-        if (a.d) {   // null when no later step reads the direction
-          a.d[r] = e0;
-          a.d[N + r] = e1;
+      }
+      store_cell<T, TY>(yg, N, L, n, i, j, x);
+      if constexpr (DOT) {
+        V2<double> r[4];
+        if (!std::is_same<T, double>::value && a.b64) {   // the FP64 right-hand side
+          load_cell(a.b64 + (int64_t)blockIdx.y * a.lb64, N, L, n, i, j, r);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) r[q] = V2<double>{(double)b[q].x, (double)b[q].y};
         }
-        a.y[r] = (TY)y0;
-        a.y[N + r] = (TY)y1;
-        if constexpr (DOT) {
-          if constexpr (std::is_same<T, double>::value) {   // b is the FP64 right-hand side
-            by += (double)b0 * (double)(TY)y0 + (double)b1 * (double)(TY)y1;
-          } else {
-            const double f0 = a.b64 ? a.b64[r] : (double)b0, f1 = a.b64 ? a.b64[N + r] : (double)b1;
-            by += f0 * (double)(TY)y0 + f1 * (double)(TY)y1;
-          }
-        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)   // r = 0 outside the lattice
+          if ((i < n || !(q & 1)) && (j < n || q < 2))
+            by += r[q].x * (double)(TY)x[q].x + r[q].y * (double)(TY)x[q].y;
       }
     }
   }
   if constexpr (DOT) {   // the tile's sum in a fixed order: lanes by shuffles, then waves
-    __shared__ double red[RR];
+    __shared__ double red[kPostR];
     by = wave_sum(by);
-    if (lane == 0) red[w] = by;
+    if (lane == 0 && w >= 2 && w < 2 + kPostR) red[w - 2] = by;
     __syncthreads();
-    if (tid == 0) {
-      double s = 0.0;
+    if (threadIdx.x == 0) {
+      double s0 = 0.0;
 #pragma unroll
-      for (int k = 0; k < RR; ++k) s += red[k];
-      a.dot[t] = s;
+      for (int k = 0; k < kPostR; ++k) s0 += red[k];
+      a.dot[(int64_t)blockIdx.y * a.ldot + t] = s0;
     }
   }
 }
 
-int cheb3_dot_count(int n) {
-  const int L = 2 * n + 1;
-  return ((L + kC3W - 1) / kC3W) * ((L + kC3R - 1) / kC3R);
+int post3_dot_count(int n) { return ((n + kPostW) / kPostW) * ((n + kPostR) / kPostR); }
+
+// tiles of W x R cells over the n + 1 cell columns and rows that hold nodes
+static int cell_tiles(int n, int W, int R, int &tx) {
+  tx = (n + W) / W;
+  return tx * ((n + R) / R);
 }
 
-template <typename T, typename TY>
-void cheb3_post(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<TY> y, T c2a, T c1b,
-                T c2b, T c1c, T c2c, hipStream_t st, int K, LP<const T> xc, LP<double> dot,
-                LP<const double> b64) {
+static void cell_launch_checks(int n, int K) {
   FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
   FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
-  FSI_REQUIRE(!xc.p || (n % 2 == 0 && n >= 4), FSI_E_ARG, "a coarse correction needs an even fluid grid");
-  FSI_REQUIRE(!xc.p || K == 1 || xc.s > 0, FSI_E_ARG, "lane views of the coarse correction need a stride");
-  const int L = 2 * n + 1;
-  const int tx = (L + kC3W - 1) / kC3W, ty = (L + kC3R - 1) / kC3R;
-  const int tiles = tx * ty, band = (tiles + kXcd - 1) / kXcd;
-  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}, {d.p, d.s}, {y.p, y.s}}, K);
+}
+
+template <typename T>
+void pre3(int n, const AfCoef<T> &cf, LP<const T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K) {
+  cell_launch_checks(n, K);
+  int tx;
+  const int tiles = cell_tiles(n, kPreW, kPreR, tx), band = (tiles + kXcd - 1) / kXcd;
+  const int64_t lv = common_stride({{b.p, b.s}, {x.p, x.s}}, K);
+  PreArgs<T> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, lv};
+  hipLaunchKernelGGL(k_pre3<T>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, st, a, tx,
+                     tiles, band);
+  FSI_CHECK_LAUNCH();
+}
+template void pre3<double>(int, const AfCoef<double> &, LP<const double>, LP<double>, double, double, double, double,
+                           double, hipStream_t, int);
+template void pre3<float>(int, const AfCoef<float> &, LP<const float>, LP<float>, float, float, float, float, float,
+                          hipStream_t, int);
+
+template <typename T, typename TY>
+void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
+           hipStream_t st, int K, LP<const T> xc, LP<double> dot, LP<const double> b64) {
+  cell_launch_checks(n, K);
+  FSI_REQUIRE(xc.p && n % 2 == 0 && n >= 4, FSI_E_ARG, "a coarse correction needs an even fluid grid");
+  FSI_REQUIRE(K == 1 || xc.s > 0, FSI_E_ARG, "lane views of the coarse correction need a stride");
+  int tx;
+  const int tiles = cell_tiles(n, kPostW, kPostR, tx), band = (tiles + kXcd - 1) / kXcd;
+  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}, {y.p, y.s}}, K);
   FSI_REQUIRE(!dot.p || K == 1 || dot.s >= tiles, FSI_E_ARG, "lane stride of the tile sums too small");
   FSI_REQUIRE(!b64.p || (dot.p && (K == 1 || b64.s > 0) && !std::is_same<T, double>::value), FSI_E_ARG,
               "an FP64 right-hand side only for the sums of the FP32 form");
-  Cheb3Args<T, TY> a{n, tab, x.p, b.p, d.p, y.p, L * L, c2a, c1b, c2b, c1c, c2c, lv, xc.p, xc.s, dot.p, dot.s,
-                     b64.p, b64.s};
-  const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(64 * kC3R);
-  if (xc.p && dot.p)
-    hipLaunchKernelGGL((k_cheb3<T, kC3R, TY, true, true>), grid, block, 0, st, a, tx, tiles, band);
-  else if (xc.p)
-    hipLaunchKernelGGL((k_cheb3<T, kC3R, TY, true, false>), grid, block, 0, st, a, tx, tiles, band);
-  else if (dot.p)
-    hipLaunchKernelGGL((k_cheb3<T, kC3R, TY, false, true>), grid, block, 0, st, a, tx, tiles, band);
-  else
-    hipLaunchKernelGGL((k_cheb3<T, kC3R, TY, false, false>), grid, block, 0, st, a, tx, tiles, band);
+  PostArgs<T, TY> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, lv, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
+  const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(kWave * kCellWaves);
+  if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, true>), grid, block, 0, st, a, tx, tiles, band);
+  else hipLaunchKernelGGL((k_post3<T, TY, false>), grid, block, 0, st, a, tx, tiles, band);
   FSI_CHECK_LAUNCH();
 }
-template void cheb3_post<double, double>(int, const StencilTable<double> *, LP<const double>, LP<const double>,
-                                         LP<double>, LP<double>, double, double, double, double, double, hipStream_t,
-                                         int, LP<const double>, LP<double>, LP<const double>);
-template void cheb3_post<float, float>(int, const StencilTable<float> *, LP<const float>, LP<const float>, LP<float>,
-                                       LP<float>, float, float, float, float, float, hipStream_t, int,
-                                       LP<const float>, LP<double>, LP<const double>);
-template void cheb3_post<float, double>(int, const StencilTable<float> *, LP<const float>, LP<const float>,
-                                        LP<float>, LP<double>, float, float, float, float, float, hipStream_t, int,
-                                        LP<const float>, LP<double>, LP<const double>);
-
-template <typename T>
-void cheb2_pre(int n, const StencilTable<T> *tab, LP<const T> b, LP<T> d, LP<T> x, T s, T c1a, T c2a, T c1b,
-               T c2b, hipStream_t st, int K) {
-  FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
-  const int L = 2 * n + 1;
-  const int tx = (L + kC2W - 1) / kC2W, ty = (L + kC2R - 1) / kC2R;
-  const int tiles = tx * ty, band = (tiles + kXcd - 1) / kXcd;
-  const int64_t lv = common_stride({{b.p, b.s}, {d.p, d.s}, {x.p, x.s}}, K);
-  Cheb2Args<T> a{n, tab, nullptr, b.p, d.p, x.p, L * L, s, c1a, c2a, c1b, c2b, lv};
-  hipLaunchKernelGGL((k_cheb2<T, C2_PRE, kC2R>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(64 * kC2R), 0,
-                     st, a, tx, tiles, band);
-  FSI_CHECK_LAUNCH();
-}
-
-template <typename T>
-void cheb2_post(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<T> y, T c2a, T c1b,
-                T c2b, hipStream_t st, int K) {
-  FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
-  const int L = 2 * n + 1;
-  const int tx = (L + kC2W - 1) / kC2W, ty = (L + kC2R - 1) / kC2R;
-  const int tiles = tx * ty, band = (tiles + kXcd - 1) / kXcd;
-  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}, {d.p, d.s}, {y.p, y.s}}, K);
-  Cheb2Args<T> a{n, tab, x.p, b.p, d.p, y.p, L * L, T(0), T(0), c2a, c1b, c2b, lv};
-  hipLaunchKernelGGL((k_cheb2<T, C2_POST, kC2R>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(64 * kC2R), 0,
-                     st, a, tx, tiles, band);
-  FSI_CHECK_LAUNCH();
-}
-
-#define FSI_CHEB2_INST(T)                                                                                   \
-  template void cheb2_pre<T>(int, const StencilTable<T> *, LP<const T>, LP<T>, LP<T>, T, T, T, T, T,         \
-                             hipStream_t, int);                                                             \
-  template void cheb2_post<T>(int, const StencilTable<T> *, LP<const T>, LP<const T>, LP<T>, LP<T>, T, T, T, \
-                              hipStream_t, int);
-FSI_CHEB2_INST(double)
-FSI_CHEB2_INST(float)
-#undef FSI_CHEB2_INST
+#define FSI_POST3_INST(T, TY)                                                                                    \
+  template void post3<T, TY>(int, const AfCoef<T> &, LP<const T>, LP<const T>, LP<TY>, T, T, T, T, T, hipStream_t, \
+                             int, LP<const T>, LP<double>, LP<const double>);
+FSI_POST3_INST(double, double)
+FSI_POST3_INST(float, float)
+FSI_POST3_INST(float, double)
+#undef FSI_POST3_INST
 
 // ---------------------------------------------------------------- residual and restriction
-// bc = R (b - A_f x) = P^T r for the multigrid descent (Sec. 4): the residual of the fine
-// nodes under a coarse tile is computed from x staged in LDS and kept in LDS for the
-// restriction sums, so r never goes to HBM (reads x and b, writes bc).  A block of 8 waves
-// owns kRRr coarse rows x kRRc coarse columns; a coarse node (Ic, Jc) gathers the interior
-// fine nodes within 3 of (2 Ic, 2 Jc), so the residual covers 2 kRRr + 5 fine rows and
-// 2 kRRc + 5 columns (region origin (2 Ic0 - 4, 2 Jc0 - 4), lanes on columns 2 lane + par as
-// in the smoothing kernels) and x is staged with 2 more on every side.  Restriction sums in
-// the order of the restriction table; residual products in the order of the stencil table.
-constexpr int kRRr = 8, kRRc = 60;
-static_assert(2 * kRRc + 8 == 2 * kWave, "residual region fits the lane layout");
+// bc = R (b - A_f x) = P^T r for the multigrid descent (Sec. 4): the residual of the fine cells
+// under a coarse tile is computed as in the smoothing launches and kept in LDS for the
+// restriction sums, so r never goes to HBM (reads x and b, writes bc).  A coarse node gathers the
+// interior fine nodes within 3 of its place, so C coarse cells need the residual of 2 C + 3 fine
+// cells: a block takes Q rows of fine cells per wave, 30 coarse columns and (8 Q - 3) / 2 coarse
+// rows.  Q = 2 recomputes less (15 rows for 6 coarse rows, against 7 for 2) and is taken where
+// that leaves the chip enough blocks; Q = 1 shortens the two dependent passes of a block.
+// The restriction runs by coarse classes, one per wave pass, with compile-time weights.
+constexpr int kRRc = (kWave - 3) / 2;
 
 template <typename T>
 struct ResidRestrArgs {
   int n;
-  const StencilTable<T> *tab;
-  const P2RestrTable<T> *rt;
+  AfCoef<T> cf;
   const T *x, *b;
   T *bc;
   int64_t lv, lc;   // lane strides of the fine (x, b) and coarse (bc) vectors
 };
 
-template <typename T>
-__global__ void __launch_bounds__(512, 4) k_resid_restrict(ResidRestrArgs<T> a0, int tiles_x, int tiles, int band) {
-  constexpr int NT = 512;
-  constexpr int H1 = 2 * kRRr + 8;                   // residual region rows (1 .. H1 - 3 used)
-  constexpr int H0 = H1 + 2, W0 = kC2W0, HW0 = W0 / 2;
-  constexpr int RW = 2 * kWave;                      // residual region columns
-  static_assert(kRRr == 8, "one coarse row per wave");
-  __shared__ T X0[2 * 2 * H0 * HW0];                 // x: [component][parity][row][column / 2]
-  T *const R = X0;                                   // then r: [component][row][column]
-  static_assert(2 * H1 * RW <= 2 * 2 * H0 * HW0, "the residual fits over the staged x");
+template <typename T, int Q>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4)
+    k_resid_restrict(ResidRestrArgs<T> a, int tiles_x, int tiles, int band) {
+  constexpr int ROWS = 2 * kCellWaves * Q + 3, PL = ROWS * kCellHW;
+  constexpr int CR = (kCellWaves * Q - 3) / 2;                      // coarse rows
+  constexpr int RH = 2 * kCellWaves * Q, RPL = RH * kWave;          // residual planes
+  static_assert(RPL <= PL, "the residual fits over the staged x");
+  __shared__ V2<T> X[2 * PL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
-  ResidRestrArgs<T> a = a0;
-  lane_shift(a.x, a.lv);
-  lane_shift(a.b, a.lv);
-  lane_shift(a.bc, a.lc);
-  const int n2 = 2 * a.n, L = n2 + 1, Lc = a.n + 1;
+  const T *xg = a.x + (int64_t)blockIdx.y * a.lv, *bg = a.b + (int64_t)blockIdx.y * a.lv;
+  T *bcg = a.bc + (int64_t)blockIdx.y * a.lc;
+  const int n = a.n, L = 2 * n + 1, Lc = n + 1;
   const int64_t N = (int64_t)L * L, Nc = (int64_t)Lc * Lc;
-  const int Ic0 = (t % tiles_x) * kRRc, Jc0 = (t / tiles_x) * kRRr;
-  const int IR = 2 * Ic0 - 4, JR = 2 * Jc0 - 4;      // residual region origin (even)
-  const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-  const StencilTable<T> &tb = *a.tab;
-  auto inside = [&](int I, int J) { return I > 0 && J > 0 && I < n2 && J < n2; };
-  // residual rows 1 + w, 9 + w, 17 + w (the third for waves 0-4): one parity per wave
-  const bool three = w < 5;
-  const int rows[3] = {1 + w, 9 + w, 17 + w};
-  auto needed = [&](int i, int I, int J) { return i >= 1 && i < RW - 2 && inside(I, J); };
-  T bv[3][2][2];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const int J = JR + rows[q];
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int i = 2 * lane + par, I = IR + i;
-      bv[q][par][0] = 0;
-      bv[q][par][1] = 0;
-      if ((q < 2 || three) && needed(i, I, J)) {
-        const int64_t r = (int64_t)J * L + I;
-        bv[q][par][0] = a.b[r];
-        bv[q][par][1] = a.b[N + r];
-      }
-    }
-  }
-  // stage x with a halo of 2 around the residual region (0 at Dirichlet nodes and outside)
-  constexpr int NE = H0 * W0, IT = (NE + NT - 1) / NT;
-  T v[IT][2];
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / W0, tc = e % W0;
-    const int I = IR - 2 + tc, J = JR - 2 + tr;
-    v[q][0] = 0;
-    v[q][1] = 0;
-    if (e < NE && inside(I, J)) {
-      const int64_t r = (int64_t)J * L + I;
-      v[q][0] = a.x[r];
-      v[q][1] = a.x[N + r];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + NT * q, tr = e / W0, tc = e % W0;
-    if (e < NE) {
-      const int o = ((tc & 1) * H0 + tr) * HW0 + (tc >> 1);
-      X0[o] = v[q][0];
-      X0[2 * H0 * HW0 + o] = v[q][1];
-    }
-  }
+  const int C0 = (t % tiles_x) * kRRc, R0 = (t / tiles_x) * CR;     // first coarse cell of the tile
+  const int i0 = 2 * C0 - 2, j0 = 2 * R0 - 2;                       // first fine cell of the region
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i = i0 + lane;
+  const AfCoef<T> &cf = a.cf;
+  V2<T> b[Q][4];
+  stage_pairs<T, ROWS>(X, xg, N, L, n, i0, j0, [](int, int, V2<T> v) -> V2<T> { return v; });
+  load_cell(bg, N, L, n, i, j0 + w * Q, b[0]);   // after the staging, whose registers it takes over
   __syncthreads();
-  const int jodd = __builtin_amdgcn_readfirstlane((JR + rows[0]) & 1);
-  // rows 0-1 of the wave together (one pass over the coefficients), then row 2
-  auto resid = [&](auto q0_tag, auto nr_tag) {   // r over b (0 where not needed: b was not read)
-    constexpr int Q0 = decltype(q0_tag)::value, NR = decltype(nr_tag)::value;
 #pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int i = 2 * lane + par, I = IR + i;
-      int xr[NR];
+  for (int q = 0; q < Q; ++q) {
+    const int j = j0 + w * Q + q;
+    if (q > 0) load_cell(bg, N, L, n, i, j, b[q]);
+    const CellIn in = cell_inside(i, j, n);
+    V2<T> x[4], s[4];
+    cell_products<T, PL, kCellHW>(X + (2 * (w * Q + q) + 2) * kCellHW + lane + 1, cf, x, s);
 #pragma unroll
-      for (int k = 0; k < NR; ++k) xr[k] = rows[Q0 + k] + 2;
-      T sp[NR][2];
-      if (par) class_products<T, 1, H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-      else class_products<T, 0, H0, HW0, NR>(tb, jodd, X0, xr, lane + 1, sp);
-#pragma unroll
-      for (int k = 0; k < NR; ++k)
-        if (needed(i, I, JR + rows[Q0 + k])) {
-          bv[Q0 + k][par][0] -= sp[k][0];
-          bv[Q0 + k][par][1] -= sp[k][1];
-        }
-    }
-  };
-  resid(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
-  if (three) resid(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});
+    for (int k = 0; k < 4; ++k)
+      b[q][k] = in.q[k] ? V2<T>{b[q][k].x - s[k].x, b[q][k].y - s[k].y} : V2<T>{T(0), T(0)};
+  }
   __syncthreads();   // every wave has read x: r goes over it
+  V2<T> *const R = X;
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    if (q == 2 && !three) continue;
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int o = rows[q] * RW + 2 * lane + par;
-      R[o] = bv[q][par][0];
-      R[H1 * RW + o] = bv[q][par][1];
-    }
-  }
+  for (int q = 0; q < Q; ++q) put_cell<T, RPL, kWave>(R, 2 * (w * Q + q), lane, b[q]);
   __syncthreads();
-  // restriction: wave w owns coarse row Jc0 + w; lanes 0-29 the even columns, 32-61 the odd
-  const int Jc = Jc0 + w, hi = lane >> 5, Ic = Ic0 + 2 * (lane & 31) + hi;
-  if ((lane & 31) >= kRRc / 2 || Ic >= Lc || Jc >= Lc) return;
-  T s0 = 0, s1 = 0;
-  if (!(Ic == 0 || Jc == 0 || Ic == a.n || Jc == a.n)) {
-    const P2RestrTable<T> &rt = *a.rt;
-    constexpr RestrOffsets ro = restrict_offsets();
-    const int c0 = (2 * w + 4) * RW + 2 * (Ic - Ic0) + 4;   // the coarse node's fine position
-    auto gather = [&](auto cls_tag) {
-      constexpr int CLS = decltype(cls_tag)::value;
-#pragma unroll
-      for (int k = 0; k < kRestrCount[CLS]; ++k) {
-        const int o = c0 + ro.d[CLS][k][1] * RW + ro.d[CLS][k][0];
-        const T wk = rt.w[CLS][k];
-        s0 = fma(wk, R[o], s0);
-        s1 = fma(wk, R[H1 * RW + o], s1);
+  // coarse classes (vertex, (1, 0), (0, 1), (1, 1)) of the kRRc x CR coarse cells, 64 cells a pass
+  constexpr int NC = kRRc * CR, PASS = (NC + kWave - 1) / kWave;
+  for (int u = w; u < 4 * PASS; u += kCellWaves) {
+    const int c = (u >> 2) * kWave + lane;
+    if (c >= NC) continue;
+    const int ck = c % kRRc, cr = c / kRRc;
+    auto gather = [&](auto pa_tag, auto pb_tag) {
+      constexpr int PA = decltype(pa_tag)::value, PB = decltype(pb_tag)::value;
+      const int Ic = 2 * (C0 + ck) + PA, Jc = 2 * (R0 + cr) + PB;
+      if (Ic >= Lc || Jc >= Lc) return;
+      V2<T> sum{T(0), T(0)};
+      if (Ic > 0 && Jc > 0 && Ic < n && Jc < n) {
+        // fine node (2 Ic + dI, 2 Jc + dJ) relative to the region's first node (2 i0, 2 j0)
+        const V2<T> *r = R + (4 * cr + 4) * kWave + 2 * ck + 2;
+        auto row = [&](auto dj_tag) {
+          constexpr int DJ = decltype(dj_tag)::value;
+          auto term = [&](auto di_tag) {
+            constexpr int DI = decltype(di_tag)::value;
+            constexpr double wt = restrict_weight(PA, PB, DI, DJ);
+            if constexpr (wt != 0.0) {
+              constexpr int u0 = 2 * PA + DI, v0 = 2 * PB + DJ;
+              const V2<T> v = r[(u0 & 1) * RPL + v0 * kWave + (u0 >> 1)];
+              sum.x = fma(T(wt), v.x, sum.x);
+              sum.y = fma(T(wt), v.y, sum.y);
+            }
+          };
+          term(std::integral_constant<int, -3>{});
+          term(std::integral_constant<int, -2>{});
+          term(std::integral_constant<int, -1>{});
+          term(std::integral_constant<int, 0>{});
+          term(std::integral_constant<int, 1>{});
+          term(std::integral_constant<int, 2>{});
+          term(std::integral_constant<int, 3>{});
+        };
+        row(std::integral_constant<int, -3>{});
+        row(std::integral_constant<int, -2>{});
+        row(std::integral_constant<int, -1>{});
+        row(std::integral_constant<int, 0>{});
+        row(std::integral_constant<int, 1>{});
+        row(std::integral_constant<int, 2>{});
+        row(std::integral_constant<int, 3>{});
       }
+      const int64_t k = (int64_t)Jc * Lc + Ic;
+      bcg[k] = sum.x;
+      bcg[Nc + k] = sum.y;
     };
-    if (Jc & 1) {
-      if (hi) gather(std::integral_constant<int, 3>{});
-      else gather(std::integral_constant<int, 2>{});
-    } else {
-      if (hi) gather(std::integral_constant<int, 1>{});
-      else gather(std::integral_constant<int, 0>{});
+    using std::integral_constant;
+    switch (u & 3) {
+      case 0: gather(integral_constant<int, 0>{}, integral_constant<int, 0>{}); break;
+      case 1: gather(integral_constant<int, 1>{}, integral_constant<int, 0>{}); break;
+      case 2: gather(integral_constant<int, 0>{}, integral_constant<int, 1>{}); break;
+      default: gather(integral_constant<int, 1>{}, integral_constant<int, 1>{}); break;
     }
   }
-  const int64_t q = (int64_t)Jc * Lc + Ic;
-  a.bc[q] = s0;
-  a.bc[Nc + q] = s1;
 }
 
+constexpr int kRestrictWideN = 256;   // cells per side from which a block takes two rows per wave
+
 template <typename T>
-void resid_restrict(int nf, const StencilTable<T> *tab, const P2RestrTable<T> *rtab, LP<const T> x, LP<const T> b,
-                    LP<T> bc, hipStream_t s, int K) {
-  FSI_REQUIRE((int64_t)(2 * nf + 1) * (2 * nf + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
+void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K) {
+  cell_launch_checks(nf, K);
   FSI_REQUIRE(nf % 2 == 0 && nf >= 4, FSI_E_ARG, "restriction needs an even fluid grid");
   FSI_REQUIRE(K == 1 || bc.s > 0, FSI_E_ARG, "lane views of the coarse vector need a stride");
-  const int Lc = nf + 1;
-  const int tx = (Lc + kRRc - 1) / kRRc, ty = (Lc + kRRr - 1) / kRRr;
-  const int tiles = tx * ty, band = (tiles + kXcd - 1) / kXcd;
   const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}}, K);
-  ResidRestrArgs<T> a{nf, tab, rtab, x.p, b.p, bc.p, lv, bc.s};
-  hipLaunchKernelGGL(k_resid_restrict<T>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(512), 0, s, a, tx, tiles,
-                     band);
+  ResidRestrArgs<T> a{nf, cf, x.p, b.p, bc.p, lv, bc.s};
+  auto go = [&](auto q_tag) {
+    constexpr int Q = decltype(q_tag)::value;
+    int tx;
+    const int tiles = cell_tiles(nf / 2, kRRc, (kCellWaves * Q - 3) / 2, tx), band = (tiles + kXcd - 1) / kXcd;
+    hipLaunchKernelGGL((k_resid_restrict<T, Q>), dim3((unsigned)(band * kXcd), (unsigned)K),
+                       dim3(kWave * kCellWaves), 0, s, a, tx, tiles, band);
+  };
+  if (nf >= kRestrictWideN) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 1>{});
   FSI_CHECK_LAUNCH();
 }
-template void resid_restrict<double>(int, const StencilTable<double> *, const P2RestrTable<double> *,
-                                     LP<const double>, LP<const double>, LP<double>, hipStream_t, int);
-template void resid_restrict<float>(int, const StencilTable<float> *, const P2RestrTable<float> *, LP<const float>,
-                                    LP<const float>, LP<float>, hipStream_t, int);
+template void resid_restrict<double>(int, const AfCoef<double> &, LP<const double>, LP<const double>, LP<double>,
+                                     hipStream_t, int);
+template void resid_restrict<float>(int, const AfCoef<float> &, LP<const float>, LP<const float>, LP<float>,
+                                    hipStream_t, int);
 
 #define FSI_STENCIL_INST(T, M)                                                                              \
   template void stencil_launch<T, M>(int, const StencilTable<T> *, LP<const T>, LP<const T>, LP<T>, LP<T>, T, T, \
