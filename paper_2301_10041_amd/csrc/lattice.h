@@ -147,28 +147,19 @@ template <typename T, typename TZ, int S, bool ZERO, int OUT>
 void p1_multi(const P1MultiArgs<T, TZ> &a, hipStream_t s, int K = 1);
 // The coarse end of a velocity V-cycle in one launch per system (mgtail.hip): levels
 // lv[0..nlev) (n <= kTailMaxN cells, each the next one's fine level) and the coarsest
-// level's dense inverse.  Vectors in LDS (offsets in T): level l's b at lv[l].off and x
-// right after it (2 N each, N = tail_plane_entries(n)), one shared direction at offd (2 N of
-// lv[0]),
-// the coarsest b at offc and x after it (m each), then the stencil coefficients and
-// inverse diagonal blocks of every level (kTailTab each) and the restriction weights
-// (kTailRw) at offt; the dense inverse of the coarsest level (m x m, row-major) at offm when
-// it fits the block's LDS, else offm = -1 and it is read from device memory; lds = the
-// total.  b and x in device memory: the first level's right-hand side and result (lane
-// stride lb).
-constexpr int kTailMax = 4, kTailDeg = 8, kTailMaxN = 16, kTailDenseMax = 6 * 64;
-constexpr int kTailCoef[4] = {0, 76, 112, 148};   // class offsets of 4 coefficients per entry
-constexpr int kTailTab = 184 + 16, kTailRw = 25 + 9 + 9 + 9;
-constexpr int kTailRs[4] = {0, 25, 34, 43};       // class offsets of the restriction weights
+// level's dense inverse cinv (m x m, symmetric).  LDS: two buffers of kTailLevelV2 nodes per
+// level, the right-hand sides (two nodes per thread and level), the coarsest b and x (m each)
+// and, at byte offp, the partial sums of the dense solve in FP64; lds = the total in bytes.  b and x
+// in device memory: the first level's right-hand side and result (lane stride lb).
+constexpr int kTailMax = 3, kTailDeg = 8, kTailMaxN = 16, kTailDenseMax = 6 * 64;
+constexpr int kTailDenseReg = 54;   // entries of the dense inverse that a thread keeps in registers
+constexpr int kTailLevelV2 = 2 * (2 * kTailMaxN + 5) * (kTailMaxN + 3);
 // Largest LDS block of the tail launch on the current device (queried once, at most 160 KiB).
 int tail_lds_limit();
-// Entries per component of a smoothing level of n cells in the tail's LDS: even and odd
-// column planes of n + 1 columns and 2n + 1 rows.
-inline int tail_plane_entries(int n) { return 2 * (2 * n + 1) * (n + 1); }
 template <typename T>
 struct TailLevel {
-  int n, off;
-  const StencilTable<T> *tab;
+  int n;
+  AfCoef<T> cf;
   T s;                                     // 1 / theta: the first step of both smoothings
   T c1[kTailDeg - 1], c2[kTailDeg - 1];    // the later Chebyshev steps
 };
@@ -176,8 +167,7 @@ template <typename T>
 struct TailArgs {
   int nlev, degree;
   TailLevel<T> lv[kTailMax];
-  int offd, offc, offt, offm, m, lds;
-  const P2RestrTable<T> *rt;
+  int offp, m, lds;
   const T *cinv;
   const T *b;
   T *x;

@@ -1,24 +1,27 @@
 // The coarse end of the velocity V-cycle in one launch per system (Sec. 4 multigrid).  On
 // levels of at most 16 x 16 cells every smoothing step, residual and transfer of the
 // separate launches costs the latency of a whole kernel while the level holds a few
-// thousand nodes; here one 1024-thread block keeps the right-hand side and iterate of every
-// remaining level in LDS and runs pre-smoothing, residual, restriction, the dense solve on
-// the coarsest level, prolongation and post-smoothing with block barriers in between.
-// The steps are those of the per-level launches: the same Chebyshev coefficients, the same
-// stencil tables and restriction weights, the coarse quadratic for the prolongation.
+// thousand nodes; here one 512-thread block keeps the iterate of every remaining level in LDS
+// and runs pre-smoothing, residual, restriction, the dense solve on the coarsest level,
+// prolongation and post-smoothing with block barriers in between.  The steps are those of the
+// per-level launches (the same Chebyshev coefficients, cell products and transfer weights).
 //
-// Threads: four groups of 256, one per node class (vertex, horizontal edge, vertical edge,
-// diagonal: the parities of the lattice coordinates), so the stencil of a wave is uniform;
-// on a level of n <= 16 cells every class has at most 256 interior nodes, one per thread.
-// Dirichlet nodes hold 0 in every vector (a restricted right-hand side vanishes there and
-// the identity rows keep it so), so only interior nodes are stepped.  A smoothing level's
-// vectors lie in LDS as even and odd column planes ([component][parity][row][column / 2]):
-// the lanes of a wave (one class, consecutive nodes of a row) then read consecutive words,
-// without the bank conflicts of the stride-2 row-major order.  The coarsest level keeps the
-// row-major order of its dense inverse.  The stencil
-// coefficients, inverse diagonal blocks and restriction weights are copied to LDS first:
-// read from device memory at every step they cost a scalar-cache round trip per few
-// neighbours.
+// Threads: cell (i, j) of a level belongs to two threads, one for its nodes on the even lattice
+// row (vertex and (1, 0): the first four waves) and one for those on the odd row, so that a wave's
+// work is uniform and both halves of a cell run at once on two waves per SIMD.  A thread's
+// right-hand side and direction stay in its registers over the steps of a level.  The iterate lies
+// in LDS in two buffers, one step reading one and writing the other (one barrier per step), as
+// even and odd column planes with both components of a node together and a halo of zeros; the
+// residual takes the buffer that the iterate has left.  Dirichlet nodes hold 0 (a restricted
+// right-hand side vanishes there), so only interior nodes are ever written.
+//
+// What bounds it is the latency of about 20 dependent passes.  The A_f entries come from the
+// kernel arguments into scalar registers (AfCoef): read from LDS by every wave in every pass they
+// took two thirds of a pass (6,800 of its cycles at 16^2; an LDS read of one uniform word costs
+// as much as one of 64 words).  The dense inverse (162 x 162 words on 4^2) is fetched into
+// registers at the start, behind the descent; read at its turn it took 9 of 43 us.
+#include <cmath>
+
 #include "ctx.h"
 #include "kernels.h"
 #include "lattice.h"
@@ -28,97 +31,55 @@ namespace fsi {
 
 namespace {
 
-constexpr int kTailThreads = 1024, kTailGroup = kTailThreads / 4;
+constexpr int kTailThreads = 512, kTailHalf = kTailThreads / 2;
+// staged planes of a level: lattice columns -2 .. 2n + 2 as planes of n + 3, rows -2 .. 2n + 2
+constexpr int kTailHW = kTailMaxN + 3, kTailPL = (2 * kTailMaxN + 5) * kTailHW;
+static_assert(2 * kTailPL == kTailLevelV2, "LDS size of a level's buffer");
+static_assert(kTailMaxN * kTailMaxN <= kTailHalf, "one thread per half cell");
 
-// LDS layout of a smoothing level of n cells: planes of n + 1 columns
-struct TailGrid {
-  int L, HW, N;   // lattice side 2n + 1, plane width, entries per component (2 L HW)
-  __device__ int at(int I, int J) const { return ((I & 1) * L + J) * HW + (I >> 1); }
-};
-__device__ __forceinline__ TailGrid tail_grid(int n) {
-  const int L = 2 * n + 1;
-  return TailGrid{L, n + 1, 2 * L * (n + 1)};
-}
-// floor(v / 2) for the small offsets of the stencils (v >= -4)
-__host__ __device__ constexpr int half_floor(int v) { return (v + 4) / 2 - 2; }
+// position of node (I, J) in a level's buffer
+__device__ __forceinline__ int tail_at(int I, int J) { return (I & 1) * kTailPL + (J + 2) * kTailHW + (I >> 1) + 1; }
 
-// interior node of class c (I parity c & 1, J parity c >> 1) number i on a level of n cells
-__device__ __forceinline__ bool class_node(int c, int i, int n, int &I, int &J) {
-  const int pi = c & 1, pj = c >> 1;
-  const int ni = pi ? n : n - 1, nj = pj ? n : n - 1;
-  if (i >= ni * nj) return false;
-  I = (pi ? 1 : 2) + 2 * (i % ni);
-  J = (pj ? 1 : 2) + 2 * (i / ni);
-  return true;
-}
-
-// (A_f x) at the node of LDS index idx (layout g); cf: the level's coefficients in LDS
-// (class CLS at kTailCoef[CLS], four per entry).  A neighbour (dI, dJ) of a node of column
-// parity P lies in plane (P + dI) mod 2, floor((P + dI) / 2) columns over.
-template <typename T, int CLS>
-__device__ __forceinline__ void tail_product(const T *cf, const T *x, const TailGrid &g, int idx, T &s0, T &s1) {
-  constexpr StencilOffsets so = stencil_offsets();
-  constexpr CrossZero cz = cross_zero();
-  constexpr int P = CLS & 1;
-  const int N = g.N;
-  s0 = 0;
-  s1 = 0;
-#pragma unroll
-  for (int k = 0; k < kStencilCount[CLS]; ++k) {
-    const int dI = so.d[CLS][k][0], dJ = so.d[CLS][k][1];
-    const int o = idx + ((((P + dI) & 1) - P) * g.L + dJ) * g.HW + half_floor(P + dI);
-    const T y0 = x[o], y1 = x[N + o];
-    const T *ck = cf + kTailCoef[CLS] + 4 * k;
-    const T c0 = ck[0], c1 = ck[1], c2 = ck[2], c3 = ck[3];
-    if (cz.z[CLS][k]) {
-      s0 = fma(c0, y0, s0);
-      s1 = fma(c3, y1, s1);
-    } else {
-      s0 = fma(c1, y1, fma(c0, y0, s0));
-      s1 = fma(c3, y1, fma(c2, y0, s1));
-    }
-  }
+// restriction sum at coarse node (2 i + PA, 2 j + PB) from the fine residual r of a level
+template <typename T, int PA, int PB>
+__device__ __forceinline__ V2<T> tail_restrict(const V2<T> *r, int i, int j) {
+  V2<T> sum{T(0), T(0)};
+  const V2<T> *p = r + tail_at(4 * i, 4 * j);
+  auto row = [&](auto dj_tag) {
+    constexpr int DJ = decltype(dj_tag)::value;
+    auto term = [&](auto di_tag) {
+      constexpr int DI = decltype(di_tag)::value;
+      constexpr double wt = restrict_weight(PA, PB, DI, DJ);
+      if constexpr (wt != 0.0) {
+        constexpr int U = 2 * PA + DI, V = 2 * PB + DJ;
+        const V2<T> v = p[(U & 1) * kTailPL + V * kTailHW + (U >> 1)];
+        sum.x = fma(T(wt), v.x, sum.x);
+        sum.y = fma(T(wt), v.y, sum.y);
+      }
+    };
+    term(std::integral_constant<int, -3>{});
+    term(std::integral_constant<int, -2>{});
+    term(std::integral_constant<int, -1>{});
+    term(std::integral_constant<int, 0>{});
+    term(std::integral_constant<int, 1>{});
+    term(std::integral_constant<int, 2>{});
+    term(std::integral_constant<int, 3>{});
+  };
+  row(std::integral_constant<int, -3>{});
+  row(std::integral_constant<int, -2>{});
+  row(std::integral_constant<int, -1>{});
+  row(std::integral_constant<int, 0>{});
+  row(std::integral_constant<int, 1>{});
+  row(std::integral_constant<int, 2>{});
+  row(std::integral_constant<int, 3>{});
+  return sum;
 }
 
-template <typename T>
-__device__ __forceinline__ void class_product(int c, const T *cf, const T *x, const TailGrid &g, int idx, T &s0,
-                                              T &s1) {
-  switch (c) {   // uniform over the wave
-    case 0: tail_product<T, 0>(cf, x, g, idx, s0, s1); break;
-    case 1: tail_product<T, 1>(cf, x, g, idx, s0, s1); break;
-    case 2: tail_product<T, 2>(cf, x, g, idx, s0, s1); break;
-    default: tail_product<T, 3>(cf, x, g, idx, s0, s1); break;
-  }
-}
-
-// restriction sum at coarse node (Ic, Jc) of class CLS from the fine residual r (weights
-// rw in LDS, class CLS at kTailRs[CLS])
-template <typename T, int CLS>
-__device__ __forceinline__ void tail_restrict(const T *rw, const T *r, const TailGrid &g, int Ic, int Jc, T &s0,
-                                              T &s1) {
-  constexpr RestrOffsets ro = restrict_offsets();
-  const int N = g.N;
-  s0 = 0;
-  s1 = 0;
-  const int c = 2 * Jc * g.HW + Ic;   // fine (2 Ic, 2 Jc): even plane
-#pragma unroll
-  for (int k = 0; k < kRestrCount[CLS]; ++k) {
-    const int dI = ro.d[CLS][k][0], dJ = ro.d[CLS][k][1];
-    const int o = c + ((dI & 1) * g.L + dJ) * g.HW + half_floor(dI);
-    const T w = rw[kTailRs[CLS] + k];
-    s0 = fma(w, r[o], s0);
-    s1 = fma(w, r[N + o], s1);
-  }
-}
-
-// coarse quadratic at fine node (I, J): the six P2 basis values of the coarse cell's
-// triangle at the local position, in the order vertices 0, 1, 2, edges 01, 12, 20 (exact in
-// float).  The coarse vector xc is a smoothing level (layout gc) or, when natural, the
-// coarsest level in row-major order (side gc.L, gc.N nodes per component).
-template <typename T>
-__device__ __forceinline__ void tail_prolong(const T *xc, const TailGrid &gc, bool natural, int I, int J, T &s0,
-                                             T &s1) {
-  const int A = I & 3, B = J & 3, Ib = 2 * (I >> 2), Jb = 2 * (J >> 2);
+// coarse quadratic at fine node (A, B) (0 .. 3) of a coarse cell: the six P2 basis values of the
+// triangle that holds it, in the order vertices 0, 1, 2, edges 01, 12, 20 (exact in float); c(a, b)
+// reads the coarse node (a, b) (0 .. 2) of the cell
+template <typename T, typename C>
+__device__ __forceinline__ V2<T> tail_prolong(C c, int A, int B) {
   const bool lo = A >= B;
   const float xi = 0.25f * (float)A, eta = 0.25f * (float)B;
   const float l0 = lo ? 1.0f - xi : 1.0f - eta, l1 = lo ? xi - eta : xi, l2 = lo ? eta : eta - xi;
@@ -126,231 +87,230 @@ __device__ __forceinline__ void tail_prolong(const T *xc, const TailGrid &gc, bo
                         4.0f * l0 * l1,         4.0f * l1 * l2,         4.0f * l2 * l0};
   const int di[6] = {0, 2, lo ? 2 : 0, 1, lo ? 2 : 1, lo ? 1 : 0};
   const int dj[6] = {0, lo ? 0 : 2, 2, lo ? 0 : 1, lo ? 1 : 2, 1};
-  s0 = 0;
-  s1 = 0;
+  V2<T> s{T(0), T(0)};
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
-    const T w = (T)phi[q];
-    const int Ic = Ib + di[q], Jc = Jb + dj[q];
-    const int k = natural ? Jc * gc.L + Ic : gc.at(Ic, Jc);
-    s0 = fma(w, xc[k], s0);
-    s1 = fma(w, xc[gc.N + k], s1);
+    const V2<T> v = c(di[q], dj[q]);
+    s.x = fma((T)phi[q], v.x, s.x);
+    s.y = fma((T)phi[q], v.y, s.y);
   }
+  return s;
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kTailThreads) k_mg_tail(TailArgs<T> a) {
+__global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   extern __shared__ unsigned char tail_smem[];
-  T *sm = reinterpret_cast<T *>(tail_smem);
-  // the class group is uniform over a wave: scalar branches and scalar table loads
-  const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid / kTailGroup), gi = tid % kTailGroup;
+  V2<T> *const sv = reinterpret_cast<V2<T> *>(tail_smem);   // level l: buffers 2 l, 2 l + 1; then its b
+  const int tid = threadIdx.x, half = __builtin_amdgcn_readfirstlane(tid / kTailHalf), cell = tid % kTailHalf;
   const T *bg = a.b + (int64_t)blockIdx.y * a.lb;
   T *xg = a.x + (int64_t)blockIdx.y * a.lb;
-  // device-memory operands of the start issued first, so that their latency overlaps the
-  // clearing of the vectors and the table copies: the dense inverse (when it goes to LDS,
-  // kPre entries per thread at once) and the first level's right-hand side (stored after
-  // the clearing barrier)
-  constexpr int kPre = 12;
-  const int mm = a.offm >= 0 ? a.m * a.m : 0;
-  T pre[kPre];
-#pragma unroll
-  for (int q = 0; q < kPre; ++q) {
-    const int i = tid + kTailThreads * q;
-    pre[q] = i < mm ? a.cinv[i] : T(0);
-  }
-  T b0v = 0, b1v = 0;
-  int bk = -1;
+  // the dense inverse: P threads per row, kp consecutive columns each; the matrix is symmetric, so
+  // thread (row, part) reads its entries down column `row` and the loads are coalesced
+  const int m = a.m, P = kTailThreads / m, kp = (m + P - 1) / P, drow = tid % m, dpart = tid / m;
+  const bool dlive = dpart < P;
+  const bool pre = kp <= kTailDenseReg;   // uniform
+  T cr[kTailDenseReg];
   {
-    const TailGrid g = tail_grid(a.lv[0].n);
-    const int NG = g.L * g.L;   // nodes per component in device memory (row-major)
-    int I, J;
-    if (class_node(grp, gi, a.lv[0].n, I, J)) {
-      const int kg = J * g.L + I;
-      bk = g.at(I, J);
-      b0v = bg[kg];
-      b1v = bg[NG + kg];
-    }
-  }
-  for (int i = tid; i < a.offt; i += kTailThreads) sm[i] = T(0);
-  for (int l = 0; l < a.nlev; ++l)   // coefficients (class-compact) and inverse diagonal blocks
-    for (int i = tid; i < kTailTab; i += kTailThreads) {
-      const StencilTable<T> &tb = *a.lv[l].tab;
-      T v;
-      if (i >= kTailCoef[3] + 4 * kStencilCount[3]) {
-        const int j = i - (kTailCoef[3] + 4 * kStencilCount[3]);
-        v = tb.dinv[j / 4][j % 4];
-      } else {
-        const int c = i < kTailCoef[1] ? 0 : i < kTailCoef[2] ? 1 : i < kTailCoef[3] ? 2 : 3;
-        const int j = i - kTailCoef[c];
-        v = tb.coef[c][j / 4][j % 4];
-      }
-      sm[a.offt + l * kTailTab + i] = v;
-    }
-  for (int i = tid; i < kTailRw; i += kTailThreads) {
-    const int c = i < kTailRs[1] ? 0 : i < kTailRs[2] ? 1 : i < kTailRs[3] ? 2 : 3;
-    sm[a.offt + a.nlev * kTailTab + i] = a.rt->w[c][i - kTailRs[c]];
-  }
+    const int c0 = (dlive ? dpart : 0) * kp;
 #pragma unroll
-  for (int q = 0; q < kPre; ++q) {
-    const int i = tid + kTailThreads * q;
-    if (i < mm) sm[a.offm + i] = pre[q];
-  }
-  for (int i = tid + kTailThreads * kPre; i < mm; i += kTailThreads) sm[a.offm + i] = a.cinv[i];
-  __syncthreads();
-  const T *rw = sm + a.offt + a.nlev * kTailTab;
-  auto coefs = [&](int l) { return (const T *)(sm + a.offt + l * kTailTab); };
-  auto dinv = [&](int l) { return (const T *)(sm + a.offt + l * kTailTab + kTailCoef[3] + 4 * kStencilCount[3]); };
-  T *d = sm + a.offd;   // the direction (then residual) of the level being smoothed
-  if (bk >= 0) {        // right-hand side of the first level (interior nodes)
-    T *b = sm + a.lv[0].off;
-    b[bk] = b0v;
-    b[tail_grid(a.lv[0].n).N + bk] = b1v;
-  }
-  __syncthreads();
-  // one Chebyshev step on level l from x (first: c1 = 0, the direction is not read)
-  auto cheb_step = [&](int l, bool first, T c1, T c2) {
-    const TailLevel<T> &lv = a.lv[l];
-    const TailGrid g = tail_grid(lv.n);
-    const int N = g.N;
-    T *b = sm + lv.off, *x = b + 2 * N;
-    int I, J;
-    const bool mine = class_node(grp, gi, lv.n, I, J);
-    const int k = mine ? g.at(I, J) : 0;
-    T x0 = 0, x1 = 0, d0 = 0, d1 = 0;
-    if (mine) {
-      T s0, s1;
-      class_product<T>(grp, coefs(l), x, g, k, s0, s1);
-      const T r0 = b[k] - s0, r1 = b[N + k] - s1;
-      const T *di = dinv(l) + 4 * grp;
-      const T z0 = di[0] * r0 + di[1] * r1, z1 = di[2] * r0 + di[3] * r1;
-      d0 = first ? c2 * z0 : c1 * d[k] + c2 * z0;
-      d1 = first ? c2 * z1 : c1 * d[N + k] + c2 * z1;
-      x0 = x[k] + d0;
-      x1 = x[N + k] + d1;
+    for (int q = 0; q < kTailDenseReg; ++q) cr[q] = T(0);
+    if (pre) {
+#pragma unroll
+      for (int q = 0; q < kTailDenseReg; ++q)   // past the last column: any entry (it meets a zero of b)
+        if (q < kp) cr[q] = a.cinv[(c0 + q < m ? c0 + q : 0) * m + drow];
     }
-    __syncthreads();
-    if (mine) {
-      x[k] = x0;
-      x[N + k] = x1;
-      d[k] = d0;
-      d[N + k] = d1;
+  }
+  auto buf = [&](int l, int k) -> V2<T> * { return sv + (2 * l + k) * kTailLevelV2; };
+  V2<T> *const bs = sv + 2 * a.nlev * kTailLevelV2;         // right-hand sides: 2 per thread and level
+  T *const db = reinterpret_cast<T *>(bs + 2 * kTailThreads * a.nlev), *const dx = db + m + kTailDenseReg;   // coarsest b (zeros after it) and x
+  double *const dp = reinterpret_cast<double *>(tail_smem + a.offp);                         // partial sums
+  // the first level's right-hand side (interior nodes), and the zeros of its last column and row
+  V2<T> b[2] = {{T(0), T(0)}, {T(0), T(0)}};
+  {
+    const int n = a.lv[0].n, L = 2 * n + 1, NG = L * L, i = cell % n, j = cell / n;
+    if (j < n) {
+      const int r = (2 * j + half) * L + 2 * i;
+      b[0] = V2<T>{bg[r], bg[NG + r]};
+      b[1] = V2<T>{bg[r + 1], bg[NG + r + 1]};
     }
-    __syncthreads();
+    for (int q = tid; q < L; q += kTailThreads) {
+      xg[q * L + 2 * n] = xg[NG + q * L + 2 * n] = T(0);
+      xg[2 * n * L + q] = xg[NG + 2 * n * L + q] = T(0);
+    }
+  }
+  for (int q = tid; q < 2 * a.nlev * kTailLevelV2; q += kTailThreads) sv[q] = V2<T>{T(0), T(0)};
+  for (int q = tid; q < m + kTailDenseReg; q += kTailThreads) db[q] = T(0);
+  __syncthreads();
+  // the thread's place on a level: its two nodes (2 i, J), (2 i + 1, J), J = 2 j + half
+  struct Place {
+    int i, j, at;
+    bool in[2];
+  };
+  auto place = [&](int n) -> Place {
+    const int i = cell % n, j = cell / n;
+    const bool row = j < n && (half == 1 || j > 0);
+    return Place{i, j, tail_at(2 * i, 2 * j), {row && i > 0, row}};
+  };
+  // products at the thread's nodes from buffer x (threads past the level's cells read cell 0)
+  auto product = [&](const V2<T> *x, const Place &pl, const AfCoef<T> &cf, V2<T> (&xo)[2], V2<T> (&so)[2]) {
+    const V2<T> *p = x + (pl.in[1] ? pl.at : tail_at(0, 0));
+    V2<T> xx[4], ss[4];
+    if (half) {
+      cell_products<T, kTailPL, kTailHW, CELL_ROW1>(p, cf, xx, ss);
+      xo[0] = xx[2];
+      xo[1] = xx[3];
+      so[0] = ss[2];
+      so[1] = ss[3];
+    } else {
+      cell_products<T, kTailPL, kTailHW, CELL_ROW0>(p, cf, xx, ss);
+      xo[0] = xx[0];
+      xo[1] = xx[1];
+      so[0] = ss[0];
+      so[1] = ss[1];
+    }
+  };
+  auto put = [&](V2<T> *x, const Place &pl, const V2<T> (&v)[2]) {
+    V2<T> *p = x + pl.at + half * kTailHW;
+    if (pl.in[0]) p[0] = v[0];
+    if (pl.in[1]) p[kTailPL] = v[1];
+  };
+  V2<T> d[2];
+  // one Chebyshev step on level l from buffer src: the new values of the thread's nodes
+  auto cheb_step = [&](const TailLevel<T> &lv, const Place &pl, const V2<T> *src, T c1, T c2, V2<T> (&x)[2]) {
+    V2<T> s[2];
+    product(src, pl, lv.cf, x, s);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const V2<T> z = cell_dinv(lv.cf, 2 * half + q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+      d[q] = V2<T>{(T)fma(c2, z.x, c1 * d[q].x), (T)fma(c2, z.y, c1 * d[q].y)};
+      x[q] = V2<T>{x[q].x + d[q].x, x[q].y + d[q].y};
+    }
   };
   // descent: pre-smoothing, residual, restriction
+#pragma unroll 1
   for (int l = 0; l < a.nlev; ++l) {
     const TailLevel<T> &lv = a.lv[l];
-    const TailGrid g = tail_grid(lv.n);
-    const int N = g.N;
-    T *b = sm + lv.off, *x = b + 2 * N;
-    {   // first step from zero: x = d = s D^{-1} b
-      int I, J;
-      if (class_node(grp, gi, lv.n, I, J)) {
-        const int k = g.at(I, J);
-        const T *di = dinv(l) + 4 * grp;
-        const T b0 = b[k], b1 = b[N + k];
-        const T z0 = lv.s * (di[0] * b0 + di[1] * b1), z1 = lv.s * (di[2] * b0 + di[3] * b1);
-        x[k] = d[k] = z0;
-        x[N + k] = d[N + k] = z1;
-      }
+    const Place pl = place(lv.n);
+    V2<T> x[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {   // first step from zero: x = d = s D^{-1} b
+      bs[2 * (kTailThreads * l) + kTailThreads * q + tid] = b[q];
+      const V2<T> z = cell_dinv(lv.cf, 2 * half + q, b[q]);
+      x[q] = d[q] = V2<T>{lv.s * z.x, lv.s * z.y};
+    }
+    int k = 0;
+    put(buf(l, k), pl, x);
+    __syncthreads();
+#pragma unroll 1
+    for (int j = 0; j + 1 < a.degree; ++j, k ^= 1) {
+      cheb_step(lv, pl, buf(l, k), lv.c1[j], lv.c2[j], x);
+      put(buf(l, k ^ 1), pl, x);
+      __syncthreads();
+    }
+    {   // the residual into the other buffer
+      V2<T> s[2];
+      product(buf(l, k), pl, lv.cf, x, s);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) s[q] = V2<T>{b[q].x - s[q].x, b[q].y - s[q].y};
+      put(buf(l, k ^ 1), pl, s);
     }
     __syncthreads();
-    for (int j = 0; j + 1 < a.degree; ++j) cheb_step(l, false, lv.c1[j], lv.c2[j]);
-    {   // residual over the direction (not read again before the post-smoothing)
-      int I, J;
-      if (class_node(grp, gi, lv.n, I, J)) {
-        const int k = g.at(I, J);
-        T s0, s1;
-        class_product<T>(grp, coefs(l), x, g, k, s0, s1);
-        d[k] = b[k] - s0;
-        d[N + k] = b[N + k] - s1;
+    {   // restriction: the next level's right-hand side at the thread's nodes there
+      const int nc = lv.n / 2;
+      const Place pc = place(nc);
+      const V2<T> *r = buf(l, k ^ 1);
+      b[0] = b[1] = V2<T>{T(0), T(0)};
+      if (half) {
+        if (pc.in[0]) b[0] = tail_restrict<T, 0, 1>(r, pc.i, pc.j);
+        if (pc.in[1]) b[1] = tail_restrict<T, 1, 1>(r, pc.i, pc.j);
+      } else {
+        if (pc.in[0]) b[0] = tail_restrict<T, 0, 0>(r, pc.i, pc.j);
+        if (pc.in[1]) b[1] = tail_restrict<T, 1, 0>(r, pc.i, pc.j);
       }
-    }
-    __syncthreads();
-    {   // restriction into the next level's right-hand side (interior coarse nodes)
-      const int nc = lv.n / 2, Lc = lv.n + 1;
-      const bool coarsest = l + 1 == a.nlev;   // row-major, as its dense inverse
-      const TailGrid gc = coarsest ? TailGrid{Lc, 0, Lc * Lc} : tail_grid(nc);
-      T *bc = coarsest ? sm + a.offc : sm + a.lv[l + 1].off;
-      int Ic, Jc;
-      if (class_node(grp, gi, nc, Ic, Jc)) {
-        const int k = coarsest ? Jc * Lc + Ic : gc.at(Ic, Jc);
-        T s0, s1;
-        switch (grp) {
-          case 0: tail_restrict<T, 0>(rw, d, g, Ic, Jc, s0, s1); break;
-          case 1: tail_restrict<T, 1>(rw, d, g, Ic, Jc, s0, s1); break;
-          case 2: tail_restrict<T, 2>(rw, d, g, Ic, Jc, s0, s1); break;
-          default: tail_restrict<T, 3>(rw, d, g, Ic, Jc, s0, s1); break;
+      if (l + 1 == a.nlev) {   // the coarsest level, row-major as its dense inverse
+        const int Lc = lv.n + 1, q = (2 * pc.j + half) * Lc + 2 * pc.i;
+        if (pc.in[0]) {
+          db[q] = b[0].x;
+          db[Lc * Lc + q] = b[0].y;
         }
-        bc[k] = s0;
-        bc[gc.N + k] = s1;
+        if (pc.in[1]) {
+          db[q + 1] = b[1].x;
+          db[Lc * Lc + q + 1] = b[1].y;
+        }
       }
     }
-    __syncthreads();
   }
-  {   // coarsest level: x = C^{-1} b, one wave per row (sums in double, as the dense kernel);
-      // a wave loads kRows rows at once (coalesced, one memory round trip per batch), from
-      // LDS when the inverse was copied there
-    constexpr int kRows = 4, kSeg = kTailDenseMax / kWave, NW = kTailThreads / kWave;
-    const T *b = sm + a.offc;
-    T *x = sm + a.offc + a.m;
-    const int w = tid / kWave, lane = tid % kWave;
-    auto dense = [&](const T *cm) {
-      for (int r0 = w; r0 < a.m; r0 += kRows * NW) {
-        T c[kRows][kSeg];
+  __syncthreads();
+  // coarsest level: x = C^{-1} b, sums in double
+  if (dlive) {
+    double s0 = 0.0, s1 = 0.0;
+    const int k0 = dpart * kp;
+    if (pre) {
 #pragma unroll
-        for (int q = 0; q < kRows; ++q)
-#pragma unroll
-          for (int j = 0; j < kSeg; ++j) {
-            const int r = r0 + q * NW, k = lane + kWave * j;
-            c[q][j] = (r < a.m && k < a.m) ? cm[(int64_t)r * a.m + k] : T(0);
-          }
-#pragma unroll
-        for (int q = 0; q < kRows; ++q) {
-          double s = 0.0;
-#pragma unroll
-          for (int j = 0; j < kSeg; ++j)
-            if (lane + kWave * j < a.m) s += (double)c[q][j] * (double)b[lane + kWave * j];
-          s = wave_sum(s);
-          if (lane == 0 && r0 + q * NW < a.m) x[r0 + q * NW] = (T)s;
-        }
-      }
-    };
-    if (a.offm >= 0) dense(sm + a.offm);
-    else dense(a.cinv);
+      for (int q = 0; q < kTailDenseReg; ++q)
+        if (q < kp) (q & 1 ? s1 : s0) += (double)cr[q] * (double)db[k0 + q];
+    } else {
+      const int k1 = k0 + kp < m ? k0 + kp : m;
+#pragma unroll 8
+      for (int k = k0; k < k1; ++k) s0 += (double)a.cinv[(int64_t)k * m + drow] * (double)db[k];
+    }
+    dp[dpart * m + drow] = s0 + s1;
+  }
+  __syncthreads();
+  if (tid < m) {
+    double s = 0.0;
+    for (int q = 0; q < P; ++q) s += dp[q * m + tid];
+    dx[tid] = (T)s;
   }
   __syncthreads();
   // ascent: coarse correction, post-smoothing
+  const int kend = (a.degree - 1) & 1;   // buffer that the pre-smoothing left the iterate in
+#pragma unroll 1
   for (int l = a.nlev - 1; l >= 0; --l) {
     const TailLevel<T> &lv = a.lv[l];
-    const TailGrid g = tail_grid(lv.n);
-    const int N = g.N;
-    T *b = sm + lv.off, *x = b + 2 * N;
-    const int Lc = lv.n + 1;
-    const bool coarsest = l + 1 == a.nlev;
-    const TailGrid gc = coarsest ? TailGrid{Lc, 0, Lc * Lc} : tail_grid(lv.n / 2);
-    const T *xc = coarsest ? sm + a.offc + a.m : sm + a.lv[l + 1].off + 2 * gc.N;
-    int I, J;
-    if (class_node(grp, gi, lv.n, I, J)) {
-      const int k = g.at(I, J);
-      T s0, s1;
-      tail_prolong<T>(xc, gc, coarsest, I, J, s0, s1);
-      x[k] += s0;
-      x[N + k] += s1;
+    const Place pl = place(lv.n);
+    V2<T> x[2];
+    b[0] = bs[2 * (kTailThreads * l) + tid];
+    b[1] = bs[2 * (kTailThreads * l) + kTailThreads + tid];
+    if (pl.in[1]) {
+      const int Ib = 2 * (pl.i >> 1), Jb = 2 * (pl.j >> 1), A = 2 * (pl.i & 1), B = 2 * (pl.j & 1) + half;
+      const V2<T> *p = buf(l, kend) + pl.at + half * kTailHW;
+      x[0] = p[0];
+      x[1] = p[kTailPL];
+      auto add = [&](auto c) {
+        const V2<T> p0 = tail_prolong<T>(c, A, B), p1 = tail_prolong<T>(c, A + 1, B);
+        x[0] = V2<T>{x[0].x + p0.x, x[0].y + p0.y};
+        x[1] = V2<T>{x[1].x + p1.x, x[1].y + p1.y};
+      };
+      if (l + 1 == a.nlev) {
+        const int Lc = lv.n + 1;
+        add([&](int ai, int bj) -> V2<T> {
+          const int q = (Jb + bj) * Lc + Ib + ai;
+          return V2<T>{dx[q], dx[Lc * Lc + q]};
+        });
+      } else {   // the next level's iterate: the buffer that its post-smoothing ended on
+        const V2<T> *xc = buf(l + 1, kend ^ (a.degree & 1));
+        add([&](int ai, int bj) -> V2<T> { return xc[tail_at(Ib + ai, Jb + bj)]; });
+      }
     }
+    put(buf(l, kend), pl, x);
     __syncthreads();
-    cheb_step(l, true, T(0), lv.s);
-    for (int j = 0; j + 1 < a.degree; ++j) cheb_step(l, false, lv.c1[j], lv.c2[j]);
-    (void)b;
-  }
-  {   // result of the first level in row-major order, Dirichlet nodes included (0)
-    const TailGrid g = tail_grid(a.lv[0].n);
-    const int NG = g.L * g.L;
-    const T *x = sm + a.lv[0].off + 2 * g.N;
-    for (int i = tid; i < NG; i += kTailThreads) {
-      const int k = g.at(i % g.L, i / g.L);
-      xg[i] = x[k];
-      xg[NG + i] = x[g.N + k];
+    int k = kend;
+#pragma unroll 1
+    for (int j = 0; j < a.degree; ++j, k ^= 1) {
+      if (j == 0) d[0] = d[1] = V2<T>{T(0), T(0)};
+      cheb_step(lv, pl, buf(l, k), j == 0 ? T(0) : lv.c1[j - 1], j == 0 ? lv.s : lv.c2[j - 1], x);
+      if (l == 0 && j + 1 == a.degree) break;   // the result goes to device memory
+      put(buf(l, k ^ 1), pl, x);
+      __syncthreads();
+    }
+    if (l == 0 && pl.j < lv.n) {
+      const int L = 2 * lv.n + 1, NG = L * L, r = (2 * pl.j + half) * L + 2 * pl.i;
+      const V2<T> v0 = pl.in[0] ? x[0] : V2<T>{T(0), T(0)}, v1 = pl.in[1] ? x[1] : V2<T>{T(0), T(0)};
+      xg[r] = v0.x;
+      xg[r + 1] = v1.x;
+      xg[NG + r] = v0.y;
+      xg[NG + r + 1] = v1.y;
     }
   }
 }
@@ -365,6 +325,8 @@ __global__ void __launch_bounds__(kTailThreads) k_mg_tail(TailArgs<T> a) {
 // the dense coarsest solve of k_dense_mv and the linear prolongation of k_p1_prolong_add.
 // Node r of a level belongs to thread r mod 1024 in every pass, so its search direction stays
 // in that thread's registers.
+
+constexpr int kPTailThreads = 1024;
 
 // (A x)_r on a P1 level of n cells (row-major x, side L = n + 1), as k_p1 sums it
 template <typename T>
@@ -394,7 +356,7 @@ __device__ __forceinline__ T p1_dinv(const T *tb, int n, int r) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
+__global__ void __launch_bounds__(kPTailThreads) k_p1_tail(PTailArgs<T> a) {
   extern __shared__ unsigned char ptail_smem[];
   T *sm = reinterpret_cast<T *>(ptail_smem);
   const int tid = threadIdx.x;
@@ -402,14 +364,14 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
   T *xg = a.x + (int64_t)blockIdx.y * a.lb;
   {   // the first level's right-hand side, the tables, the dense inverse (when in LDS)
     const int L0 = a.lv[0].n + 1, N0 = L0 * L0;
-    for (int r = tid; r < N0; r += kTailThreads) sm[a.lv[0].off + r] = bg[r];
+    for (int r = tid; r < N0; r += kPTailThreads) sm[a.lv[0].off + r] = bg[r];
     for (int l = 0; l < a.nlev; ++l)
-      for (int i = tid; i < kPTailTab; i += kTailThreads) {
+      for (int i = tid; i < kPTailTab; i += kPTailThreads) {
         const P1Table<T> &tb = *a.lv[l].tab;
         sm[a.offt + l * kPTailTab + i] = i < 9 * kP1Nbr ? tb.coef[i / kP1Nbr][i % kP1Nbr] : tb.dinv[i - 9 * kP1Nbr];
       }
     if (a.offm >= 0)
-      for (int i = tid; i < a.m * a.m; i += kTailThreads) sm[a.offm + i] = a.cinv[i];
+      for (int i = tid; i < a.m * a.m; i += kPTailThreads) sm[a.offm + i] = a.cinv[i];
   }
   __syncthreads();
   T *x2 = sm + a.offx2;
@@ -425,7 +387,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
     if (zero) {   // x = d = c2[0] D^{-1} b
 #pragma unroll
       for (int q = 0; q < kPTailPer; ++q) {
-        const int r = tid + kTailThreads * q;
+        const int r = tid + kPTailThreads * q;
         if (r < N) {
           const T z = lv.c2[0] * (p1_dinv(tb, n, r) * b[r]);
           dreg[q] = z;
@@ -442,7 +404,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
     for (int k = k0; k < a.degree; ++k) {
 #pragma unroll
       for (int q = 0; q < kPTailPer; ++q) {
-        const int r = tid + kTailThreads * q;
+        const int r = tid + kPTailThreads * q;
         if (r < N) {
           const T sum = p1_apply(tb, pin, src, n, r);
           const T z = p1_dinv(tb, n, r) * (b[r] - sum);
@@ -457,7 +419,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
       dst = t;
     }
     if (src != x) {   // an odd number of steps from x left the result in the second buffer
-      for (int r = tid; r < N; r += kTailThreads) x[r] = src[r];
+      for (int r = tid; r < N; r += kPTailThreads) x[r] = src[r];
       __syncthreads();
     }
   };
@@ -469,12 +431,12 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
     T *b = sm + lv.off, *x = b + N;
     smooth(l, true);
     const int pin = lv.tab->pin;
-    for (int r = tid; r < N; r += kTailThreads) x2[r] = b[r] - p1_apply(tb, pin, x, n, r);
+    for (int r = tid; r < N; r += kPTailThreads) x2[r] = b[r] - p1_apply(tb, pin, x, n, r);
     __syncthreads();
     const int nc = n / 2, Lc = nc + 1;
     const bool coarsest = l + 1 == a.nlev;
     T *bc = coarsest ? sm + a.offc : sm + a.lv[l + 1].off;
-    for (int q = tid; q < Lc * Lc; q += kTailThreads) {
+    for (int q = tid; q < Lc * Lc; q += kPTailThreads) {
       if (q == 0) {
         bc[0] = T(0);
         continue;
@@ -496,7 +458,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
     T *x = sm + a.offc + a.m;
     const T *cm = a.offm >= 0 ? sm + a.offm : a.cinv;
     const int w = tid / kWave, lane = tid % kWave;
-    for (int r = w; r < a.m; r += kTailThreads / kWave) {
+    for (int r = w; r < a.m; r += kPTailThreads / kWave) {
       double s = 0.0;
       for (int k = lane; k < a.m; k += kWave) s += (double)cm[(int64_t)r * a.m + k] * (double)b[k];
       s = wave_sum(s);
@@ -510,7 +472,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
     const int n = lv.n, L = n + 1, N = L * L, Lc = n / 2 + 1;
     T *x = sm + lv.off + N;
     const T *xc = l + 1 == a.nlev ? sm + a.offc + a.m : sm + a.lv[l + 1].off + Lc * Lc;
-    for (int r = tid; r < N; r += kTailThreads) {
+    for (int r = tid; r < N; r += kPTailThreads) {
       if (r == 0) continue;
       const int i = r % L, j = r / L, ci = i >> 1, cj = j >> 1;
       auto cv = [&](int u, int v) -> T {
@@ -530,7 +492,7 @@ __global__ void __launch_bounds__(kTailThreads) k_p1_tail(PTailArgs<T> a) {
   {
     const int N0 = (a.lv[0].n + 1) * (a.lv[0].n + 1);
     const T *x = sm + a.lv[0].off + N0;
-    for (int r = tid; r < N0; r += kTailThreads) xg[r] = x[r];
+    for (int r = tid; r < N0; r += kPTailThreads) xg[r] = x[r];
   }
 }
 
@@ -562,14 +524,16 @@ int tail_lds_limit() {
 
 template <typename T>
 void mg_tail(const TailArgs<T> &a, hipStream_t s, int K) {
-  FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kTailMax && a.degree >= 1 && a.degree <= kTailDeg, FSI_E_ARG,
+  FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kTailMax && a.degree >= 2 && a.degree <= kTailDeg, FSI_E_ARG,
               "coarse tail shape out of range");
   FSI_REQUIRE(a.lv[0].n <= kTailMaxN, FSI_E_ARG, "coarse tail level too fine");
-  FSI_REQUIRE(a.m <= kTailDenseMax, FSI_E_ARG, "coarsest level too large for the tail");
+  for (int l = 0; l + 1 < a.nlev; ++l)
+    FSI_REQUIRE(a.lv[l + 1].n * 2 == a.lv[l].n, FSI_E_ARG, "coarse tail levels not nested");
+  FSI_REQUIRE(a.m == 2 * (a.lv[a.nlev - 1].n + 1) * (a.lv[a.nlev - 1].n + 1) && a.m <= kTailDenseMax, FSI_E_ARG,
+              "coarse tail coarsest level out of range");
   FSI_REQUIRE(K >= 1 && K <= 65535 && (K == 1 || a.lb > 0), FSI_E_ARG, "lane count out of range");
-  const int bytes = a.lds * (int)sizeof(T);
-  FSI_REQUIRE(bytes <= tail_lds_limit(), FSI_E_ARG, "coarse tail exceeds the LDS of a block");
-  hipLaunchKernelGGL(k_mg_tail<T>, dim3(1, (unsigned)K), dim3(kTailThreads), bytes, s, a);
+  FSI_REQUIRE(a.lds <= tail_lds_limit(), FSI_E_ARG, "coarse tail exceeds the LDS of a block");
+  hipLaunchKernelGGL(k_mg_tail<T>, dim3(1, (unsigned)K), dim3(kTailThreads), a.lds, s, a);
   FSI_CHECK_LAUNCH();
 }
 template void mg_tail<double>(const TailArgs<double> &, hipStream_t, int);
@@ -579,7 +543,7 @@ template <typename T>
 void p1_tail(const PTailArgs<T> &a, hipStream_t s, int K) {
   FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kPTailMax && a.degree >= 1 && a.degree <= kPTailDeg, FSI_E_ARG,
               "pressure tail shape out of range");
-  FSI_REQUIRE(a.lv[0].n <= kPTailMaxN && (a.lv[0].n + 1) * (a.lv[0].n + 1) <= kPTailPer * kTailThreads, FSI_E_ARG,
+  FSI_REQUIRE(a.lv[0].n <= kPTailMaxN && (a.lv[0].n + 1) * (a.lv[0].n + 1) <= kPTailPer * kPTailThreads, FSI_E_ARG,
               "pressure tail level too fine");
   for (int l = 0; l + 1 < a.nlev; ++l)
     FSI_REQUIRE(a.lv[l + 1].n * 2 == a.lv[l].n, FSI_E_ARG, "pressure tail levels not nested");
@@ -588,7 +552,7 @@ void p1_tail(const PTailArgs<T> &a, hipStream_t s, int K) {
   FSI_REQUIRE(K >= 1 && K <= 65535 && (K == 1 || a.lb > 0), FSI_E_ARG, "lane count out of range");
   const int bytes = a.lds * (int)sizeof(T);
   FSI_REQUIRE(bytes <= tail_lds_limit(), FSI_E_ARG, "pressure tail exceeds the LDS of a block");
-  hipLaunchKernelGGL(k_p1_tail<T>, dim3(1, (unsigned)K), dim3(kTailThreads), bytes, s, a);
+  hipLaunchKernelGGL(k_p1_tail<T>, dim3(1, (unsigned)K), dim3(kPTailThreads), bytes, s, a);
   FSI_CHECK_LAUNCH();
 }
 template void p1_tail<double>(const PTailArgs<double> &, hipStream_t, int);

@@ -431,10 +431,6 @@ template <> const StencilTable<float> *stab<float>(const MgLevel &L) {
 template <typename T> static const P1Table<T> *p1tab(const MgLevel &L) {
   return (const P1Table<T> *)(std::is_same<T, double>::value ? L.p1tab64.p : L.p1tab32.p);
 }
-template <typename T> static const P2RestrTable<T> *rtab(const Mg &mg) {
-  return (const P2RestrTable<T> *)(std::is_same<T, double>::value ? mg.rtab64.p : mg.rtab32.p);
-}
-
 // The arguments of the one-launch coarse end of the velocity V-cycle from level l (l >= 1,
 // where the restricted right-hand side vanishes at Dirichlet nodes), or false when the
 // remaining levels do not fit it (too fine, too many, smoothing degree or LDS).
@@ -442,20 +438,17 @@ template <typename T>
 static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, TailArgs<T> &a) {
   const int last = (int)mg.lv.size() - 1;   // the dense coarsest level
   const int nlev = last - l;
-  if (!mg.stencil || mg.comps != 2 || l < 1 || nlev < 1 || nlev > kTailMax || degree < 1 || degree > kTailDeg ||
+  if (!mg.stencil || mg.comps != 2 || l < 1 || nlev < 1 || nlev > kTailMax || degree < 2 || degree > kTailDeg ||
       mg.lv[l].n > kTailMaxN)
     return false;
   a = TailArgs<T>{};
   a.nlev = nlev;
   a.degree = degree;
-  int off = 0;
   for (int k = 0; k < nlev; ++k) {
     const MgLevel &L = mg.lv[l + k];
     TailLevel<T> &t = a.lv[k];
     t.n = L.n;
-    t.off = off;
-    off += 4 * tail_plane_entries(L.n);
-    t.tab = stab<T>(L);
+    t.cf = afc<T>(L);
     // the coefficients of cheb3_coefs on [lmax / 15, lmax]
     const double lmax = L.lmax, lmin = L.lmax / 15.0;
     const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin), sigma = theta / delta;
@@ -468,24 +461,16 @@ static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, T
       rho = rho1;
     }
   }
-  a.offd = off;
-  off += 2 * tail_plane_entries(mg.lv[l].n);
-  a.offc = off;
   a.m = (int)mg.ncoarse;
   FSI_REQUIRE(a.m == 2 * (int)mg.lv[last].nodes, FSI_E_STATE, "coarsest level size");
   if (a.m > kTailDenseMax) return false;
-  off += 2 * a.m;
-  a.offt = off;
-  off += nlev * kTailTab + kTailRw;
-  a.lds = off;
-  if ((int64_t)a.lds * (int64_t)sizeof(T) > tail_lds_limit()) return false;
-  // the dense inverse in LDS too when it fits (loaded with the tables at the start)
-  a.offm = -1;
-  if ((int64_t)(off + (int64_t)a.m * a.m) * (int64_t)sizeof(T) <= tail_lds_limit()) {
-    a.offm = off;
-    a.lds = off + a.m * a.m;
-  }
-  a.rt = rtab<T>(mg);
+  int64_t bytes = (int64_t)nlev * (2 * kTailLevelV2 + 2 * 512) * 2 * (int64_t)sizeof(T) +
+                  (2 * a.m + kTailDenseReg) * (int64_t)sizeof(T);
+  bytes = (bytes + 7) / 8 * 8;
+  a.offp = (int)bytes;
+  bytes += 512 * 8;   // one partial sum per thread
+  if (bytes > tail_lds_limit()) return false;
+  a.lds = (int)bytes;
   a.cinv = Pr<T>::cinv(mg);
   a.b = b;
   a.x = x;
