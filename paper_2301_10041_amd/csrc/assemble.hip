@@ -670,13 +670,6 @@ void build_fluid(Ctx &c) {
     upload_bytes(c.divtab64, &t64, sizeof(t64), s);
     upload_bytes(c.divtab32, &t32, sizeof(t32), s);
   }
-  {
-    P1Table<double> t64;
-    P1Table<float> t32;
-    p1_tables(n, EM_MP, 0, t64, t32);
-    upload_bytes(c.mptab64, &t64, sizeof(t64), s);
-    upload_bytes(c.mptab32, &t32, sizeof(t32), s);
-  }
   c.bnd.alloc(n2);
   hipLaunchKernelGGL(k_p2_boundary_flags, dim3(g2), dim3(256), 0, s, n, c.bnd.p);
   FSI_CHECK_LAUNCH();
@@ -1254,10 +1247,10 @@ static void coarse_inverse_spd_device(Mg &mg, hipStream_t s) {
 }
 
 size_t Mg::bytes() const {
-  size_t b = cinv.bytes() + cinv32.bytes() + rtab64.bytes() + rtab32.bytes();
+  size_t b = cinv.bytes() + cinv32.bytes();
   for (auto &L : lv) {
     b += L.A.bytes() + L.P.bytes() + L.R.bytes() + L.dinv.bytes() + L.dinv32.bytes() + L.stab64.bytes() +
-         L.stab32.bytes() + L.p1tab64.bytes() + L.p1tab32.bytes() + L.q2tab64.bytes() + L.q2tab32.bytes();
+         L.stab32.bytes() + L.q2tab64.bytes() + L.q2tab32.bytes();
     for (int i = 0; i < 5; ++i) b += L.w64[i].bytes() + L.w32[i].bytes();
   }
   return b;
@@ -1319,13 +1312,6 @@ void build_multigrid(Ctx &c) {
       FSI_HIP(hipMemcpyAsync(U.stab32.p, &t32, sizeof(t32), hipMemcpyHostToDevice, s));
       FSI_HIP(hipStreamSynchronize(s));
     }
-    if (m >= 2) {
-      P1Table<double> t64;
-      P1Table<float> t32;
-      p1_tables(m, EM_LP, 1, t64, t32);
-      upload_bytes(P.p1tab64, &t64, sizeof(t64), s);
-      upload_bytes(P.p1tab32, &t32, sizeof(t32), s);
-    }
     P.lmax = 1.1 * power_lmax(P, 1, s);
     if (l + 1 < ns.size()) {
       int64_t nc2 = (int64_t)(m + 1) * (m + 1);          // coarse P2 nodes = (2 (m/2) + 1)^2
@@ -1354,16 +1340,15 @@ void build_multigrid(Ctx &c) {
       P.w64[i].alloc(P.nodes);
     }
   }
-  {
+  {   // (checks the compiled transfer weights)
     P2RestrTable<double> t64;
     P2RestrTable<float> t32;
     p2_restrict_tables(t64, t32);
-    upload_bytes(c.mgu.rtab64, &t64, sizeof(t64), s);
-    upload_bytes(c.mgu.rtab32, &t32, sizeof(t32), s);
   }
   if (nu < ns.size()) coarse_inverse_spd_device(c.mgu, s);
   else coarse_inverse(c.mgu, s);
   coarse_inverse(c.mgp, s);
+  (void)p1_tail_lds_limit();
   (void)tail_lds_limit();   // the LDS grant of the coarse-tail launches, outside any graph capture
   FSI_HIP(hipStreamSynchronize(s));
 }

@@ -60,7 +60,6 @@ struct MgLevel {
   DevBuf<unsigned char> stab64, stab32;   // StencilTable<double/float> (velocity levels)
   AfCoef<double> af64{};                  // the level's A_f entries (velocity levels)
   AfCoef<float> af32{};
-  DevBuf<unsigned char> p1tab64, p1tab32; // P1Table<double/float> of L_p (pressure levels)
   DevBuf<unsigned char> q2tab64, q2tab32; // Q2Table<double/float> (velocity levels of the Q2 pair)
 };
 
@@ -75,7 +74,6 @@ struct Mg {
   int64_t ncoarse = 0;     // unknowns of the coarsest level
   DevBuf<double> cinv;     // dense inverse of the coarsest operator (row major)
   DevBuf<float> cinv32;
-  DevBuf<unsigned char> rtab64, rtab32;   // P2RestrTable<double/float> (velocity)
   size_t bytes() const;
 };
 
@@ -110,7 +108,6 @@ struct Ctx {
   Csr Mp;                  // pressure mass, width 1
   DevBuf<double> Mp_dinv;  // 1 / diag(M_p)
   DevBuf<float> Mp_dinv32;
-  DevBuf<unsigned char> mptab64, mptab32;  // P1Table<double/float> of M_p
   DevBuf<unsigned char> divtab64, divtab32;  // DivTable<double/float> (B and B^T)
   DevBuf<unsigned char> bnd;  // 1 on boundary P2 nodes
 

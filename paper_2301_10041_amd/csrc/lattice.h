@@ -107,44 +107,74 @@ void p1_tables(int n, int which, int pin, P1Table<double> &t64, P1Table<float> &
 void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32);          // lattice.hip
 
 // Launchers (stream-ordered, no synchronisation) over K independent systems (lane =
-// blockIdx.y; each vector is a per-lane view, see LP; K = 1 for one system).  Vectors are
-// component-major with the level's node count as stride.
-template <typename T, int MODE>   // SP_APPLY, SP_RESID or SP_CHEB as for the A_f stencil
-void p1_launch(int n, const P1Table<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<T> y, T c1, T c2,
-               hipStream_t s, int K = 1);
-// d = x = scale D^{-1} b (first Chebyshev step from zero), class-wise diagonal
-template <typename T>
-void p1_first(int n, const P1Table<T> *tab, LP<const T> b, T scale, LP<T> d, LP<T> x, hipStream_t s, int K = 1);
-// y += P xc (fine grid nf; coarse vector on the nf / 2 grid)
-template <typename T>
-void p1_prolong_add(int nf, LP<const T> xc, LP<T> y, hipStream_t s, int K = 1);
-// bc = R r (pressure levels; the velocity levels restrict in resid_restrict)
-template <typename T>
-void p1_restrict(int nf, LP<const T> r, LP<T> bc, hipStream_t s, int K = 1);
-// S Chebyshev steps on a P1 operator in one launch (lattice.hip, k_p1_multi): from zero or
-// from x, the result to y or combined into the Schur output z = a x + b2 w (pinned entry
-// r[0], per-tile parts of sum r z).  Lane strides: lb for b, x, y, w; lz for z, r, r64; lp
-// for part (p1_multi_tiles(n) parts per lane).
-constexpr int kP1T = 16, kP1C = 64;   // tile rows and columns (256 threads)
-enum { P1_OUT_X = 0, P1_OUT_SCHUR = 1 };
-template <typename T, typename TZ>
-struct P1MultiArgs {
+// blockIdx.y; each vector is a per-lane view, K = 1 for one system).
+
+// The pressure part of the A11 preconditioner (pressure.hip).  L_p V-cycle with two Chebyshev steps
+// before and after the coarse correction; s, c1, c2: the coefficients of p1_cheb_coefs.
+// Descent of a level of n cells (even): x = the steps from zero for right-hand side b (of type TB,
+// rounded to T; b[0] read as 0), bc = R (b - L_p x).  Lane strides lb, lx, lc.
+template <typename T, typename TB>
+struct P1DownArgs {
   int n;
-  const P1Table<T> *tab;
-  const T *b, *x;
-  T *y;
-  T c1[3], c2[3];   // step k: d = c1[k] d + c2[k] D^{-1} (b - A x); from zero c2[0] scales D^{-1} b
-  TZ *z;
-  const TZ *r;
-  const double *r64;
-  const T *w;
-  T a, b2;
-  double *part;
-  int64_t lb, lz, lp;
+  const TB *b;
+  T *x, *bc;
+  T s, c1, c2;
+  int64_t lb, lx, lc;
 };
-int p1_multi_tiles(int n);
-template <typename T, typename TZ, int S, bool ZERO, int OUT>
-void p1_multi(const P1MultiArgs<T, TZ> &a, hipStream_t s, int K = 1);
+template <typename T, typename TB>
+void p1_down(const P1DownArgs<T, TB> &a, hipStream_t s, int K);
+// Ascent: y = the steps from x + P xc (P1_Y); on the finest level z = nu M_p^{-1} b + rdt y with the
+// pinned entry z[0] = b[0] rounded through T, the mass solve from zero (scale ms[0], steps m1, m2; mdinv
+// = 12 / h^2, munit = h^2 / 12), and per tile the part of sum r64 z (b z when r64 is null) at
+// part, if given (P1_Z; p1_up_tiles(n) parts per lane); the same with y read from xc (P1_ZW).  Lane
+// strides: lb for b, lx for x and y, lc for xc, lz for z and r64, lp for part.
+enum { P1_Y = 0, P1_Z = 1, P1_ZW = 2 };
+template <typename T, typename TB, typename TZ>
+struct P1UpArgs {
+  int n;
+  const TB *b;
+  const T *x, *xc;
+  T *y;
+  T c1[2], c2[2];
+  TZ *z;
+  const double *r64;
+  T ms[1], m1[2], m2[2], mdinv, munit, nu, rdt;
+  double *part;
+  int64_t lb, lx, lc, lz, lp;
+};
+template <typename T, typename TB, typename TZ, int OUT>
+void p1_up(const P1UpArgs<T, TB, TZ> &a, hipStream_t s, int K);
+int p1_up_tiles(int n);
+// The coarse end in one launch per system: levels lv[0..nlev) (n <= kPTailMaxN cells, each the next
+// one's fine level) and the coarsest level's dense inverse cinv (m x m).  LDS (offsets in T): level
+// l's two buffers at lv[l].off ((n + 3)^2 each), its right-hand side at lv[l].offb (l > 0), the
+// second buffer of the mass solve at offw (OUT), all zeroed up to offz; the coarsest b and x at
+// offc (m each), its inverse at offm when it fits (else -1: read from device memory); lds = the
+// total.  Result: x, or with OUT (lv[0] the finest level) z and one part of sum r z as p1_up's.
+constexpr int kPTailMax = 6, kPTailMaxN = 64, kPTailPer = 5, kPTailDenseMax = 6 * 64;
+template <typename T>
+struct PTailLevel {
+  int n, off, offb;
+  T c1[2], c2[2];
+};
+template <typename T, typename TB, typename TZ>
+struct PTailArgs {
+  int nlev;
+  PTailLevel<T> lv[kPTailMax];
+  int offc, offm, offw, offz, m, lds;
+  const T *cinv;
+  const TB *b;
+  T *x;
+  TZ *z;
+  const double *r64;
+  T ms, m1[2], m2[2], mdinv, munit, nu, rdt;
+  double *part;
+  int64_t lb, lx, lz, lp;
+};
+template <typename T, typename TB, typename TZ, bool OUT>
+void p1_tail(const PTailArgs<T, TB, TZ> &a, hipStream_t s, int K);
+int p1_tail_lds_limit();
+
 // The coarse end of a velocity V-cycle in one launch per system (mgtail.hip): levels
 // lv[0..nlev) (n <= kTailMaxN cells, each the next one's fine level) and the coarsest
 // level's dense inverse cinv (m x m, symmetric).  LDS: two buffers of kTailLevelV2 nodes per
@@ -175,36 +205,6 @@ struct TailArgs {
 };
 template <typename T>
 void mg_tail(const TailArgs<T> &a, hipStream_t s, int K = 1);
-// The coarse end of a pressure (P1) V-cycle in one launch per system (mgtail.hip): levels
-// lv[0..nlev) of at most kPTailMaxN cells (each the next one's fine level) and the dense
-// inverse of the coarsest.  LDS (offsets in T): level l's b at lv[l].off and x right after it
-// ((n + 1)^2 each, row-major), a shared second iterate at offx2 ((n + 1)^2 of lv[0]: the
-// ping-pong buffer of the smoothing steps, then the residual), the coarsest b at offc and x
-// after it (m each), the P1 tables of the levels (kPTailTab each) at offt, and the dense
-// inverse at offm when it fits (else offm = -1: read from device memory); lds = the total.
-// b and x in device memory: the first level's right-hand side and result (lane stride lb).
-// Each node's search direction stays in a register of the thread that owns it
-// (kPTailPer nodes per thread).
-constexpr int kPTailMax = 6, kPTailDeg = 4, kPTailMaxN = 64, kPTailPer = 5, kPTailDenseMax = 6 * 64;
-constexpr int kPTailTab = 9 * kP1Nbr + 9;   // coef[9][7], dinv[9]
-template <typename T>
-struct PTailLevel {
-  int n, off;
-  const P1Table<T> *tab;
-  T c1[kPTailDeg], c2[kPTailDeg];   // p1_cheb_coefs of the level
-};
-template <typename T>
-struct PTailArgs {
-  int nlev, degree;
-  PTailLevel<T> lv[kPTailMax];
-  int offx2, offc, offt, offm, m, lds;
-  const T *cinv;
-  const T *b;
-  T *x;
-  int64_t lb;
-};
-template <typename T>
-void p1_tail(const PTailArgs<T> &a, hipStream_t s, int K = 1);
 // bc = R (b - A_f x) in one launch (stencil.hip): the residual lives only in LDS
 template <typename T>
 void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K = 1);

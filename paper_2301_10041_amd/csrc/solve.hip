@@ -174,40 +174,8 @@ __global__ void k_q_pres(TZ *z, const TZ *r, const T *xl, const T *mpinv, T nu, 
 }
 
 template <typename T>
-__global__ void k_set_pinned(T *z, const T *r, int64_t ls) {   // lane blockIdx.y at + lane ls
-  if (threadIdx.x == 0 && blockIdx.x == 0) z[(int64_t)blockIdx.y * ls] = r[(int64_t)blockIdx.y * ls];
-}
-
-// The pressure part of the A11 preconditioner's output with the dot product r . z of its
-// entries: z = a x + b y computed in T and stored as TZ, except z[0] = r[0] rounded through T
-// (pinned entry), and block k of kPresDotBlocks stores its part of sum r z (FP64, fixed
-// partition and order) at part[k]; the sums take r64 in place of r when given (an FP32
-// output of the mixed form, r its FP32 copy).  Lane blockIdx.y: z, r, r64 at + lane ls, x, y
-// at + lane lx, part at + lane lp.
-constexpr int kPresDotBlocks = 256;
-// Parts of r . z from the pressure output: one per tile of the fused launch (matrix-free
-// pressure hierarchy) or kPresDotBlocks; the slots per lane hold either
-static int pres_dot_slots(int n) { return std::max(kPresDotBlocks, p1_multi_tiles(n)); }
-static int pres_dot_count(const Ctx &c) { return c.mgp.stencil ? p1_multi_tiles(c.n) : kPresDotBlocks; }
-template <typename TZ, typename T>
-__global__ void __launch_bounds__(kRedBlock) k_pres_out_dot(TZ *z, const TZ *r, const T *x, const T *y, T a, T b,
-                                                            int64_t n, int64_t ls, int64_t lx, double *part,
-                                                            int64_t lp, const double *r64) {
-  z += (int64_t)blockIdx.y * ls;
-  r += (int64_t)blockIdx.y * ls;
-  if (r64) r64 += (int64_t)blockIdx.y * ls;
-  x += (int64_t)blockIdx.y * lx;
-  y += (int64_t)blockIdx.y * lx;
-  const int64_t chunk = (n + kPresDotBlocks - 1) / kPresDotBlocks;
-  const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-  double s = 0.0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kRedBlock) {
-    const TZ v = (TZ)(i == 0 ? (T)r[0] : a * x[i] + b * y[i]);
-    z[i] = v;
-    s += (r64 ? r64[i] : (double)r[i]) * (double)v;
-  }
-  const double t = block_sum(s);
-  if (threadIdx.x == 0) part[(int64_t)blockIdx.y * lp + blockIdx.x] = t;
+__global__ void k_set_pinned(T *z, const T *r) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) z[0] = r[0];
 }
 
 // z[0] = r[0] rounded through T (the value an FP32 preconditioner would pass on)
@@ -293,8 +261,6 @@ static T *chebyshev(int64_t nrows, const int *rp, const int *col, const T *val, 
   return x;
 }
 
-// The same Chebyshev iteration with matrix-free products: first(scale, d, x) does the
-// step from zero (d = x = scale D^{-1} b), step(x, x2, c1, c2) one step from x into x2.
 // The same iteration on the velocity levels of the Q2 pair with the class stencils
 // (q2_stencil) in place of the assembled rows; the first step from zero as chebyshev's.
 template <typename T>
@@ -324,37 +290,12 @@ static T *chebyshev_q2(const MgLevel &L, const Q2Table<T> *tab, const T *dinv, d
   return x;
 }
 
-template <typename T, typename First, typename Step>
-static T *chebyshev_mf(First first, Step step, double lmin, double lmax, int steps, T *x, T *x2,
-                       bool zero_init, hipStream_t s, Prof *prof) {
-  const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
-  const double sigma = theta / delta;
-  double rho = 1.0 / sigma;
-  if (zero_init) {
-    first((T)(1.0 / theta), x);
-  } else {
-    if (prof) prof->begin(s);
-    step(x, x2, (T)0, (T)(1.0 / theta));
-    if (prof) prof->end(s);
-    std::swap(x, x2);
-  }
-  for (int k = 1; k < steps; ++k) {
-    double rho1 = 1.0 / (2.0 * sigma - rho);
-    if (prof) prof->begin(s);
-    step(x, x2, (T)(rho1 * rho), (T)(2.0 * rho1 / delta));
-    if (prof) prof->end(s);
-    std::swap(x, x2);
-    rho = rho1;
-  }
-  return x;
-}
-
 // The level's A_f entries in the arithmetic of the cycle
 template <typename T> static const AfCoef<T> &afc(const MgLevel &L);
 template <> const AfCoef<double> &afc<double>(const MgLevel &L) { return L.af64; }
 template <> const AfCoef<float> &afc<float>(const MgLevel &L) { return L.af32; }
 
-// The Chebyshev coefficients of chebyshev_mf for three steps: s = 1 / theta, then (c1, c2) of
+// The Chebyshev coefficients of chebyshev for three steps: s = 1 / theta, then (c1, c2) of
 // the two later steps
 template <typename T>
 struct Cheb3Coef {
@@ -368,20 +309,7 @@ static Cheb3Coef<T> cheb3_coefs(double lmin, double lmax) {
                       (T)(2.0 * rho2 / delta)};
 }
 
-template <typename T>
-static T *chebyshev_p1(int n, const P1Table<T> *tab, double lmin, double lmax, int steps, const T *b,
-                       T *x, T *x2, T *d, bool zero_init, hipStream_t s, int K = 1, int64_t ls = 0) {
-  const LP<const T> lb(b, ls);
-  const LP<T> ld(d, ls);
-  return chebyshev_mf<T>([&](T sc, T *xo) { p1_first<T>(n, tab, lb, sc, ld, LP<T>(xo, ls), s, K); },
-                         [&](const T *xi, T *xo, T c1, T c2) {
-                           p1_launch<T, SP_CHEB>(n, tab, LP<const T>(xi, ls), lb, ld, LP<T>(xo, ls), c1, c2, s,
-                                                 K);
-                         },
-                         lmin, lmax, steps, x, x2, zero_init, s, nullptr);
-}
-
-// The Chebyshev coefficients of chebyshev_mf: step k updates d = c1[k] d + c2[k] D^{-1} r
+// The Chebyshev coefficients of chebyshev: step k updates d = c1[k] d + c2[k] D^{-1} r
 // (from zero, step 0 is x = d = c2[0] D^{-1} b; from x, c1[0] = 0).
 template <typename T>
 static void p1_cheb_coefs(double lmin, double lmax, int steps, T *c1, T *c2) {
@@ -397,40 +325,6 @@ static void p1_cheb_coefs(double lmin, double lmax, int steps, T *c1, T *c2) {
   }
 }
 
-// The steps of chebyshev_p1 (2 or 3, the same coefficients) in one launch (k_p1_multi): the
-// result goes to y.  Returns false for other step counts.
-template <typename T>
-static bool p1_cheb_fused(int n, const P1Table<T> *tab, double lmin, double lmax, int steps, const T *b, const T *x,
-                          T *y, bool zero, hipStream_t s, int K, int64_t ls) {
-  if (steps != 2 && steps != 3) return false;
-  P1MultiArgs<T, T> a{};
-  a.n = n;
-  a.tab = tab;
-  a.b = b;
-  a.x = x;
-  a.y = y;
-  a.lb = ls;
-  p1_cheb_coefs<T>(lmin, lmax, steps, a.c1, a.c2);
-  if (steps == 2) {
-    if (zero) p1_multi<T, T, 2, true, P1_OUT_X>(a, s, K);
-    else p1_multi<T, T, 2, false, P1_OUT_X>(a, s, K);
-  } else {
-    if (zero) p1_multi<T, T, 3, true, P1_OUT_X>(a, s, K);
-    else p1_multi<T, T, 3, false, P1_OUT_X>(a, s, K);
-  }
-  return true;
-}
-
-template <typename T> static const StencilTable<T> *stab(const MgLevel &L);
-template <> const StencilTable<double> *stab<double>(const MgLevel &L) {
-  return (const StencilTable<double> *)L.stab64.p;
-}
-template <> const StencilTable<float> *stab<float>(const MgLevel &L) {
-  return (const StencilTable<float> *)L.stab32.p;
-}
-template <typename T> static const P1Table<T> *p1tab(const MgLevel &L) {
-  return (const P1Table<T> *)(std::is_same<T, double>::value ? L.p1tab64.p : L.p1tab32.p);
-}
 // The arguments of the one-launch coarse end of the velocity V-cycle from level l (l >= 1,
 // where the restricted right-hand side vanishes at Dirichlet nodes), or false when the
 // remaining levels do not fit it (too fine, too many, smoothing degree or LDS).
@@ -479,48 +373,45 @@ static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, T
 }
 
 // The arguments of the one-launch coarse end of the pressure V-cycle from level l, or false
-// when the remaining levels do not fit it (too fine, too many, smoothing degree or LDS).
-template <typename T>
-static bool p1_tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, PTailArgs<T> &a) {
+// when the remaining levels do not fit it (too fine, too many or LDS).  out: level l is the finest and
+// the launch adds the mass solve and the output (its arguments are the caller's).
+template <typename T, typename TB, typename TZ>
+static bool p1_tail_args(const Mg &mg, int l, bool out, PTailArgs<T, TB, TZ> &a) {
   const int last = (int)mg.lv.size() - 1;   // the dense coarsest level
   const int nlev = last - l;
-  if (!mg.stencil || mg.comps != 1 || nlev < 1 || nlev > kPTailMax || degree < 1 || degree > kPTailDeg ||
-      mg.lv[l].n > kPTailMaxN || (mg.lv[l].n + 1) * (mg.lv[l].n + 1) > kPTailPer * 1024)
-    return false;
-  a = PTailArgs<T>{};
+  if (!mg.tail || nlev < 1 || nlev > kPTailMax || mg.lv[l].n > kPTailMaxN) return false;
+  a = PTailArgs<T, TB, TZ>{};
   a.nlev = nlev;
-  a.degree = degree;
   int off = 0;
   for (int k = 0; k < nlev; ++k) {
     const MgLevel &L = mg.lv[l + k];
     PTailLevel<T> &t = a.lv[k];
     t.n = L.n;
     t.off = off;
-    off += 2 * (L.n + 1) * (L.n + 1);
-    t.tab = p1tab<T>(L);
-    // the coefficients of the per-level launches on [lmax / 30, lmax]
-    p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, degree, t.c1, t.c2);
+    off += 2 * (L.n + 3) * (L.n + 3);
+    p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, t.c1, t.c2);
   }
-  a.offx2 = off;
-  off += (mg.lv[l].n + 1) * (mg.lv[l].n + 1);
+  a.offw = off;
+  if (out) off += (mg.lv[l].n + 3) * (mg.lv[l].n + 3);
+  a.offz = off;
+  for (int k = 1; k < nlev; ++k) {
+    a.lv[k].offb = off;
+    off += (int)mg.lv[l + k].nodes;
+  }
   a.offc = off;
   a.m = (int)mg.ncoarse;
   FSI_REQUIRE(a.m == (int)mg.lv[last].nodes, FSI_E_STATE, "coarsest level size");
   if (a.m > kPTailDenseMax) return false;
   off += 2 * a.m;
-  a.offt = off;
-  off += nlev * kPTailTab;
-  a.lds = off;
-  if ((int64_t)a.lds * (int64_t)sizeof(T) > tail_lds_limit()) return false;
+  const int64_t room = p1_tail_lds_limit() - 256;   // 256: the reduction's static part
+  if (off * (int64_t)sizeof(T) > room) return false;
   a.offm = -1;
-  if ((int64_t)(off + (int64_t)a.m * a.m) * (int64_t)sizeof(T) <= tail_lds_limit()) {
+  if ((off + (int64_t)a.m * a.m) * (int64_t)sizeof(T) <= room) {
     a.offm = off;
-    a.lds = off + a.m * a.m;
+    off += a.m * a.m;
   }
+  a.lds = off;
   a.cinv = Pr<T>::cinv(mg);
-  a.b = b;
-  a.x = x;
-  a.lb = ls;
   return true;
 }
 
@@ -565,12 +456,6 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
       mg_tail<T>(ta, s, K);
       return x;
     }
-  } else {                  // the coarse end of the pressure cycle in one launch
-    PTailArgs<T> pa;
-    if (mg.tail && p1_tail_args<T>(mg, l, degree, b, x, ls, pa)) {
-      p1_tail<T>(pa, s, K);
-      return x;
-    }
   }
   if (mg.stencil) {   // matrix-free smoothing, residual and transfers
     if constexpr (W == 4) {
@@ -597,19 +482,7 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
       if (pl) pl->end(s);
       return out64 ? nullptr : y;
     } else {
-      auto smooth = [&](T *x0, T *x1, bool zero) -> T * {
-        if (p1_cheb_fused<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, zero ? x0 : x1, zero, s, K, ls))
-          return zero ? x0 : x1;
-        return chebyshev_p1<T>(L.n, p1tab<T>(L), lmin, lmax, degree, b, x0, x1, d, zero, s, K, ls);
-      };
-      T *xs = smooth(x, x2, true);
-      T *xo = (xs == x) ? x2 : x;
-      p1_launch<T, SP_RESID>(L.n, p1tab<T>(L), LP<const T>(xs, ls), LP<const T>(b, ls), LP<T>(), LP<T>(r, ls),
-                             (T)0, (T)0, s, K);
-      p1_restrict<T>(L.n, LP<const T>(r, ls), LP<T>(bc, lc), s, K);
-      T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s, nullptr, K);
-      p1_prolong_add<T>(L.n, LP<const T>(xc, lc), LP<T>(xs, ls), s, K);
-      return smooth(xs, xo, false);
+      FSI_REQUIRE(false, FSI_E_STATE, "the matrix-free pressure cycle is p1_cycle");
     }
   }
   // the Q2 pair's velocity levels: class stencils for the smoothing steps and the residual
@@ -642,6 +515,115 @@ template <> const float *mp_dinv<float>(Ctx &c) { return c.Mp_dinv32.p; }
 // 4 steps 163/201/81, 3 steps 144/204/83, 2 steps 229/228/92; 3 is the fastest overall)
 constexpr int kMpSteps = 3;
 
+// The pressure V-cycle on L_p from level l for right-hand side b (type TB, lane stride lb); returns
+// the level work vector that holds the result (lane stride: the level's nodes).  down and up: one
+// launch each per level, from kPTailMaxN cells on one launch for all that remains.
+template <typename T>
+static T *p1_cycle(Mg &mg, int l, const T *b, int64_t lb, hipStream_t s, int K);
+template <typename T, typename TB>
+static T *p1_descend(Mg &mg, int l, const TB *b, int64_t lb, hipStream_t s, int K) {
+  MgLevel &L = mg.lv[l], &C = mg.lv[l + 1];
+  FSI_REQUIRE((std::is_same<T, float>::value ? mg.degree32 : mg.degree) == 2, FSI_E_STATE,
+              "the matrix-free pressure cycle takes two steps");
+  T c1[2], c2[2], *bc = Pr<T>::w(C, 1);
+  p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, c1, c2);
+  P1DownArgs<T, TB> a{L.n, b, Pr<T>::w(L, 0), bc, c2[0], c1[1], c2[1], lb, L.nodes, C.nodes};
+  p1_down<T, TB>(a, s, K);
+  return p1_cycle<T>(mg, l + 1, bc, C.nodes, s, K);
+}
+template <typename T>
+static T *p1_cycle(Mg &mg, int l, const T *b, int64_t lb, hipStream_t s, int K) {
+  MgLevel &L = mg.lv[l];
+  T *x = Pr<T>::w(L, 0);
+  if (l + 1 == (int)mg.lv.size()) {
+    FSI_REQUIRE(K == 1 || lb == L.nodes, FSI_E_STATE, "the dense solve takes contiguous lanes");
+    dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), b, x, K, s);
+    return x;
+  }
+  PTailArgs<T, T, T> ta;
+  if (p1_tail_args<T>(mg, l, false, ta)) {
+    ta.b = b;
+    ta.x = x;
+    ta.lb = lb;
+    ta.lx = L.nodes;
+    p1_tail<T, T, T, false>(ta, s, K);
+    return x;
+  }
+  P1UpArgs<T, T, T> a{};
+  a.xc = p1_descend<T, T>(mg, l, b, lb, s, K);
+  a.n = L.n;
+  a.b = b;
+  a.x = x;
+  a.y = Pr<T>::w(L, 4);
+  p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, a.c1, a.c2);
+  a.lb = lb;
+  a.lx = L.nodes;
+  a.lc = mg.lv[l + 1].nodes;
+  p1_up<T, T, T, P1_Y>(a, s, K);
+  return a.y;
+}
+
+// Parts of r . z that the matrix-free pressure part stores per lane: one per tile of the finest
+// level's ascent, or one where the finest level is the tail's
+static bool p1_tail_all(const Ctx &c) {
+  PTailArgs<double, double, double> a;   // the larger of the two precisions
+  return p1_tail_args<double>(c.mgp, 0, true, a);
+}
+static int pres_dot_count(const Ctx &c) { return p1_tail_all(c) ? 1 : p1_up_tiles(c.n); }
+
+// z = nu M_p^{-1} r + (rho/dt) L_p^{-1} r on the pressure unknowns of K systems (lane stride lz of r, z
+// and r64), the pinned entry r[0], and with part the parts of sum r z (sum r64 z when r64 is given)
+template <typename T, typename TZ>
+static void p1_schur(Ctx &c, const TZ *r, TZ *z, const double *r64, int64_t lz, double *part, int64_t lp,
+                     hipStream_t s, int K) {
+  Mg &mg = c.mgp;
+  MgLevel &L = mg.lv[0];
+  static_assert(kMpSteps == 3, "the fused mass solve takes three steps");
+  T m1[3], m2[3];
+  p1_cheb_coefs<T>(0.5, 2.0, kMpSteps, m1, m2);
+  auto mass = [&](auto &a, T &ms) {   // the mass solve and the output
+    a.b = r;
+    a.z = z;
+    a.r64 = r64;
+    ms = m2[0];
+    for (int k = 0; k < 2; ++k) {
+      a.m1[k] = m1[k + 1];
+      a.m2[k] = m2[k + 1];
+    }
+    a.mdinv = (T)(12.0 * c.n * c.n);
+    a.munit = (T)(1.0 / (12.0 * c.n * c.n));
+    a.nu = (T)c.nu;
+    a.rdt = (T)(c.rho / c.dt);
+    a.part = part;
+    a.lb = a.lz = lz;
+    a.lp = lp;
+  };
+  PTailArgs<T, TZ, TZ> ta;
+  if (p1_tail_all(c) && p1_tail_args<T>(mg, 0, true, ta)) {
+    mass(ta, ta.ms);
+    p1_tail<T, TZ, TZ, true>(ta, s, K);
+    return;
+  }
+  P1UpArgs<T, TZ, TZ> a{};
+  mass(a, a.ms[0]);
+  a.n = c.n;
+  if (mg.lv.size() == 1) {   // the dense level alone: its right-hand side in T, contiguous, pinned entry 0
+    T *rp = Pr<T>::inner(c, 8).p;
+    convert_l(LP<T>(rp, c.Np), LP<const TZ>(r, lz), c.Np, s, K);
+    fill_l(LP<T>(rp, c.Np), 1, (T)0, s, K);
+    a.xc = p1_cycle<T>(mg, 0, rp, c.Np, s, K);
+    a.lc = L.nodes;
+    p1_up<T, TZ, TZ, P1_ZW>(a, s, K);
+    return;
+  }
+  a.xc = p1_descend<T, TZ>(mg, 0, r, lz, s, K);
+  a.x = Pr<T>::w(L, 0);
+  p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, a.c1, a.c2);
+  a.lx = L.nodes;
+  a.lc = mg.lv[1].nodes;
+  p1_up<T, TZ, TZ, P1_Z>(a, s, K);
+}
+
 // z = diag(V, S^{-1}) r on [u | p], for K systems at once (lane k of r and z at + k nf,
 // nf = 2 N2 + Np; K > 1 needs the matrix-free hierarchies).  The two blocks share no
 // buffer: outside graph capture the pressure part runs on the auxiliary stream beside the
@@ -651,8 +633,8 @@ constexpr int kMpSteps = 3;
 // r64, z64 (FP32 arithmetic, one system): the results are stored straight into the FP64 vector
 // z64 (z unused) and the pressure residual is read from r64 (r holds the velocity part).
 // dot (FP64 form, tile_dot_ok): the launches that write z also store per-tile / per-block
-// parts of r . z: post3_dot_count(n) velocity tile sums, then kPresDotBlocks pressure
-// block sums, per lane (lane stride dot.s).
+// parts of r . z: post3_dot_count(n) velocity tile sums, then pres_dot_count pressure parts,
+// per lane (lane stride dot.s).
 // part: PC_BOTH, or only the velocity cycle (PC_VEL) or only the pressure part (PC_PRES); the
 // other part of z is left as it is.
 enum { PC_BOTH = 0, PC_VEL = 1, PC_PRES = 2 };
@@ -691,103 +673,51 @@ static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 =
     FSI_CHECK_LAUNCH();
     return;
   }
+  auto join = [&] {
+    FSI_CHECK_LAUNCH();
+    if (fork) {
+      FSI_HIP(hipEventRecord(c.ev_join, sp));
+      FSI_HIP(hipStreamWaitEvent(s, c.ev_join, 0));
+    }
+  };
+  if (c.mgp.stencil) {
+    double *parts = dot.p ? dot.p + post3_dot_count(c.n) : nullptr;
+    if (z64)
+      p1_schur<T, double>(c, r64 + 2 * N2, z64 + 2 * N2, nullptr, nf, parts, dot.s, sp, 1);
+    else
+      p1_schur<T, T>(c, r + 2 * N2, z + 2 * N2, r64 ? r64 + 2 * N2 : nullptr, nf, parts, dot.s, sp, K);
+    join();
+    return;
+  }
+  FSI_REQUIRE(!dot.p && K == 1, FSI_E_STATE, "the assembled form runs one system and forms no tile sums");
   // r' = pressure residual with the pinned entry removed (keeps the operator symmetric)
   T *rp = Pr<T>::inner(c, 8).p;
   if (z64) convert(rp, r64 + 2 * N2, Np, sp);
-  else convert_l(LP<T>(rp, Np), LP<const T>(r + 2 * N2, nf), Np, sp, K);
-  fill_l(LP<T>(rp, Np), 1, (T)0, sp, K);
-  T *xp = vcycle<T, 1, 1>(c.mgp, 0, rp, sp, nullptr, K);
+  else convert(rp, r + 2 * N2, Np, sp);
+  fill(rp, 1, (T)0, sp);
+  T *xp = vcycle<T, 1, 1>(c.mgp, 0, rp, sp, nullptr);
   if (c.pair == FSI_PAIR_Q2P1DISC) {   // M_p of the discontinuous pressure is diagonal: no mass solve
-    FSI_REQUIRE(!dot.p && K == 1, FSI_E_STATE, "the Q2 / P1-disc pair runs one system and forms no tile sums");
     if (z64)
       hipLaunchKernelGGL((k_q_pres<double, T>), dim3(vgrid(Np)), dim3(256), 0, sp, z64 + 2 * N2, r64 + 2 * N2, xp,
                          mp_dinv<T>(c), (T)c.nu, (T)(c.rho / c.dt), Np);
     else
       hipLaunchKernelGGL((k_q_pres<T, T>), dim3(vgrid(Np)), dim3(256), 0, sp, z + 2 * N2, r + 2 * N2, xp,
                          mp_dinv<T>(c), (T)c.nu, (T)(c.rho / c.dt), Np);
-    FSI_CHECK_LAUNCH();
-    if (fork) {
-      FSI_HIP(hipEventRecord(c.ev_join, sp));
-      FSI_HIP(hipStreamWaitEvent(s, c.ev_join, 0));
-    }
+    join();
     return;
   }
-  if (c.mgp.stencil) {
-    // the mass solve (kMpSteps Chebyshev steps from zero) and the output z_p = nu x + (rho/dt) x_L
-    // with the pinned entry and the parts of r . z, in one launch
-    static_assert(kMpSteps == 3, "the fused mass solve takes three steps");
-    const P1Table<T> *mtab = (const P1Table<T> *)(std::is_same<T, double>::value ? c.mptab64.p : c.mptab32.p);
-    double *part = dot.p ? dot.p + post3_dot_count(c.n) : nullptr;
-    if (z64) {
-      P1MultiArgs<T, double> a{};
-      a.n = c.n;
-      a.tab = mtab;
-      a.b = rp;
-      p1_cheb_coefs<T>(0.5, 2.0, kMpSteps, a.c1, a.c2);
-      a.z = z64 + 2 * N2;
-      a.r = r64 + 2 * N2;
-      a.w = xp;
-      a.a = (T)c.nu;
-      a.b2 = (T)(c.rho / c.dt);
-      a.part = part;
-      a.lb = Np;
-      a.lz = nf;
-      a.lp = dot.s;
-      p1_multi<T, double, 3, true, P1_OUT_SCHUR>(a, sp, 1);
-    } else {
-      P1MultiArgs<T, T> a{};
-      a.n = c.n;
-      a.tab = mtab;
-      a.b = rp;
-      p1_cheb_coefs<T>(0.5, 2.0, kMpSteps, a.c1, a.c2);
-      a.z = z + 2 * N2;
-      a.r = r + 2 * N2;
-      a.r64 = r64 ? r64 + 2 * N2 : nullptr;
-      a.w = xp;
-      a.a = (T)c.nu;
-      a.b2 = (T)(c.rho / c.dt);
-      a.part = part;
-      a.lb = Np;
-      a.lz = nf;
-      a.lp = dot.s;
-      p1_multi<T, T, 3, true, P1_OUT_SCHUR>(a, sp, K);
-    }
-    FSI_CHECK_LAUNCH();
-    if (fork) {
-      FSI_HIP(hipEventRecord(c.ev_join, sp));
-      FSI_HIP(hipStreamWaitEvent(s, c.ev_join, 0));
-    }
-    return;
-  }
-  // mass solve scratch: x, x2, d of every lane (3 Np each) in one inner vector
-  T *mx = Pr<T>::inner(c, 7).p, *mx2 = mx + (int64_t)K * Np, *md = mx + 2 * (int64_t)K * Np;
-  T *mres = c.mgp.stencil
-                ? chebyshev_p1<T>(c.n, (const P1Table<T> *)(std::is_same<T, double>::value ? c.mptab64.p
-                                                                                          : c.mptab32.p),
-                                  0.5, 2.0, kMpSteps, rp, mx, mx2, md, true, sp, K, Np)
-                : chebyshev<T, 1, 1>(Np, c.Mp.rowptr.p, c.Mp.col.p, Pr<T>::val(c.Mp), mp_dinv<T>(c), 0.5,
-                                     2.0, kMpSteps, rp, mx, mx2, md, true, sp);
-  if (z64 && dot.p) {
-    hipLaunchKernelGGL((k_pres_out_dot<double, T>), dim3(kPresDotBlocks, 1), dim3(kRedBlock), 0, sp, z64 + 2 * N2,
-                       r64 + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, nf, Np,
-                       dot.p + post3_dot_count(c.n), dot.s, nullptr);
-  } else if (z64) {
+  // mass solve scratch: x, x2, d (3 Np) in one inner vector
+  T *mx = Pr<T>::inner(c, 7).p, *mx2 = mx + Np, *md = mx + 2 * Np;
+  T *mres = chebyshev<T, 1, 1>(Np, c.Mp.rowptr.p, c.Mp.col.p, Pr<T>::val(c.Mp), mp_dinv<T>(c), 0.5, 2.0, kMpSteps, rp,
+                               mx, mx2, md, true, sp);
+  if (z64) {
     lincomb_to<double, T>(z64 + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
     hipLaunchKernelGGL((k_set_pinned_to<double, T>), dim3(1), dim3(1), 0, sp, z64 + 2 * N2, r64 + 2 * N2);
-  } else if (dot.p) {
-    hipLaunchKernelGGL((k_pres_out_dot<T, T>), dim3(kPresDotBlocks, K), dim3(kRedBlock), 0, sp, z + 2 * N2,
-                       r + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, nf, Np,
-                       dot.p + post3_dot_count(c.n), dot.s, r64 ? r64 + 2 * N2 : nullptr);
   } else {
-    lincomb_l(LP<T>(z + 2 * N2, nf), LP<const T>(mres, Np), LP<const T>(xp, Np), (T)c.nu, (T)(c.rho / c.dt), Np,
-              sp, K);
-    hipLaunchKernelGGL(k_set_pinned<T>, dim3(1, K), dim3(1), 0, sp, z + 2 * N2, r + 2 * N2, nf);
+    lincomb(z + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
+    hipLaunchKernelGGL(k_set_pinned<T>, dim3(1), dim3(1), 0, sp, z + 2 * N2, r + 2 * N2);
   }
-  FSI_CHECK_LAUNCH();
-  if (fork) {
-    FSI_HIP(hipEventRecord(c.ev_join, sp));
-    FSI_HIP(hipStreamWaitEvent(s, c.ev_join, 0));
-  }
+  join();
 }
 
 // ---------------------------------------------------------------- inner MINRES
@@ -1209,7 +1139,7 @@ static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) 
     hipLaunchKernelGGL(k_ms_axpy, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, 1, nf);
   if (dot_ok) {   // beta^2 = r . z from the launches that write z
     const int nu = post3_dot_count(c.n), np = pres_dot_count(c);
-    const int64_t ld = nu + pres_dot_slots(c.n);
+    const int64_t ld = nu + pres_dot_count(c);
     const LP<double> dot(c.ms_dot.p, ld);
     if constexpr (f32) {   // the same arithmetic as a11_precond_on64<float>, sums on FP64 r
       if (K == 1) {
@@ -1670,7 +1600,7 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
     c.ms_state.alloc(nl * kMsDoubles);
     c.ms_red.alloc(nl * red_blocks(nf));   // dot products of one system per lane: never regrown
     c.ms_part.alloc(nl * stencil_tile_count(c.n));
-    c.ms_dot.alloc(nl * (post3_dot_count(c.n) + pres_dot_slots(c.n)));
+    c.ms_dot.alloc(nl * (post3_dot_count(c.n) + pres_dot_count(c)));
   }
   if (!c.pc_in.p) {
     c.pc_in.alloc(nl * nf);
