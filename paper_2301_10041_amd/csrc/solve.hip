@@ -1365,29 +1365,30 @@ static void a11_fixed_tri(Ctx &c, const double *const *r, double *const *z, int 
 // unchanged and saved 2% of the step; the exact form is kept.
 static int cs_steps(const Ctx &c) { return c.cs_nsteps; }
 
-static const double *cs_solve(Ctx &c, const double *b, double *scratch, int steps) {
-  const int64_t ns = c.Ns;
-  double *t = scratch, *t2 = t + 2 * ns, *d = t + 4 * ns;
-  return chebyshev<double, 1, 2>(ns, c.S.rowptr.p, c.S.col.p, c.Cs.p, c.Cs_dinv.p, c.cs_lo, c.cs_hi,
-                                 steps, b, t, t2, d, true, c.stream);
-}
-
-// The same closed form for every system of a batch in one launch: one 1024-thread block per
-// system.  A_s and C_s act on each component alone, so the two components run one after the
-// other: the iterate of the current Chebyshev solve lies in LDS as two buffers of Ns entries
-// (read one, write the other), a thread's rows (at most kA22Rows) keep their right-hand side
-// and direction in registers, and the rows of A_s and C_s come from device memory in the
-// transposed layout (entry u of row r at u Ns + r: the lanes of a wave, consecutive rows,
-// read consecutive words; the row-major CSR made every load of a wave touch a dozen or more
-// cache lines).  Same steps as a22_solve: t = C_s^{-1} r_lam, z_X = -dt t,
-// u = r_X - A_s z_X, z_lam = -C_s^{-1} u.
-constexpr int kA22Threads = 1024, kA22Rows = 7, kA22Nnz = 7;
+// The rows of A_s and C_s come in the transposed layout of the solid pattern (entry u of row r at
+// u Ns + r, short rows padded with value 0): the lanes of a wave, consecutive rows, read consecutive
+// words.  Two forms with the same operations in the same order for every row (so the same
+// results, bitwise):
+//  * one block per system and component (k_a22_block): the iterate of a Chebyshev solve in LDS as
+//    two buffers (read one, write the other), one barrier per step; a thread keeps its rows' right-hand
+//    side and direction in registers and, up to kA22RegRows rows per thread, the matrix rows too
+//    (values and 16-bit columns), so a step reads nothing but LDS;
+//  * one launch per step over all systems of the call (k_cs_step), for systems larger than a block's
+//    LDS and for single systems whose rows a block would have to read again in every step.
+// A block is bound by the latency of its 72 dependent steps.  Measured per application (two solves of
+// 36 steps, FP64): 127 solid nodes 318 -> 22 us, 1,800 nodes 550 -> 68 us, 676 nodes with a tangent 290
+// (72 launches) -> 40 us, against one block for both components that read its rows from device
+// memory in every step; 6,211 nodes 1,260 -> 380 us with the launches over the whole chip.
+constexpr int kA22Threads = 1024, kA22Rows = 7;
+constexpr int kA22RegRows = 3;   // rows per thread with the matrix in registers (4 spill)
 struct A22Lane {
-  const int *rp, *ecol;            // CSR row pointer (row lengths); transposed columns
+  const int *ecol;                 // transposed columns
   const double *eas, *ecs, *csd;   // A_s and C_s values (transposed); C_s inverse diagonal
   const double *rX, *rl;
   double *zX, *zl;
-  int ns;
+  double *u;                       // r_X - A_s z_X where the two solves are separate launches
+  double *t, *t2, *d;              // k_cs_step: iterate (two buffers) and direction, 2 Ns each
+  int ns, ew;                      // rows, entries per row
   double dt;
 };
 struct A22Args {
@@ -1395,76 +1396,108 @@ struct A22Args {
   int steps;
   double theta, delta;             // Chebyshev interval of D^{-1} C_s: centre and half width
 };
+// which part of the closed form a launch takes: both solves, the first (z_X), the second (z_lam from u)
+enum { A22_ALL = 0, A22_FIRST = 1, A22_SECOND = 2 };
 
-// s[q] = sum over the len[q] entries of row tid + kA22Threads q (in CSR order) of val x[col]
-// in the transposed layout (row stride ns): entry u of every row of the thread at a time (one
-// uniform base per entry, the loads of all rows issued together), the entries beyond
-// kA22Nnz (rare on a triangle mesh) in order after them
-__device__ __forceinline__ void a22_rows(const int *ecol, const double *eval, const double *x, int tid, int ns,
-                                         const int (&len)[kA22Rows], double (&s)[kA22Rows]) {
-#pragma unroll
-  for (int q = 0; q < kA22Rows; ++q) s[q] = 0.0;
-#pragma unroll
-  for (int u = 0; u < kA22Nnz; ++u) {
-    const int *cu = ecol + (size_t)u * ns;
-    const double *vu = eval + (size_t)u * ns;
-#pragma unroll
-    for (int q = 0; q < kA22Rows; ++q) {
-      const unsigned r = (unsigned)(tid + kA22Threads * q);
-      if (u < len[q]) s[q] += vu[r] * x[cu[r]];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < kA22Rows; ++q) {
-    const size_t r = (size_t)(tid + kA22Threads * q);
-    for (int u = kA22Nnz; u < len[q]; ++u) s[q] += eval[(size_t)u * ns + r] * x[ecol[(size_t)u * ns + r]];
-  }
+// coefficients of Chebyshev step k >= 1, from rho of the step before (1 / sigma at the start)
+__device__ __forceinline__ void cs_coefs(double theta, double delta, double &rho, double &c1, double &c2) {
+  const double sigma = theta / delta, rho1 = 1.0 / (2.0 * sigma - rho);
+  c1 = rho1 * rho;
+  c2 = 2.0 * rho1 / delta;
+  rho = rho1;
+}
+__device__ __forceinline__ double cs_first(double theta, double csd, double b) { return 1.0 / theta * csd * b; }
+__device__ __forceinline__ double cs_next(double c1, double c2, double d, double csd, double b, double s) {
+  return fma(c2, csd * (b - s), c1 * d);
 }
 
-__global__ void __launch_bounds__(kA22Threads) k_a22_lanes(A22Args a) {
+// NNZ entries of a row lie in registers (REG), the others are read from the transposed arrays
+template <int NR, int NNZ, bool REG>
+__global__ void __launch_bounds__(kA22Threads) k_a22_block(A22Args a, int phase) {
   extern __shared__ double a22_x[];   // two buffers of ns entries
   const A22Lane &L = a.lane[blockIdx.y];
-  const int ns = L.ns, tid = threadIdx.x;
-  int len[kA22Rows];                  // lengths of this thread's rows (the pattern of both matrices)
+  const int ns = L.ns, ew = L.ew, tid = threadIdx.x, T = blockDim.x;
+  const int64_t o = (int64_t)blockIdx.x * ns;   // the component
+  double vr[REG ? NR : 1][REG ? NNZ : 1], cd[NR];
+  unsigned cr[REG ? NR : 1][REG ? (NNZ + 1) / 2 : 1];   // two 16-bit columns each
 #pragma unroll
-  for (int q = 0; q < kA22Rows; ++q) {
-    const int r = tid + kA22Threads * q;
-    len[q] = r < ns ? L.rp[r + 1] - L.rp[r] : 0;
+  for (int q = 0; q < NR; ++q) {
+    const int r = tid + T * q, rc = r < ns ? r : 0;
+    cd[q] = L.csd[rc];
+    if constexpr (REG) {
+#pragma unroll
+      for (int u = 0; u < NNZ; ++u) {
+        const bool in = u < ew;   // uniform
+        vr[q][u] = in ? L.ecs[(size_t)u * ns + rc] : 0.0;
+        const unsigned c = in ? (unsigned)L.ecol[(size_t)u * ns + rc] : (unsigned)rc;
+        if (u & 1) cr[q][u / 2] |= c << 16;
+        else cr[q][u / 2] = c;
+      }
+    }
   }
-  // C_s^{-1} b by the Chebyshev steps of chebyshev<double, 1, 2> from zero (b: this thread's
-  // rows); returns the buffer holding the result
-  auto cs_solve = [&](const double (&b)[kA22Rows]) -> double * {
-    const double sigma = a.theta / a.delta;
-    double rho = 1.0 / sigma;
-    double d[kA22Rows];
+  // sum over the entries of row tid + T q, in order
+  auto row = [&](int q, const double *ev, const double *x, bool reg) -> double {
+    const int r = tid + T * q;
+    double s = 0.0;
+    if (REG && reg) {
+#pragma unroll
+      for (int u = 0; u < NNZ; ++u) s = fma(vr[q][u], x[(cr[q][u / 2] >> (16 * (u & 1))) & 0xffffu], s);
+      for (int u = NNZ; u < ew; ++u) s = fma(ev[(size_t)u * ns + r], x[L.ecol[(size_t)u * ns + r]], s);
+    } else {
+      for (int u = 0; u < ew; ++u) s = fma(ev[(size_t)u * ns + r], x[L.ecol[(size_t)u * ns + r]], s);
+    }
+    return s;
+  };
+  // C_s^{-1} b by Chebyshev steps from zero (b: this thread's rows); returns the buffer holding
+  // the result
+  auto solve = [&](const double (&b)[NR]) -> double * {
+    double rho = a.delta / a.theta, d[NR];
     double *x = a22_x, *x2 = a22_x + ns;
 #pragma unroll
-    for (int q = 0; q < kA22Rows; ++q) {
-      const int r = tid + kA22Threads * q;
-      if (r < ns) {
-        const double z = 1.0 / a.theta * L.csd[r] * b[q];
-        d[q] = z;
-        x[r] = z;
-      }
+    for (int q = 0; q < NR; ++q) {
+      const int r = tid + T * q;
+      d[q] = cs_first(a.theta, cd[q], b[q]);
+      if (r < ns) x[r] = d[q];
     }
     __syncthreads();
     for (int k = 1; k < a.steps; ++k) {
-      const double rho1 = 1.0 / (2.0 * sigma - rho);
-      const double c1 = rho1 * rho, c2 = 2.0 * rho1 / a.delta;
-      rho = rho1;
-      // the row stride, opaque to the compiler within the step: the entry addresses are
-      // formed in the step instead of being held, all of them, across the steps
-      int nss = ns;
-      asm volatile("" : "+s"(nss));
-      double sr[kA22Rows];
-      a22_rows(L.ecol, L.ecs, x, tid, nss, len, sr);
+      double c1, c2;
+      cs_coefs(a.theta, a.delta, rho, c1, c2);
+      if constexpr (REG) {
 #pragma unroll
-      for (int q = 0; q < kA22Rows; ++q) {
-        const int r = tid + kA22Threads * q;
-        if (r < ns) {
-          const double s0 = sr[q];
-          d[q] = c1 * d[q] + c2 * (L.csd[r] * (b[q] - s0));
-          x2[r] = x[r] + d[q];
+        for (int q = 0; q < NR; ++q) {
+          const int r = tid + T * q;
+          if (r < ns) {
+            d[q] = cs_next(c1, c2, d[q], cd[q], b[q], row(q, L.ecs, x, true));
+            x2[r] = x[r] + d[q];
+          }
+        }
+      } else {
+        // entry u of every row of the thread at a time: the loads of all rows issue together
+        double s[NR];
+#pragma unroll
+        for (int q = 0; q < NR; ++q) s[q] = 0.0;
+        for (int u = 0; u < ew; ++u) {
+          const int *cu = L.ecol + (size_t)u * ns;
+          const double *vu = L.ecs + (size_t)u * ns;
+          double v[NR];
+          int c[NR];
+#pragma unroll
+          for (int q = 0; q < NR; ++q) {
+            const int r = tid + T * q, rc = r < ns ? r : 0;
+            v[q] = vu[rc];
+            c[q] = cu[rc];
+          }
+#pragma unroll
+          for (int q = 0; q < NR; ++q) s[q] = fma(v[q], x[c[q]], s[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+          const int r = tid + T * q;
+          if (r < ns) {
+            d[q] = cs_next(c1, c2, d[q], cd[q], b[q], s[q]);
+            x2[r] = x[r] + d[q];
+          }
         }
       }
       __syncthreads();
@@ -1474,50 +1507,115 @@ __global__ void __launch_bounds__(kA22Threads) k_a22_lanes(A22Args a) {
     }
     return x;
   };
-  for (int c = 0; c < 2; ++c) {
-    const int64_t o = (int64_t)c * ns;
-    double b[kA22Rows];
+  double b[NR];
+  if (phase != A22_SECOND) {
 #pragma unroll
-    for (int q = 0; q < kA22Rows; ++q) {
-      const int r = tid + kA22Threads * q;
+    for (int q = 0; q < NR; ++q) {
+      const int r = tid + T * q;
       b[q] = r < ns ? L.rl[o + r] : 0.0;
     }
-    double *t = cs_solve(b);
+    double *t = solve(b);
     // z_X = -dt t (stored; kept in the other buffer for the A_s rows)
     double *zx = t == a22_x ? a22_x + ns : a22_x;
 #pragma unroll
-    for (int q = 0; q < kA22Rows; ++q) {
-      const int r = tid + kA22Threads * q;
-      if (r < ns) {
-        const double tv = t[r];
-        const double z = -L.dt * tv + 0.0 * tv;
-        L.zX[o + r] = z;
-        zx[r] = z;
-      }
+    for (int q = 0; q < NR; ++q) {
+      const int r = tid + T * q;
+      if (r < ns) zx[r] = L.zX[o + r] = -L.dt * t[r];
     }
+    if (phase == A22_FIRST) return;
     __syncthreads();
-    // u = r_X - A_s z_X
-    {
-      double sr[kA22Rows];
-      a22_rows(L.ecol, L.eas, zx, tid, ns, len, sr);
 #pragma unroll
-      for (int q = 0; q < kA22Rows; ++q) {
-        const int r = tid + kA22Threads * q;
-        if (r < ns) b[q] = L.rX[o + r] - sr[q];
-      }
+    for (int q = 0; q < NR; ++q) {   // u = r_X - A_s z_X
+      const int r = tid + T * q;
+      if (r < ns) b[q] = L.rX[o + r] - row(q, L.eas, zx, false);
     }
     __syncthreads();   // every row has read z_X: the next solve starts over both buffers
-    const double *t2 = cs_solve(b);
+  } else {
 #pragma unroll
-    for (int q = 0; q < kA22Rows; ++q) {
-      const int r = tid + kA22Threads * q;
-      if (r < ns) L.zl[o + r] = -t2[r];
+    for (int q = 0; q < NR; ++q) {
+      const int r = tid + T * q;
+      b[q] = r < ns ? L.u[o + r] : 0.0;
     }
-    __syncthreads();   // the buffers are free for the next component
+  }
+  const double *t2 = solve(b);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int r = tid + T * q;
+    if (r < ns) L.zl[o + r] = -t2[r];
   }
 }
 
-// LDS grant of the batched closed form (device limit, at most 160 KiB), set once
+// One Chebyshev step of every system (thread = row, both components): k = 0 the step from zero.  b is
+// r_lam (second = 0) or u.  x: the buffer the step reads (t or t2); the last step also scales the
+// result out: z_X = -dt x or z_lam = -x.
+__global__ void __launch_bounds__(256) k_cs_step(A22Args a, int second, int k, int flip, double c1, double c2) {
+  const A22Lane &L = a.lane[blockIdx.y];
+  const int ns = L.ns, r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= ns) return;
+  const double *b = second ? L.u : L.rl;
+  const double cd = L.csd[r];
+  double d0, d1, x0, x1;
+  double *xo = flip ? L.t2 : L.t;
+  if (k == 0) {
+    x0 = d0 = cs_first(a.theta, cd, b[r]);
+    x1 = d1 = cs_first(a.theta, cd, b[ns + r]);
+  } else {
+    const double *x = flip ? L.t : L.t2;
+    double s0 = 0.0, s1 = 0.0;
+    for (int u = 0; u < L.ew; ++u) {
+      const double v = L.ecs[(size_t)u * ns + r];
+      const int c = L.ecol[(size_t)u * ns + r];
+      s0 = fma(v, x[c], s0);
+      s1 = fma(v, x[ns + c], s1);
+    }
+    d0 = cs_next(c1, c2, L.d[r], cd, b[r], s0);
+    d1 = cs_next(c1, c2, L.d[ns + r], cd, b[ns + r], s1);
+    x0 = x[r] + d0;
+    x1 = x[ns + r] + d1;
+  }
+  if (k + 1 == a.steps) {
+    double *z = second ? L.zl : L.zX;
+    z[r] = second ? -x0 : -L.dt * x0;
+    z[ns + r] = second ? -x1 : -L.dt * x1;
+  } else {
+    xo[r] = x0;
+    xo[ns + r] = x1;
+    L.d[r] = d0;
+    L.d[ns + r] = d1;
+  }
+}
+
+// u = r_X - A_s z_X of every system
+__global__ void __launch_bounds__(256) k_a22_mid(A22Args a) {
+  const A22Lane &L = a.lane[blockIdx.y];
+  const int ns = L.ns, r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= ns) return;
+  double s0 = 0.0, s1 = 0.0;
+  for (int u = 0; u < L.ew; ++u) {
+    const double v = L.eas[(size_t)u * ns + r];
+    const int c = L.ecol[(size_t)u * ns + r];
+    s0 = fma(v, L.zX[c], s0);
+    s1 = fma(v, L.zX[ns + c], s1);
+  }
+  L.u[r] = L.rX[r] - s0;
+  L.u[ns + r] = L.rX[ns + r] - s1;
+}
+
+using A22Kernel = void (*)(A22Args, int);
+// the block form for the largest row count and width of a call (nullptr: none)
+static A22Kernel a22_kernel(int rows, int ew) {
+  if (ew <= 7) switch (rows) {
+    case 1: return k_a22_block<1, 7, true>;
+    case 2: return k_a22_block<2, 7, true>;
+    case 3: return k_a22_block<3, 7, true>;
+    default: return k_a22_block<kA22Rows, 7, false>;
+  }
+  if (rows == 1) return k_a22_block<1, 9, true>;
+  if (rows == 2) return k_a22_block<2, 9, true>;
+  return k_a22_block<kA22Rows, 9, false>;
+}
+
+// LDS grant of the block form (device limit, at most 160 KiB), set once
 static int a22_lds_limit() {
   static int limit = [] {
     int dev = 0, v = 0;
@@ -1525,35 +1623,92 @@ static int a22_lds_limit() {
         hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
       v = 65536;
     v = v < 65536 ? v : v > 163840 ? 163840 : v;
-    if (v > 65536 &&
-        hipFuncSetAttribute((const void *)k_a22_lanes, hipFuncAttributeMaxDynamicSharedMemorySize, v) != hipSuccess) {
-      (void)hipGetLastError();
-      v = 65536;
-    }
+    if (v > 65536)
+      for (int rows : {3, kA22Rows})   // the forms that can exceed 64 KiB (the others: at most 32 KiB)
+        for (int ew : {7, 9})
+          if (hipFuncSetAttribute((const void *)a22_kernel(rows, ew), hipFuncAttributeMaxDynamicSharedMemorySize, v) !=
+              hipSuccess) {
+            (void)hipGetLastError();
+            v = 65536;
+          }
     return v;
   }();
   return limit;
 }
 
-// Whether a system's solid block fits the one-launch form
+// Whether a system's solid block fits the block form
 static bool a22_fits(const Ctx &c) {
-  return c.Ns >= 1 && c.Ns <= (int64_t)kA22Threads * kA22Rows && c.s_ecol.p && c.s_ew >= 1 &&
+  return c.Ns >= 1 && c.Ns <= (int64_t)kA22Threads * kA22Rows &&
          (int64_t)2 * c.Ns * (int64_t)sizeof(double) <= a22_lds_limit();   // two buffers of Ns
 }
 
-// z2 = A22^{-1} r2 on [X | lam] (4 Ns entries)
-static void a22_solve(Ctx &c, const double *rX, const double *rl, double *zX, double *zl, int steps) {
-  hipStream_t s = c.stream;
-  const int64_t ns = c.Ns;
-  double *scr = c.tmpS.p, *u = c.tmpS.p + 6 * ns;
-  const double *t = cs_solve(c, rl, scr, steps);
-  lincomb(zX, t, t, -c.dt, 0.0, 2 * ns, s);
-  // u = r_X - A_s z_X;  z_lam = C_s^{-1} (A_s z_X - r_X) = -C_s^{-1} u  (the tangent of the
-  // nonlinear solid in place of A_s while it is set: 2 x 2 blocks)
-  if (c.use_kt) spmv<double, 4, 2, SP_RESID>(ns, c.S.rowptr.p, c.S.col.p, c.Kt.p, zX, ns, u, ns, s, rX);
-  else spmv<double, 1, 2, SP_RESID>(ns, c.S.rowptr.p, c.S.col.p, c.S.val.p, zX, ns, u, ns, s, rX);
-  const double *t2 = cs_solve(c, u, scr, steps);
-  hipLaunchKernelGGL(k_negate<double>, dim3(vgrid(2 * ns)), dim3(256), 0, s, zl, t2, 2 * ns);
+// z2 = A22^{-1} r2 of K systems whose C_s solves share steps and interval (z_X, z_lam of 2 Ns entries
+// each).  A system whose context holds a tangent (use_kt; K = 1) takes it in place of A_s: 2 x 2 blocks
+// that join the components, so its two solves are launches of their own.
+static void a22_solve(Ctx *const *cs, int K, const double *const *rX, const double *const *rl, double *const *zX,
+                      double *const *zl, hipStream_t s) {
+  A22Args aa{};
+  bool fit = true, kt = false;
+  int ns_max = 0, ew_max = 0;
+  for (int k = 0; k < K; ++k) {
+    Ctx &c = *cs[k];
+    const int64_t ns = c.Ns;
+    double *scr = c.tmpS.p;   // t, t2, d, u: 2 Ns each
+    aa.lane[k] = A22Lane{c.s_ecol.p, c.s_eas.p, c.s_ecs.p, c.Cs_dinv.p, rX[k], rl[k], zX[k], zl[k],
+                         scr + 6 * ns, scr, scr + 2 * ns, scr + 4 * ns, (int)ns, c.s_ew, c.dt};
+    fit = fit && a22_fits(c);
+    kt = kt || c.use_kt;
+    ns_max = std::max(ns_max, (int)ns);
+    ew_max = std::max(ew_max, c.s_ew);
+  }
+  FSI_REQUIRE(!kt || K == 1, FSI_E_STATE, "a solid tangent takes one system per call");
+  aa.steps = cs_steps(*cs[0]);
+  aa.theta = 0.5 * (cs[0]->cs_hi + cs[0]->cs_lo);
+  aa.delta = 0.5 * (cs[0]->cs_hi - cs[0]->cs_lo);
+  auto tangent = [&] {
+    Ctx &c = *cs[0];
+    spmv<double, 4, 2, SP_RESID>(c.Ns, c.S.rowptr.p, c.S.col.p, c.Kt.p, zX[0], c.Ns, aa.lane[0].u, c.Ns, s, rX[0]);
+  };
+  const int threads = std::min(kA22Threads, (ns_max + kWave - 1) / kWave * kWave);
+  const int rows = (ns_max + threads - 1) / threads;
+  const bool reg = rows <= (ew_max <= 7 ? kA22RegRows : 2);
+  // a block reads the rows again in every step when they do not fit its registers: for one system the
+  // launches over the whole chip are faster then, for several the blocks run side by side
+  if (fit && (reg || K > 1)) {
+    const A22Kernel kern = a22_kernel(rows, ew_max);
+    auto go = [&](int phase) {
+      hipLaunchKernelGGL(kern, dim3(2, (unsigned)K), dim3((unsigned)threads), (size_t)2 * ns_max * sizeof(double), s, aa,
+                         phase);
+    };
+    if (kt) {
+      go(A22_FIRST);
+      tangent();
+      go(A22_SECOND);
+    } else {
+      go(A22_ALL);
+    }
+    FSI_CHECK_LAUNCH();
+    return;
+  }
+  const dim3 grid(grid_for(ns_max, 256), (unsigned)K);
+  for (int second = 0; second < 2; ++second) {
+    const double sigma = aa.theta / aa.delta;
+    double rho = aa.delta / aa.theta;
+    for (int k = 0; k < aa.steps; ++k) {
+      double c1 = 0.0, c2 = 0.0;
+      if (k > 0) {   // as cs_coefs
+        const double rho1 = 1.0 / (2.0 * sigma - rho);
+        c1 = rho1 * rho;
+        c2 = 2.0 * rho1 / aa.delta;
+        rho = rho1;
+      }
+      hipLaunchKernelGGL(k_cs_step, grid, dim3(256), 0, s, aa, second, k, k & 1, c1, c2);
+    }
+    if (second == 0) {
+      if (kt) tangent();
+      else hipLaunchKernelGGL(k_a22_mid, grid, dim3(256), 0, s, aa);
+    }
+  }
   FSI_CHECK_LAUNCH();
 }
 
@@ -1708,45 +1863,30 @@ void apply_precond_lanes(Ctx &c, Ctx *const *cs, int K, int pc, int prec, const 
   } else {
     minres_a11<float>(c, r, z, K, tol, c.inner_maxit, its);
   }
-  // the solid blocks: every system's closed form in one launch when all fit, else one by one.
-  // The one-workgroup form serves the 36-step mass solves of P1 solids; for the 56 steps of Q1
-  // solids the launches over the whole GPU measured faster (256^2 bar, 2,781 solid nodes: 102.4
-  // against 109.5 ms per FP64 step)
-  bool fit = true;
-  int ns_max = 0;
-  for (int k = 0; k < K; ++k) {
-    fit = fit && a22_fits(*cs[k]) && !cs[k]->use_kt && cs[k]->cs_nsteps <= 36 && cs[k]->cs_lo == cs[0]->cs_lo &&
-          cs[k]->cs_hi == cs[0]->cs_hi && cs[k]->cs_nsteps == cs[0]->cs_nsteps;
-    ns_max = std::max(ns_max, (int)cs[k]->Ns);
-  }
-  A22Args aa{};
+  // the solid blocks
+  const double *rX[FSI_MAX_LANES], *rl[FSI_MAX_LANES];
+  double *zX[FSI_MAX_LANES], *zl[FSI_MAX_LANES];
+  bool one = true;   // the systems' C_s solves agree: one call for all
   for (int k = 0; k < K; ++k) {
     Ctx &ck = *cs[k];
     ck.inner_its_total += its[k];
-    hipStream_t s = ck.stream;
     const int64_t nf = 2 * ck.N2 + ck.Np, ns = ck.Ns;
-    const double *rX = r[k] + nf, *rl = r[k] + nf + 2 * ns;
-    double *zX = z[k] + nf, *zl = z[k] + nf + 2 * ns;
+    rX[k] = r[k] + nf;
+    rl[k] = r[k] + nf + 2 * ns;
+    zX[k] = z[k] + nf;
+    zl[k] = z[k] + nf + 2 * ns;
     if (pc == FSI_PC_TRI) {
       // r_lam - C_f z_u  (A21 z1 = [0; C_f z_u])
       double *t = ck.tmpS.p + 8 * ns;
-      spmv<double, 1, 2, SP_RESID>(ns, ck.Cf.rowptr.p, ck.Cf.col.p, ck.Cf.val.p, z[k], ck.N2, t, ns, s, rl);
-      rl = t;
+      spmv<double, 1, 2, SP_RESID>(ns, ck.Cf.rowptr.p, ck.Cf.col.p, ck.Cf.val.p, z[k], ck.N2, t, ns, ck.stream, rl[k]);
+      rl[k] = t;
     }
-    if (fit)
-      aa.lane[k] = A22Lane{ck.S.rowptr.p, ck.s_ecol.p, ck.s_eas.p, ck.s_ecs.p, ck.Cs_dinv.p, rX, rl, zX, zl, (int)ns,
-                           ck.dt};
-    else
-      a22_solve(ck, rX, rl, zX, zl, cs_steps(ck));
+    one = one && ck.stream == c.stream && !(K > 1 && ck.use_kt) && ck.cs_lo == cs[0]->cs_lo &&
+          ck.cs_hi == cs[0]->cs_hi && ck.cs_nsteps == cs[0]->cs_nsteps;
   }
-  if (fit) {
-    aa.steps = cs_steps(*cs[0]);
-    aa.theta = 0.5 * (cs[0]->cs_hi + cs[0]->cs_lo);   // the C_s interval of cs_solve
-    aa.delta = 0.5 * (cs[0]->cs_hi - cs[0]->cs_lo);
-    hipLaunchKernelGGL(k_a22_lanes, dim3(1, (unsigned)K), dim3(kA22Threads), (size_t)2 * ns_max * sizeof(double),
-                       c.stream, aa);
-    FSI_CHECK_LAUNCH();
-  }
+  if (one) a22_solve(cs, K, rX, rl, zX, zl, c.stream);
+  else
+    for (int k = 0; k < K; ++k) a22_solve(cs + k, 1, rX + k, rl + k, zX + k, zl + k, cs[k]->stream);
 }
 
 void apply_precond(Ctx &c, int pc, int prec, const double *r, double *z) {
