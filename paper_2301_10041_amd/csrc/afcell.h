@@ -119,6 +119,18 @@ __device__ __forceinline__ V2<T> cell_dinv(const AfCoef<T> &c, int q, V2<T> r) {
   return V2<T>{fma(o, r.y, d * r.x), fma(d, r.y, o * r.x)};
 }
 
+// The coefficients as values of their own in scalar registers: used straight from the kernel
+// arguments they may be loaded again in every pass, a scalar-cache round trip each time
+template <typename T>
+__device__ __forceinline__ AfCoef<T> pinned_coefs(const AfCoef<T> &c) {
+  AfCoef<T> r = c;
+  T *const v[18] = {&r.cv,  &r.ce,  &r.k2, &r.k8, &r.k12, &r.k16, &r.k32, &r.v2p, &r.v2n,
+                    &r.e1p, &r.e1n, &r.m4, &r.m8, &r.m32, &r.dvd, &r.dvo, &r.ded, &r.deo};
+#pragma unroll
+  for (int i = 0; i < 18; ++i) asm volatile("" : "+s"(*v[i]));
+  return r;
+}
+
 // Which of the cell's four nodes are interior: not on the Dirichlet boundary and in the lattice
 struct CellIn {
   bool q[4];

@@ -19,7 +19,9 @@
 // kernel arguments into scalar registers (AfCoef): read from LDS by every wave in every pass they
 // took two thirds of a pass (6,800 of its cycles at 16^2; an LDS read of one uniform word costs
 // as much as one of 64 words).  The dense inverse (162 x 162 words on 4^2) is fetched into
-// registers at the start, behind the descent; read at its turn it took 9 of 43 us.
+// registers at the start, behind the descent; read at its turn it took 9 of 43 us.  Now 20.6 us
+// in FP64 and 17.0 in FP32 (43.6 and 41 in the form before); one thread per node, 1024 threads,
+// measured 23.2 and 17.5 (registers spill in FP64, twice the waves per barrier).
 #include <cmath>
 
 #include "ctx.h"
@@ -108,16 +110,18 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   // thread (row, part) reads its entries down column `row` and the loads are coalesced
   const int m = a.m, P = kTailThreads / m, kp = (m + P - 1) / P, drow = tid % m, dpart = tid / m;
   const bool dlive = dpart < P;
-  const bool pre = kp <= kTailDenseReg;   // uniform
+  const bool pre = kp <= kTailDenseReg, even = kp == kTailDenseReg && P * kp == m;   // uniform
   T cr[kTailDenseReg];
   {
     const int c0 = (dlive ? dpart : 0) * kp;
+    if (even) {   // no column to guard (a coarsest level of 4 x 4 cells: 162 = 3 x 54)
+      const T *p = a.cinv + c0 * m + drow;
 #pragma unroll
-    for (int q = 0; q < kTailDenseReg; ++q) cr[q] = T(0);
-    if (pre) {
+      for (int q = 0; q < kTailDenseReg; ++q) cr[q] = p[q * m];
+    } else {
 #pragma unroll
       for (int q = 0; q < kTailDenseReg; ++q)   // past the last column: any entry (it meets a zero of b)
-        if (q < kp) cr[q] = a.cinv[(c0 + q < m ? c0 + q : 0) * m + drow];
+        cr[q] = pre && q < kp ? a.cinv[(c0 + q < m ? c0 + q : 0) * m + drow] : T(0);
     }
   }
   auto buf = [&](int l, int k) -> V2<T> * { return sv + (2 * l + k) * kTailLevelV2; };
@@ -176,12 +180,12 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   };
   V2<T> d[2];
   // one Chebyshev step on level l from buffer src: the new values of the thread's nodes
-  auto cheb_step = [&](const TailLevel<T> &lv, const Place &pl, const V2<T> *src, T c1, T c2, V2<T> (&x)[2]) {
+  auto cheb_step = [&](const AfCoef<T> &cf, const Place &pl, const V2<T> *src, T c1, T c2, V2<T> (&x)[2]) {
     V2<T> s[2];
-    product(src, pl, lv.cf, x, s);
+    product(src, pl, cf, x, s);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const V2<T> z = cell_dinv(lv.cf, 2 * half + q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
+      const V2<T> z = cell_dinv(cf, 2 * half + q, V2<T>{b[q].x - s[q].x, b[q].y - s[q].y});
       d[q] = V2<T>{(T)fma(c2, z.x, c1 * d[q].x), (T)fma(c2, z.y, c1 * d[q].y)};
       x[q] = V2<T>{x[q].x + d[q].x, x[q].y + d[q].y};
     }
@@ -191,11 +195,12 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   for (int l = 0; l < a.nlev; ++l) {
     const TailLevel<T> &lv = a.lv[l];
     const Place pl = place(lv.n);
+    const AfCoef<T> cf = pinned_coefs(lv.cf);
     V2<T> x[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {   // first step from zero: x = d = s D^{-1} b
       bs[2 * (kTailThreads * l) + kTailThreads * q + tid] = b[q];
-      const V2<T> z = cell_dinv(lv.cf, 2 * half + q, b[q]);
+      const V2<T> z = cell_dinv(cf, 2 * half + q, b[q]);
       x[q] = d[q] = V2<T>{lv.s * z.x, lv.s * z.y};
     }
     int k = 0;
@@ -203,13 +208,13 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
     __syncthreads();
 #pragma unroll 1
     for (int j = 0; j + 1 < a.degree; ++j, k ^= 1) {
-      cheb_step(lv, pl, buf(l, k), lv.c1[j], lv.c2[j], x);
+      cheb_step(cf, pl, buf(l, k), lv.c1[j], lv.c2[j], x);
       put(buf(l, k ^ 1), pl, x);
       __syncthreads();
     }
     {   // the residual into the other buffer
       V2<T> s[2];
-      product(buf(l, k), pl, lv.cf, x, s);
+      product(buf(l, k), pl, cf, x, s);
 #pragma unroll
       for (int q = 0; q < 2; ++q) s[q] = V2<T>{b[q].x - s[q].x, b[q].y - s[q].y};
       put(buf(l, k ^ 1), pl, s);
@@ -245,7 +250,14 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   if (dlive) {
     double s0 = 0.0, s1 = 0.0;
     const int k0 = dpart * kp;
-    if (pre) {
+    // the loads' first use: without this the FP32 kernel converts to double as they arrive and so
+    // waits for all of them at the start (31 us a launch instead of 17)
+#pragma unroll
+    for (int q = 0; q < kTailDenseReg; ++q) asm volatile("" : "+v"(cr[q]));
+    if (even) {
+#pragma unroll
+      for (int q = 0; q < kTailDenseReg; ++q) (q & 1 ? s1 : s0) += (double)cr[q] * (double)db[k0 + q];
+    } else if (pre) {
 #pragma unroll
       for (int q = 0; q < kTailDenseReg; ++q)
         if (q < kp) (q & 1 ? s1 : s0) += (double)cr[q] * (double)db[k0 + q];
@@ -269,6 +281,7 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   for (int l = a.nlev - 1; l >= 0; --l) {
     const TailLevel<T> &lv = a.lv[l];
     const Place pl = place(lv.n);
+    const AfCoef<T> cf = pinned_coefs(lv.cf);
     V2<T> x[2];
     b[0] = bs[2 * (kTailThreads * l) + tid];
     b[1] = bs[2 * (kTailThreads * l) + kTailThreads + tid];
@@ -299,7 +312,7 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
 #pragma unroll 1
     for (int j = 0; j < a.degree; ++j, k ^= 1) {
       if (j == 0) d[0] = d[1] = V2<T>{T(0), T(0)};
-      cheb_step(lv, pl, buf(l, k), j == 0 ? T(0) : lv.c1[j - 1], j == 0 ? lv.s : lv.c2[j - 1], x);
+      cheb_step(cf, pl, buf(l, k), j == 0 ? T(0) : lv.c1[j - 1], j == 0 ? lv.s : lv.c2[j - 1], x);
       if (l == 0 && j + 1 == a.degree) break;   // the result goes to device memory
       put(buf(l, k ^ 1), pl, x);
       __syncthreads();
