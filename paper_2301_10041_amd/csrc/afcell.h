@@ -40,10 +40,13 @@ struct AfCoef {
 // planes of even and odd lattice columns (plane stride PL, row stride HW): x (the four values
 // themselves) and s (the products), in the order vertex, (1, 0), (0, 1), (1, 1).  PART 1: only the
 // vertex and (1, 0) (all 19 nodes); PART 2: only (0, 1) and (1, 1) (12 nodes); the other entries of
-// x and s are left alone.
+// x and s are left alone.  DIV: also *div = 6 / h times the row of B at the cell's P1 vertex times x
+// (B_q = int q div u: its entries are 0, +-h/6 and +-h/3, none of them at vertices).
 enum { CELL_ALL = 0, CELL_ROW0 = 1, CELL_ROW1 = 2 };
-template <typename T, int PL, int HW, int PART = CELL_ALL>
-__device__ __forceinline__ void cell_products(const V2<T> *p, const AfCoef<T> &c, V2<T> (&x)[4], V2<T> (&s)[4]) {
+template <typename T, int PL, int HW, int PART = CELL_ALL, bool DIV = false>
+__device__ __forceinline__ void cell_products(const V2<T> *p, const AfCoef<T> &c, V2<T> (&x)[4], V2<T> (&s)[4],
+                                              T *div = nullptr) {
+  static_assert(!DIV || PART == CELL_ALL, "the B row needs all the edge nodes");
   constexpr bool R0 = PART != CELL_ROW1, R1 = PART != CELL_ROW0;
   auto W = [&](int dI, int dJ) -> V2<T> { return p[(dI & 1) * PL + dJ * HW + (dI >> 1)]; };
   auto add = [](V2<T> a, V2<T> b) -> V2<T> { return V2<T>{a.x + b.x, a.y + b.y}; };
@@ -72,6 +75,9 @@ __device__ __forceinline__ void cell_products(const V2<T> *p, const AfCoef<T> &c
   const V2<T> lm20 = W(-2, 0), lm10 = W(-1, 0), lm11 = W(-1, 1);
   hold();
   V2<T> v1, v2, six;
+  if constexpr (DIV)
+    *div = 2 * (e.x - lm10.x + f.y - l0m1.y) + (l0m1.x - f.x) + (lm10.y - e.y) + (l1m1.x - lm11.x) + (lm11.y - l1m1.y) +
+           (g.x + g.y) + n21.x + n12.y;
   if constexpr (R0) {   // (1, 0)
     const V2<T> p10 = add(o, n20), p01 = add(l1m1, g), p11 = add(l0m1, n21), p12 = add(l0m2, n22);
     const T cx = p10.x + p01.x - p11.x, cy = p10.y + p01.y - p11.y;
@@ -97,6 +103,7 @@ __device__ __forceinline__ void cell_products(const V2<T> *p, const AfCoef<T> &c
     s[2].x = fma(c.k8, cy, fma(-c.k16, f.y, fma(c.m8, p21.x, fma(c.m32, p11.x, fma(-c.k16, p01.x, fma(c.e1p, p10.x, c.ce * f.x))))));
     s[2].y = fma(c.k8, cx, fma(-c.k16, f.x, fma(c.m8, p21.y, fma(c.m32, p11.y, fma(-c.k32, p01.y, fma(c.e1n, p10.y, c.ce * f.y))))));
   }
+  if constexpr (DIV) *div -= (lm1m1.x + lm1m1.y) + lm2m1.x + lm1m2.y;
   if constexpr (R0) {   // (0, 0)
     const V2<T> h1 = add(lm10, e), h2 = add(lm20, n20), d1 = add(lm1m1, g), d2 = add(lm2m2, n22);
     six = add(six, add(add(lm1m2, lm2m1), lm11));

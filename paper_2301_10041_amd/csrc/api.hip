@@ -627,9 +627,8 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
     std::fill(vals, vals + 9 * E * 4, 0.0);
     switch (table) {
       case FSI_LAT_AF: {
-        fsi::StencilTable<double> t;
-        fsi::StencilTable<float> tf;
-        fsi::stencil_tables(n, nu, rdt, t, tf);
+        fsi::StencilTable t;
+        fsi::stencil_tables(n, nu, rdt, t);
         for (int c = 0; c < 4; ++c) {
           counts[c] = t.count[c];
           for (int k = 0; k < t.count[c]; ++k) {
@@ -658,9 +657,8 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
       }
       case FSI_LAT_BT:
       case FSI_LAT_B: {
-        fsi::DivTable<double> t;
-        fsi::DivTable<float> tf;
-        fsi::div_tables(n, t, tf);
+        fsi::DivTable t;
+        fsi::div_tables(n, t);
         if (table == FSI_LAT_BT) {
           for (int c = 0; c < 4; ++c) {
             counts[c] = t.bt_count[c];

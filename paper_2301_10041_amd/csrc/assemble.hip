@@ -106,22 +106,21 @@ __global__ void k_diag_inv(int64_t nrows, const int *rowptr, const int *col, con
 
 // Host: rows of A_f at one interior node of each class, gathered like k_asm_p2p2 (the same
 // window order and the same order of triangles), with offsets relative to the node.
-void stencil_tables(int n, double nu, double rdt, StencilTable<double> &t64, StencilTable<float> &t32) {
+void stencil_tables(int n, double nu, double rdt, StencilTable &t) {
   FSI_REQUIRE(n >= 2, FSI_E_ARG, "stencil tables need n >= 2");
   std::vector<double> E;
   element_tables(n, nu, E);
-  std::memset(&t64, 0, sizeof(t64));
-  std::memset(&t32, 0, sizeof(t32));
+  std::memset(&t, 0, sizeof(t));
   for (int cls = 0; cls < 4; ++cls) {
     const int I = 2 + (cls & 1), J = 2 + ((cls >> 1) & 1);   // interior for n >= 2
     struct A { int ci, cj, t, a; } adj[8];
     int na = 0;
     for (int cj = std::max(0, (J - 1) >> 1); cj <= std::min(n - 1, J >> 1); ++cj)
       for (int ci = std::max(0, (I - 1) >> 1); ci <= std::min(n - 1, I >> 1); ++ci)
-        for (int t = 0; t < 2; ++t)
+        for (int tr = 0; tr < 2; ++tr)
           for (int a = 0; a < 6; ++a)
-            if (2 * ci + hOff[t][a][0] == I && 2 * cj + hOff[t][a][1] == J) {
-              adj[na++] = A{ci, cj, t, a};
+            if (2 * ci + hOff[tr][a][0] == I && 2 * cj + hOff[tr][a][1] == J) {
+              adj[na++] = A{ci, cj, tr, a};
               break;
             }
     int cnt = 0;
@@ -146,33 +145,25 @@ void stencil_tables(int n, double nu, double rdt, StencilTable<double> &t64, Ste
         if (!touched) continue;
         FSI_REQUIRE(cnt < kStencilMax, FSI_E_ARG, "stencil too wide");
         double v[4] = {rdt * m + kxx, kxy, kyx, rdt * m + kyy};
-        t64.off[cls][cnt][0] = t32.off[cls][cnt][0] = dI;
-        t64.off[cls][cnt][1] = t32.off[cls][cnt][1] = dJ;
-        t64.lin[cls][cnt] = t32.lin[cls][cnt] = dJ * (2 * n + 1) + dI;
-        t64.lds[cls][cnt] = t32.lds[cls][cnt] = dJ * (kTileC + 4) + dI;
-        for (int q = 0; q < 4; ++q) {
-          t64.coef[cls][cnt][q] = v[q];
-          t32.coef[cls][cnt][q] = (float)v[q];
-        }
+        t.off[cls][cnt][0] = dI;
+        t.off[cls][cnt][1] = dJ;
+        for (int q = 0; q < 4; ++q) t.coef[cls][cnt][q] = v[q];
         if (dI == 0 && dJ == 0) {
           double det = v[0] * v[3] - v[1] * v[2];
           double di[4] = {v[3] / det, -v[1] / det, -v[2] / det, v[0] / det};
-          for (int q = 0; q < 4; ++q) {
-            t64.dinv[cls][q] = di[q];
-            t32.dinv[cls][q] = (float)di[q];
-          }
+          for (int q = 0; q < 4; ++q) t.dinv[cls][q] = di[q];
         }
         ++cnt;
       }
-    t64.count[cls] = t32.count[cls] = cnt;
+    t.count[cls] = cnt;
     FSI_REQUIRE(cnt == kStencilCount[cls], FSI_E_ARG, "unexpected stencil width");
     constexpr StencilOffsets so = stencil_offsets();
     for (int k = 0; k < cnt; ++k)
-      FSI_REQUIRE(t64.off[cls][k][0] == so.d[cls][k][0] && t64.off[cls][k][1] == so.d[cls][k][1], FSI_E_ARG,
+      FSI_REQUIRE(t.off[cls][k][0] == so.d[cls][k][0] && t.off[cls][k][1] == so.d[cls][k][1], FSI_E_ARG,
                   "stencil offsets differ from the compiled pattern");
     constexpr CrossZero cz = cross_zero();
     for (int k = 0; k < cnt; ++k)
-      FSI_REQUIRE(!cz.z[cls][k] || (t64.coef[cls][k][1] == 0.0 && t64.coef[cls][k][2] == 0.0), FSI_E_ARG,
+      FSI_REQUIRE(!cz.z[cls][k] || (t.coef[cls][k][1] == 0.0 && t.coef[cls][k][2] == 0.0), FSI_E_ARG,
                   "a cross coupling compiled as zero is not");
   }
 }
@@ -205,9 +196,8 @@ void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f)
   static_assert(sizeof(AfCoef<double>) == 18 * sizeof(double) && sizeof(AfCoef<float>) == 18 * sizeof(float),
                 "coefficients only");
   for (int i = 0; i < 18; ++i) q[i] = (float)p[i];
-  StencilTable<double> t;
-  StencilTable<float> tf;
-  stencil_tables(n, nu, rdt, t, tf);
+  StencilTable t;
+  stencil_tables(n, nu, rdt, t);
   // entry (class, offset): along and across the x component, and the cross coupling
   struct E { double xx, yy, xy; };
   auto entry = [&](int cls, int I, int J) -> E {
@@ -246,12 +236,11 @@ void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f)
 // Host: B^T rows of the four interior P2 node classes and the B row of an interior P1
 // node, summed over the triangles around the node from the element blocks
 // B_alpha(k, i) = int d_alpha phi_i lam_k.
-void div_tables(int n, DivTable<double> &t64, DivTable<float> &t32) {
+void div_tables(int n, DivTable &t64) {
   FSI_REQUIRE(n >= 2, FSI_E_ARG, "divergence tables need n >= 2");
   std::vector<double> E;
   element_tables(n, 1.0, E);
   std::memset(&t64, 0, sizeof(t64));
-  std::memset(&t32, 0, sizeof(t32));
   struct A { int ci, cj, t, a; };
   auto around = [&](int I, int J, A *adj) {
     int na = 0;
@@ -278,14 +267,14 @@ void div_tables(int n, DivTable<double> &t64, DivTable<float> &t32) {
         while (k < cnt && !(t64.bt_off[cls][k][0] == di && t64.bt_off[cls][k][1] == dj)) ++k;
         if (k == cnt) {
           FSI_REQUIRE(cnt < kBtMax, FSI_E_ARG, "B^T stencil too wide");
-          t64.bt_off[cls][k][0] = t32.bt_off[cls][k][0] = di;
-          t64.bt_off[cls][k][1] = t32.bt_off[cls][k][1] = dj;
+          t64.bt_off[cls][k][0] = di;
+          t64.bt_off[cls][k][1] = dj;
           ++cnt;
         }
         const double *e = E.data() + adj[q].t * EM_SIZE + EM_B;
         for (int al = 0; al < 2; ++al) t64.bt_coef[cls][k][al] += e[(al * 3 + v) * 6 + adj[q].a];
       }
-    t64.bt_count[cls] = t32.bt_count[cls] = cnt;
+    t64.bt_count[cls] = cnt;
   }
   {
     const int na = around(2, 2, adj);   // P1 node (1, 1)
@@ -298,19 +287,18 @@ void div_tables(int n, DivTable<double> &t64, DivTable<float> &t32) {
         while (k < cnt && !(t64.b_off[k][0] == dI && t64.b_off[k][1] == dJ)) ++k;
         if (k == cnt) {
           FSI_REQUIRE(cnt < kBMax, FSI_E_ARG, "B stencil too wide");
-          t64.b_off[k][0] = t32.b_off[k][0] = dI;
-          t64.b_off[k][1] = t32.b_off[k][1] = dJ;
-          t64.b_lds[k] = t32.b_lds[k] = dJ * (kTileC + 4) + dI;
+          t64.b_off[k][0] = dI;
+          t64.b_off[k][1] = dJ;
           ++cnt;
         }
         const double *e = E.data() + adj[q].t * EM_SIZE + EM_B;
         for (int al = 0; al < 2; ++al) t64.b_coef[k][al] += e[(al * 3 + adj[q].a) * 6 + b];
       }
     }
-    t64.b_count = t32.b_count = cnt;
+    t64.b_count = cnt;
   }
   // canonical order (dJ, then dI), checked against the offsets the kernels are compiled with
-  auto sort_entries = [](int cnt, int (*off)[2], double (*coef)[2], int *lds) {
+  auto sort_entries = [](int cnt, int (*off)[2], double (*coef)[2]) {
     for (int a = 1; a < cnt; ++a)
       for (int b = a; b > 0; --b) {
         const bool less = off[b][1] < off[b - 1][1] || (off[b][1] == off[b - 1][1] && off[b][0] < off[b - 1][0]);
@@ -319,35 +307,49 @@ void div_tables(int n, DivTable<double> &t64, DivTable<float> &t32) {
         std::swap(off[b][1], off[b - 1][1]);
         std::swap(coef[b][0], coef[b - 1][0]);
         std::swap(coef[b][1], coef[b - 1][1]);
-        if (lds) std::swap(lds[b], lds[b - 1]);
       }
   };
   constexpr DivOffsets dofs = div_offsets();
   constexpr StencilOffsets sofs = stencil_offsets();
   for (int c = 0; c < 4; ++c) {
-    sort_entries(t64.bt_count[c], t64.bt_off[c], t64.bt_coef[c], nullptr);
+    sort_entries(t64.bt_count[c], t64.bt_off[c], t64.bt_coef[c]);
     FSI_REQUIRE(t64.bt_count[c] == kBtCount[c], FSI_E_ARG, "unexpected B^T stencil width");
     for (int k = 0; k < t64.bt_count[c]; ++k) {
       FSI_REQUIRE(t64.bt_off[c][k][0] == dofs.bt[c][k][0] && t64.bt_off[c][k][1] == dofs.bt[c][k][1], FSI_E_ARG,
                   "B^T offsets differ from the compiled pattern");
-      t32.bt_off[c][k][0] = t64.bt_off[c][k][0];
-      t32.bt_off[c][k][1] = t64.bt_off[c][k][1];
     }
   }
-  sort_entries(t64.b_count, t64.b_off, t64.b_coef, t64.b_lds);
+  sort_entries(t64.b_count, t64.b_off, t64.b_coef);
   FSI_REQUIRE(t64.b_count == kStencilCount[0], FSI_E_ARG, "unexpected B stencil width");
   for (int k = 0; k < t64.b_count; ++k) {
     FSI_REQUIRE(t64.b_off[k][0] == sofs.d[0][k][0] && t64.b_off[k][1] == sofs.d[0][k][1], FSI_E_ARG,
                 "B offsets differ from the compiled pattern");
-    t32.b_off[k][0] = t64.b_off[k][0];
-    t32.b_off[k][1] = t64.b_off[k][1];
-    t32.b_lds[k] = t64.b_lds[k];
   }
+}
+
+// The entries that cell_products (DIV) and the A11 rows take for B and B^T in units of h / 6: none at
+// vertices, and at the edge nodes those below; B is B^T by columns.
+void check_div_closed_form(int n) {
+  DivTable t;
+  div_tables(n, t);
+  // B^T rows of the edge nodes (1, 0), (0, 1), (1, 1) in the order of div_offsets
+  static const int bt[4][4][2] = {{{0, 0}, {0, 0}, {0, 0}, {0, 0}},
+                                  {{0, 1}, {2, -1}, {-2, 1}, {0, -1}},
+                                  {{1, 0}, {-1, 2}, {1, -2}, {-1, 0}},
+                                  {{1, 1}, {-1, 1}, {1, -1}, {-1, -1}}};
+  // the B row in the order of the vertex class of stencil_offsets
+  static const int br[kBMax][2] = {{0, 0},  {0, -1}, {0, 0}, {-1, 0}, {-1, -1}, {1, -2}, {1, -1}, {0, 0}, {-2, 1}, {0, 0},
+                                   {2, -1}, {0, 0},  {-1, 1}, {-1, 2}, {1, 1},  {1, 0},  {0, 0},  {0, 1}, {0, 0}};
+  const double g = 1.0 / (6.0 * n), tol = 1e-13 * g;
   for (int c = 0; c < 4; ++c)
-    for (int k = 0; k < kBtMax; ++k)
-      for (int al = 0; al < 2; ++al) t32.bt_coef[c][k][al] = (float)t64.bt_coef[c][k][al];
+    for (int k = 0; k < kBtCount[c]; ++k)
+      for (int al = 0; al < 2; ++al)
+        FSI_REQUIRE(std::abs(t.bt_coef[c][k][al] - (c ? g * bt[c][k][al] : 0.0)) <= tol, FSI_E_STATE,
+                    "an entry of B^T differs from its closed form");
   for (int k = 0; k < kBMax; ++k)
-    for (int al = 0; al < 2; ++al) t32.b_coef[k][al] = (float)t64.b_coef[k][al];
+    for (int al = 0; al < 2; ++al)
+      FSI_REQUIRE(std::abs(t.b_coef[k][al] - g * br[k][al]) <= tol, FSI_E_STATE,
+                  "an entry of B differs from its closed form");
 }
 
 // Host: rows of a P1 x P1 matrix (EM_MP: mass, EM_LP: Laplacian) at one node of each of
@@ -663,13 +665,7 @@ void build_fluid(Ctx &c) {
   c.Mp_dinv.alloc(np);
   hipLaunchKernelGGL(k_diag_inv, dim3(gp), dim3(256), 0, s, np, c.Mp.rowptr.p, c.Mp.col.p, c.Mp.val.p,
                      c.Mp_dinv.p);
-  {
-    DivTable<double> t64;
-    DivTable<float> t32;
-    div_tables(n, t64, t32);
-    upload_bytes(c.divtab64, &t64, sizeof(t64), s);
-    upload_bytes(c.divtab32, &t32, sizeof(t32), s);
-  }
+  check_div_closed_form(n);
   c.bnd.alloc(n2);
   hipLaunchKernelGGL(k_p2_boundary_flags, dim3(g2), dim3(256), 0, s, n, c.bnd.p);
   FSI_CHECK_LAUNCH();
@@ -1249,8 +1245,8 @@ static void coarse_inverse_spd_device(Mg &mg, hipStream_t s) {
 size_t Mg::bytes() const {
   size_t b = cinv.bytes() + cinv32.bytes();
   for (auto &L : lv) {
-    b += L.A.bytes() + L.P.bytes() + L.R.bytes() + L.dinv.bytes() + L.dinv32.bytes() + L.stab64.bytes() +
-         L.stab32.bytes() + L.q2tab64.bytes() + L.q2tab32.bytes();
+    b += L.A.bytes() + L.P.bytes() + L.R.bytes() + L.dinv.bytes() + L.dinv32.bytes() + L.q2tab64.bytes() +
+         L.q2tab32.bytes();
     for (int i = 0; i < 5; ++i) b += L.w64[i].bytes() + L.w32[i].bytes();
   }
   return b;
@@ -1301,17 +1297,7 @@ void build_multigrid(Ctx &c) {
                        P.A.rowptr.p, P.A.col.p, P.A.val.p, P.dinv.p);
     FSI_CHECK_LAUNCH();
     if (vel) U.lmax = 1.1 * power_lmax(U, 2, s);
-    if (vel) {
-      StencilTable<double> t64;
-      StencilTable<float> t32;
-      stencil_tables(m, c.nu, c.rho / c.dt, t64, t32);
-      af_coefs(m, c.nu, c.rho / c.dt, U.af64, U.af32);
-      U.stab64.alloc(sizeof(t64));
-      U.stab32.alloc(sizeof(t32));
-      FSI_HIP(hipMemcpyAsync(U.stab64.p, &t64, sizeof(t64), hipMemcpyHostToDevice, s));
-      FSI_HIP(hipMemcpyAsync(U.stab32.p, &t32, sizeof(t32), hipMemcpyHostToDevice, s));
-      FSI_HIP(hipStreamSynchronize(s));
-    }
+    if (vel) af_coefs(m, c.nu, c.rho / c.dt, U.af64, U.af32);
     P.lmax = 1.1 * power_lmax(P, 1, s);
     if (l + 1 < ns.size()) {
       int64_t nc2 = (int64_t)(m + 1) * (m + 1);          // coarse P2 nodes = (2 (m/2) + 1)^2

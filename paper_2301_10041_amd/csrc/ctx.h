@@ -57,7 +57,6 @@ struct MgLevel {
   Csr P, R;                // prolongation from the next coarser level into this one; R = P^T
   DevBuf<double> w64[5];   // x, b, r, d, x2 work vectors
   DevBuf<float> w32[5];
-  DevBuf<unsigned char> stab64, stab32;   // StencilTable<double/float> (velocity levels)
   AfCoef<double> af64{};                  // the level's A_f entries (velocity levels)
   AfCoef<float> af32{};
   DevBuf<unsigned char> q2tab64, q2tab32; // Q2Table<double/float> (velocity levels of the Q2 pair)
@@ -108,7 +107,6 @@ struct Ctx {
   Csr Mp;                  // pressure mass, width 1
   DevBuf<double> Mp_dinv;  // 1 / diag(M_p)
   DevBuf<float> Mp_dinv32;
-  DevBuf<unsigned char> divtab64, divtab32;  // DivTable<double/float> (B and B^T)
   DevBuf<unsigned char> bnd;  // 1 on boundary P2 nodes
 
   // solid blocks

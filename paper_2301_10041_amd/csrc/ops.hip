@@ -169,15 +169,13 @@ static void launch_operator(Ctx &c, const Tx *x, Ty *y, bool fluid_only, bool so
   FSI_CHECK_LAUNCH();
 }
 
-// Fluid rows matrix-free (structured-grid products enabled, FP64): one tiled launch for
+// Fluid rows matrix-free (structured-grid products enabled, FP64): one launch for
 // the velocity and pressure rows, then the solid row group of the fused kernel.
 static void fluid_rows_stencil(Ctx &c, const double *x, double *y, bool fluid_only) {
   const bool cft = !fluid_only && c.CfT.rowptr.p != nullptr;
   const double *xl = x + 2 * c.N2 + c.Np + 2 * c.Ns;
-  stencil_fluid_rows<double>(c.n, (const StencilTable<double> *)c.mgu.lv[0].stab64.p,
-                             (const DivTable<double> *)c.divtab64.p, x, y, cft ? c.CfT.rowptr.p : nullptr,
-                             cft ? c.CfT.col.p : nullptr, cft ? c.CfT.val.p : nullptr, cft ? xl : nullptr,
-                             c.Ns, c.stream);
+  a11_rows(c.n, c.mgu.lv[0].af64, x, y, cft ? c.CfT.rowptr.p : nullptr, cft ? c.CfT.col.p : nullptr,
+           cft ? c.CfT.val.p : nullptr, cft ? xl : nullptr, c.Ns, c.stream);
 }
 
 template <typename T, typename Tx>

@@ -1123,12 +1123,11 @@ static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) 
   const int64_t nf = 2 * c.N2 + c.Np;
   const unsigned g = vgrid(nf);
   double *dv = (double *)st;
-  const int tiles = stencil_tile_count(c.n);
-  stencil_a11_minres(c.n, (const StencilTable<double> *)c.mgu.lv[0].stab64.p, (const DivTable<double> *)c.divtab64.p,
-                     LP<const double>(b.y, nf), LP<double>(c.ms_vh.p, nf), LP<double>(b.r1, nf),
-                     LP<const double>(&st->s, kMsDoubles), LP<const double>(&st->c_r1, kMsDoubles),
-                     LP<const double>(&st->slot, kMsDoubles), (int64_t)c.lanes * nf, c.ms_B,
-                     LP<double>(c.ms_part.p, tiles), s, K);
+  const int tiles = a11_tile_count(c.n);
+  a11_minres(c.n, c.mgu.lv[0].af64, LP<const double>(b.y, nf), LP<double>(c.ms_vh.p, nf), LP<double>(b.r1, nf),
+             LP<const double>(&st->s, kMsDoubles), LP<const double>(&st->c_r1, kMsDoubles),
+             LP<const double>(&st->slot, kMsDoubles), (int64_t)c.lanes * nf, c.ms_B, LP<double>(c.ms_part.p, tiles), s,
+             K);
   hipLaunchKernelGGL(k_ms_alfa, dim3(1, K), dim3(1024), 0, s, c.ms_part.p, tiles, st);
   constexpr bool f32 = std::is_same<TA, float>::value;
   const bool dot_ok = tile_dot_ok(c, f32);
@@ -1754,7 +1753,7 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
     c.ms_x.alloc(nl * nf);
     c.ms_state.alloc(nl * kMsDoubles);
     c.ms_red.alloc(nl * red_blocks(nf));   // dot products of one system per lane: never regrown
-    c.ms_part.alloc(nl * stencil_tile_count(c.n));
+    c.ms_part.alloc(nl * a11_tile_count(c.n));
     c.ms_dot.alloc(nl * (post3_dot_count(c.n) + pres_dot_count(c)));
   }
   if (!c.pc_in.p) {
@@ -1796,9 +1795,8 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
 // 1.5e-9 and 5.6e-9 with w = n (4 n and 16 n: the same errors, more inner steps).
 double inner_pressure_weight(Ctx &c) {
   if (c.gi_wp > 0) return c.gi_wp;
-  StencilTable<double> a;
-  StencilTable<float> af;
-  stencil_tables(c.n, c.nu, c.rho / c.dt, a, af);
+  StencilTable a;
+  stencil_tables(c.n, c.nu, c.rho / c.dt, a);
   double au = 0.0;
   for (int k = 0; k < 4; ++k) {   // the diagonal of the inverse of each class's D^{-1} block
     const double *d = a.dinv[k];

@@ -7,21 +7,16 @@
 namespace fsi {
 
 constexpr int kStencilMax = 25;   // a P2 node couples with at most 19 nodes (5 x 5 window)
-constexpr int kTileC = 128;       // tile of the tiled kernel: kTileR lattice rows x kTileC nodes
-constexpr int kTileR = 4;
 
 // Node classes: bit 0 = I odd, bit 1 = J odd (0 vertex, 1 horizontal edge, 2 vertical
 // edge, 3 diagonal edge).  coef[c][k] is the 2x2 block (xx, xy, yx, yy) of A_f coupling a
 // node of class c with the node at lattice offset off[c][k]; dinv[c] is the inverse of the
 // diagonal block.
-template <typename T>
 struct StencilTable {
   int count[4];
   int off[4][kStencilMax][2];
-  int lin[4][kStencilMax];       // dJ (2n+1) + dI: offset of the neighbour's index
-  int lds[4][kStencilMax];       // dJ (kTileC + 4) + dI: offset inside the LDS tile
-  T coef[4][kStencilMax][4];
-  T dinv[4][4];
+  double coef[4][kStencilMax][4];
+  double dinv[4][4];
 };
 
 // Neighbour counts of the classes on the triangulated grid (vertex, h-edge, v-edge, diagonal).
@@ -29,8 +24,6 @@ constexpr int kStencilCount[4] = {19, 9, 9, 9};
 
 // The neighbour offsets (dI, dJ) of each class, in the order of the tables (dJ, then dI,
 // ascending).  They follow from the triangulation alone; the table builder checks them.
-// Kernels index them with compile-time class and neighbour, so LDS addresses become
-// instruction immediates.
 struct StencilOffsets {
   int d[4][kStencilMax][2];
 };
@@ -47,7 +40,7 @@ __host__ __device__ constexpr StencilOffsets stencil_offsets() {
 // Entries whose cross-component couplings (xy, yx) vanish for every viscosity and time step:
 // the symmetric-gradient form couples the components only through mixed derivatives, which
 // integrate to zero for these neighbour pairs on the triangulated grid (the table builder
-// checks that both values are exactly 0).  Kernels skip their two cross products.
+// checks that both values are exactly 0).
 struct CrossZero {
   bool z[4][kStencilMax];
 };
@@ -83,27 +76,23 @@ __host__ __device__ constexpr DivOffsets div_offsets() {
       {{0, 0}, {1, 0}, {0, 1}, {1, 1}},
   }};
 }
-template <typename T>
 struct DivTable {
   int bt_count[4];
   int bt_off[4][kBtMax][2];
-  T bt_coef[4][kBtMax][2];
+  double bt_coef[4][kBtMax][2];
   int b_count;
   int b_off[kBMax][2];
-  int b_lds[kBMax];              // dJ (kTileC + 4) + dI
-  T b_coef[kBMax][2];
+  double b_coef[kBMax][2];
 };
 
 // Launchers run K independent systems (lane = blockIdx.y) over per-lane views (LP); the
 // vector views of one launch share one lane stride.  K = 1: one system.
 
-// Fluid rows of the operator on [u_x | u_y | p] in one tiled launch:
+// Fluid rows of the operator on [u_x | u_y | p] in one launch:
 //   y_u = A_f x_u - B^T x_p (+ C_f^T x_lam when cft_rp is given; lam_x at xl, lam_y at xl + Ns)
 //   y_p = -B x_u, and y_p[0] = x_p[0] (pinned node)
-template <typename T>
-void stencil_fluid_rows(int n, const StencilTable<T> *tab, const DivTable<T> *dv, const T *x, T *y,
-                        const int *cft_rp, const int *cft_col, const T *cft_val, const T *xl, int64_t Ns,
-                        hipStream_t s);
+void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
+              const double *cft_val, const double *xl, int64_t Ns, hipStream_t s);
 
 // Chebyshev smoothing of a velocity level, three steps per launch:
 // pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x
@@ -121,19 +110,18 @@ void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T
            LP<const double> b64 = LP<const double>());
 int post3_dot_count(int n);
 
-// The same launch inside the inner MINRES (FP64): v = s x, y = s (A11 x) + c r1 written over
+// The A11 rows inside the inner MINRES: v = s x, y = s (A11 x) + c r1 written over
 // r1, and one partial sum of v . y per tile in part[] (s, c read from device memory;
-// r1 read only when c != 0).  v goes to slot *slot_dev (a device scalar, clamped to
-// [0, nslot - 1]) of the Lanczos block: v.p + slot vs + lane v.s.  Returns the number of
-// tiles (entries of part per lane).
-int stencil_a11_minres(int n, const StencilTable<double> *tab, const DivTable<double> *dv, LP<const double> x,
-                       LP<double> v, LP<double> r1y, LP<const double> s_dev, LP<const double> c_dev,
-                       LP<const double> slot_dev, int64_t vs, int nslot, LP<double> part, hipStream_t s,
-                       int K = 1);
-int stencil_tile_count(int n);
+// r1 used only when c != 0).  v goes to slot *slot_dev (a device scalar, clamped to
+// [0, nslot - 1]) of the Lanczos block: v.p + slot vs + lane v.s.  a11_tile_count(n) parts per lane.
+void a11_minres(int n, const AfCoef<double> &cf, LP<const double> x, LP<double> v, LP<double> r1y,
+                LP<const double> s_dev, LP<const double> c_dev, LP<const double> slot_dev, int64_t vs, int nslot,
+                LP<double> part, hipStream_t s, int K = 1);
+int a11_tile_count(int n);
 
 // Host: the tables of A_f on an n x n grid from the element matrices (assemble.hip).
-void stencil_tables(int n, double nu, double rdt, StencilTable<double> &t64, StencilTable<float> &t32);
-void div_tables(int n, DivTable<double> &t64, DivTable<float> &t32);
+void stencil_tables(int n, double nu, double rdt, StencilTable &t);
+void div_tables(int n, DivTable &t);
+void check_div_closed_form(int n);   // the entries of B and B^T that the kernels are compiled with
 
 }  // namespace fsi

@@ -2,12 +2,9 @@
 // residuals).  Every interior row of A_f = (rho/dt) M_f + K_f is one of four stencils,
 // fixed by the parities of the node's lattice coordinates (vertex, horizontal edge,
 // vertical edge, diagonal edge); rows of boundary nodes are the identity and columns of
-// boundary nodes are zero (the Dirichlet condition imposed by value).  The coefficients
-// come from the same element matrices as the assembled A_f (host tables per level), so the
-// stencil product equals the CSR product up to the order of the sums.
-//
-// Bytes per node in the Chebyshev step: x, b, d read, d and y written (5 two-component
-// vectors); no matrix and no indices.
+// boundary nodes are zero (the Dirichlet condition imposed by value).  The coefficients are
+// closed forms (AfCoef), checked on the host against the sums over the element matrices that the
+// assembled A_f holds; products read no matrix and no indices.
 #include <initializer_list>
 #include <type_traits>
 #include <utility>
@@ -20,360 +17,10 @@
 
 namespace fsi {
 
-template <typename T>
-struct StencilArgs {
-  int n;
-  const StencilTable<T> *tab;   // device
-  const T *x, *b;
-  T *d, *y;
-  int L2;                      // nodes per component (2n+1)^2
-  T c1, c2;
-  // SP_A11 only: fluid rows on [u_x | u_y | p] (x and y hold all three; see
-  // stencil_fluid_rows), optional C_f^T x_lam on the velocity rows
-  const DivTable<T> *dv;
-  const int *cft_rp, *cft_col;
-  const T *cft_val, *xlx, *xly;
-  // SP_A11 inside MINRES (ms_s set): with device scalars s = *ms_s, c = *ms_c, write
-  // v = s x and y = s (A11 x) + c r1 over r1 (ms_r1y; r1 read only where c != 0), and the
-  // block's part of v . y to ms_part[tile]
-  const double *ms_s, *ms_c;
-  T *ms_v, *ms_r1y;
-  double *ms_part;
-  // lane strides (blockIdx.y = lane): vectors, MINRES scalars, per-tile parts.  The C_f^T
-  // term (cft_*, xlx, xly) is one system's and is not shifted.
-  int64_t lv, ls, lp;
-  // in MINRES: ms_v is the base of the Lanczos block; v goes to slot *ms_slot (a device
-  // scalar of the lane's state, clamped to [0, ms_nslot - 1]) at stride ms_vs
-  const double *ms_slot;
-  int64_t ms_vs;
-  int ms_nslot;
-};
-
-// Views of lane blockIdx.y (null pointers stay null).
-template <typename P>
-__device__ __forceinline__ void lane_shift(P *&p, int64_t stride) {
-  if (p) p += (int64_t)blockIdx.y * stride;
-}
-template <typename T>
-__device__ __forceinline__ StencilArgs<T> lane_args(const StencilArgs<T> &a0) {
-  StencilArgs<T> a = a0;
-  lane_shift(a.x, a.lv);
-  lane_shift(a.b, a.lv);
-  lane_shift(a.d, a.lv);
-  lane_shift(a.y, a.lv);
-  lane_shift(a.ms_v, a.lv);
-  lane_shift(a.ms_r1y, a.lv);
-  lane_shift(a.ms_s, a.ls);
-  lane_shift(a.ms_c, a.ls);
-  lane_shift(a.ms_part, a.lp);
-  lane_shift(a.ms_slot, a.ls);
-  if (a.ms_slot) {
-    int sl = (int)*a.ms_slot;
-    sl = sl < 0 ? 0 : sl >= a.ms_nslot ? a.ms_nslot - 1 : sl;
-    a.ms_v += (int64_t)sl * a.ms_vs;
-  }
-  return a;
-}
-
-// Tiled kernel.  A block owns kTileR lattice rows x kTileC nodes.  Phase 1 stages x with a
-// halo of two nodes into LDS (stride-1, coalesced), storing 0 for boundary nodes and for
-// nodes outside the lattice, so that interior rows need no column test.  Phase 2: wave w
-// computes row w of the tile, first the even-I nodes then the odd-I nodes, so the node
-// class (and the coefficient addresses) are uniform over the wave.  Phase 3 reads the
-// products back in row-major order and does the mode's epilogue with coalesced global
-// accesses.  Boundary rows are the identity.
-constexpr int kTW = kTileC + 4;                 // tile width with halo
-constexpr int kTH = kTileR + 4;
-
-template <typename T, int CLS>
-__device__ __forceinline__ void tile_row_products(const StencilTable<T> &tb, const T *X0, const T *X1,
-                                                  int base, T &s0, T &s1) {
-  constexpr StencilOffsets so = stencil_offsets();
-  constexpr CrossZero cz = cross_zero();
-  s0 = 0;
-  s1 = 0;
-#pragma unroll
-  for (int k = 0; k < kStencilCount[CLS]; ++k) {
-    const int o = base + so.d[CLS][k][1] * kTW + so.d[CLS][k][0];
-    const T y0 = X0[o], y1 = X1[o];
-    if (cz.z[CLS][k]) {   // xy = yx = 0 (fma with a zero coefficient adds nothing)
-      s0 = fma(tb.coef[CLS][k][0], y0, s0);
-      s1 = fma(tb.coef[CLS][k][3], y1, s1);
-    } else {
-      s0 = fma(tb.coef[CLS][k][1], y1, fma(tb.coef[CLS][k][0], y0, s0));
-      s1 = fma(tb.coef[CLS][k][3], y1, fma(tb.coef[CLS][k][2], y0, s1));
-    }
-  }
-}
-
-// B^T x_p of a class-CLS node from the staged pressure tile (row width kPW), base = the
-// tile position of P1 node (I >> 1, J >> 1)
-constexpr int kPW = kTileC / 2 + 2, kPH = kTileR / 2 + 2;   // P1 tile with a halo of one
-template <typename T, int CLS>
-__device__ __forceinline__ void tile_bt_products(const DivTable<T> &dv, const T *XP, int base, T &s0, T &s1) {
-  constexpr DivOffsets so = div_offsets();
-#pragma unroll
-  for (int k = 0; k < kBtCount[CLS]; ++k) {
-    const T pv = XP[base + so.bt[CLS][k][1] * kPW + so.bt[CLS][k][0]];
-    s0 = fma(-dv.bt_coef[CLS][k][0], pv, s0);
-    s1 = fma(-dv.bt_coef[CLS][k][1], pv, s1);
-  }
-}
-
 // Workgroups are dispatched to the 8 XCDs round-robin (block b to XCD b % 8); each XCD
 // gets a contiguous band of tiles in row-major order, so the halo rows a tile shares with
 // the tile below are still in that XCD's L2.
 constexpr int kXcd = 8;
-
-template <typename T, int MODE>
-__global__ void __launch_bounds__(256) k_stencil(StencilArgs<T> a0, int tiles_x, int tiles, int band) {
-  __shared__ T X[2][kTH * kTW];
-  __shared__ T S[2][kTileR * kTileC];
-  __shared__ T XP[MODE == SP_A11 ? kPH * kPW : 1];   // SP_A11: x_p tile (column 0 read as 0)
-  const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
-  if (t >= tiles) return;
-  const StencilArgs<T> a = lane_args(a0);
-  const int n2 = 2 * a.n, L = n2 + 1;
-  const int I0 = (t % tiles_x) * kTileC, J0 = (t / tiles_x) * kTileR;
-  const int tid = threadIdx.x;
-  const StencilTable<T> &tb = *a.tab;
-  double ms_acc = 0.0;   // SP_A11 in MINRES: this thread's part of v . y
-  // epilogue operands of this thread's nodes (row-major, coalesced), loaded first; x only at
-  // Dirichlet nodes (the staged tile holds 0 there), the interior x comes from the tile
-  constexpr int EIT = kTileR * kTileC / 256;
-  T ex[EIT][2], eb[EIT][2], ed[EIT][2];
-#pragma unroll
-  for (int q = 0; q < EIT; ++q) {
-    const int e = tid + 256 * q, I = I0 + e % kTileC, J = J0 + e / kTileC;
-    ex[q][0] = ex[q][1] = eb[q][0] = eb[q][1] = ed[q][0] = ed[q][1] = 0;
-    if (I <= n2 && J <= n2) {
-      const int r = J * L + I;
-      if (I == 0 || J == 0 || I == n2 || J == n2) {
-        ex[q][0] = a.x[r];
-        ex[q][1] = a.x[a.L2 + r];
-      }
-      if constexpr (MODE == SP_RESID || MODE == SP_CHEB) {
-        eb[q][0] = a.b[r];
-        eb[q][1] = a.b[a.L2 + r];
-      }
-      if constexpr (MODE == SP_CHEB) {
-        ed[q][0] = a.d[r];
-        ed[q][1] = a.d[a.L2 + r];
-      }
-      if constexpr (MODE == SP_A11) {   // in MINRES: r1 (ed holds it)
-        if (a.ms_s) {
-          ed[q][0] = a.ms_r1y[r];
-          ed[q][1] = a.ms_r1y[a.L2 + r];
-        }
-      }
-    }
-  }
-  // SP_A11: the pressure tile (P1 rows J0/2 - 1 .. J0/2 + 2, columns I0/2 - 1 .. I0/2 + 64)
-  // and, for the pressure rows of the tile (threads 0..127), x_p and r1 at the own node
-  T pp_x = 0, pp_r1 = 0;
-  if constexpr (MODE == SP_A11) {
-    const int64_t o2 = 2 * (int64_t)a.L2;
-    for (int e = tid; e < kPH * kPW; e += 256) {
-      const int pi = (I0 >> 1) - 1 + e % kPW, pj = (J0 >> 1) - 1 + e / kPW;
-      T pv = 0;
-      if (pi >= 0 && pj >= 0 && pi <= a.n && pj <= a.n) {
-        const int64_t q = (int64_t)pj * (a.n + 1) + pi;
-        if (q != 0) pv = a.x[o2 + q];
-      }
-      XP[e] = pv;
-    }
-    if (tid < 2 * kWave) {
-      const int pi = (I0 >> 1) + tid % kWave, pj = (J0 >> 1) + tid / kWave;
-      if (pi <= a.n && pj <= a.n) {
-        const int64_t q = (int64_t)pj * (a.n + 1) + pi;
-        pp_x = a.x[o2 + q];
-        if (a.ms_s) pp_r1 = a.ms_r1y[o2 + q];
-      }
-    }
-  }
-  // phase 1: x tile with halo (all loads issued before the LDS stores)
-  constexpr int NE = kTH * kTW, IT = (NE + 255) / 256;
-  T v[IT][2];
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + 256 * q, tr = e / kTW, tc = e % kTW;
-    const int I = I0 - 2 + tc, J = J0 - 2 + tr;
-    v[q][0] = 0;
-    v[q][1] = 0;
-    if (e < NE && I > 0 && J > 0 && I < n2 && J < n2) {
-      const int r = J * L + I;
-      v[q][0] = a.x[r];
-      v[q][1] = a.x[a.L2 + r];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < IT; ++q) {
-    const int e = tid + 256 * q;
-    if (e < NE) {
-      X[0][e] = v[q][0];
-      X[1][e] = v[q][1];
-    }
-  }
-  __syncthreads();
-  // phase 2: products of the interior rows, one tile row per wave
-  {
-    const int w = tid / kWave, lane = tid % kWave;
-    const int J = J0 + w;
-    if (J > 0 && J < n2) {
-#pragma unroll
-      for (int par = 0; par < 2; ++par) {
-        const int i = 2 * lane + par;
-        const int I = I0 + i;
-        T s0 = 0, s1 = 0;
-        const int base = (w + 2) * kTW + (i + 2);
-        if (I > 0 && I < n2) {
-          // SP_A11: - B^T x_p from the pressure tile; P1 node (I >> 1, J >> 1) sits at
-          // tile row (w >> 1) + 1, column lane + 1 (I0 and J0 are even)
-          const int pbase = ((w >> 1) + 1) * kPW + lane + 1;
-          if (J & 1) {
-            if (par) {
-              tile_row_products<T, 3>(tb, X[0], X[1], base, s0, s1);
-              if constexpr (MODE == SP_A11) tile_bt_products<T, 3>(*a.dv, XP, pbase, s0, s1);
-            } else {
-              tile_row_products<T, 2>(tb, X[0], X[1], base, s0, s1);
-              if constexpr (MODE == SP_A11) tile_bt_products<T, 2>(*a.dv, XP, pbase, s0, s1);
-            }
-          } else {
-            if (par) {
-              tile_row_products<T, 1>(tb, X[0], X[1], base, s0, s1);
-              if constexpr (MODE == SP_A11) tile_bt_products<T, 1>(*a.dv, XP, pbase, s0, s1);
-            } else {
-              tile_row_products<T, 0>(tb, X[0], X[1], base, s0, s1);
-              if constexpr (MODE == SP_A11) tile_bt_products<T, 0>(*a.dv, XP, pbase, s0, s1);
-            }
-          }
-        }
-        S[0][w * kTileC + i] = s0;
-        S[1][w * kTileC + i] = s1;
-      }
-    }
-  }
-  __syncthreads();
-  // phase 3: epilogue, row-major and coalesced
-#pragma unroll
-  for (int q = 0; q < EIT; ++q) {
-    const int e = tid + 256 * q;
-    const int j = e / kTileC, i = e % kTileC;
-    const int I = I0 + i, J = J0 + j;
-    if (I > n2 || J > n2) continue;
-    const int r = J * L + I;
-    const bool bnd = I == 0 || J == 0 || I == n2 || J == n2;
-    const int xo = (j + 2) * kTW + (i + 2);   // the node in the staged tile
-    const T x0 = bnd ? ex[q][0] : X[0][xo], x1 = bnd ? ex[q][1] : X[1][xo];
-    const T s0 = bnd ? x0 : S[0][e], s1 = bnd ? x1 : S[1][e];
-    if constexpr (MODE == SP_APPLY) {
-      a.y[r] = s0;
-      a.y[a.L2 + r] = s1;
-    } else if constexpr (MODE == SP_A11) {
-      T t0 = s0, t1 = s1;   // A_f x_u - B^T x_p (identity on Dirichlet rows)
-      if (a.cft_rp) {
-        for (int k = a.cft_rp[r]; k < a.cft_rp[r + 1]; ++k) {
-          const T cv = a.cft_val[k];
-          const int j = a.cft_col[k];
-          t0 += cv * a.xlx[j];
-          t1 += cv * a.xly[j];
-        }
-      }
-      if (a.ms_s) {
-        const T sc = (T)*a.ms_s, cc = (T)*a.ms_c;
-        T y0 = sc * t0, y1 = sc * t1;
-        if (cc != T(0)) {
-          y0 += cc * ed[q][0];
-          y1 += cc * ed[q][1];
-        }
-        const T v0 = sc * x0, v1 = sc * x1;
-        a.ms_r1y[r] = y0;
-        a.ms_r1y[a.L2 + r] = y1;
-        a.ms_v[r] = v0;
-        a.ms_v[a.L2 + r] = v1;
-        ms_acc += (double)v0 * (double)y0 + (double)v1 * (double)y1;
-      } else {
-        a.y[r] = t0;
-        a.y[a.L2 + r] = t1;
-      }
-    } else if constexpr (MODE == SP_RESID) {
-      a.y[r] = eb[q][0] - s0;
-      a.y[a.L2 + r] = eb[q][1] - s1;
-    } else {
-      const T r0 = eb[q][0] - s0, r1 = eb[q][1] - s1;
-      T z0 = r0, z1 = r1;
-      if (!bnd) {   // class-wise D^{-1}: scalar loads, picked per node
-        const int cls = (I & 1) | ((J & 1) << 1);
-        T di[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          di[k] = cls == 0 ? tb.dinv[0][k] : cls == 1 ? tb.dinv[1][k] : cls == 2 ? tb.dinv[2][k] : tb.dinv[3][k];
-        z0 = di[0] * r0 + di[1] * r1;
-        z1 = di[2] * r0 + di[3] * r1;
-      }
-      const T d0 = a.c1 * ed[q][0] + a.c2 * z0, d1 = a.c1 * ed[q][1] + a.c2 * z1;
-      a.d[r] = d0;
-      a.d[a.L2 + r] = d1;
-      a.y[r] = x0 + d0;
-      a.y[a.L2 + r] = x1 + d1;
-    }
-  }
-  if constexpr (MODE == SP_A11) {
-    // phase 4: pressure rows of the P1 nodes at even lattice positions of the tile
-    // (2 rows x 64 nodes), -B x_u from the staged x tile (Dirichlet values read as zero)
-    if (tid < 2 * kWave) {
-      const int pr = tid / kWave, pc = tid % kWave;
-      const int pi = (I0 >> 1) + pc, pj = (J0 >> 1) + pr;
-      if (pi <= a.n && pj <= a.n) {
-        const DivTable<T> &dv = *a.dv;
-        constexpr StencilOffsets so = stencil_offsets();   // B rows: the vertex pattern
-        const int base = (2 * pr + 2) * kTW + (2 * pc + 2);
-        T sp = 0;
-#pragma unroll
-        for (int k = 0; k < kBMax; ++k) {
-          const int o = base + so.d[0][k][1] * kTW + so.d[0][k][0];
-          sp = fma(dv.b_coef[k][1], X[1][o], fma(dv.b_coef[k][0], X[0][o], sp));
-        }
-        const int64_t q = (int64_t)pj * (a.n + 1) + pi;
-        const int64_t o2 = 2 * (int64_t)a.L2;
-        const T val = q == 0 ? pp_x : -sp;
-        if (a.ms_s) {
-          const T sc = (T)*a.ms_s, cc = (T)*a.ms_c;
-          T yv = sc * val;
-          if (cc != T(0)) yv += cc * pp_r1;
-          const T vv = sc * pp_x;
-          a.ms_r1y[o2 + q] = yv;
-          a.ms_v[o2 + q] = vv;
-          ms_acc += (double)vv * (double)yv;
-        } else {
-          a.y[o2 + q] = val;
-        }
-      }
-    }
-    if (a.ms_s) {   // the block's part of v . y (fixed order: deterministic)
-      __shared__ double red[256 / kWave];
-      const double wsum = wave_sum(ms_acc);
-      if (tid % kWave == 0) red[tid / kWave] = wsum;
-      __syncthreads();
-      if (tid == 0) {
-        double b = 0.0;
-        for (int k = 0; k < 256 / kWave; ++k) b += red[k];
-        a.ms_part[t] = b;
-      }
-    }
-  }
-}
-
-template <typename T, int MODE>
-static void launch_tiles(int n, const StencilArgs<T> &a, hipStream_t s, int K) {
-  const int L = 2 * n + 1;
-  const int tx = (L + kTileC - 1) / kTileC, ty = (L + kTileR - 1) / kTileR;
-  const int tiles = tx * ty, band = (tiles + kXcd - 1) / kXcd;
-  FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
-  hipLaunchKernelGGL((k_stencil<T, MODE>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(256), 0, s, a, tx,
-                     tiles, band);
-  FSI_CHECK_LAUNCH();
-}
 
 // One lane stride for the vectors of a launch (null views take any)
 static int64_t common_stride(std::initializer_list<std::pair<const void *, int64_t>> v, int K) {
@@ -385,56 +32,6 @@ static int64_t common_stride(std::initializer_list<std::pair<const void *, int64
   }
   return s < 0 ? 0 : s;
 }
-
-template <typename T, int MODE>
-void stencil_launch(int n, const StencilTable<T> *tab, LP<const T> x, LP<const T> b, LP<T> d, LP<T> y, T c1,
-                    T c2, hipStream_t s, int K) {
-  FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  static_assert(kTileR * kWave == 256 && 2 * kWave == kTileC, "one tile row per wave, two nodes per lane");
-  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}, {d.p, d.s}, {y.p, y.s}}, K);
-  StencilArgs<T> a{n, tab, x.p, b.p, d.p, y.p, (2 * n + 1) * (2 * n + 1), c1, c2, nullptr, nullptr, nullptr,
-                   nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, lv, 0, 0};
-  launch_tiles<T, MODE>(n, a, s, K);
-}
-
-template <typename T>
-void stencil_fluid_rows(int n, const StencilTable<T> *tab, const DivTable<T> *dv, const T *x, T *y,
-                        const int *cft_rp, const int *cft_col, const T *cft_val, const T *xl, int64_t Ns,
-                        hipStream_t s) {
-  FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  static_assert(kTileC % 2 == 0 && kTileR % 2 == 0 && kTileC / 2 == kWave && kTileR / 2 * kWave <= 256,
-                "a tile holds 2 x 64 P1 nodes, one per thread of the first two waves");
-  const int L = 2 * n + 1, L2 = L * L;
-  StencilArgs<T> a{n, tab, x, nullptr, nullptr, y, L2, T(0), T(0), dv, cft_rp, cft_col, cft_val, xl,
-                   xl ? xl + Ns : nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0};
-  launch_tiles<T, SP_A11>(n, a, s, 1);
-}
-
-int stencil_a11_minres(int n, const StencilTable<double> *tab, const DivTable<double> *dv, LP<const double> x,
-                       LP<double> v, LP<double> r1y, LP<const double> s_dev, LP<const double> c_dev,
-                       LP<const double> slot_dev, int64_t vs, int nslot, LP<double> part, hipStream_t s, int K) {
-  FSI_REQUIRE((int64_t)(2 * n + 1) * (2 * n + 1) < INT32_MAX, FSI_E_ARG, "grid too large for 32-bit stencil indices");
-  FSI_REQUIRE(slot_dev.p && nslot >= 1, FSI_E_ARG, "the Lanczos block needs a slot index and at least one slot");
-  const int L = 2 * n + 1, L2 = L * L;
-  const int64_t lv = common_stride({{x.p, x.s}, {v.p, v.s}, {r1y.p, r1y.s}}, K);
-  const int64_t ls = common_stride({{s_dev.p, s_dev.s}, {c_dev.p, c_dev.s}, {slot_dev.p, slot_dev.s}}, K);
-  StencilArgs<double> a{n, tab, x.p, nullptr, nullptr, nullptr, L2, 0.0, 0.0, dv, nullptr, nullptr, nullptr, nullptr,
-                        nullptr, s_dev.p, c_dev.p, v.p, r1y.p, part.p, lv, ls, part.s, slot_dev.p, vs, nslot};
-  launch_tiles<double, SP_A11>(n, a, s, K);
-  const int tx = (L + kTileC - 1) / kTileC, ty = (L + kTileR - 1) / kTileR;
-  return tx * ty;
-}
-
-int stencil_tile_count(int n) {
-  const int L = 2 * n + 1;
-  return ((L + kTileC - 1) / kTileC) * ((L + kTileR - 1) / kTileR);
-}
-template void stencil_fluid_rows<double>(int, const StencilTable<double> *, const DivTable<double> *,
-                                         const double *, double *, const int *, const int *, const double *,
-                                         const double *, int64_t, hipStream_t);
-template void stencil_fluid_rows<float>(int, const StencilTable<float> *, const DivTable<float> *, const float *,
-                                        float *, const int *, const int *, const float *, const float *, int64_t,
-                                        hipStream_t);
 
 // ---------------------------------------------------------------- smoothing, cell by cell
 // The Chebyshev steps of a velocity level and its residual with one thread per cell
@@ -1001,15 +598,242 @@ template void resid_restrict<double>(int, const AfCoef<double> &, LP<const doubl
 template void resid_restrict<float>(int, const AfCoef<float> &, LP<const float>, LP<const float>, LP<float>,
                                     hipStream_t, int);
 
-#define FSI_STENCIL_INST(T, M)                                                                              \
-  template void stencil_launch<T, M>(int, const StencilTable<T> *, LP<const T>, LP<const T>, LP<T>, LP<T>, T, T, \
-                                     hipStream_t, int);
-FSI_STENCIL_INST(double, SP_APPLY)
-FSI_STENCIL_INST(double, SP_RESID)
-FSI_STENCIL_INST(double, SP_CHEB)
-FSI_STENCIL_INST(float, SP_APPLY)
-FSI_STENCIL_INST(float, SP_RESID)
-FSI_STENCIL_INST(float, SP_CHEB)
-#undef FSI_STENCIL_INST
+// ---------------------------------------------------------------- A11 rows
+// y = A11 x on [u_x | u_y | p] with one thread per cell: the cell's four velocity rows
+// (cell_products and, from a staged pressure tile, the B^T rows of its three edge nodes; vertices
+// have none) and the pressure row of its P1 vertex, whose 19 velocity nodes are the window the
+// thread reads anyway.  No row is computed twice: a block of 8 waves owns 8 x 64 cells.
+//
+// Bound by memory where the vectors leave the caches: the form in MINRES reads x and r1 and writes
+// y and v, 302 MB at
+// 1024^2 in 59 us, more than a copy from device memory reaches, since part of them is still in the
+// last-level cache.  One thread per node with the coefficients of its class read through the scalar
+// cache took 84 us, and 8.0 against 6.6 at 32^2.
+struct A11Args {
+  int n;
+  AfCoef<double> cf;
+  double g;             // h / 6, the unit of the entries of B
+  const double *x;
+  double *y;            // in MINRES: r1, overwritten
+  int64_t lv;           // lane stride of x, y and vh (lane = blockIdx.y)
+  const int *cft_rp, *cft_col;   // C_f^T of one system (K = 1), or null
+  const double *cft_val, *xlx, *xly;
+  const double *ms_s, *ms_c, *ms_slot;   // in MINRES: scalars s, c and the slot of v
+  int64_t ls;           // their lane stride
+  double *vh;           // the Lanczos block: slot stride vs, nslot slots
+  int64_t vs;
+  int nslot;
+  double *part;         // per-tile sums of v . y, lane stride lp
+  int64_t lp;
+};
+
+template <bool MS>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int tiles_x, int tiles, int band) {
+  __shared__ V2<double> X[2 * kCellPL];
+  __shared__ double XP[(kCellWaves + 2) * kCellHW];   // P1 rows j0 - 1 .. j0 + 8; the pinned entry read as 0
+  const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
+  if (t >= tiles) return;
+  const double *xg = a.x + (int64_t)blockIdx.y * a.lv;
+  double *yg = a.y + (int64_t)blockIdx.y * a.lv;
+  const int n = a.n, L = 2 * n + 1;
+  const int64_t N = (int64_t)L * L, o2 = 2 * N;
+  const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellWaves;
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i = i0 + lane, j = j0 + w;
+  const bool node = i <= n && j <= n;   // the cell's P1 vertex is in the lattice
+  const int64_t q0 = (int64_t)j * (n + 1) + i;
+  {   // the pressure tile
+    constexpr int NE = (kCellWaves + 2) * kCellHW, NT = kWave * kCellWaves, IT = (NE + NT - 1) / NT;
+    double v[IT];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int e = threadIdx.x + NT * k, pi = i0 - 1 + e % kCellHW, pj = j0 - 1 + e / kCellHW;
+      const int64_t q = (int64_t)pj * (n + 1) + pi;
+      v[k] = e < NE && pi >= 0 && pj >= 0 && pi <= n && pj <= n && q != 0 ? xg[o2 + q] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < IT; ++k)
+      if (threadIdx.x + NT * k < NE) XP[threadIdx.x + NT * k] = v[k];
+  }
+  stage_pairs<double, kCellH>(X, xg, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
+  int ct[2][3] = {};   // C_f^T rows of the cell's nodes: consecutive on each lattice row
+  if constexpr (!MS) {
+    if (node && a.cft_rp) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h == 1 && j == n) continue;
+        const int *rp = a.cft_rp + (int64_t)(2 * j + h) * L + 2 * i;
+        ct[h][0] = rp[0];
+        ct[h][1] = rp[1];
+        ct[h][2] = i < n ? rp[2] : ct[h][1];
+      }
+    }
+  }
+  V2<double> r1[4];
+  double r1p = 0.0;
+  if constexpr (MS) {   // after the staging, whose registers it takes over
+    load_cell(yg, N, L, n, i, j, r1);
+    if (node) r1p = yg[o2 + q0];
+  }
+  __syncthreads();
+  V2<double> x[4], s[4];
+  double div;
+  cell_products<double, kCellPL, kCellHW, CELL_ALL, true>(X + (2 * w + 2) * kCellHW + lane + 1, a.cf, x, s, &div);
+  const double *P = XP + (w + 1) * kCellHW + lane + 1;
+  double xp = P[0];
+  {   // - B^T x_p at the edge nodes
+    const double p00 = P[0], p10 = P[1], p01 = P[kCellHW], p11 = P[kCellHW + 1], pm = P[-1], p0m = P[-kCellHW];
+    const double d1 = p10 - p00, d2 = p01 - p00, d3 = p11 - p01, d4 = p11 - p10;
+    s[1].x = fma(2.0 * a.g, d1, s[1].x);
+    s[1].y = fma(a.g, (p00 - p0m) + d4, s[1].y);
+    s[2].x = fma(a.g, (p00 - pm) + d3, s[2].x);
+    s[2].y = fma(2.0 * a.g, d2, s[2].y);
+    s[3].x = fma(a.g, d1 + d3, s[3].x);
+    s[3].y = fma(a.g, d2 + d4, s[3].y);
+  }
+  const CellIn in = cell_inside(i, j, n);
+  if (i == 0 || j == 0 || i >= n || j >= n) {   // Dirichlet rows: the identity; zero outside the lattice
+    V2<double> xb[4];
+    load_cell(xg, N, L, n, i, j, xb);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (!in.q[q]) x[q] = s[q] = xb[q];
+  }
+  double sp = -a.g * div;
+  if (q0 == 0) xp = sp = xg[o2];   // the pinned entry
+  if constexpr (MS) {
+    const double sc = a.ms_s[(int64_t)blockIdx.y * a.ls], cc = a.ms_c[(int64_t)blockIdx.y * a.ls];
+    int sl = (int)a.ms_slot[(int64_t)blockIdx.y * a.ls];
+    sl = sl < 0 ? 0 : sl >= a.nslot ? a.nslot - 1 : sl;
+    double *vg = a.vh + (int64_t)sl * a.vs + (int64_t)blockIdx.y * a.lv;
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      s[q] = V2<double>{sc * s[q].x, sc * s[q].y};
+      if (cc != 0.0) s[q] = V2<double>{fma(cc, r1[q].x, s[q].x), fma(cc, r1[q].y, s[q].y)};
+      x[q] = V2<double>{sc * x[q].x, sc * x[q].y};
+      acc += x[q].x * s[q].x + x[q].y * s[q].y;
+    }
+    if (node) {
+      store_cell<double, double>(yg, N, L, n, i, j, s);
+      store_cell<double, double>(vg, N, L, n, i, j, x);
+      sp *= sc;
+      if (cc != 0.0) sp = fma(cc, r1p, sp);
+      xp *= sc;
+      yg[o2 + q0] = sp;
+      vg[o2 + q0] = xp;
+      acc += xp * sp;
+    } else {
+      acc = 0.0;
+    }
+    __shared__ double red[kCellWaves];   // the tile's part of v . y in a fixed order
+    acc = wave_sum(acc);
+    if (lane == 0) red[w] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double b = 0.0;
+#pragma unroll
+      for (int k = 0; k < kCellWaves; ++k) b += red[k];
+      a.part[(int64_t)blockIdx.y * a.lp + t] = b;
+    }
+  } else {
+    if (a.cft_rp) {   // uniform: + C_f^T x_lam
+      // The rows of a wave's nodes on one lattice row are consecutive in C_f^T: the wave forms their
+      // products entry by entry (coalesced) into LDS, over the x nobody needs any more, and each
+      // thread sums its own rows there in their order.  A thread that walks its rows in device
+      // memory instead: 194 us at 1024^2 with 2.8 M entries, against
+      // 115 (141 with one thread per node).
+      constexpr int CH = 2 * kCellPL / kCellWaves / kWave * kWave;
+      V2<double> *const buf = X + w * CH;
+      const int last = min(n - i0, kWave - 1);   // the wave's last lane in the lattice
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k0 = __shfl(ct[h][0], 0), k1 = __shfl(ct[h][2], last);
+        for (int c0 = k0; c0 < k1; c0 += CH) {
+#pragma unroll
+          for (int u = 0; u < CH; u += kWave) {
+            const int k = c0 + u + lane;
+            if (k < k1) {
+              const double cv = a.cft_val[k];
+              const int c = a.cft_col[k];
+              buf[u + lane] = V2<double>{cv * a.xlx[c], cv * a.xly[c]};
+            }
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int e = min(ct[h][q + 1], c0 + CH);
+            for (int k = max(ct[h][q], c0); k < e; ++k) {
+              const V2<double> v = buf[k - c0];
+              s[2 * h + q].x += v.x;
+              s[2 * h + q].y += v.y;
+            }
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+    }
+    if (node) {
+      store_cell<double, double>(yg, N, L, n, i, j, s);
+      yg[o2 + q0] = sp;
+    }
+  }
+}
+
+template <bool MS>
+static void launch_a11(A11Args a, hipStream_t s, int K) {
+  cell_launch_checks(a.n, K);
+  int tx;
+  const int tiles = cell_tiles(a.n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
+  a.g = 1.0 / (6.0 * a.n);
+  hipLaunchKernelGGL(k_a11<MS>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
+                     tiles, band);
+  FSI_CHECK_LAUNCH();
+}
+
+void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
+              const double *cft_val, const double *xl, int64_t Ns, hipStream_t s) {
+  A11Args a{};
+  a.n = n;
+  a.cf = cf;
+  a.x = x;
+  a.y = y;
+  a.cft_rp = cft_rp;
+  a.cft_col = cft_col;
+  a.cft_val = cft_val;
+  a.xlx = xl;
+  a.xly = xl ? xl + Ns : nullptr;
+  launch_a11<false>(a, s, 1);
+}
+
+void a11_minres(int n, const AfCoef<double> &cf, LP<const double> x, LP<double> v, LP<double> r1y,
+                LP<const double> s_dev, LP<const double> c_dev, LP<const double> slot_dev, int64_t vs, int nslot,
+                LP<double> part, hipStream_t s, int K) {
+  FSI_REQUIRE(slot_dev.p && nslot >= 1, FSI_E_ARG, "the Lanczos block needs a slot index and at least one slot");
+  A11Args a{};
+  a.n = n;
+  a.cf = cf;
+  a.x = x.p;
+  a.y = r1y.p;
+  a.lv = common_stride({{x.p, x.s}, {v.p, v.s}, {r1y.p, r1y.s}}, K);
+  a.ms_s = s_dev.p;
+  a.ms_c = c_dev.p;
+  a.ms_slot = slot_dev.p;
+  a.ls = common_stride({{s_dev.p, s_dev.s}, {c_dev.p, c_dev.s}, {slot_dev.p, slot_dev.s}}, K);
+  a.vh = v.p;
+  a.vs = vs;
+  a.nslot = nslot;
+  a.part = part.p;
+  a.lp = part.s;
+  launch_a11<true>(a, s, K);
+}
+
+int a11_tile_count(int n) {
+  int tx;
+  return cell_tiles(n, kWave, kCellWaves, tx);
+}
 
 }  // namespace fsi

@@ -6,8 +6,11 @@ gives the restriction its larger tile; and the pressure part's (descent 29 x 5 c
 where it starts on the finest level): a grid with one level (5), a coarse end alone (6 to 64, dense
 levels of 16 to 256 unknowns), one and more levels above it.  The matrix-free preconditioner equals the one on the
 assembled operators (fsi_set_smoother) up to the order of the sums, in velocity and pressure each (a
-few hundred roundings of a well conditioned cycle): one application in both precisions, and one
-and two inner steps in FP64."""
+few hundred roundings of a well conditioned cycle): one application in both precisions.
+
+The A11 rows by cells (tiles of 64 x 8 cells) are held against sums in extended precision: every
+row of A_f, B^T and B from its closed form, entry by entry within 64 roundings of |A| |x| (a row has
+at most 38 products, B^T 4 more, in sums of depth under 30)."""
 import numpy as np
 import pytest
 
@@ -29,19 +32,111 @@ def test_cell_launches_equal_assembled(n):
     r = to_dev(np.random.default_rng(71 + n).uniform(-1, 1, ctx.sizes["N"]))   # boundary rows too
     sz = ctx.sizes
     for prec, tol in ((fsi.FP64, 1e-12), (fsi.FP32, 1e-5)):
-        for mode, maxit in ((fsi.INNER_FIXED_DIAG, 1), (fsi.INNER_MINRES, 1), (fsi.INNER_MINRES, 2)):
-            if mode == fsi.INNER_MINRES and (n < 60 or n > 320 or prec == fsi.FP32):
-                continue   # MINRES coefficients that nearly cancel magnify the rounding (1e4 times at 8^2)
-            out = []
-            for kind in (fsi.SMOOTH_CSR, fsi.SMOOTH_STENCIL):
-                ctx.set_smoother(kind)
-                ctx.set_inner_mode(mode)
-                ctx.set_inner(1e-30, maxit)
-                z = torch.zeros_like(r)
-                ctx.apply_precond(r, z, fsi.PC_DIAG, prec)
-                out.append(to_host(z))
-            for name, lo, hi in (("u", 0, sz["off_p"]), ("p", sz["off_p"], sz["off_Xx"])):
-                d = rel(out[1][lo:hi], out[0][lo:hi])
-                print(f"  prec {prec} mode {mode} maxit {maxit} {name}: rel diff {d:.2e}", flush=True)
-                assert d <= tol
+        out = []
+        for kind in (fsi.SMOOTH_CSR, fsi.SMOOTH_STENCIL):
+            ctx.set_smoother(kind)
+            ctx.set_inner_mode(fsi.INNER_FIXED_DIAG)
+            z = torch.zeros_like(r)
+            ctx.apply_precond(r, z, fsi.PC_DIAG, prec)
+            out.append(to_host(z))
+        for name, lo, hi in (("u", 0, sz["off_p"]), ("p", sz["off_p"], sz["off_Xx"])):
+            d = rel(out[1][lo:hi], out[0][lo:hi])
+            print(f"  prec {prec} {name}: rel diff {d:.2e}", flush=True)
+            assert d <= tol
+    ctx.close()
+
+
+def a11_rows(n, nu, rdt, x):
+    """A11 x and |A11| |x| in extended precision, x = [u_x | u_y | p] (Dirichlet rows and the pinned
+    pressure row are the identity, their columns zero)."""
+    ld = np.longdouble
+    L = 2 * n + 1
+    h = ld(1) / n
+    k, m, g = ld(nu) / 24, ld(rdt) * h * h / 720, h / 6
+    raw = [x[: L * L].reshape(L, L), x[L * L : 2 * L * L].reshape(L, L), x[2 * L * L :].reshape(n + 1, n + 1)]
+    u = [np.zeros((L + 4, L + 4), ld) for _ in range(2)]
+    for c in range(2):
+        u[c][3 : L + 1, 3 : L + 1] = raw[c][1:-1, 1:-1]
+    p = np.zeros((n + 5, n + 5), ld)
+    p[2:-2, 2:-2] = raw[2]
+    p[2, 2] = 0
+
+    def af(cls, I, J):   # (along, across, cross) of the entry towards neighbour (I, J), x component
+        if I < 0 or (I == 0 and J < 0):
+            I, J = -I, -J
+        if (I, J) == (0, 0):
+            return (72 * k + 72 * m, 72 * k + 72 * m, -12 * k) if cls == 0 else (96 * k + 128 * m, 96 * k + 128 * m, -16 * k)
+        if cls == 0:
+            return {(1, 0): (-32 * k, -16 * k, 8 * k), (0, 1): (-16 * k, -32 * k, 8 * k),
+                    (2, 0): (8 * k - 4 * m, 4 * k - 4 * m, -2 * k), (0, 2): (4 * k - 4 * m, 8 * k - 4 * m, -2 * k),
+                    (1, 1): (0 * k, 0 * k, -8 * k), (2, 2): (-4 * m, -4 * m, 2 * k)}.get((I, J), (-8 * m, -8 * m, 0 * k))
+        if (I, J) == (1, 0):
+            return (-32 * k, -16 * k, 8 * k) if cls == 1 else (32 * m - 32 * k, 32 * m - 16 * k, 8 * k)
+        if (I, J) == (0, 1):
+            return (-16 * k, -32 * k, 8 * k) if cls == 2 else (32 * m - 16 * k, 32 * m - 32 * k, 8 * k)
+        if (I, J) == (1, 1):
+            return (0 * k, 0 * k, -8 * k) if cls == 3 else (32 * m, 32 * m, -8 * k)
+        return (-8 * m, -8 * m, 0 * k)
+
+    out = [np.zeros((L, L), ld), np.zeros((L, L), ld), np.zeros((n + 1, n + 1), ld)]
+    mag = [np.zeros_like(o) for o in out]
+
+    def add(c, sl, coef, v):
+        out[c][sl] += coef * v
+        mag[c][sl] += abs(coef) * abs(v)
+
+    cnt, off, _ = fsi.export_lattice(n, fsi.LAT_AF, nu, rdt)
+    for cls in range(4):
+        sl = (slice(cls >> 1, L, 2), slice(cls & 1, L, 2))
+        r, c = out[0][sl].shape
+        for dI, dJ in off[cls, : cnt[cls]]:
+            xx, yy, xy = af(cls, int(dI), int(dJ))
+            a, b = (v[2 + dJ + (cls >> 1) :: 2, 2 + dI + (cls & 1) :: 2][:r, :c] for v in u)
+            add(0, sl, xx, a), add(0, sl, xy, b), add(1, sl, yy, b), add(1, sl, xy, a)
+    unit = 6 * n
+    cnt, off, val = fsi.export_lattice(n, fsi.LAT_BT)
+    for cls in range(4):
+        sl = (slice(cls >> 1, L, 2), slice(cls & 1, L, 2))
+        r, c = out[0][sl].shape
+        for (dI, dJ), v in zip(off[cls, : cnt[cls]], val[cls]):
+            pp = p[2 + dJ :, 2 + dI :][:r, :c]
+            for comp in range(2):
+                assert abs(v[comp] * unit - np.rint(v[comp] * unit)) < 1e-10
+                add(comp, sl, -np.rint(v[comp] * unit) * g, pp)
+    cnt, off, val = fsi.export_lattice(n, fsi.LAT_B)
+    for (dI, dJ), v in zip(off[0, : cnt[0]], val[0]):
+        for comp in range(2):
+            add(2, slice(None), -np.rint(v[comp] * unit) * g, u[comp][2 + dJ :: 2, 2 + dI :: 2][: n + 1, : n + 1])
+    for c in range(2):
+        for e in (0, -1):
+            out[c][e], out[c][:, e] = raw[c][e], raw[c][:, e]
+            mag[c][e] = mag[c][:, e] = 0
+    out[2][0, 0], mag[2][0, 0] = raw[2][0, 0], 0
+    return np.concatenate([o.ravel() for o in out]), np.concatenate([o.ravel() for o in mag])
+
+
+@pytest.mark.parametrize("n", [2, 5, 8, 56, 64, 72, 160])
+def test_a11_rows_by_cells(n):
+    print(f"[A11 rows n={n}]", flush=True)
+    torch = torch_dev()
+    wl = inputs.small_workload(n, 4, (0.5, 0.5), 0.2)
+    ctx = fsi.Context.from_workload(wl)
+    xy, _ = wl.solid_mesh()
+    ctx.assemble_coupling(to_dev(np.concatenate([xy[:, 0], xy[:, 1]])))
+    sz = ctx.sizes
+    nf = sz["off_Xx"]
+    t, q = np.linspace(0, 1, 2 * n + 1), np.linspace(0, 1, n + 1)
+    smooth = np.concatenate([np.outer(np.cos(t), np.exp(t)).ravel(), np.outer(np.exp(-t), np.sin(t)).ravel(),
+                             np.outer(np.cos(3 * q), q + 1).ravel()])
+    for name, xf in (("random", np.random.default_rng(5 + n).uniform(-1, 1, nf)), ("smooth", smooth)):
+        x = np.zeros(sz["N"])
+        x[:nf] = xf
+        y = torch.zeros(sz["N"], dtype=torch.float64, device="cuda")
+        ctx.apply_operator(to_dev(x), y)
+        want, mag = a11_rows(n, wl.nu, wl.rho / wl.dt, xf)
+        err = np.abs(to_host(y)[:nf] - want).astype(np.float64)
+        bound = 64 * 2.0**-53 * mag.astype(np.float64)
+        worst = np.max(err / np.maximum(bound, 1e-300))
+        print(f"  {name}: worst error / bound {worst:.2e}", flush=True)
+        assert np.all(err <= bound)
     ctx.close()
