@@ -288,12 +288,6 @@ constexpr unsigned kOffY = pack6(0, 0, 2, 0, 1, 1) | pack6(0, 2, 2, 1, 2, 1) << 
 __device__ __forceinline__ int off_x(int t, int b) { return (int)(kOffX >> (12 * t + 2 * b)) & 3; }
 __device__ __forceinline__ int off_y(int t, int b) { return (int)(kOffY >> (12 * t + 2 * b)) & 3; }
 
-// One row: returns false (and does nothing) when the window exceeds CAP nodes.  The block is
-// one wavefront; every thread takes the same path.  The window is in LDS (CAP > 0), or, with
-// CAP = 0, in device memory at gflag / gval (room for the row's window; each window position
-// is written by one lane only after the marking pass, so the sums keep their fixed order).
-// Rows whose window exceeds kWinCap (the wide form) are listed in huge = [count, largest
-// window, rows...] for the device-memory form.
 // Adjacency entries [qa, min(qa + 64, q1)) of a row, one per lane: the entry (element << 2 |
 // local node) and its element's piece range.  Returns the number of entries.
 __device__ __forceinline__ int load_adj(int qa, int q1, const int *__restrict__ n2e,
@@ -310,41 +304,80 @@ __device__ __forceinline__ int load_adj(int qa, int q1, const int *__restrict__ 
   return A;
 }
 
+// orders the LDS accesses of one wavefront (lane to lane) across this point
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One row: returns false (and does nothing) when the window exceeds CAP nodes.  The block is
+// one wavefront; every thread takes the same path.  The window is in LDS (CAP > 0), or, with
+// CAP = 0, in device memory at gflag / gval (room for the row's window; each window position
+// is written by one lane only after the marking pass, so the sums keep their fixed order).
+// Rows whose window exceeds kWinCap (the wide form) are listed in huge = [count, largest
+// window, rows...] for the device-memory form.
+//
+// The slots of the row's pieces, element after element, are taken 64 at a time, one per lane (a
+// node of a mesh as fine as the fluid grid has 6 elements of about 6 pieces each; one element
+// at a time left 58 lanes idle and waited for its piece list three times per element).  Up to 64
+// slots stay in registers for all three passes: window, marks, values.
 template <int CAP>
 __device__ bool cf_row(int64_t l, int pass, int n, const int *__restrict__ n2e_ptr, const int *__restrict__ n2e,
                        const int *__restrict__ e_piece, const int *__restrict__ pair_T,
                        const double *__restrict__ piece_L, int *cnt, const int *rowptr, int *col, double *val,
                        int *flag, int *huge = nullptr, int *gflag = nullptr, double *gval = nullptr) {
   constexpr int SCAP = CAP > 0 ? CAP : 1;
-  // windows of up to kWinSmall nodes keep their sums in registers (NACC per lane)
-  constexpr int NACC = CAP > 0 && CAP <= 256 ? CAP / kWave : 1;
   __shared__ int sflag[SCAP];
-  __shared__ double sval[NACC > 1 ? 1 : SCAP];
+  __shared__ double sval[SCAP];
   __shared__ int kslot[kWave], kT[kWave];
   int *wflag = CAP > 0 ? sflag : gflag;
   double *wval = CAP > 0 ? sval : gval;
-  int lane = threadIdx.x;
+  const int lane = threadIdx.x;
   const int L = 2 * n + 1;
-  // window of lattice nodes covered by the pieces around node l.  The adjacency entries are
-  // read a wavefront at a time (lane i: entry qa + i, its element's first and end piece) and
-  // passed to every lane by shuffles.
-  int imin = 1 << 30, imax = -1, jmin = 1 << 30, jmax = -1;
   const int q0 = n2e_ptr[l], q1 = n2e_ptr[l + 1];
-  int av, aps, ape;
-  for (int qa = q0; qa < q1; qa += kWave) {
-    const int A = load_adj(qa, q1, n2e, e_piece, av, aps, ape);
-    for (int i = 0; i < A; ++i) {
-      const int ps = __shfl(aps, i, kWave), pe = __shfl(ape, i, kWave);
-      for (int p = ps + lane; p < pe; p += kWave) {
-        int T = pair_T[p];
-        if (T < 0) continue;   // an empty slot of the time-coherent layout
-        int cell = T >> 1;
-        int ci = cell % n, cj = cell / n;
-        imin = min(imin, 2 * ci); imax = max(imax, 2 * ci + 2);
-        jmin = min(jmin, 2 * cj); jmax = max(jmax, 2 * cj + 2);
+  // f(T, slot, a) over the slots in order, one per lane: fluid triangle (< 0: none), slot, the local
+  // node of l in the slot's element
+  bool held = false;
+  int T1 = -1, sl1 = 0, a1 = 0;
+  auto each = [&](auto f) {
+    if (held) {
+      f(T1, sl1, a1);
+      return;
+    }
+    for (int qa = q0; qa < q1; qa += kWave) {
+      int av, aps, ape;
+      const int A = load_adj(qa, q1, n2e, e_piece, av, aps, ape);
+      int incl = ape - aps;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int t = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += t;
+      }
+      const int first = aps - (incl - (ape - aps));   // slot of the element's flat index 0
+      const int total = __shfl(incl, kWave - 1, kWave);
+      for (int f0 = 0; f0 < total; f0 += kWave) {
+        const int fl = f0 + lane;
+        int i = 0;
+        for (int k = 0; k < A - 1; ++k) i += fl >= __builtin_amdgcn_readlane(incl, k) ? 1 : 0;
+        const int sl = __shfl(first, i, kWave) + fl, a = __shfl(av, i, kWave) & 3;
+        const int T = fl < total ? pair_T[sl] : -1;   // < 0 also: an empty slot of the time-coherent layout
+        f(T, sl, a);
+        if (total <= kWave && q1 - q0 <= kWave) {
+          held = true;
+          T1 = T;
+          sl1 = sl;
+          a1 = a;
+        }
       }
     }
-  }
+  };
+  // window of lattice nodes covered by the pieces around node l
+  int imin = 1 << 30, imax = -1, jmin = 1 << 30, jmax = -1;
+  each([&](int T, int, int) {
+    if (T < 0) return;
+    const int cell = T >> 1, ci = cell % n, cj = cell / n;
+    imin = min(imin, 2 * ci); imax = max(imax, 2 * ci + 2);
+    jmin = min(jmin, 2 * cj); jmax = max(jmax, 2 * cj + 2);
+  });
   for (int off = 32; off > 0; off >>= 1) {
     imin = min(imin, __shfl_xor(imin, off, kWave));
     imax = max(imax, __shfl_xor(imax, off, kWave));
@@ -355,8 +388,8 @@ __device__ bool cf_row(int64_t l, int pass, int n, const int *__restrict__ n2e_p
     if (!pass && lane == 0) cnt[l] = 0;
     return true;
   }
-  int wI = imax - imin + 1, wJ = jmax - jmin + 1;
-  int W = wI * wJ;
+  const int wI = imax - imin + 1, wJ = jmax - jmin + 1;
+  const int W = wI * wJ;
   if (CAP > 0 && W > CAP) {
     if (CAP < kWinCap) return false;   // left to the wide form
     if (!pass && lane == 0) {          // left to the device-memory form (listed once)
@@ -367,25 +400,16 @@ __device__ bool cf_row(int64_t l, int pass, int n, const int *__restrict__ n2e_p
   }
   for (int p = lane; p < W; p += kWave) {
     wflag[p] = 0;
-    if (NACC == 1) wval[p] = 0.0;
+    wval[p] = 0.0;
   }
   __syncthreads();
   // mark the columns
-  for (int qa = q0; qa < q1; qa += kWave) {
-    const int A = load_adj(qa, q1, n2e, e_piece, av, aps, ape);
-    for (int i = 0; i < A; ++i) {
-      const int ps = __shfl(aps, i, kWave), pe = __shfl(ape, i, kWave);
-      for (int p = ps + lane; p < pe; p += kWave) {
-        int T = pair_T[p], t = T & 1, cell = T >> 1;
-        if (T < 0) continue;
-        int ci = cell % n, cj = cell / n;
-        for (int b = 0; b < 6; ++b) {
-          int I = 2 * ci + off_x(t, b) - imin, J = 2 * cj + off_y(t, b) - jmin;
-          wflag[J * wI + I] = 1;
-        }
-      }
-    }
-  }
+  each([&](int T, int, int) {
+    if (T < 0) return;
+    const int t = T & 1, cell = T >> 1, ci = cell % n, cj = cell / n;
+    const int o = (2 * cj - jmin) * wI + 2 * ci - imin;
+    for (int b = 0; b < 6; ++b) wflag[o + off_y(t, b) * wI + off_x(t, b)] = 1;
+  });
   __syncthreads();
   if (!pass) {
     int c = 0;
@@ -394,89 +418,62 @@ __device__ bool cf_row(int64_t l, int pass, int n, const int *__restrict__ n2e_p
     if (lane == 0) cnt[l] = c;
     return true;
   }
-  // values: item order is fixed (adjacency, piece, local node); window position p is summed
-  // by lane p % 64 only, so the order of every sum is fixed.  For each element, 64 slots at a
-  // time: the kept ones are listed in slot order (ballot), then the items of up to 10 kept
-  // pieces (lane 6 k + b: piece k, local node b) find their window positions and values at once,
-  // and every lane walks them in item order, adding those it owns (in registers for the small
-  // windows, in the window array otherwise).
-  double acc[NACC];
-#pragma unroll
-  for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
-  for (int qa = q0; qa < q1; qa += kWave) {
-    const int A = load_adj(qa, q1, n2e, e_piece, av, aps, ape);
-    for (int i = 0; i < A; ++i) {
-      const int a = __shfl(av, i, kWave) & 3;
-      const int ps = __shfl(aps, i, kWave), pe = __shfl(ape, i, kWave);
-      for (int sb = ps; sb < pe; sb += kWave) {
-        const int sl = sb + lane;
-        const int Tl = sl < pe ? pair_T[sl] : -1;
-        const uint64_t kept = __ballot(Tl >= 0);
-        const int nk = __popcll(kept);
-        if (Tl >= 0) {
-          const int r = __popcll(kept & ((1ull << lane) - 1));
-          kslot[r] = sl;
-          kT[r] = Tl;
+  // Values: the kept slots of the 64 are listed in slot order (ballot), then up to 10 pieces at once
+  // (lane 6 k + b: piece k, local node b) find their window positions and values.  The order of
+  // every sum is that of the pieces.  In LDS the pieces follow one another, each adding its six
+  // values to six different positions; one lane walking every item in turn (a position each by
+  // p mod 64, with a readlane per item) was bound by issue: 620 us of the rows' 720 at 1024^2 with
+  // 76 k rows, against 100 (of 150 for both passes).  In device memory position p stays lane p mod 64's.
+  each([&](int T, int sl, int a) {
+    const uint64_t kept = __ballot(T >= 0);
+    const int nk = __popcll(kept);
+    if (T >= 0) {
+      const int r = __popcll(kept & ((1ull << lane) - 1));
+      kslot[r] = sl;
+      kT[r] = T << 2 | a;
+    }
+    __syncthreads();
+    for (int k0 = 0; k0 < nk; k0 += 10) {
+      const int np = min(10, nk - k0), mine = lane / 6;
+      int posl = 0;
+      double vl = 0.0;
+      if (mine < np) {
+        const int b = lane % 6, Ta = kT[k0 + mine], t = Ta >> 2 & 1, cell = Ta >> 3;
+        const int ci = cell % n, cj = cell / n;
+        posl = (2 * cj + off_y(t, b) - jmin) * wI + 2 * ci + off_x(t, b) - imin;
+        vl = piece_L[18 * (int64_t)kslot[k0 + mine] + (Ta & 3) * 6 + b];
+      }
+      if constexpr (CAP > 0) {
+        for (int k = 0; k < np; ++k) {
+          if (mine == k) wval[posl] += vl;
+          wave_fence();
         }
-        __syncthreads();
-        for (int k0 = 0; k0 < nk; k0 += 10) {
-          const int m = 6 * min(10, nk - k0);
-          int posl = -1;
-          double vl = 0.0;
-          if (lane < m) {
-            const int k = k0 + lane / 6, b = lane % 6;
-            const int T = kT[k], t = T & 1, cell = T >> 1;
-            const int ci = cell % n, cj = cell / n;
-            posl = (2 * cj + off_y(t, b) - jmin) * wI + 2 * ci + off_x(t, b) - imin;
-            vl = piece_L[18 * (int64_t)kslot[k] + a * 6 + b];
-          }
-          // item it is read from lane it (uniform position, so the sum it belongs to is chosen
-          // by a scalar branch; only the owning lane adds)
-          for (int it = 0; it < m; ++it) {
-            const int pos = __builtin_amdgcn_readlane(posl, it);
-            const double v = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(vl), it),
-                                              __builtin_amdgcn_readlane(__double2loint(vl), it));
-            const bool own = (pos & (kWave - 1)) == lane;
-            if (NACC > 1) {
-              const int k = pos >> 6;
-#pragma unroll
-              for (int kk = 0; kk < NACC; ++kk)
-                if (k == kk) acc[kk] = own ? acc[kk] + v : acc[kk];
-            } else if (own) {
-              wval[pos] += v;
-            }
-          }
+      } else {
+        for (int it = 0; it < 6 * np; ++it) {
+          const int pos = __builtin_amdgcn_readlane(posl, it);
+          const double v = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(vl), it),
+                                            __builtin_amdgcn_readlane(__double2loint(vl), it));
+          if ((pos & (kWave - 1)) == lane) wval[pos] += v;
         }
-        __syncthreads();
       }
     }
-  }
+    __syncthreads();
+  });
   __syncthreads();
   // compact in window order (= ascending column index)
   int base = rowptr[l];
   for (int p0 = 0; p0 < W; p0 += kWave) {
-    int p = p0 + lane;
-    int f = (p < W) ? wflag[p] : 0;
-    int incl = f;
-    for (int off = 1; off < kWave; off <<= 1) {
-      int t = __shfl_up(incl, off, kWave);
-      if (lane >= off) incl += t;
-    }
+    const int p = p0 + lane;
+    const bool f = p < W && wflag[p];
+    const uint64_t set = __ballot(f);
     if (f) {
-      int I = imin + p % wI, J = jmin + p / wI;
-      bool bndc = I == 0 || J == 0 || I == 2 * n || J == 2 * n;
-      col[base + incl - 1] = J * L + I;
-      double v = 0.0;
-      if (NACC > 1) {
-#pragma unroll
-        for (int k = 0; k < NACC; ++k)
-          if (k == p0 / kWave) v = acc[k];
-      } else {
-        v = wval[p];
-      }
-      val[base + incl - 1] = bndc ? 0.0 : v;
+      const int I = imin + p % wI, J = jmin + p / wI;
+      const bool bndc = I == 0 || J == 0 || I == 2 * n || J == 2 * n;
+      const int k = base + __popcll(set & ((1ull << lane) - 1));
+      col[k] = J * L + I;
+      val[k] = bndc ? 0.0 : wval[p];
     }
-    base += __shfl(incl, kWave - 1, kWave);
+    base += __popcll(set);
   }
   return true;
 }
@@ -557,11 +554,15 @@ __global__ void k_count_cols(int64_t nnz, const int *col, int *cnt) {
   if (k < nnz) atomicAdd(&cnt[col[k]], 1);
 }
 
+// kScatterLanes lanes per row: a row's entries wait for one another's atomics no more (one thread
+// per row: 228 us at 76 k rows of 37 entries, 89 at 2.8 k, against 62 and 9)
+constexpr int kScatterLanes = 16;
 __global__ void k_scatter_t(int64_t nrows, const int *rowptr, const int *col, const double *val,
                             const int *tptr, int *fill, int *tcol, double *tval, int *tsrc) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, r = g / kScatterLanes;
   if (r >= nrows) return;
-  for (int k = rowptr[r]; k < rowptr[r + 1]; ++k) {
+  const int k1 = rowptr[r + 1];
+  for (int k = rowptr[r] + (int)(g % kScatterLanes); k < k1; k += kScatterLanes) {
     int c = col[k];
     int pos = tptr[c] + atomicAdd(&fill[c], 1);
     tcol[pos] = (int)r;
@@ -573,28 +574,59 @@ __global__ void k_scatter_t(int64_t nrows, const int *rowptr, const int *col, co
 // Ordering of the transposed rows.  The scatter above places the entries of a row of
 // C_f^T in an arbitrary order (atomic slots); each entry is then moved to its rank among the
 // solid-node indices of its row (unique within a row), so the result is deterministic.
-// Rows of up to kShortRow entries are ranked by one thread; longer rows (a solid much finer
-// than the fluid grid puts thousands of solid nodes in one P2 support) are listed and ranked
-// by a workgroup each, with the row's keys staged through LDS in chunks.
+// Rows of up to kShortRow entries are ranked 64 rows to a wavefront: their entries lie together, so
+// the wavefront stages the keys in LDS and ranks one entry per lane (a thread per row walked its
+// keys in device memory: 253 us at 1024^2 with 2.8 M entries, against 65).  Longer
+// rows (a solid much finer than the fluid grid puts thousands of solid nodes in one P2 support)
+// are listed and ranked by a workgroup each, with the row's keys staged through LDS in chunks.
 constexpr int kShortRow = 32;
 constexpr int kRankChunk = 4096;
 
-__global__ void k_rank_short(int64_t nrows, const int *rowptr, const int *tcol, const double *tval, int *col,
-                             double *val, int *long_rows, const int *tsrc, int *perm) {
+constexpr int kRankWaves = 4, kRankSeg = kWave * kShortRow;   // staged entries per wavefront
+__global__ void __launch_bounds__(kWave *kRankWaves)
+    k_rank_short(int64_t nrows, const int *rowptr, const int *tcol, const double *tval, int *col, double *val,
+                 int *long_rows, const int *tsrc, int *perm) {
+  __shared__ int keys[kRankWaves][kRankSeg];
+  __shared__ unsigned char owner[kRankWaves][kRankSeg];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrows) return;
-  const int k0 = rowptr[r], k1 = rowptr[r + 1];
-  if (k1 - k0 > kShortRow) {
-    long_rows[1 + atomicAdd(&long_rows[0], 1)] = (int)r;   // list order does not matter
-    return;
+  int k0 = 0, len = 0;
+  if (r < nrows) {
+    k0 = rowptr[r];
+    len = rowptr[r + 1] - k0;
+    if (len > kShortRow) {
+      long_rows[1 + atomicAdd(&long_rows[0], 1)] = (int)r;   // list order does not matter
+      len = 0;
+    }
   }
-  for (int i = k0; i < k1; ++i) {
-    const int c = tcol[i];
-    int rank = 0;
-    for (int j = k0; j < k1; ++j) rank += tcol[j] < c;
-    col[k0 + rank] = c;
-    val[k0 + rank] = tval[i];
-    if (perm) perm[k0 + rank] = tsrc[i];
+  // the short rows' entries one after another: this row's start among them
+  int incl = len;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int t = __shfl_up(incl, off, kWave);
+    if (lane >= off) incl += t;
+  }
+  const int total = __shfl(incl, kWave - 1, kWave), start = incl - len;
+  if (total == 0) return;   // no barrier follows: a wavefront is on its own
+  for (int i = 0; i < len; ++i) owner[w][start + i] = (unsigned char)lane;
+  wave_fence();
+  for (int f0 = 0; f0 < total; f0 += kWave) {
+    const int f = f0 + lane, o = f < total ? owner[w][f] : 0;
+    const int k = __shfl(k0 - start, o, kWave) + f;
+    if (f < total) keys[w][f] = tcol[k];
+  }
+  wave_fence();
+  for (int f0 = 0; f0 < total; f0 += kWave) {
+    const int f = f0 + lane, o = f < total ? owner[w][f] : 0;
+    const int s0 = __shfl(start, o, kWave), n0 = __shfl(len, o, kWave), g0 = __shfl(k0, o, kWave);
+    if (f < total) {
+      const int c = keys[w][f];
+      int rank = 0;
+      for (int j = 0; j < n0; ++j) rank += keys[w][s0 + j] < c;
+      const int k = g0 + f - s0;
+      col[g0 + rank] = c;
+      val[g0 + rank] = tval[k];
+      if (perm) perm[g0 + rank] = tsrc[k];
+    }
   }
 }
 
@@ -795,9 +827,9 @@ static void build_transpose(Ctx &c, Work &w, int nnz, bool keep_perm) {
   int *perm = keep_perm ? w.work(c.cft_perm, nnz, "transpose permutation") : nullptr;
   int *long_rows = w.work(c.cft_long, c.N2 + 1, "long transposed rows");
   fill(long_rows, 1, 0, s);
-  hipLaunchKernelGGL(k_scatter_t, dim3(grid_for(ns, 256)), dim3(256), 0, s, ns, cf_rp, cf_col, cf_val, ct_rp,
+  hipLaunchKernelGGL(k_scatter_t, dim3(grid_for(ns * kScatterLanes, 256)), dim3(256), 0, s, ns, cf_rp, cf_col, cf_val, ct_rp,
                      ct_fill, tcol, tval, tsrc);
-  hipLaunchKernelGGL(k_rank_short, dim3(grid_for(c.N2, 256)), dim3(256), 0, s, c.N2, ct_rp, tcol, tval, ct_col,
+  hipLaunchKernelGGL(k_rank_short, dim3(grid_for(c.N2, kWave * kRankWaves)), dim3(kWave * kRankWaves), 0, s, c.N2, ct_rp, tcol, tval, ct_col,
                      ct_val, long_rows, tsrc, perm);
   hipLaunchKernelGGL(k_rank_long, dim3(512), dim3(256), 0, s, ct_rp, tcol, tval, ct_col, ct_val, long_rows, tsrc,
                      perm);
