@@ -666,6 +666,11 @@ void build_fluid(Ctx &c) {
   hipLaunchKernelGGL(k_diag_inv, dim3(gp), dim3(256), 0, s, np, c.Mp.rowptr.p, c.Mp.col.p, c.Mp.val.p,
                      c.Mp_dinv.p);
   check_div_closed_form(n);
+  {   // the entries of (rho/dt) M_f alone, as mass_rows takes them
+    AfCoef<double> m64;
+    AfCoef<float> m32;
+    af_coefs(n, 0.0, c.rho / c.dt, m64, m32);
+  }
   c.bnd.alloc(n2);
   hipLaunchKernelGGL(k_p2_boundary_flags, dim3(g2), dim3(256), 0, s, n, c.bnd.p);
   FSI_CHECK_LAUNCH();

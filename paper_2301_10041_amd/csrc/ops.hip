@@ -217,6 +217,7 @@ template void apply_a11_on64<double>(Ctx &, const double *, double *);
 template void apply_a11_on64<float>(Ctx &, const double *, double *);
 
 // ---- right-hand side of eq. (matrix)
+// The Q2/P1 pair's velocity rows from the assembled M_f (the other pair: mass_rows)
 __global__ void k_rhs_u(int64_t N2, const int *rp, const int *col, const double *M,
                         const unsigned char *bnd, const double *u, double rdt, double *b) {
   int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -262,9 +263,13 @@ __global__ void k_rhs_s(int64_t Ns, const int *rp, const int *col, const double 
 
 void build_rhs(Ctx &c, const double *u_n, const double *X_n, double *b) {
   hipStream_t s = c.stream;
-  hipLaunchKernelGGL(k_rhs_u, dim3(grid_for(c.N2 * kG, 256)), dim3(256), 0, s, c.N2, c.Af.rowptr.p,
-                     c.Af.col.p, c.Mf.p, c.bnd.p, u_n, c.rho / c.dt, b);
-  fill(b + 2 * c.N2, c.Np, 0.0, s);
+  if (c.pair == FSI_PAIR_Q2P1DISC) {
+    hipLaunchKernelGGL(k_rhs_u, dim3(grid_for(c.N2 * kG, 256)), dim3(256), 0, s, c.N2, c.Af.rowptr.p,
+                       c.Af.col.p, c.Mf.p, c.bnd.p, u_n, c.rho / c.dt, b);
+    fill(b + 2 * c.N2, c.Np, 0.0, s);
+  } else {
+    mass_rows(c.n, c.rho / c.dt, u_n, b, s);
+  }
   hipLaunchKernelGGL(k_rhs_s, dim3(grid_for(c.Ns * kG, 256)), dim3(256), 0, s, c.Ns, c.S.rowptr.p,
                      c.S.col.p, c.Cs.p, X_n, -1.0 / c.dt, b + 2 * c.N2 + c.Np);
   FSI_CHECK_LAUNCH();

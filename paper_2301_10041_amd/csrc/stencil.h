@@ -94,6 +94,9 @@ struct DivTable {
 void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
               const double *cft_val, const double *xl, int64_t Ns, hipStream_t s);
 
+// b = [rdt M_f u | 0] on [u_x | u_y | p] (Dirichlet rows 0, Dirichlet values of u left out)
+void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s);
+
 // Chebyshev smoothing of a velocity level, three steps per launch:
 // pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x
 // post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and

@@ -742,7 +742,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
       // products entry by entry (coalesced) into LDS, over the x nobody needs any more, and each
       // thread sums its own rows there in their order.  A thread that walks its rows in device
       // memory instead: 194 us at 1024^2 with 2.8 M entries, against
-      // 115 (141 with one thread per node).
+      // 98 (141 with one thread per node; 115 without fetching a segment ahead).
       constexpr int CH = 2 * kCellPL / kCellWaves / kWave * kWave;
       V2<double> *const buf = X + w * CH;
       const int last = min(n - i0, kWave - 1);   // the wave's last lane in the lattice
@@ -750,16 +750,26 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int k0 = __shfl(ct[h][0], 0), k1 = __shfl(ct[h][2], last);
-        for (int c0 = k0; c0 < k1; c0 += CH) {
+        double cv[CH / kWave];
+        int cc[CH / kWave];
+        auto fetch = [&](int c0) {   // the entries of a segment, one segment ahead of their products
 #pragma unroll
-          for (int u = 0; u < CH; u += kWave) {
-            const int k = c0 + u + lane;
-            if (k < k1) {
-              const double cv = a.cft_val[k];
-              const int c = a.cft_col[k];
-              buf[u + lane] = V2<double>{cv * a.xlx[c], cv * a.xly[c]};
-            }
+          for (int u = 0; u < CH / kWave; ++u) {
+            const int k = c0 + kWave * u + lane;
+            cv[u] = k < k1 ? a.cft_val[k] : 0.0;
+            cc[u] = k < k1 ? a.cft_col[k] : -1;
           }
+        };
+        fetch(k0);
+        for (int c0 = k0; c0 < k1; c0 += CH) {
+          V2<double> xl[CH / kWave];
+#pragma unroll
+          for (int u = 0; u < CH / kWave; ++u)
+            if (cc[u] >= 0) xl[u] = V2<double>{cv[u] * a.xlx[cc[u]], cv[u] * a.xly[cc[u]]};
+#pragma unroll
+          for (int u = 0; u < CH / kWave; ++u)
+            if (cc[u] >= 0) buf[kWave * u + lane] = xl[u];
+          fetch(c0 + CH);
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -781,6 +791,67 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
       yg[o2 + q0] = sp;
     }
   }
+}
+
+// b_u = (rho/dt) M_f u with Dirichlet rows 0 and Dirichlet columns left out, b_p = 0: the velocity and
+// pressure part of the step's right-hand side, cell by cell.  The entries of M_f are h^2 / 720 times
+// 72, -4, -8 (vertex rows) and 128, 32, -8 (edge rows).  Bound by memory: 143 MB at 1024^2;
+// 32 us, against 283 for the assembled M_f (4 lanes per CSR row; 12 bytes per entry).
+struct MassArgs {
+  int n;
+  double m;   // (rho/dt) h^2 / 720
+  const double *u;
+  double *b;
+};
+
+__global__ void __launch_bounds__(kWave *kCellWaves) k_mass(MassArgs a, int tiles_x, int tiles, int band) {
+  __shared__ V2<double> X[2 * kCellPL];
+  const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
+  if (t >= tiles) return;
+  const int n = a.n, L = 2 * n + 1;
+  const int64_t N = (int64_t)L * L;
+  const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellWaves;
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int i = i0 + lane, j = j0 + w;
+  stage_pairs<double, kCellH>(X, a.u, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
+  __syncthreads();
+  if (i > n || j > n) return;
+  const V2<double> *p = X + (2 * w + 2) * kCellHW + lane + 1;
+  auto W = [&](int dI, int dJ) -> V2<double> { return p[(dI & 1) * kCellPL + dJ * kCellHW + (dI >> 1)]; };
+  auto sum = [](auto... v) -> V2<double> { return V2<double>{(v.x + ...), (v.y + ...)}; };
+  const V2<double> o = W(0, 0), e = W(1, 0), f = W(0, 1), g = W(1, 1);
+  const V2<double> n22 = W(2, 2), n20 = W(2, 0), n02 = W(0, 2), n12 = W(1, 2), n21 = W(2, 1);
+  const V2<double> l1m1 = W(1, -1), lm11 = W(-1, 1);
+  V2<double> far[4], edge[4];   // vertex neighbours (edge rows: vertices), edge neighbours
+  far[0] = sum(W(-2, 0), n20, W(0, -2), n02, W(-2, -2), n22);
+  edge[0] = sum(n12, n21, l1m1, lm11, W(-1, -2), W(-2, -1));
+  far[1] = sum(W(0, -2), n22);
+  edge[1] = sum(l1m1, g, W(0, -1), n21);
+  far[2] = sum(W(-2, 0), n22);
+  edge[2] = sum(lm11, g, W(-1, 0), n12);
+  far[3] = sum(n20, n02);
+  edge[3] = sum(f, n21, e, n12);
+  const V2<double> own[4] = {o, e, f, g};
+  const CellIn in = cell_inside(i, j, n);
+  V2<double> s[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double cd = q ? 128 * a.m : 72 * a.m, ce = q ? 32 * a.m : -8 * a.m, cf = q ? -8 * a.m : -4 * a.m;
+    s[q] = in.q[q] ? V2<double>{fma(cf, far[q].x, fma(ce, edge[q].x, cd * own[q].x)),
+                                fma(cf, far[q].y, fma(ce, edge[q].y, cd * own[q].y))}
+                   : V2<double>{0.0, 0.0};
+  }
+  store_cell<double, double>(a.b, N, L, n, i, j, s);
+  a.b[2 * N + (int64_t)j * (n + 1) + i] = 0.0;
+}
+
+void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s) {
+  cell_launch_checks(n, 1);
+  int tx;
+  const int tiles = cell_tiles(n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
+  hipLaunchKernelGGL(k_mass, dim3((unsigned)(band * kXcd)), dim3(kWave * kCellWaves), 0, s,
+                     MassArgs{n, rdt / (720.0 * n * n), u, b}, tx, tiles, band);
+  FSI_CHECK_LAUNCH();
 }
 
 template <bool MS>

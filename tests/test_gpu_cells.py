@@ -140,3 +140,55 @@ def test_a11_rows_by_cells(n):
         print(f"  {name}: worst error / bound {worst:.2e}", flush=True)
         assert np.all(err <= bound)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [2, 5, 56, 64, 72, 80])
+def test_mass_rows_by_cells(n):
+    """b = [(rho/dt) M_f u | 0] against the closed form of M_f in extended precision, u nonzero on the
+    boundary too (left out): within 64 roundings of the row's magnitudes (19 products)."""
+    print(f"[mass rows n={n}]", flush=True)
+    torch = torch_dev()
+    wl = inputs.small_workload(n, 4, (0.5, 0.5), 0.2)
+    ctx = fsi.Context.from_workload(wl)
+    xy, _ = wl.solid_mesh()
+    sz = ctx.sizes
+    L = 2 * n + 1
+    u = np.random.default_rng(17 + n).uniform(-1, 1, 2 * L * L)
+    b = torch.full((sz["N"],), float("nan"), dtype=torch.float64, device="cuda")
+    ctx.build_rhs(to_dev(u), to_dev(np.concatenate([xy[:, 0], xy[:, 1]])), b)
+    got = to_host(b)
+    ld = np.longdouble
+    m = ld(wl.rho) / ld(wl.dt) / (ld(n) * n * 720)
+    cnt, off, _ = fsi.export_lattice(n, fsi.LAT_AF, 1.0, 0.0)
+    for c in range(2):
+        v = np.zeros((L + 4, L + 4), ld)
+        v[3 : L + 1, 3 : L + 1] = u[c * L * L : (c + 1) * L * L].reshape(L, L)[1:-1, 1:-1]
+        want, mag = np.zeros((L, L), ld), np.zeros((L, L), ld)
+        for cls in range(4):
+            sl = (slice(cls >> 1, L, 2), slice(cls & 1, L, 2))
+            shape = want[sl].shape
+            for I, J in off[cls, : cnt[cls]]:
+                key = (abs(int(I)), abs(int(J)), int(I) * int(J) > 0)
+                if cls == 0:   # vertices: 72; two apart -4, edges of the far sides -8, the nearest 0
+                    w = {(0, 0): 72, (2, 0): -4, (0, 2): -4, (2, 2): -4, (1, 0): 0, (0, 1): 0,
+                         (1, 1): 0 if key[2] else -8}.get(key[:2], -8)
+                else:          # edges: 128; edges of the same triangle 32, the opposite vertices -8
+                    near = {1: (1, 0), 2: (0, 1), 3: (1, 1) if key[2] else None}[cls]
+                    if key[:2] == (0, 0):
+                        w = 128
+                    elif key[:2] == near:
+                        w = 0
+                    elif cls == 3:
+                        w = 32 if sum(key[:2]) == 1 else -8
+                    else:
+                        w = 32 if max(key[:2]) == 1 else -8
+                a = v[2 + J + (cls >> 1) :: 2, 2 + I + (cls & 1) :: 2][: shape[0], : shape[1]]
+                want[sl] += m * w * a
+                mag[sl] += m * abs(w) * abs(a)
+        for e in (0, -1):
+            want[e], want[:, e] = 0, 0
+        err = np.abs(got[c * L * L : (c + 1) * L * L].reshape(L, L) - want)
+        assert np.all(err[0] == 0) and np.all(err[:, -1] == 0)
+        assert np.all(err <= 64 * 2.0**-53 * mag)
+    assert np.all(got[sz["off_p"] : sz["off_Xx"]] == 0)
+    ctx.close()
