@@ -75,8 +75,7 @@ size_t Ctx::device_bytes() const {
        cft_perm.bytes();
   b += mgu.bytes() + mgp.bytes();
   for (int i = 0; i < 9; ++i) b += inner.v64[i].bytes() + inner.v32[i].bytes();
-  b += outer.V.bytes() + outer.Z.bytes() + outer.w.bytes() + outer.r.bytes() + outer.x32.bytes() +
-       outer.y32.bytes();
+  b += outer.V.bytes() + outer.Z.bytes() + outer.w.bytes() + outer.r.bytes() + outer.x32.bytes();
   b += red.bytes() + dscal.bytes() + tmpN.bytes() + tmpS.bytes();
   b += ms_state.bytes() + ms_red.bytes() + ms_x.bytes() + ms_part.bytes() + ms_dot.bytes() + ms_vh.bytes() +
        ms_hist.bytes() + ms_coef.bytes() + gi_V.bytes() + gi_Z.bytes() + gi_part.bytes() + gi_dh.bytes() +

@@ -181,7 +181,7 @@ struct Ctx {
     int m = 0;
     int64_t ncap = 0;      // N the basis was allocated for
     DevBuf<double> V, Z, w, r, t, t2;
-    DevBuf<float> x32, y32;
+    DevBuf<float> x32;
   } outer;
   DevBuf<double> red;      // reduction partials
   DevBuf<double> dscal;    // device scalars

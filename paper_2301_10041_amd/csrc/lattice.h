@@ -125,25 +125,24 @@ template <typename T, typename TB>
 void p1_down(const P1DownArgs<T, TB> &a, hipStream_t s, int K);
 // Ascent: y = the steps from x + P xc (P1_Y); on the finest level z = nu M_p^{-1} b + rdt y with the
 // pinned entry z[0] = b[0] rounded through T, the mass solve from zero (scale ms[0], steps m1, m2; mdinv
-// = 12 / h^2, munit = h^2 / 12), and per tile the part of sum r64 z (b z when r64 is null) at
+// = 12 / h^2, munit = h^2 / 12), and per tile the part of sum b z at
 // part, if given (P1_Z; p1_up_tiles(n) parts per lane); the same with y read from xc (P1_ZW).  Lane
-// strides: lb for b, lx for x and y, lc for xc, lz for z and r64, lp for part.
+// strides: lb for b, lx for x and y, lc for xc, lz for z, lp for part.
 enum { P1_Y = 0, P1_Z = 1, P1_ZW = 2 };
-template <typename T, typename TB, typename TZ>
+template <typename T, typename TB>
 struct P1UpArgs {
   int n;
   const TB *b;
   const T *x, *xc;
   T *y;
   T c1[2], c2[2];
-  TZ *z;
-  const double *r64;
+  double *z;
   T ms[1], m1[2], m2[2], mdinv, munit, nu, rdt;
   double *part;
   int64_t lb, lx, lc, lz, lp;
 };
-template <typename T, typename TB, typename TZ, int OUT>
-void p1_up(const P1UpArgs<T, TB, TZ> &a, hipStream_t s, int K);
+template <typename T, typename TB, int OUT>
+void p1_up(const P1UpArgs<T, TB> &a, hipStream_t s, int K);
 int p1_up_tiles(int n);
 // The coarse end in one launch per system: levels lv[0..nlev) (n <= kPTailMaxN cells, each the next
 // one's fine level) and the coarsest level's dense inverse cinv (m x m).  LDS (offsets in T): level
@@ -157,7 +156,7 @@ struct PTailLevel {
   int n, off, offb;
   T c1[2], c2[2];
 };
-template <typename T, typename TB, typename TZ>
+template <typename T, typename TB>
 struct PTailArgs {
   int nlev;
   PTailLevel<T> lv[kPTailMax];
@@ -165,14 +164,13 @@ struct PTailArgs {
   const T *cinv;
   const TB *b;
   T *x;
-  TZ *z;
-  const double *r64;
+  double *z;
   T ms, m1[2], m2[2], mdinv, munit, nu, rdt;
   double *part;
   int64_t lb, lx, lz, lp;
 };
-template <typename T, typename TB, typename TZ, bool OUT>
-void p1_tail(const PTailArgs<T, TB, TZ> &a, hipStream_t s, int K);
+template <typename T, typename TB, bool OUT>
+void p1_tail(const PTailArgs<T, TB> &a, hipStream_t s, int K);
 int p1_tail_lds_limit();
 
 // The coarse end of a velocity V-cycle in one launch per system (mgtail.hip): levels

@@ -152,8 +152,8 @@ __global__ void __launch_bounds__(kWave *kP1Waves) k_p1_down(P1DownArgs<T, TB> a
 // mass solve's three steps from zero, the pinned entry r[0] and the tile's part of sum r z
 // (OUT = P1_Z; P1_ZW: y is read from xc instead, the whole L_p cycle having run elsewhere).  Tile of
 // 60 x (RH - 4) nodes; the values they start from with a halo of 2, the first step 1.
-template <typename T, typename TB, typename TZ, int RPT, int OUT>
-__global__ void __launch_bounds__(kWave *kP1Waves) k_p1_up(P1UpArgs<T, TB, TZ> a, int tiles_x) {
+template <typename T, typename TB, int RPT, int OUT>
+__global__ void __launch_bounds__(kWave *kP1Waves) k_p1_up(P1UpArgs<T, TB> a, int tiles_x) {
   constexpr int RH = kP1Waves * RPT, TR = RH - 4, TC = kWave - 4, NE = (RH + 2) * kP1S;
   constexpr bool UP = OUT != P1_ZW, MASS = OUT != P1_Y;
   __shared__ T XA[UP ? NE : 1], XB[UP ? NE : 1], MA[MASS ? NE : 1], MB[MASS ? NE : 1];
@@ -216,9 +216,9 @@ __global__ void __launch_bounds__(kWave *kP1Waves) k_p1_up(P1UpArgs<T, TB, TZ> a
       T y;
       if constexpr (UP) y = xv[q];
       else y = a.xc[ln * a.lc + r];
-      const TZ rv = (TZ)b[r], v = r == 0 ? (TZ)(T)rv : (TZ)(a.nu * mv[q] + a.rdt * y);
+      const double rv = b[r], v = r == 0 ? (T)rv : (a.nu * mv[q] + a.rdt * y);
       a.z[ln * a.lz + r] = v;
-      acc += (a.r64 ? a.r64[ln * a.lz + r] : (double)rv) * (double)v;
+      acc += rv * v;
     }
   }
   if constexpr (MASS) {
@@ -244,8 +244,8 @@ __global__ void __launch_bounds__(kWave *kP1Waves) k_p1_up(P1UpArgs<T, TB, TZ> a
 // the first level is the finest: the block reads r, adds the mass solve and writes z with the sum of
 // r z.
 constexpr int kPTailThreads = 1024;
-template <typename T, typename TB, typename TZ, bool OUT>
-__global__ void __launch_bounds__(kPTailThreads) k_p1_tail(PTailArgs<T, TB, TZ> a) {
+template <typename T, typename TB, bool OUT>
+__global__ void __launch_bounds__(kPTailThreads) k_p1_tail(PTailArgs<T, TB> a) {
   extern __shared__ unsigned char ptail_smem[];
   T *const sm = reinterpret_cast<T *>(ptail_smem);
   const int tid = threadIdx.x, ln = blockIdx.y;
@@ -421,9 +421,9 @@ __global__ void __launch_bounds__(kPTailThreads) k_p1_tail(PTailArgs<T, TB, TZ> 
     for (int q = 0; q < PER; ++q) {
       const int k = tid + kPTailThreads * q;
       if (k >= N) break;
-      const TZ rv = (TZ)bg[k], v = k == 0 ? (TZ)(T)rv : (TZ)(a.nu * mv[q] + a.rdt * y[q]);
+      const double rv = bg[k], v = k == 0 ? (T)rv : (a.nu * mv[q] + a.rdt * y[q]);
       a.z[ln * a.lz + k] = v;
-      acc += (a.r64 ? a.r64[ln * a.lz + k] : (double)rv) * (double)v;
+      acc += rv * v;
     }
     if (a.part) {
       __shared__ double red[kPTailThreads / kWave];
@@ -469,15 +469,15 @@ void p1_down(const P1DownArgs<T, TB> &a, hipStream_t s, int K) {
   FSI_CHECK_LAUNCH();
 }
 
-template <typename T, typename TB, typename TZ, int OUT>
-void p1_up(const P1UpArgs<T, TB, TZ> &a, hipStream_t s, int K) {
+template <typename T, typename TB, int OUT>
+void p1_up(const P1UpArgs<T, TB> &a, hipStream_t s, int K) {
   FSI_REQUIRE((OUT == P1_ZW || (a.n % 2 == 0 && a.n >= 4)) && K >= 1 && K <= 65535, FSI_E_ARG,
               "pressure level out of range");
   auto go = [&](auto r_tag) {
     constexpr int RPT = decltype(r_tag)::value;
     int tx;
     const int tiles = p1_up_tiles_r<RPT>(a.n, tx);
-    hipLaunchKernelGGL((k_p1_up<T, TB, TZ, RPT, OUT>), dim3((unsigned)tiles, (unsigned)K), dim3(kWave * kP1Waves), 0, s,
+    hipLaunchKernelGGL((k_p1_up<T, TB, RPT, OUT>), dim3((unsigned)tiles, (unsigned)K), dim3(kWave * kP1Waves), 0, s,
                        a, tx);
   };
   if (a.n >= kP1WideN) go(std::integral_constant<int, 4>{});
@@ -494,11 +494,10 @@ int p1_tail_lds_limit() {
       v = 65536;
     v = v < 65536 ? v : v > 163840 ? 163840 : v;
     if (v > 65536) {
-      const void *ks[] = {(const void *)k_p1_tail<double, double, double, false>,
-                          (const void *)k_p1_tail<float, float, float, false>,
-                          (const void *)k_p1_tail<double, double, double, true>,
-                          (const void *)k_p1_tail<float, float, float, true>,
-                          (const void *)k_p1_tail<float, double, double, true>};
+      const void *ks[] = {(const void *)k_p1_tail<double, double, false>,
+                          (const void *)k_p1_tail<float, float, false>,
+                          (const void *)k_p1_tail<double, double, true>,
+                          (const void *)k_p1_tail<float, double, true>};
       for (const void *k : ks)
         if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, v) != hipSuccess) {
           (void)hipGetLastError();
@@ -511,8 +510,8 @@ int p1_tail_lds_limit() {
   return limit;
 }
 
-template <typename T, typename TB, typename TZ, bool OUT>
-void p1_tail(const PTailArgs<T, TB, TZ> &a, hipStream_t s, int K) {
+template <typename T, typename TB, bool OUT>
+void p1_tail(const PTailArgs<T, TB> &a, hipStream_t s, int K) {
   FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kPTailMax, FSI_E_ARG, "pressure tail shape out of range");
   FSI_REQUIRE(a.lv[0].n <= kPTailMaxN && (a.lv[0].n + 1) * (a.lv[0].n + 1) <= kPTailPer * kPTailThreads, FSI_E_ARG,
               "pressure tail level too fine");
@@ -524,23 +523,21 @@ void p1_tail(const PTailArgs<T, TB, TZ> &a, hipStream_t s, int K) {
               "pressure tail coarsest level out of range");
   FSI_REQUIRE(K >= 1 && K <= 65535 && (K == 1 || a.lb > 0), FSI_E_ARG, "lane count out of range");
   FSI_REQUIRE(a.lds * (int)sizeof(T) <= p1_tail_lds_limit(), FSI_E_ARG, "pressure tail exceeds the LDS of a block");
-  hipLaunchKernelGGL((k_p1_tail<T, TB, TZ, OUT>), dim3(1, (unsigned)K), dim3(kPTailThreads), a.lds * (int)sizeof(T), s,
+  hipLaunchKernelGGL((k_p1_tail<T, TB, OUT>), dim3(1, (unsigned)K), dim3(kPTailThreads), a.lds * (int)sizeof(T), s,
                      a);
   FSI_CHECK_LAUNCH();
 }
 
-#define FSI_P1_INST(T, TB, TZ)                                                                \
-  template void p1_up<T, TB, TZ, P1_Z>(const P1UpArgs<T, TB, TZ> &, hipStream_t, int);        \
-  template void p1_up<T, TB, TZ, P1_ZW>(const P1UpArgs<T, TB, TZ> &, hipStream_t, int);       \
-  template void p1_tail<T, TB, TZ, true>(const PTailArgs<T, TB, TZ> &, hipStream_t, int);     \
-  template void p1_down<T, TB>(const P1DownArgs<T, TB> &, hipStream_t, int);
-FSI_P1_INST(double, double, double)
-FSI_P1_INST(float, float, float)
-FSI_P1_INST(float, double, double)
+#define FSI_P1_INST(T)                                                                \
+  template void p1_up<T, double, P1_Z>(const P1UpArgs<T, double> &, hipStream_t, int);  \
+  template void p1_up<T, double, P1_ZW>(const P1UpArgs<T, double> &, hipStream_t, int); \
+  template void p1_up<T, T, P1_Y>(const P1UpArgs<T, T> &, hipStream_t, int);            \
+  template void p1_tail<T, double, true>(const PTailArgs<T, double> &, hipStream_t, int); \
+  template void p1_tail<T, T, false>(const PTailArgs<T, T> &, hipStream_t, int);        \
+  template void p1_down<T, double>(const P1DownArgs<T, double> &, hipStream_t, int);
+FSI_P1_INST(double)
+FSI_P1_INST(float)
 #undef FSI_P1_INST
-template void p1_up<double, double, double, P1_Y>(const P1UpArgs<double, double, double> &, hipStream_t, int);
-template void p1_up<float, float, float, P1_Y>(const P1UpArgs<float, float, float> &, hipStream_t, int);
-template void p1_tail<double, double, double, false>(const PTailArgs<double, double, double> &, hipStream_t, int);
-template void p1_tail<float, float, float, false>(const PTailArgs<float, float, float> &, hipStream_t, int);
+template void p1_down<float, float>(const P1DownArgs<float, float> &, hipStream_t, int);
 
 }  // namespace fsi

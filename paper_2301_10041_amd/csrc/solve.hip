@@ -173,11 +173,6 @@ __global__ void k_q_pres(TZ *z, const TZ *r, const T *xl, const T *mpinv, T nu, 
   }
 }
 
-template <typename T>
-__global__ void k_set_pinned(T *z, const T *r) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) z[0] = r[0];
-}
-
 // z[0] = r[0] rounded through T (the value an FP32 preconditioner would pass on)
 template <typename TZ, typename T>
 __global__ void k_set_pinned_to(TZ *z, const TZ *r) {
@@ -375,12 +370,12 @@ static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, T
 // The arguments of the one-launch coarse end of the pressure V-cycle from level l, or false
 // when the remaining levels do not fit it (too fine, too many or LDS).  out: level l is the finest and
 // the launch adds the mass solve and the output (its arguments are the caller's).
-template <typename T, typename TB, typename TZ>
-static bool p1_tail_args(const Mg &mg, int l, bool out, PTailArgs<T, TB, TZ> &a) {
+template <typename T, typename TB>
+static bool p1_tail_args(const Mg &mg, int l, bool out, PTailArgs<T, TB> &a) {
   const int last = (int)mg.lv.size() - 1;   // the dense coarsest level
   const int nlev = last - l;
   if (!mg.tail || nlev < 1 || nlev > kPTailMax || mg.lv[l].n > kPTailMaxN) return false;
-  a = PTailArgs<T, TB, TZ>{};
+  a = PTailArgs<T, TB>{};
   a.nlev = nlev;
   int off = 0;
   for (int k = 0; k < nlev; ++k) {
@@ -416,27 +411,28 @@ static bool p1_tail_args(const Mg &mg, int l, bool out, PTailArgs<T, TB, TZ> &a)
 }
 
 // ---------------------------------------------------------------- V-cycle
-// One V-cycle at level l for right-hand side b (comps * nodes entries, component-major).
-// Returns the level work vector that holds the result.
-// out (optional): where the matrix-free velocity cycle writes its result (the returned
-// pointer); otherwise a level work vector.  out64 (optional, FP32 cycle): an FP64 vector the
-// result goes to when the last smoothing launch can store it there (then nullptr is returned).
-// dot (optional, level 0 of a velocity cycle with tile_dot_ok): the last launch stores the
-// per-tile sums of b . result (post3_dot_count(n) per lane), with b64 (FP32 cycle) in place
-// of b.
+// One V-cycle at level l for right-hand side b (comps * nodes entries, component-major; lane
+// stride b.s).  Returns the level work vector that holds the result.
+// The rest at level 0 of a matrix-free velocity cycle only:
+// out64: the FP64 vector the last smoothing launch stores its result in (nullptr is returned).
+// dot (tile_dot_ok): that launch also stores the per-tile sums of b . result (post3_dot_count(n)
+// per lane), with b64 (FP32 cycle) in place of b.
+// fold (tile_dot_ok): the first launch makes the right-hand side (see MsFold): b is where the FP32
+// cycle finds its copy (FP64: fold->q); ev is recorded behind that launch.
 template <typename T, int W, int NC>
-static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr, int K = 1, T *out = nullptr,
-                 double *out64 = nullptr, LP<double> dot = LP<double>(),
-                 LP<const double> b64 = LP<const double>()) {
+static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullptr, int K = 1,
+                 LP<double> out64 = LP<double>(), LP<double> dot = LP<double>(),
+                 LP<const double> b64 = LP<const double>(), const MsFold *fold = nullptr, hipEvent_t ev = nullptr) {
   MgLevel &L = mg.lv[l];
   T *x = Pr<T>::w(L, 0), *x2 = Pr<T>::w(L, 4), *r = Pr<T>::w(L, 2), *d = Pr<T>::w(L, 3);
   // K systems (matrix-free hierarchy only): lane k of every level vector at + k comps nodes
   FSI_REQUIRE(K == 1 || mg.stencil, FSI_E_STATE, "several systems per V-cycle need the matrix-free smoother");
-  FSI_REQUIRE(!dot.p || (l == 0 && W == 4 && mg.stencil && l + 1 < (int)mg.lv.size()), FSI_E_STATE,
-              "tile sums only from the finest velocity level of a matrix-free cycle");
+  FSI_REQUIRE((!dot.p && !fold) || (l == 0 && W == 4 && mg.stencil && l + 1 < (int)mg.lv.size()), FSI_E_STATE,
+              "tile sums and updates only at the finest velocity level of a matrix-free cycle");
   const int64_t ls = (int64_t)mg.comps * L.nodes;
   if (l + 1 == (int)mg.lv.size()) {
-    dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), b, x, K, s);
+    FSI_REQUIRE(K == 1 || b.s == ls, FSI_E_STATE, "the dense solve takes contiguous lanes");
+    dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), b.p, x, K, s);
     return x;
   }
   // Chebyshev interval [lmax / R, lmax] of D^{-1} A: R = 15 on the velocity levels, 30 on the
@@ -452,7 +448,7 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
   const int64_t lc = (int64_t)mg.comps * C.nodes;
   if constexpr (W == 4) {   // the coarse end of the velocity cycle in one launch
     TailArgs<T> ta;
-    if (mg.tail && tail_args<T>(mg, l, degree, b, x, ls, ta)) {
+    if (mg.tail && tail_args<T>(mg, l, degree, b.p, x, ls, ta)) {   // l >= 1: b has the level's stride
       mg_tail<T>(ta, s, K);
       return x;
     }
@@ -467,20 +463,19 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
       (void)d;
       const AfCoef<T> &cf = afc<T>(L);
       const Cheb3Coef<T> cc = cheb3_coefs<T>(lmin, lmax);
-      const LP<const T> lb(b, ls), lx(x, ls);
-      pre3<T>(L.n, cf, lb, LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K);
-      resid_restrict<T>(L.n, cf, lx, lb, LP<T>(bc, lc), s, K);
-      T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s, nullptr, K);
+      const LP<const T> lx(x, ls);
+      pre3<T>(L.n, cf, LP<T>(const_cast<T *>(b.p), b.s), LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, fold);
+      if (ev) FSI_HIP(hipEventRecord(ev, s));
+      resid_restrict<T>(L.n, cf, lx, b, LP<T>(bc, lc), s, K);
+      T *xc = vcycle<T, W, NC>(mg, l + 1, LP<const T>(bc, lc), s, nullptr, K);
       const LP<const T> lxc(xc, lc);
-      T *y = out ? out : x2;
       if (pl) pl->begin(s);
-      if (out64)
-        post3<T, double>(L.n, cf, lx, lb, LP<double>(out64, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot,
-                         b64);
+      if (out64.p)
+        post3<T, double>(L.n, cf, lx, b, out64, cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot, b64);
       else
-        post3<T, T>(L.n, cf, lx, lb, LP<T>(y, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot, b64);
+        post3<T, T>(L.n, cf, lx, b, LP<T>(x2, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot, b64);
       if (pl) pl->end(s);
-      return out64 ? nullptr : y;
+      return out64.p ? nullptr : x2;
     } else {
       FSI_REQUIRE(false, FSI_E_STATE, "the matrix-free pressure cycle is p1_cycle");
     }
@@ -489,19 +484,19 @@ static T *vcycle(Mg &mg, int l, const T *b, hipStream_t s, Prof *prof = nullptr,
   const Q2Table<T> *q2 = nullptr;
   if constexpr (W == 4)
     q2 = (const Q2Table<T> *)(std::is_same<T, double>::value ? L.q2tab64.p : L.q2tab32.p);
-  T *xs = q2 ? chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b, x, x2, d, true, s, pl)
-             : chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b, x,
+  T *xs = q2 ? chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b.p, x, x2, d, true, s, pl)
+             : chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b.p, x,
                                    x2, d, true, s, pl);
   T *xo = (xs == x) ? x2 : x;
-  if (q2) q2_stencil<T>(L.n, q2, xs, b, nullptr, r, (T)0, (T)0, true, s);
-  else spmv<T, W, NC, SP_RESID>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, xs, L.nodes, r, L.nodes, s, b);
+  if (q2) q2_stencil<T>(L.n, q2, xs, b.p, nullptr, r, (T)0, (T)0, true, s);
+  else spmv<T, W, NC, SP_RESID>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, xs, L.nodes, r, L.nodes, s, b.p);
   spmv<T, 1, NC, SP_APPLY>(L.R.nrows, L.R.rowptr.p, L.R.col.p, Pr<T>::val(L.R), r, L.nodes, bc,
                            C.nodes, s);
-  T *xc = vcycle<T, W, NC>(mg, l + 1, bc, s);
+  T *xc = vcycle<T, W, NC>(mg, l + 1, LP<const T>(bc, lc), s);
   spmv<T, 1, NC, SP_ADD>(L.P.nrows, L.P.rowptr.p, L.P.col.p, Pr<T>::val(L.P), xc, C.nodes, xs,
                          L.nodes, s);
-  if (q2) return chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b, xs, xo, d, false, s, pl);
-  return chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b,
+  if (q2) return chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b.p, xs, xo, d, false, s, pl);
+  return chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b.p,
                              xs, xo, d, false, s, pl);
 }
 
@@ -540,16 +535,16 @@ static T *p1_cycle(Mg &mg, int l, const T *b, int64_t lb, hipStream_t s, int K) 
     dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), b, x, K, s);
     return x;
   }
-  PTailArgs<T, T, T> ta;
+  PTailArgs<T, T> ta;
   if (p1_tail_args<T>(mg, l, false, ta)) {
     ta.b = b;
     ta.x = x;
     ta.lb = lb;
     ta.lx = L.nodes;
-    p1_tail<T, T, T, false>(ta, s, K);
+    p1_tail<T, T, false>(ta, s, K);
     return x;
   }
-  P1UpArgs<T, T, T> a{};
+  P1UpArgs<T, T> a{};
   a.xc = p1_descend<T, T>(mg, l, b, lb, s, K);
   a.n = L.n;
   a.b = b;
@@ -559,23 +554,22 @@ static T *p1_cycle(Mg &mg, int l, const T *b, int64_t lb, hipStream_t s, int K) 
   a.lb = lb;
   a.lx = L.nodes;
   a.lc = mg.lv[l + 1].nodes;
-  p1_up<T, T, T, P1_Y>(a, s, K);
+  p1_up<T, T, P1_Y>(a, s, K);
   return a.y;
 }
 
 // Parts of r . z that the matrix-free pressure part stores per lane: one per tile of the finest
 // level's ascent, or one where the finest level is the tail's
 static bool p1_tail_all(const Ctx &c) {
-  PTailArgs<double, double, double> a;   // the larger of the two precisions
+  PTailArgs<double, double> a;   // the larger of the two precisions
   return p1_tail_args<double>(c.mgp, 0, true, a);
 }
 static int pres_dot_count(const Ctx &c) { return p1_tail_all(c) ? 1 : p1_up_tiles(c.n); }
 
-// z = nu M_p^{-1} r + (rho/dt) L_p^{-1} r on the pressure unknowns of K systems (lane stride lz of r, z
-// and r64), the pinned entry r[0], and with part the parts of sum r z (sum r64 z when r64 is given)
-template <typename T, typename TZ>
-static void p1_schur(Ctx &c, const TZ *r, TZ *z, const double *r64, int64_t lz, double *part, int64_t lp,
-                     hipStream_t s, int K) {
+// z = nu M_p^{-1} r + (rho/dt) L_p^{-1} r on the pressure unknowns of K systems (lane stride lz of r
+// and z), the pinned entry r[0], and with part the parts of sum r z
+template <typename T>
+static void p1_schur(Ctx &c, const double *r, double *z, int64_t lz, double *part, int64_t lp, hipStream_t s, int K) {
   Mg &mg = c.mgp;
   MgLevel &L = mg.lv[0];
   static_assert(kMpSteps == 3, "the fused mass solve takes three steps");
@@ -584,7 +578,6 @@ static void p1_schur(Ctx &c, const TZ *r, TZ *z, const double *r64, int64_t lz, 
   auto mass = [&](auto &a, T &ms) {   // the mass solve and the output
     a.b = r;
     a.z = z;
-    a.r64 = r64;
     ms = m2[0];
     for (int k = 0; k < 2; ++k) {
       a.m1[k] = m1[k + 1];
@@ -598,81 +591,80 @@ static void p1_schur(Ctx &c, const TZ *r, TZ *z, const double *r64, int64_t lz, 
     a.lb = a.lz = lz;
     a.lp = lp;
   };
-  PTailArgs<T, TZ, TZ> ta;
+  PTailArgs<T, double> ta;
   if (p1_tail_all(c) && p1_tail_args<T>(mg, 0, true, ta)) {
     mass(ta, ta.ms);
-    p1_tail<T, TZ, TZ, true>(ta, s, K);
+    p1_tail<T, double, true>(ta, s, K);
     return;
   }
-  P1UpArgs<T, TZ, TZ> a{};
+  P1UpArgs<T, double> a{};
   mass(a, a.ms[0]);
   a.n = c.n;
   if (mg.lv.size() == 1) {   // the dense level alone: its right-hand side in T, contiguous, pinned entry 0
     T *rp = Pr<T>::inner(c, 8).p;
-    convert_l(LP<T>(rp, c.Np), LP<const TZ>(r, lz), c.Np, s, K);
+    convert_l(LP<T>(rp, c.Np), LP<const double>(r, lz), c.Np, s, K);
     fill_l(LP<T>(rp, c.Np), 1, (T)0, s, K);
     a.xc = p1_cycle<T>(mg, 0, rp, c.Np, s, K);
     a.lc = L.nodes;
-    p1_up<T, TZ, TZ, P1_ZW>(a, s, K);
+    p1_up<T, double, P1_ZW>(a, s, K);
     return;
   }
-  a.xc = p1_descend<T, TZ>(mg, 0, r, lz, s, K);
+  a.xc = p1_descend<T, double>(mg, 0, r, lz, s, K);
   a.x = Pr<T>::w(L, 0);
   p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, a.c1, a.c2);
   a.lx = L.nodes;
   a.lc = mg.lv[1].nodes;
-  p1_up<T, TZ, TZ, P1_Z>(a, s, K);
+  p1_up<T, double, P1_Z>(a, s, K);
 }
 
 // z = diag(V, S^{-1}) r on [u | p], for K systems at once (lane k of r and z at + k nf,
-// nf = 2 N2 + Np; K > 1 needs the matrix-free hierarchies).  The two blocks share no
+// nf = 2 N2 + Np; K > 1 needs the matrix-free hierarchies), in arithmetic T on FP64 vectors.  ru is
+// the velocity part of r in T (lane stride ru.s): r itself, or its FP32 copy.  The two blocks share no
 // buffer: outside graph capture the pressure part runs on the auxiliary stream beside the
 // velocity V-cycle (both chains are latency-bound on the coarse levels), forked after the
 // producer of r and joined before the consumer of z.  Captured graphs keep the whole
 // preconditioner on one stream.
-// r64, z64 (FP32 arithmetic, one system): the results are stored straight into the FP64 vector
-// z64 (z unused) and the pressure residual is read from r64 (r holds the velocity part).
-// dot (FP64 form, tile_dot_ok): the launches that write z also store per-tile / per-block
-// parts of r . z: post3_dot_count(n) velocity tile sums, then pres_dot_count pressure parts,
-// per lane (lane stride dot.s).
+// dot (tile_dot_ok): the launches that write z also store per-tile / per-block parts of r . z:
+// post3_dot_count(n) velocity tile sums, then pres_dot_count pressure parts, per lane (lane
+// stride dot.s).
+// fold (tile_dot_ok): the velocity cycle's first launch makes r = fold->q (and ru) first; the
+// pressure part starts behind that launch.
 // part: PC_BOTH, or only the velocity cycle (PC_VEL) or only the pressure part (PC_PRES); the
 // other part of z is left as it is.
 enum { PC_BOTH = 0, PC_VEL = 1, PC_PRES = 2 };
 template <typename T>
-static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 = nullptr, double *z64 = nullptr,
-                        LP<double> dot = LP<double>(), int part = PC_BOTH) {
-  FSI_REQUIRE((!dot.p || std::is_same<T, double>::value || r64), FSI_E_STATE,
-              "sums of r . z in the FP32 form need the FP64 residual");
-  FSI_REQUIRE(!dot.p || part == PC_BOTH, FSI_E_STATE, "the sums of r . z need both parts");
+static void a11_precond(Ctx &c, LP<const T> ru, const double *r, double *z, int K = 1, LP<double> dot = LP<double>(),
+                        int part = PC_BOTH, const MsFold *fold = nullptr) {
+  FSI_REQUIRE((!dot.p && !fold) || part == PC_BOTH, FSI_E_STATE, "the sums of r . z and the update need both parts");
+  FSI_REQUIRE(!fold || fold->q.p == r, FSI_E_STATE, "the update makes the right-hand side");
   const bool fork = !c.capturing && part == PC_BOTH;
   hipStream_t s = c.stream, sp = fork ? c.aux_stream : c.stream;
   const int64_t N2 = c.N2, Np = c.Np, nf = 2 * N2 + Np;
   Prof *pf = std::is_same<T, double>::value ? &c.prof64 : &c.prof32;
-  if (fork) {
+  if (fork && !fold) {
     FSI_HIP(hipEventRecord(c.ev_fork, s));
     FSI_HIP(hipStreamWaitEvent(sp, c.ev_fork, 0));
   }
-  if (part == PC_PRES) {
-    // the velocity cycle is not run
-  } else if (z64) {
-    T *xu = vcycle<T, 4, 2>(c.mgu, 0, r, s, pf->on ? pf : nullptr, 1, nullptr, z64, dot,
-                            LP<const double>(dot.p ? r64 : nullptr));
-    FSI_REQUIRE(!dot.p || !xu, FSI_E_STATE, "the sums of r . z need the direct FP64 output");
-    if (xu) convert(z64, xu, 2 * N2, s);
-  } else if (K == 1) {   // the cycle reads r and writes z in place (one system: no lane stride)
-    T *xu = vcycle<T, 4, 2>(c.mgu, 0, r, s, pf->on ? pf : nullptr, 1, z, nullptr, dot);
-    if (xu != z) convert(z, xu, 2 * N2, s);
-  } else {   // the finest level's right-hand side: the velocity part of each lane, contiguous
-    T *bu = Pr<T>::w(c.mgu.lv[0], 1);
-    convert_l(LP<T>(bu, 2 * N2), LP<const T>(r, nf), 2 * N2, s, K);
-    T *xu = vcycle<T, 4, 2>(c.mgu, 0, bu, s, nullptr, K, nullptr, nullptr, dot,
-                            LP<const double>(dot.p && r64 ? r64 : nullptr, nf));
-    convert_l(LP<T>(z, nf), LP<const T>(xu, 2 * N2), 2 * N2, s, K);
+  if (part != PC_PRES) {
+    const bool one = c.mgu.lv.size() == 1;
+    if (K > 1 && one) {   // the dense level alone takes contiguous lanes
+      T *bu = Pr<T>::w(c.mgu.lv[0], 1);
+      convert_l(LP<T>(bu, 2 * N2), ru, 2 * N2, s, K);
+      ru = LP<const T>(bu, 2 * N2);
+    }
+    const bool direct = c.mgu.stencil && !one;   // the last smoothing launch writes z
+    T *xu = vcycle<T, 4, 2>(c.mgu, 0, ru, s, K == 1 && pf->on ? pf : nullptr, K,
+                            direct ? LP<double>(z, nf) : LP<double>(), dot,
+                            LP<const double>(dot.p && !std::is_same<T, double>::value ? r : nullptr, nf), fold,
+                            fork && fold ? c.ev_fork : nullptr);
+    FSI_REQUIRE(direct == !xu, FSI_E_STATE, "the velocity cycle's output");
+    if (xu) convert_l(LP<double>(z, nf), LP<const T>(xu, 2 * N2), 2 * N2, s, K);
   }
   if (part == PC_VEL) {
     FSI_CHECK_LAUNCH();
     return;
   }
+  if (fork && fold) FSI_HIP(hipStreamWaitEvent(sp, c.ev_fork, 0));
   auto join = [&] {
     FSI_CHECK_LAUNCH();
     if (fork) {
@@ -682,27 +674,19 @@ static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 =
   };
   if (c.mgp.stencil) {
     double *parts = dot.p ? dot.p + post3_dot_count(c.n) : nullptr;
-    if (z64)
-      p1_schur<T, double>(c, r64 + 2 * N2, z64 + 2 * N2, nullptr, nf, parts, dot.s, sp, 1);
-    else
-      p1_schur<T, T>(c, r + 2 * N2, z + 2 * N2, r64 ? r64 + 2 * N2 : nullptr, nf, parts, dot.s, sp, K);
+    p1_schur<T>(c, r + 2 * N2, z + 2 * N2, nf, parts, dot.s, sp, K);
     join();
     return;
   }
   FSI_REQUIRE(!dot.p && K == 1, FSI_E_STATE, "the assembled form runs one system and forms no tile sums");
   // r' = pressure residual with the pinned entry removed (keeps the operator symmetric)
   T *rp = Pr<T>::inner(c, 8).p;
-  if (z64) convert(rp, r64 + 2 * N2, Np, sp);
-  else convert(rp, r + 2 * N2, Np, sp);
+  convert(rp, r + 2 * N2, Np, sp);
   fill(rp, 1, (T)0, sp);
-  T *xp = vcycle<T, 1, 1>(c.mgp, 0, rp, sp, nullptr);
+  T *xp = vcycle<T, 1, 1>(c.mgp, 0, LP<const T>(rp, Np), sp, nullptr);
   if (c.pair == FSI_PAIR_Q2P1DISC) {   // M_p of the discontinuous pressure is diagonal: no mass solve
-    if (z64)
-      hipLaunchKernelGGL((k_q_pres<double, T>), dim3(vgrid(Np)), dim3(256), 0, sp, z64 + 2 * N2, r64 + 2 * N2, xp,
-                         mp_dinv<T>(c), (T)c.nu, (T)(c.rho / c.dt), Np);
-    else
-      hipLaunchKernelGGL((k_q_pres<T, T>), dim3(vgrid(Np)), dim3(256), 0, sp, z + 2 * N2, r + 2 * N2, xp,
-                         mp_dinv<T>(c), (T)c.nu, (T)(c.rho / c.dt), Np);
+    hipLaunchKernelGGL((k_q_pres<double, T>), dim3(vgrid(Np)), dim3(256), 0, sp, z + 2 * N2, r + 2 * N2, xp,
+                       mp_dinv<T>(c), (T)c.nu, (T)(c.rho / c.dt), Np);
     join();
     return;
   }
@@ -710,35 +694,23 @@ static void a11_precond(Ctx &c, const T *r, T *z, int K = 1, const double *r64 =
   T *mx = Pr<T>::inner(c, 7).p, *mx2 = mx + Np, *md = mx + 2 * Np;
   T *mres = chebyshev<T, 1, 1>(Np, c.Mp.rowptr.p, c.Mp.col.p, Pr<T>::val(c.Mp), mp_dinv<T>(c), 0.5, 2.0, kMpSteps, rp,
                                mx, mx2, md, true, sp);
-  if (z64) {
-    lincomb_to<double, T>(z64 + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
-    hipLaunchKernelGGL((k_set_pinned_to<double, T>), dim3(1), dim3(1), 0, sp, z64 + 2 * N2, r64 + 2 * N2);
-  } else {
-    lincomb(z + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
-    hipLaunchKernelGGL(k_set_pinned<T>, dim3(1), dim3(1), 0, sp, z + 2 * N2, r + 2 * N2);
-  }
+  lincomb_to<double, T>(z + 2 * N2, mres, xp, (T)c.nu, (T)(c.rho / c.dt), Np, sp);
+  hipLaunchKernelGGL((k_set_pinned_to<double, T>), dim3(1), dim3(1), 0, sp, z + 2 * N2, r + 2 * N2);
   join();
 }
 
 // ---------------------------------------------------------------- inner MINRES
 // The A11 preconditioner on FP64 vectors with arithmetic TA: FP32 runs on a converted copy
 // of the velocity residual (read three times by the finest level) and stores its results
-// straight into z; several systems run on converted copies of whole vectors.
+// straight into z.
 template <typename TA>
 static void a11_precond_on64(Ctx &c, const double *r, double *z, int K = 1, int part = PC_BOTH) {
+  const int64_t nf = 2 * c.N2 + c.Np, nv = 2 * c.N2;
   if constexpr (std::is_same<TA, double>::value) {
-    a11_precond<double>(c, r, z, K, nullptr, nullptr, LP<double>(), part);
-  } else if (K == 1) {
-    if (part != PC_PRES) convert(c.outer.x32.p, r, 2 * c.N2, c.stream);
-    a11_precond<float>(c, c.outer.x32.p, nullptr, 1, r, z, LP<double>(), part);
+    a11_precond<double>(c, LP<const double>(r, nf), r, z, K, LP<double>(), part);
   } else {
-    const int64_t nf = 2 * c.N2 + c.Np, nv = 2 * c.N2;
-    convert_l(LP<float>(c.outer.x32.p, nf), LP<const double>(r, nf), nf, c.stream, K);
-    a11_precond<float>(c, c.outer.x32.p, c.outer.y32.p, K, nullptr, nullptr, LP<double>(), part);
-    if (part != PC_PRES)
-      convert_l(LP<double>(z, nf), LP<const float>(c.outer.y32.p, nf), nv, c.stream, K);
-    if (part != PC_VEL)
-      convert_l(LP<double>(z + nv, nf), LP<const float>(c.outer.y32.p + nv, nf), nf - nv, c.stream, K);
+    if (part != PC_PRES) convert_l(LP<float>(c.outer.x32.p, nv), LP<const double>(r, nf), nv, c.stream, K);
+    a11_precond<float>(c, LP<const float>(c.outer.x32.p, nv), r, z, K, LP<double>(), part);
   }
 }
 
@@ -939,25 +911,6 @@ __global__ void k_ms_axpy(double *y, const double *r, const MinresState *st, int
     y[o + i] += a * r[o + i];
 }
 
-// y -= (alfa s) r2 as k_ms_axpy (which = 1), then the FP32 copy of the first n32 entries
-// of y for the FP32 preconditioner (lane stride l32)
-__global__ void k_ms_axpy_f32(double *y, const double *r, const MinresState *st, int64_t n, float *y32, int64_t n32,
-                              int64_t l32) {
-  const MinresState &q = st[blockIdx.y];
-  const double a = -q.alfa * q.s;
-  const int64_t o = (int64_t)blockIdx.y * n;
-  y32 += (int64_t)blockIdx.y * l32;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    double v = y[o + i];
-    if (a != 0.0) {
-      v += a * r[o + i];
-      y[o + i] = v;
-    }
-    if (i < n32) y32[i] = (float)v;
-  }
-}
-
 // Coefficients of a block of m iterations (block = lane): the direction recurrence run on
 // coefficient vectors over the basis (v slot 0 .. m - 1, w_{k0-1}, w_{k0}), stopping at the
 // first slot the lane did not apply; thread k follows coefficient k (the recurrence acts on
@@ -1095,9 +1048,9 @@ static MsBufs ms_bufs(Ctx &c, double *x, int phase) {
   return b;
 }
 
-// Buffers with the matrix-free A11 product (fused iteration below): the new Lanczos vector
-// is written over r1, so r1 and r2 alternate between two buffers and the preconditioned
-// vector always lives in the third (period 2).
+// Buffers with the matrix-free A11 product and an update in place (the fused iteration below without
+// tile_dot_ok): the new Lanczos vector is written over r1, so r1 and r2 alternate between two buffers
+// and the preconditioned vector always lives in the third (period 2).
 static MsBufs ms_bufs_fused(Ctx &c, double *x, int it) {
   MsBufs b = ms_bufs(c, x, 0);
   double *B0 = c.inner.v64[2].p, *B1 = c.inner.v64[3].p;
@@ -1107,7 +1060,12 @@ static MsBufs ms_bufs_fused(Ctx &c, double *x, int it) {
   return b;
 }
 
-// The preconditioner can hand over r . z as tile and block sums when the velocity cycle of
+// The first smoothing launch sums up to this many parts of alfa itself, in every block: at 1024^2
+// (2,193 parts) 17 KB from the L2 beside a block's 300 KB of operands, and the launch that it saves is
+// 4 us; beyond that the sum is a launch of its own.
+constexpr int kMsFoldParts = 4096;
+
+// The preconditioner can take the update and hand over r . z as tile and block sums when the velocity cycle of
 // its precision ends with the fused three-step launch on a matrix-free hierarchy of two or
 // more levels (the FP32 form for one system, on FP64 vectors).
 static bool tile_dot_ok(const Ctx &c, bool fp32) {
@@ -1115,8 +1073,10 @@ static bool tile_dot_ok(const Ctx &c, bool fp32) {
 }
 
 // One inner iteration with the matrix-free A11 (FP64) for K systems: the scaling v = s y,
-// the product, the first three-term update and the dot product alfa = v . y are one tiled
-// launch (new y over r1); then y -= alfa s r2, z = M y into the y buffer, beta^2 = y . z.
+// the product, the first three-term update and the parts of alfa = v . y are one launch (new y over
+// r1).  Then q = y - alfa s r2, z = M q, beta^2 = q . z: with tile_dot_ok the update is the first
+// smoothing launch's (q over the old z, z over y: the rotation of ms_bufs) and the sums are the last
+// ones'; else they are launches of their own (q in place, z in the y buffer: ms_bufs_fused).
 template <typename TA>
 static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) {
   hipStream_t s = c.stream;
@@ -1128,31 +1088,29 @@ static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) 
              LP<const double>(&st->s, kMsDoubles), LP<const double>(&st->c_r1, kMsDoubles),
              LP<const double>(&st->slot, kMsDoubles), (int64_t)c.lanes * nf, c.ms_B, LP<double>(c.ms_part.p, tiles), s,
              K);
-  hipLaunchKernelGGL(k_ms_alfa, dim3(1, K), dim3(1024), 0, s, c.ms_part.p, tiles, st);
+  const bool fold_sum = tiles <= kMsFoldParts;
   constexpr bool f32 = std::is_same<TA, float>::value;
   const bool dot_ok = tile_dot_ok(c, f32);
-  if (f32 && dot_ok)   // the three-term update also writes the FP32 copy the preconditioner reads
-    hipLaunchKernelGGL(k_ms_axpy_f32, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, nf, c.outer.x32.p,
-                       K == 1 ? 2 * c.N2 : nf, nf);
-  else
-    hipLaunchKernelGGL(k_ms_axpy, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, 1, nf);
-  if (dot_ok) {   // beta^2 = r . z from the launches that write z
+  if (!dot_ok || !fold_sum) hipLaunchKernelGGL(k_ms_alfa, dim3(1, K), dim3(1024), 0, s, c.ms_part.p, tiles, st);
+  if (dot_ok) {
     const int nu = post3_dot_count(c.n), np = pres_dot_count(c);
-    const int64_t ld = nu + pres_dot_count(c);
-    const LP<double> dot(c.ms_dot.p, ld);
-    if constexpr (f32) {   // the same arithmetic as a11_precond_on64<float>, sums on FP64 r
-      if (K == 1) {
-        a11_precond<float>(c, c.outer.x32.p, nullptr, 1, b.r1, b.y, dot);
-      } else {
-        a11_precond<float>(c, c.outer.x32.p, c.outer.y32.p, K, b.r1, nullptr, dot);
-        convert_l(LP<double>(b.y, nf), LP<const float>(c.outer.y32.p, nf), nf, s, K);
-      }
-    } else {
-      a11_precond<double>(c, b.r1, b.y, K, nullptr, nullptr, dot);
-    }
+    const int64_t ld = nu + np;
+    MsFold f;
+    f.y1 = LP<const double>(b.r1, nf);
+    f.r2 = LP<const double>(b.r2, nf);
+    f.q = LP<double>(b.y, nf);
+    f.part = c.ms_part.p;
+    f.nparts = fold_sum ? tiles : 0;
+    f.lp = tiles;
+    f.alfa = &st->alfa;
+    f.s = &st->s;
+    f.ls = kMsDoubles;
+    const LP<const TA> ru = f32 ? LP<const TA>((const TA *)c.outer.x32.p, 2 * c.N2) : LP<const TA>((const TA *)b.y, nf);
+    a11_precond<TA>(c, ru, b.y, b.r1, K, LP<double>(c.ms_dot.p, ld), PC_BOTH, &f);
     hipLaunchKernelGGL(k_ms_beta_step, dim3(1, K), dim3(1024), 0, s, c.ms_dot.p, nu, np, ld, st,
                        c.ms_hist.p, c.ms_B);
   } else {
+    hipLaunchKernelGGL(k_ms_axpy, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, 1, nf);
     a11_precond_on64<TA>(c, b.r1, b.y, K);
     dot_l(LP<const double>(b.r1, nf), LP<const double>(b.y, nf), nf, LP<double>(dv + 1, kMsDoubles), c.ms_red.p, s,
           K);
@@ -1190,6 +1148,7 @@ static void minres_a11(Ctx &c, const double *const *b, double *const *xout, int 
   hipStream_t s = c.stream;
   const int64_t nf = 2 * c.N2 + c.Np;
   const bool fused = c.mgu.stencil;   // matrix-free FP64 A11
+  const bool in_place = fused && !tile_dot_ok(c, std::is_same<TA, float>::value);
   FSI_REQUIRE(K >= 1 && K <= c.lanes, FSI_E_ARG, "more systems than inner lanes");
   FSI_REQUIRE(K == 1 || fused, FSI_E_STATE, "several systems per inner solve need the matrix-free smoother");
   MinresState *st = (MinresState *)c.ms_state.p;
@@ -1248,8 +1207,8 @@ static void minres_a11(Ctx &c, const double *const *b, double *const *xout, int 
   };
   while (it < maxit) {
     // the rotation: in phase p the roles are shifted by p (r2 of phase p is y of p-1, ...)
-    const int phase = fused ? it % 2 : it % 3;
-    const MsBufs bq = fused ? ms_bufs_fused(c, x, it) : ms_bufs(c, x, phase);
+    const int phase = in_place ? it % 2 : it % 3;
+    const MsBufs bq = in_place ? ms_bufs_fused(c, x, it) : ms_bufs(c, x, phase);
     if (graphs) {
       hipGraphExec_t &ge = c.ms_graph[pk][K][phase];
       if (!ge)
@@ -1730,7 +1689,6 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
                     &c.ms_hist, &c.ms_coef})
       b->release();
     c.outer.x32.release();
-    c.outer.y32.release();
     for (Mg *mg : {&c.mgu, &c.mgp})
       for (auto &L : mg->lv)
         for (int i = 0; i < 5; ++i) {
@@ -1764,7 +1722,7 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
     ensure_fp32_mg(c);
     for (int i = 7; i < 9; ++i)       // pressure scratch of the FP32 preconditioner
       if (!c.inner.v32[i].p) c.inner.v32[i].alloc(nl * nf);
-    if (!c.outer.x32.p) { c.outer.x32.alloc(nl * nf); c.outer.y32.alloc(nl * nf); }
+    if (!c.outer.x32.p) { c.outer.x32.alloc(nl * 2 * c.N2); }
     if (!c.Mp_dinv32.p) {
       c.Mp_dinv32.alloc(c.Np);
       convert(c.Mp_dinv32.p, c.Mp_dinv.p, c.Np, c.stream);

@@ -97,16 +97,31 @@ void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const
 // b = [rdt M_f u | 0] on [u_x | u_y | p] (Dirichlet rows 0, Dirichlet values of u left out)
 void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s);
 
+// The three-term update of the inner MINRES, taken by pre3 while it stages its right-hand side:
+// q = y1 - alfa s r2 on [u_x | u_y | p], alfa the sum of nparts parts (of stride lp per lane; stored to
+// *alfa), or with nparts = 0 the value of *alfa.  y1, r2 and q have one lane stride, alfa and s another.
+struct MsFold {
+  LP<const double> y1, r2;
+  LP<double> q;
+  const double *part = nullptr;
+  int nparts = 0;
+  int64_t lp = 0;
+  double *alfa = nullptr;
+  const double *s = nullptr;
+  int64_t ls = 0;
+};
+
 // Chebyshev smoothing of a velocity level, three steps per launch:
-// pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x
+// pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x.  With fold, b is the velocity
+//        part of q; q (all three parts) is written, and for T = float also the copy b.
 // post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and
 //        the steps (c1b, c2b), (c1c, c2c); writes y (stored as TY: double or T; x is not
 //        written).  With dot, tile t of lane k stores the sum over its nodes of b . y (FP64, y as
 //        stored) at dot.at(k)[t] (post3_dot_count(n) tiles); with b64 the sums take that FP64
 //        right-hand side in place of b (the FP32 cycle of the mixed form).
 template <typename T>
-void pre3(int n, const AfCoef<T> &cf, LP<const T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st,
-          int K = 1);
+void pre3(int n, const AfCoef<T> &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
+          const MsFold *fold = nullptr);
 template <typename T, typename TY>
 void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
            hipStream_t st, int K, LP<const T> xc, LP<double> dot = LP<double>(),

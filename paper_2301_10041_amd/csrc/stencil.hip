@@ -143,35 +143,142 @@ template <typename T>
 struct PreArgs {
   int n;
   AfCoef<T> cf;
-  const T *b;
+  T *b;                      // read, or written with the update (FP32 only)
   T *y;
   T s, c1a, c2a, c1b, c2b;   // the first step's scale, the two stencil steps
-  int64_t lv;                // lane stride of b and y (lane = blockIdx.y)
+  int64_t lb, ly;            // lane strides of b and y (lane = blockIdx.y)
+  MsFold f;                  // k_pre3<T, true>
+  int64_t np;                // its pressure entries
 };
 
 // The pre-smoothing of a degree-3 smoother: x = d = s D^{-1} b, then two steps; reads b, writes x
 // (4 w per node).  The first stencil step runs on 8 x 64 cells, the second on the inner 6 x 62,
 // which are the block's tile.
+//
+// MS: in MINRES b is made here, q = y1 - alfa s r2, from the parts of alfa that the A11 launch
+// left: every block sums them (in the same order) while its loads of y1 and r2 are in flight, and
+// blocks past the tiles update the pressure part.  Two launches and one pass over three vectors
+// less per inner step: 9 us against 6.2 + 2.6 + 1.9 and two gaps at 32^2, 83 against 37 + 38 + 4 and
+// two gaps at 1024^2 (FP64); 35 at 768^2 with FP32 arithmetic, where the FP32 copy of q is written
+// here too.
 constexpr int kPreW = kWave - 2, kPreR = kCellWaves - 2;
-template <typename T>
+constexpr int kPrePres = 4 * kWave * kCellWaves;   // pressure entries per block
+template <typename T, bool MS>
 __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T> a, int tiles_x, int tiles, int band) {
-  __shared__ V2<T> X[2 * kCellPL];
+  using TS = typename std::conditional<MS, double, T>::type;   // staged first
+  __shared__ V2<TS> XS[2 * kCellPL];
+  V2<T> *const X = reinterpret_cast<V2<T> *>(XS);
+  const bool pres = MS && (int)blockIdx.x >= band * kXcd;
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
-  if (t >= tiles) return;
-  const T *bg = a.b + (int64_t)blockIdx.y * a.lv;
-  T *yg = a.y + (int64_t)blockIdx.y * a.lv;
+  if (!pres && t >= tiles) return;
+  T *bg = a.b + (int64_t)blockIdx.y * a.lb;
+  T *yg = a.y + (int64_t)blockIdx.y * a.ly;
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
   const int i0 = (t % tiles_x) * kPreW - 1, j0 = (t / tiles_x) * kPreR - 1;   // first cell of the region
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
   const AfCoef<T> &cf = a.cf;
-  V2<T> b[4];
-  load_cell(bg, N, L, n, i, j, b);
-  stage_pairs<T, kCellH>(X, bg, N, L, n, i0, j0, [&](int pj, int pi, V2<T> v) -> V2<T> {
+  auto first = [&](int pj, int pi, V2<T> v) -> V2<T> {
     const V2<T> z = cell_dinv(cf, pi | pj, v);
     return V2<T>{a.s * z.x, a.s * z.y};
-  });
+  };
+  V2<T> b[4];
+  if constexpr (MS) {
+    const int64_t lane_v = (int64_t)blockIdx.y * a.f.q.s;
+    const double *y1 = a.f.y1.p + lane_v, *r2 = a.f.r2.p + lane_v;
+    double *q = a.f.q.p + lane_v;
+    // the staged nodes (as in stage_pairs), in flight over the sum of alfa
+    constexpr int NT = kWave * kCellWaves, NE = kCellH * kCellHW, IT = (NE + NT - 1) / NT;
+    NodePair<double> ya[IT], yb[IT], ra[IT], rb[IT];
+    if (!pres) {
+#pragma unroll
+      for (int k = 0; k < IT; ++k) {
+        const int e = threadIdx.x + NT * k, lr = e / kCellHW, ci = i0 - 1 + e % kCellHW, J = 2 * (j0 - 1) + lr;
+        ya[k] = yb[k] = ra[k] = rb[k] = NodePair<double>{0.0, 0.0};
+        if (e < NE && ci >= 0 && ci < n && J > 0 && J < 2 * n) {
+          const int64_t r = (int64_t)J * L + 2 * ci;
+          ya[k] = ld_pair(y1, r);
+          yb[k] = ld_pair(y1, N + r);
+          ra[k] = ld_pair(r2, r);
+          rb[k] = ld_pair(r2, N + r);
+          if (ci == 0) ya[k].a = yb[k].a = ra[k].a = rb[k].a = 0.0;
+        }
+      }
+    }
+    __shared__ double red[kCellWaves];
+    double *alfa = a.f.alfa + (int64_t)blockIdx.y * a.f.ls;
+    double al = 0.0;
+    if (a.f.nparts > 0) {
+      const double *part = a.f.part + (int64_t)blockIdx.y * a.f.lp;
+      for (int k = threadIdx.x; k < a.f.nparts; k += NT) al += part[k];
+      al = wave_sum(al);
+      if (lane == 0) red[w] = al;
+      __syncthreads();
+      al = 0.0;
+#pragma unroll
+      for (int k = 0; k < kCellWaves; ++k) al += red[k];
+      if (blockIdx.x == 0 && threadIdx.x == 0) *alfa = al;
+    } else {
+      al = *alfa;
+    }
+    al *= -a.f.s[(int64_t)blockIdx.y * a.f.ls];
+    auto upd = [&](double y, double r) -> double { return al != 0.0 ? fma(al, r, y) : y; };
+    if (pres) {
+      const int64_t p0 = (int64_t)((int)blockIdx.x - band * kXcd) * kPrePres + threadIdx.x;
+#pragma unroll
+      for (int k = 0; k < kPrePres / NT; ++k) {
+        const int64_t e = p0 + NT * k;
+        if (e < a.np) q[2 * N + e] = upd(y1[2 * N + e], r2[2 * N + e]);
+      }
+      return;
+    }
+    // q through LDS: a thread's own cell is read there, not once more from device memory
+    V2<double> qa[IT], qb[IT], by[4];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int e = threadIdx.x + NT * k;
+      qa[k] = V2<double>{upd(ya[k].a, ra[k].a), upd(yb[k].a, rb[k].a)};
+      qb[k] = V2<double>{upd(ya[k].b, ra[k].b), upd(yb[k].b, rb[k].b)};
+      if (e < NE) {
+        XS[e] = qa[k];
+        XS[kCellPL + e] = qb[k];
+      }
+    }
+    __syncthreads();
+    {
+      const V2<TS> *p = XS + (2 * w + 2) * kCellHW + lane + 1;
+      by[0] = p[0];
+      by[1] = p[kCellPL];
+      by[2] = p[kCellHW];
+      by[3] = p[kCellPL + kCellHW];
+    }
+    if (i == 0 || j == 0 || i >= n || j >= n) {   // Dirichlet nodes, staged as 0 (none outside the lattice)
+      V2<double> y4[4], r4[4];
+      load_cell(y1, N, L, n, i, j, y4);
+      load_cell(r2, N, L, n, i, j, r4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) by[k] = V2<double>{upd(y4[k].x, r4[k].x), upd(y4[k].y, r4[k].y)};
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) b[k] = V2<T>{(T)by[k].x, (T)by[k].y};
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int e = threadIdx.x + NT * k, lr = e / kCellHW;
+      if (e < NE) {
+        X[e] = first(lr & 1, 0, V2<T>{(T)qa[k].x, (T)qa[k].y});
+        X[kCellPL + e] = first(lr & 1, 1, V2<T>{(T)qb[k].x, (T)qb[k].y});
+      }
+    }
+    if (w >= 1 && w <= kPreR && j <= n && lane >= 1 && lane <= kPreW && i <= n) {
+      store_cell<double, double>(q, N, L, n, i, j, by);
+      if constexpr (!std::is_same<T, double>::value) store_cell<T, T>(bg, N, L, n, i, j, b);
+    }
+  } else {
+    load_cell((const T *)bg, N, L, n, i, j, b);
+    stage_pairs<T, kCellH>(X, (const T *)bg, N, L, n, i0, j0, first);
+  }
   const CellIn in = cell_inside(i, j, n);
   const int row = 2 * w + 2, h = lane + 1;
   const V2<T> *p = X + row * kCellHW + h;
@@ -223,7 +330,7 @@ struct PostArgs {
   const T *x, *b;
   TY *y;
   T c2a, c1b, c2b, c1c, c2c;
-  int64_t lv;          // lane stride of x, b, y (lane = blockIdx.y)
+  int64_t lx, lb, ly;  // lane strides of x, b, y (lane = blockIdx.y)
   const T *xc;         // coarse correction (lattice n / 2, two components)
   int64_t lc;          // its lane stride
   double *dot;         // per-tile sums of b . y (FP64), or null
@@ -237,9 +344,9 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY> 
   __shared__ V2<T> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
-  const T *xg = a.x + (int64_t)blockIdx.y * a.lv, *bg = a.b + (int64_t)blockIdx.y * a.lv;
+  const T *xg = a.x + (int64_t)blockIdx.y * a.lx, *bg = a.b + (int64_t)blockIdx.y * a.lb;
   const T *xcg = a.xc + (int64_t)blockIdx.y * a.lc;
-  TY *yg = a.y + (int64_t)blockIdx.y * a.lv;
+  TY *yg = a.y + (int64_t)blockIdx.y * a.ly;
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
   const int i0 = (t % tiles_x) * kPostW - 2, j0 = (t / tiles_x) * kPostR - 2;   // first cell of the region
@@ -417,20 +524,32 @@ static void cell_launch_checks(int n, int K) {
 }
 
 template <typename T>
-void pre3(int n, const AfCoef<T> &cf, LP<const T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K) {
+void pre3(int n, const AfCoef<T> &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
+          const MsFold *fold) {
   cell_launch_checks(n, K);
   int tx;
   const int tiles = cell_tiles(n, kPreW, kPreR, tx), band = (tiles + kXcd - 1) / kXcd;
-  const int64_t lv = common_stride({{b.p, b.s}, {x.p, x.s}}, K);
-  PreArgs<T> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, lv};
-  hipLaunchKernelGGL(k_pre3<T>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, st, a, tx,
-                     tiles, band);
+  FSI_REQUIRE(K == 1 || (x.s > 0 && (b.s > 0 || !b.p)), FSI_E_ARG, "lane views need a stride");
+  PreArgs<T> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
+  const dim3 block(kWave * kCellWaves);
+  if (fold) {
+    a.f = *fold;
+    a.np = (int64_t)(n + 1) * (n + 1);
+    a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
+    FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
+    const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
+    hipLaunchKernelGGL((k_pre3<T, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx, tiles,
+                       band);
+  } else {
+    hipLaunchKernelGGL((k_pre3<T, false>), dim3((unsigned)(band * kXcd), (unsigned)K), block, 0, st, a, tx, tiles,
+                       band);
+  }
   FSI_CHECK_LAUNCH();
 }
-template void pre3<double>(int, const AfCoef<double> &, LP<const double>, LP<double>, double, double, double, double,
-                           double, hipStream_t, int);
-template void pre3<float>(int, const AfCoef<float> &, LP<const float>, LP<float>, float, float, float, float, float,
-                          hipStream_t, int);
+template void pre3<double>(int, const AfCoef<double> &, LP<double>, LP<double>, double, double, double, double, double,
+                           hipStream_t, int, const MsFold *);
+template void pre3<float>(int, const AfCoef<float> &, LP<float>, LP<float>, float, float, float, float, float,
+                          hipStream_t, int, const MsFold *);
 
 template <typename T, typename TY>
 void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
@@ -440,11 +559,11 @@ void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T
   FSI_REQUIRE(K == 1 || xc.s > 0, FSI_E_ARG, "lane views of the coarse correction need a stride");
   int tx;
   const int tiles = cell_tiles(n, kPostW, kPostR, tx), band = (tiles + kXcd - 1) / kXcd;
-  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}, {y.p, y.s}}, K);
+  FSI_REQUIRE(K == 1 || (x.s > 0 && b.s > 0 && y.s > 0), FSI_E_ARG, "lane views need a stride");
   FSI_REQUIRE(!dot.p || K == 1 || dot.s >= tiles, FSI_E_ARG, "lane stride of the tile sums too small");
   FSI_REQUIRE(!b64.p || (dot.p && (K == 1 || b64.s > 0) && !std::is_same<T, double>::value), FSI_E_ARG,
               "an FP64 right-hand side only for the sums of the FP32 form");
-  PostArgs<T, TY> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, lv, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
+  PostArgs<T, TY> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, x.s, b.s, y.s, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
   const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(kWave * kCellWaves);
   if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, true>), grid, block, 0, st, a, tx, tiles, band);
   else hipLaunchKernelGGL((k_post3<T, TY, false>), grid, block, 0, st, a, tx, tiles, band);
@@ -475,7 +594,7 @@ struct ResidRestrArgs {
   AfCoef<T> cf;
   const T *x, *b;
   T *bc;
-  int64_t lv, lc;   // lane strides of the fine (x, b) and coarse (bc) vectors
+  int64_t lx, lb, lc;   // lane strides of x, b and bc
 };
 
 template <typename T, int Q>
@@ -488,7 +607,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
   __shared__ V2<T> X[2 * PL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
-  const T *xg = a.x + (int64_t)blockIdx.y * a.lv, *bg = a.b + (int64_t)blockIdx.y * a.lv;
+  const T *xg = a.x + (int64_t)blockIdx.y * a.lx, *bg = a.b + (int64_t)blockIdx.y * a.lb;
   T *bcg = a.bc + (int64_t)blockIdx.y * a.lc;
   const int n = a.n, L = 2 * n + 1, Lc = n + 1;
   const int64_t N = (int64_t)L * L, Nc = (int64_t)Lc * Lc;
@@ -579,9 +698,8 @@ template <typename T>
 void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K) {
   cell_launch_checks(nf, K);
   FSI_REQUIRE(nf % 2 == 0 && nf >= 4, FSI_E_ARG, "restriction needs an even fluid grid");
-  FSI_REQUIRE(K == 1 || bc.s > 0, FSI_E_ARG, "lane views of the coarse vector need a stride");
-  const int64_t lv = common_stride({{x.p, x.s}, {b.p, b.s}}, K);
-  ResidRestrArgs<T> a{nf, cf, x.p, b.p, bc.p, lv, bc.s};
+  FSI_REQUIRE(K == 1 || (x.s > 0 && b.s > 0 && bc.s > 0), FSI_E_ARG, "lane views need a stride");
+  ResidRestrArgs<T> a{nf, cf, x.p, b.p, bc.p, x.s, b.s, bc.s};
   auto go = [&](auto q_tag) {
     constexpr int Q = decltype(q_tag)::value;
     int tx;
