@@ -456,9 +456,10 @@ int fsi_set_graphs(fsi_ctx *ctx, int enable);
 
 /* When the inner MINRES solve learns that it has converged (without graphs).
  *  FSI_CHECK_AUTO (default): FSI_CHECK_LAGGED on grids of n <= 256, FSI_CHECK_EVERY_STEP above.
- *  FSI_CHECK_EVERY_STEP: the state of each step is copied back and the host waits for it
- *    before it enqueues the next step (the device idles for that round trip).
- *  FSI_CHECK_LAGGED: the state of step k - 1 is read after step k has been enqueued, so the
+ *  FSI_CHECK_EVERY_STEP: the host waits for the state of each step before it enqueues more of the
+ *    next one than its operator product (which covers the round trip on large grids; the device
+ *    idles for it on small ones).
+ *  FSI_CHECK_LAGGED: the state of step k - 1 is looked at after step k has been enqueued, so the
  *    device does not wait for the host; the step enqueued past convergence is frozen by the
  *    device-side done flag (the same results, bitwise; one extra step of work per solve).
  *    Faster for one solve on an idle device (32^2-256^2: 4-15% per step), slower where other

@@ -23,8 +23,7 @@ Ctx::~Ctx() {
   if (aux_stream) (void)hipStreamDestroy(aux_stream);
   if (ev_fork) (void)hipEventDestroy(ev_fork);
   if (ev_join) (void)hipEventDestroy(ev_join);
-  for (hipEvent_t e : ev_ms)
-    if (e) (void)hipEventDestroy(e);
+  if (ms_word) (void)hipHostFree(ms_word);
   if (hpin) (void)hipHostFree(hpin);
   if (bat_h) (void)hipHostFree(bat_h);
   if (gi_h) (void)hipHostFree(gi_h);
@@ -175,7 +174,9 @@ static int create_ctx(const fsi_fluid_desc *fluid, const fsi_solid_desc *solid, 
     FSI_HIP(hipStreamCreateWithFlags(&c.aux_stream, hipStreamNonBlocking));
     FSI_HIP(hipEventCreateWithFlags(&c.ev_fork, hipEventDisableTiming));
     FSI_HIP(hipEventCreateWithFlags(&c.ev_join, hipEventDisableTiming));
-    for (hipEvent_t &e : c.ev_ms) FSI_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    FSI_HIP(hipHostMalloc((void **)&c.ms_word, FSI_MAX_LANES * sizeof(*c.ms_word), hipHostMallocDefault));
+    std::fill(c.ms_word, c.ms_word + FSI_MAX_LANES, 0ull);
+    FSI_HIP(hipHostGetDevicePointer((void **)&c.ms_word_dev, c.ms_word, 0));
     fsi::build_solid(c);
     if (quads) {   // the assembled operators only: the matrix-free kernels are the triangle pair's
       fsi::build_fluid_q2(c);

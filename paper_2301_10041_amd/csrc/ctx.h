@@ -216,7 +216,9 @@ struct Ctx {
   // (default priority; created with the context)
   hipStream_t aux_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  hipEvent_t ev_ms[2] = {nullptr, nullptr};   // the inner MINRES state copies of two steps
+  // what the inner MINRES launches tell the host (ms_tell): a word per lane in pinned memory, its device
+  // address, and the next state number
+  unsigned long long *ms_word = nullptr, *ms_word_dev = nullptr, ms_seq = 1;
   int ms_check = FSI_CHECK_AUTO;              // fsi_set_inner_check
   bool capturing = false;     // inside a graph capture: the preconditioner stays on one stream
   // inner MINRES: device-side scalar state, its own reduction buffer and solution vector

@@ -27,6 +27,7 @@
 #include "ctx.h"
 #include "kernels.h"
 #include "lattice.h"
+#include "minres.h"
 #include "q2.h"
 #include "stencil.h"
 
@@ -799,20 +800,10 @@ void Ctx::drop_graphs() {
 // w_{k0}) and one pass forms x, w_{k-1} and w_k as those combinations (ms_B + 3 reads and 3
 // writes per block).  Once converged, a lane records no more updates, so its x does not
 // depend on how often the host checks, nor on the other lanes of a batch.
-struct MinresState {
-  double alfa, beta2;                         // dot products of the iteration
-  double beta, oldb, dbar, epsln, phibar, cs, sn, beta1, tol;
-  double s, c_r1;                             // 1 / beta, -beta / oldb
-  double e, d, ginv, phi;                     // direction update
-  double it, done, apply;                     // iterations; converged; update valid
-  double slot;                                // slot of this iteration's Lanczos vector
-};
-constexpr int kMsRec = 5;                     // recorded per iteration: e, d, 1/gamma, phi, applied
 constexpr int kMsBMax = 32;                   // Lanczos vectors per block at most
 static_assert(kMsBMax + 2 <= kWave, "one wave computes the coefficients of a block");
-constexpr int kMsDoubles = sizeof(MinresState) / sizeof(double);
-constexpr int kMsLagMaxN = 256;   // grids whose inner steps read the state back one step late
-constexpr int kHpinHalf = 2048;   // doubles: the two halves of the pinned host buffer
+constexpr int kMsLagMaxN = 256;   // grids whose inner steps look at the state one step late
+constexpr int kHpinDoubles = 4096;   // the pinned host buffer
 
 // The kernels below run K systems (lane = blockIdx.y): lane k uses st + k and vectors at
 // + k n (n = nf, the lane stride of every inner vector).
@@ -833,54 +824,10 @@ __global__ void k_ms_init(MinresState *st, double tol) {
   st->slot = 0.0;
 }
 
-// After the two dot products of an iteration: Givens rotation and the next coefficients,
-// recorded in slot st->slot of the lane's history (B slots of kMsRec; the host starts a new
-// block before the slots run out, and a slot out of range records nothing).
-__device__ void ms_step(MinresState *st, double *hist, int B) {
-  const int sl = (int)st->slot;
-  double *h = (sl >= 0 && sl < B) ? hist + kMsRec * sl : nullptr;
-  st->slot += 1.0;
-  if (st->done != 0.0) {
-    st->apply = 0.0;
-    if (h) h[4] = 0.0;
-    return;
-  }
-  const double alfa = st->alfa, nb2 = st->beta2;
-  const double oldb = st->beta;
-  const double beta = sqrt(nb2 > 0.0 ? nb2 : 0.0);
-  const double oldeps = st->epsln;
-  const double delta = st->cs * st->dbar + st->sn * alfa;
-  const double gbar = st->sn * st->dbar - st->cs * alfa;
-  st->epsln = st->sn * beta;
-  st->dbar = -st->cs * beta;
-  double gamma = sqrt(gbar * gbar + beta * beta);
-  if (gamma < 1e-300) gamma = 1e-300;
-  st->cs = gbar / gamma;
-  st->sn = beta / gamma;
-  st->phi = st->cs * st->phibar;
-  st->phibar = st->sn * st->phibar;
-  st->e = oldeps;
-  st->d = delta;
-  st->ginv = 1.0 / gamma;
-  st->apply = 1.0;
-  if (h) {
-    h[0] = st->e;
-    h[1] = st->d;
-    h[2] = st->ginv;
-    h[3] = st->phi;
-    h[4] = 1.0;
-  }
-  st->it += 1.0;
-  st->oldb = oldb;
-  st->beta = beta;
-  st->s = beta > 0.0 ? 1.0 / beta : 0.0;
-  st->c_r1 = beta > 0.0 ? -beta / oldb : 0.0;
-  if (!(st->phibar > st->tol * st->beta1) || beta == 0.0 || !(alfa == alfa)) st->done = 1.0;
-}
-
-__global__ void k_ms_step(MinresState *st, double *hist, int B) {
+__global__ void k_ms_step(MinresState *st, double *hist, int B, unsigned long long *word, unsigned long long seq) {
   if (threadIdx.x || blockIdx.x) return;
   ms_step(st + blockIdx.y, hist + (int64_t)blockIdx.y * kMsRec * B, B);
+  ms_tell(word ? word + blockIdx.y : nullptr, seq, st[blockIdx.y]);
 }
 
 // v = s y, also stored in slot st->slot of the Lanczos block vh (slot stride vs; the slot is
@@ -1007,23 +954,19 @@ __global__ void __launch_bounds__(1024) k_ms_alfa(const double *part, int n, Min
   }
 }
 
-// beta^2 = the velocity tile sums, then the pressure block sums (one 1024-thread block per
-// lane, fixed order; lane k's sums at part + k lp, its state at st + k), then the step
-// (ms_step) of that lane
-__global__ void __launch_bounds__(1024) k_ms_beta_step(const double *part, int nu, int np, int64_t lp,
-                                                       MinresState *st, double *hist, int B) {
+// beta^2 of lane k from its parts at part + k lp (one 1024-thread block per lane), then the step
+// (ms_step) of that lane from the state st to the state out (which may be the same)
+__global__ void __launch_bounds__(1024) k_ms_beta_step(const double *part, int n, int64_t lp, const MinresState *st,
+                                                       MinresState *out, double *hist, int B,
+                                                       unsigned long long *word, unsigned long long seq) {
   __shared__ double red[1024 / kWave];
-  part += (int64_t)blockIdx.y * lp;
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nu + np; i += 1024) acc += part[i];
-  acc = wave_sum(acc);
-  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = acc;
-  __syncthreads();
+  const double b = ms_beta2<1024>(part + (int64_t)blockIdx.y * lp, n, red);
   if (threadIdx.x == 0) {
-    double b = 0.0;
-    for (int k = 0; k < 1024 / kWave; ++k) b += red[k];
-    st[blockIdx.y].beta2 = b;
-    ms_step(st + blockIdx.y, hist + (int64_t)blockIdx.y * kMsRec * B, B);
+    MinresState q = st[blockIdx.y];
+    q.beta2 = b;
+    ms_step(&q, hist + (int64_t)blockIdx.y * kMsRec * B, B);
+    out[blockIdx.y] = q;
+    ms_tell(word ? word + blockIdx.y : nullptr, seq, q);
   }
 }
 
@@ -1072,29 +1015,55 @@ static bool tile_dot_ok(const Ctx &c, bool fp32) {
   return c.mgu.stencil && c.mgu.lv.size() > 1 && (fp32 ? c.mgu.degree32 : c.mgu.degree) == 3 && c.ms_dot.p;
 }
 
-// One inner iteration with the matrix-free A11 (FP64) for K systems: the scaling v = s y,
-// the product, the first three-term update and the parts of alfa = v . y are one launch (new y over
-// r1).  Then q = y - alfa s r2, z = M q, beta^2 = q . z: with tile_dot_ok the update is the first
+// A11 launches take the step of the recurrence at their head where beta^2 has at most this many parts
+// (512^2: 1,161 tiles and 190 sums): every block sums them behind its loads, a launch of 3-4 us and a
+// gap less per inner step.  At 1024^2 (5,035) the blocks would read 88 MB of them; there the sum and
+// the step stay a launch of their own.
+constexpr int kMsFoldBeta = 2048;
+
+// One inner iteration with the matrix-free A11 (FP64) for K systems, as a head and a tail.
+// Head: the scaling v = s y, the product, the first three-term update and the parts of alfa = v . y in one
+// launch (new y over r1); where the step of the iteration before is still to come (fold, its parts of
+// beta^2 in ms_dot), the launch takes it first, from the state `prev` to the state `st`.
+// Tail: q = y - alfa s r2, z = M q, beta^2 = q . z: with tile_dot_ok the update is the first
 // smoothing launch's (q over the old z, z over y: the rotation of ms_bufs) and the sums are the last
-// ones'; else they are launches of their own (q in place, z in the y buffer: ms_bufs_fused).
+// ones'; else they are launches of their own (q in place, z in the y buffer: ms_bufs_fused).  Without
+// fold the step ends the tail, in place.  seq: the number of the state that a step makes (word: where the
+// host looks for it, or null).
+struct MsTell {
+  unsigned long long *word;
+  unsigned long long seq;
+};
+static void ms_head(Ctx &c, const MsBufs &b, const MinresState *prev, MinresState *st, int K, MsTell tell) {
+  const int64_t nf = 2 * c.N2 + c.Np;
+  const int nb = post3_dot_count(c.n) + pres_dot_count(c);
+  MsA11 m;
+  m.st = prev ? prev : st;
+  m.out = prev ? st : nullptr;
+  m.bpart = LP<const double>(c.ms_dot.p, nb);
+  m.nb = prev ? nb : 0;
+  m.hist = c.ms_hist.p;
+  m.vh = c.ms_vh.p;
+  m.vs = (int64_t)c.lanes * nf;
+  m.B = c.ms_B;
+  m.part = LP<double>(c.ms_part.p, a11_tile_count(c.n));
+  m.word = tell.word;
+  m.seq = tell.seq;
+  a11_minres(c.n, c.mgu.lv[0].af64, LP<const double>(b.y, nf), LP<double>(b.r1, nf), m, c.stream, K);
+}
+
 template <typename TA>
-static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) {
+static void ms_tail(Ctx &c, const MsBufs &b, MinresState *st, int K, bool fold, MsTell tell) {
   hipStream_t s = c.stream;
   const int64_t nf = 2 * c.N2 + c.Np;
   const unsigned g = vgrid(nf);
-  double *dv = (double *)st;
   const int tiles = a11_tile_count(c.n);
-  a11_minres(c.n, c.mgu.lv[0].af64, LP<const double>(b.y, nf), LP<double>(c.ms_vh.p, nf), LP<double>(b.r1, nf),
-             LP<const double>(&st->s, kMsDoubles), LP<const double>(&st->c_r1, kMsDoubles),
-             LP<const double>(&st->slot, kMsDoubles), (int64_t)c.lanes * nf, c.ms_B, LP<double>(c.ms_part.p, tiles), s,
-             K);
   const bool fold_sum = tiles <= kMsFoldParts;
   constexpr bool f32 = std::is_same<TA, float>::value;
   const bool dot_ok = tile_dot_ok(c, f32);
   if (!dot_ok || !fold_sum) hipLaunchKernelGGL(k_ms_alfa, dim3(1, K), dim3(1024), 0, s, c.ms_part.p, tiles, st);
   if (dot_ok) {
-    const int nu = post3_dot_count(c.n), np = pres_dot_count(c);
-    const int64_t ld = nu + np;
+    const int nb = post3_dot_count(c.n) + pres_dot_count(c);
     MsFold f;
     f.y1 = LP<const double>(b.r1, nf);
     f.r2 = LP<const double>(b.r2, nf);
@@ -1106,22 +1075,23 @@ static void ms_iteration_fused(Ctx &c, const MsBufs &b, MinresState *st, int K) 
     f.s = &st->s;
     f.ls = kMsDoubles;
     const LP<const TA> ru = f32 ? LP<const TA>((const TA *)c.outer.x32.p, 2 * c.N2) : LP<const TA>((const TA *)b.y, nf);
-    a11_precond<TA>(c, ru, b.y, b.r1, K, LP<double>(c.ms_dot.p, ld), PC_BOTH, &f);
-    hipLaunchKernelGGL(k_ms_beta_step, dim3(1, K), dim3(1024), 0, s, c.ms_dot.p, nu, np, ld, st,
-                       c.ms_hist.p, c.ms_B);
+    a11_precond<TA>(c, ru, b.y, b.r1, K, LP<double>(c.ms_dot.p, nb), PC_BOTH, &f);
+    if (!fold)
+      hipLaunchKernelGGL(k_ms_beta_step, dim3(1, K), dim3(1024), 0, s, c.ms_dot.p, nb, (int64_t)nb, st, st,
+                         c.ms_hist.p, c.ms_B, tell.word, tell.seq);
   } else {
     hipLaunchKernelGGL(k_ms_axpy, dim3(g, K), dim3(256), 0, s, b.r1, b.r2, st, 1, nf);
     a11_precond_on64<TA>(c, b.r1, b.y, K);
-    dot_l(LP<const double>(b.r1, nf), LP<const double>(b.y, nf), nf, LP<double>(dv + 1, kMsDoubles), c.ms_red.p, s,
+    dot_l(LP<const double>(b.r1, nf), LP<const double>(b.y, nf), nf, LP<double>(&st->beta2, kMsDoubles), c.ms_red.p, s,
           K);
-    hipLaunchKernelGGL(k_ms_step, dim3(1, K), dim3(1), 0, s, st, c.ms_hist.p, c.ms_B);
+    hipLaunchKernelGGL(k_ms_step, dim3(1, K), dim3(1), 0, s, st, c.ms_hist.p, c.ms_B, tell.word, tell.seq);
   }
   FSI_CHECK_LAUNCH();
 }
 
-// The same with the assembled A11 (one system)
+// An iteration with the assembled A11 (one system)
 template <typename TA>
-static void ms_iteration(Ctx &c, const MsBufs &b, MinresState *st) {
+static void ms_iteration(Ctx &c, const MsBufs &b, MinresState *st, MsTell tell) {
   hipStream_t s = c.stream;
   const int64_t nf = 2 * c.N2 + c.Np;
   const unsigned g = vgrid(nf);
@@ -1135,7 +1105,7 @@ static void ms_iteration(Ctx &c, const MsBufs &b, MinresState *st) {
   // new Lanczos vector is b.y: precondition it into the buffer of r1 (no longer needed)
   a11_precond_on64<TA>(c, b.y, b.r1);
   multidot(b.y, 0, 1, b.r1, nf, dv + 1, c.ms_red, s);
-  hipLaunchKernelGGL(k_ms_step, dim3(1), dim3(1), 0, s, st, c.ms_hist.p, c.ms_B);
+  hipLaunchKernelGGL(k_ms_step, dim3(1), dim3(1), 0, s, st, c.ms_hist.p, c.ms_B, tell.word, tell.seq);
   FSI_CHECK_LAUNCH();
 }
 
@@ -1164,80 +1134,139 @@ static void minres_a11(Ctx &c, const double *const *b, double *const *xout, int 
   hipLaunchKernelGGL(k_ms_init, dim3(1, K), dim3(1), 0, s, st, tol);
   FSI_CHECK_LAUNCH();
   const bool graphs = c.use_graphs && !(c.prof64.on || c.prof32.on);
-  // with graphs the state is read back every second step (a replay costs far more than the
+  // The step inside the next head (two states in turn); not in a graph, whose launches are fixed.
+  const bool fold = fused && !in_place && !graphs && post3_dot_count(c.n) + pres_dot_count(c) <= kMsFoldBeta;
+  // With graphs the state is read back every second step (a replay costs far more than the
   // read-back; checking every 8 steps measured 5-12% slower at 64^2 and 128^2 from the
-  // frozen steps run past convergence)
-  const int check_every = graphs ? 2 : 1;
-  // Lagged check (eager launches; by default on grids of n <= kMsLagMaxN): the state of step
-  // it - 1 is read back after step it has been enqueued (a copy and an event per step, two
-  // host buffers), so the device does not wait for the host between steps; the step enqueued
-  // past convergence is frozen by the done flag, which costs one step per solve.  On larger
-  // grids a step takes long enough that the wait is the smaller cost.
+  // frozen steps run past convergence).  Eager launches leave a word per system in pinned memory,
+  // which the host polls: a read-back by copy and event per step cost the device 4-5 us at 32^2.
+  // Lagged check (by default on grids of n <= kMsLagMaxN): the state that step k starts from is
+  // looked at after the whole of step k has been enqueued, so the device does not wait for the host
+  // between steps; the step enqueued past convergence is frozen by the done flag, which costs
+  // one step per solve.  Otherwise it is looked at behind the head of step k: while the host
+  // answers, the device runs the A11 launch (59 us at 1024^2 against 25-30 us of idling behind a
+  // full stop), and only that launch is wasted past convergence.  Below 256^2 the head alone is too
+  // short to cover the host.
   const bool lag = !graphs && (c.ms_check == FSI_CHECK_LAGGED ||
                                (c.ms_check == FSI_CHECK_AUTO && c.n <= kMsLagMaxN));
   const int pk = std::is_same<TA, double>::value ? 0 : 1;
   int it = 0, k0 = 0;   // iterations done; iterations before the current block
   const int B = c.ms_B;
+  MinresState *cur = st;   // the newest state that a launch has been enqueued for
+  struct Drain {   // no launch that tells the host outlives this call, also when it throws
+    hipStream_t s;
+    bool armed = true;
+    ~Drain() {
+      if (armed) (void)hipStreamSynchronize(s);
+    }
+  } drain{s};
   // x (and, unless last, the carried directions) from the block of iterations k0 .. it - 1
   auto flush = [&](bool last) {
     const int m = it - k0;
     if (m == 0) return;
-    hipLaunchKernelGGL(k_ms_coef, dim3(K), dim3(kWave), 0, s, c.ms_hist.p, B, m, c.ms_coef.p, st);
+    hipLaunchKernelGGL(k_ms_coef, dim3(K), dim3(kWave), 0, s, c.ms_hist.p, B, m, c.ms_coef.p, cur);
     hipLaunchKernelGGL(k_ms_combine, dim3((unsigned)((nf + 255) / 256), K), dim3(256), 0, s, x, b0.W2, b0.W1,
                        c.ms_vh.p, (int64_t)c.lanes * nf, c.ms_coef.p, B, m, nf, k0 == 0 ? 1 : 0, last ? 1 : 0);
     FSI_CHECK_LAUNCH();
     k0 = it;
   };
   double *h = c.hpin;
-  static_assert(FSI_MAX_LANES * kMsDoubles <= kHpinHalf, "two state copies in the pinned buffer");
-  auto states_done = [&](const double *hb) {
+  static_assert(FSI_MAX_LANES * kMsDoubles <= kHpinDoubles, "the states fit the pinned buffer");
+  auto finite = [](bool ok) { FSI_REQUIRE(ok, FSI_E_NONFINITE, "non-finite value in the inner A11 solve"); };
+  auto all_done = [&]() {
+    FSI_HIP(hipMemcpyAsync(h, cur, (size_t)K * kMsDoubles * sizeof(double), hipMemcpyDeviceToHost, s));
+    FSI_HIP(hipStreamSynchronize(s));
     bool done = true;
     for (int k = 0; k < K; ++k) {
-      const MinresState *hs = (const MinresState *)hb + k;
-      FSI_REQUIRE(hs->phibar == hs->phibar && hs->beta == hs->beta, FSI_E_NONFINITE,
-                  "non-finite value in the inner A11 solve");
+      const MinresState *hs = (const MinresState *)h + k;
+      finite(hs->phibar == hs->phibar && hs->beta == hs->beta);
       done = done && hs->done != 0.0;
     }
     return done;
   };
-  auto all_done = [&]() {
-    FSI_HIP(hipMemcpyAsync(h, st, (size_t)K * kMsDoubles * sizeof(double), hipMemcpyDeviceToHost, s));
-    FSI_HIP(hipStreamSynchronize(s));
-    return states_done(h);
-  };
-  while (it < maxit) {
-    // the rotation: in phase p the roles are shifted by p (r2 of phase p is y of p-1, ...)
-    const int phase = in_place ? it % 2 : it % 3;
-    const MsBufs bq = in_place ? ms_bufs_fused(c, x, it) : ms_bufs(c, x, phase);
-    if (graphs) {
+  if (graphs) {
+    const int check_every = 2;
+    while (it < maxit) {
+      // the rotation: in phase p the roles are shifted by p (r2 of phase p is y of p-1, ...)
+      const int phase = in_place ? it % 2 : it % 3;
+      const MsBufs bq = in_place ? ms_bufs_fused(c, x, it) : ms_bufs(c, x, phase);
       hipGraphExec_t &ge = c.ms_graph[pk][K][phase];
       if (!ge)
         capture_graph(c, ge, [&] {
-          if (fused) ms_iteration_fused<TA>(c, bq, st, K);
-          else ms_iteration<TA>(c, bq, st);
+          const MsTell none{nullptr, 0};
+          if (fused) {
+            ms_head(c, bq, nullptr, st, K, none);
+            ms_tail<TA>(c, bq, st, K, false, none);
+          } else {
+            ms_iteration<TA>(c, bq, st, none);
+          }
         });
       FSI_HIP(hipGraphLaunch(ge, s));
-    } else if (fused) {
-      ms_iteration_fused<TA>(c, bq, st, K);
-    } else {
-      ms_iteration<TA>(c, bq, st);
+      ++it;
+      if (it - k0 == B) flush(false);
+      if ((it % check_every == 0 || it == maxit) && all_done()) break;
     }
-    ++it;
-    if (it - k0 == B) flush(false);
-    if (lag) {
-      double *hb = h + (it & 1) * kHpinHalf;
-      FSI_HIP(hipMemcpyAsync(hb, st, (size_t)K * kMsDoubles * sizeof(double), hipMemcpyDeviceToHost, s));
-      FSI_HIP(hipEventRecord(c.ev_ms[it & 1], s));
-      if (it >= 2) {   // step it - 1, while step it runs
-        FSI_HIP(hipEventSynchronize(c.ev_ms[(it - 1) & 1]));
-        if (states_done(h + ((it - 1) & 1) * kHpinHalf)) break;
+  } else {
+    // State number j (after j steps) is told as base + j; with fold it lies at st (j even) or behind it.
+    const unsigned long long base = c.ms_seq;
+    c.ms_seq += (unsigned long long)maxit + 2;
+    auto tell = [&](int j) { return MsTell{c.ms_word_dev, base + (unsigned long long)j}; };
+    auto state = [&](int j) { return fold && (j & 1) ? st + K : st; };
+    int have = 0;   // the newest state enqueued
+    auto step_alone = [&] {   // with fold: the step of iteration it - 1, not yet taken by a head
+      const int nb = post3_dot_count(c.n) + pres_dot_count(c);
+      const MsTell t = tell(it);
+      hipLaunchKernelGGL(k_ms_beta_step, dim3(1, K), dim3(1024), 0, s, c.ms_dot.p, nb, (int64_t)nb, state(it - 1),
+                         state(it), c.ms_hist.p, B, t.word, t.seq);
+      FSI_CHECK_LAUNCH();
+      have = it;
+      cur = state(it);
+    };
+    auto converged = [&](int j) {   // waits for state j of every system
+      bool done = true;
+      for (int k = 0; k < K; ++k) {
+        const unsigned long long *w = c.ms_word + k;
+        unsigned long long v;
+        for (unsigned spin = 1; (v = __atomic_load_n(w, __ATOMIC_RELAXED)) >> 2 < base + (unsigned long long)j; ++spin) {
+          __builtin_ia32_pause();
+          if (spin % 4096) continue;
+          const hipError_t e = hipStreamQuery(s);   // the wait ends with the stream at the latest
+          if (e == hipErrorNotReady) continue;
+          FSI_HIP(e);
+          v = __atomic_load_n(w, __ATOMIC_RELAXED);
+          FSI_REQUIRE(v >> 2 >= base + (unsigned long long)j, FSI_E_HIP, "the inner solve's state was not told");
+        }
+        finite(!(v & 2));
+        done = done && (v & 1);
       }
-    } else if ((it % check_every == 0 || it == maxit) && all_done()) {
-      break;
+      return done;
+    };
+    while (it < maxit) {
+      const MsBufs bq = in_place ? ms_bufs_fused(c, x, it) : ms_bufs(c, x, it % 3);
+      if (fused) {
+        const bool step = fold && it > have;
+        ms_head(c, bq, step ? state(it - 1) : nullptr, state(it), K, tell(it));
+        FSI_CHECK_LAUNCH();
+        have = it;
+        cur = state(it);
+      }
+      if (!lag && it > 0 && converged(it)) break;
+      if (fused) ms_tail<TA>(c, bq, state(it), K, fold, tell(it + 1));
+      else ms_iteration<TA>(c, bq, st, tell(it + 1));
+      const bool stop = lag && it > 0 && converged(it);
+      ++it;
+      if (!fold) have = it;
+      if (it - k0 == B) {
+        if (it > have) step_alone();
+        flush(false);
+      }
+      if (stop) break;
     }
+    if (it > have) step_alone();
   }
   flush(true);
   all_done();
+  drain.armed = false;
   for (int k = 0; k < K; ++k) {
     const MinresState *hs = (const MinresState *)h + k;
     its[k] = (int)hs->it;
@@ -1709,7 +1738,7 @@ static void ensure_inner(Ctx &c, int prec, int K = 1) {
   }
   if (!c.ms_x.p) {
     c.ms_x.alloc(nl * nf);
-    c.ms_state.alloc(nl * kMsDoubles);
+    c.ms_state.alloc(2 * nl * kMsDoubles);   // two states per system in turn
     c.ms_red.alloc(nl * red_blocks(nf));   // dot products of one system per lane: never regrown
     c.ms_part.alloc(nl * a11_tile_count(c.n));
     c.ms_dot.alloc(nl * (post3_dot_count(c.n) + pres_dot_count(c)));

@@ -128,13 +128,26 @@ void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T
            LP<const double> b64 = LP<const double>());
 int post3_dot_count(int n);
 
-// The A11 rows inside the inner MINRES: v = s x, y = s (A11 x) + c r1 written over
-// r1, and one partial sum of v . y per tile in part[] (s, c read from device memory;
-// r1 used only when c != 0).  v goes to slot *slot_dev (a device scalar, clamped to
-// [0, nslot - 1]) of the Lanczos block: v.p + slot vs + lane v.s.  a11_tile_count(n) parts per lane.
-void a11_minres(int n, const AfCoef<double> &cf, LP<const double> x, LP<double> v, LP<double> r1y,
-                LP<const double> s_dev, LP<const double> c_dev, LP<const double> slot_dev, int64_t vs, int nslot,
-                LP<double> part, hipStream_t s, int K = 1);
+// The A11 rows inside the inner MINRES, per lane: v = s y, then s (A11 y) + c r1 written over r1, with s
+// and c of the lane's state, and one partial sum of their product per tile in part
+// (a11_tile_count(n); r1 used only when c != 0).  v goes to the state's slot (clamped to [0, B - 1]) of the
+// Lanczos block: vh + slot vs + lane r1.s.  nb > 0: the state is first taken one step further, from
+// st with the nb parts of beta^2 at bpart to out (other memory than st), recorded in hist and told.
+struct MinresState;
+struct MsA11 {
+  const MinresState *st = nullptr;
+  MinresState *out = nullptr;
+  LP<const double> bpart;
+  int nb = 0;
+  double *hist = nullptr;
+  double *vh = nullptr;
+  int64_t vs = 0;
+  int B = 0;
+  LP<double> part;
+  unsigned long long *word = nullptr, seq = 0;
+};
+void a11_minres(int n, const AfCoef<double> &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
+                int K = 1);
 int a11_tile_count(int n);
 
 // Host: the tables of A_f on an n x n grid from the element matrices (assemble.hip).

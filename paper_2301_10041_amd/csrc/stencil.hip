@@ -13,6 +13,7 @@
 #include "ctx.h"
 #include "kernels.h"
 #include "lattice.h"
+#include "minres.h"
 #include "stencil.h"
 
 namespace fsi {
@@ -733,20 +734,17 @@ struct A11Args {
   double g;             // h / 6, the unit of the entries of B
   const double *x;
   double *y;            // in MINRES: r1, overwritten
-  int64_t lv;           // lane stride of x, y and vh (lane = blockIdx.y)
+  int64_t lv;           // lane stride of x, y and v (lane = blockIdx.y)
   const int *cft_rp, *cft_col;   // C_f^T of one system (K = 1), or null
   const double *cft_val, *xlx, *xly;
-  const double *ms_s, *ms_c, *ms_slot;   // in MINRES: scalars s, c and the slot of v
-  int64_t ls;           // their lane stride
-  double *vh;           // the Lanczos block: slot stride vs, nslot slots
-  int64_t vs;
-  int nslot;
-  double *part;         // per-tile sums of v . y, lane stride lp
-  int64_t lp;
+  MsA11 m;              // in MINRES
 };
 
-template <bool MS>
+// the operator's rows; a step's head; the head with the step before it
+enum { A11_ROWS = 0, A11_MS = 1, A11_MS_STEP = 2 };
+template <int MODE>
 __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int tiles_x, int tiles, int band) {
+  constexpr bool MS = MODE != A11_ROWS, STEP = MODE == A11_MS_STEP;
   __shared__ V2<double> X[2 * kCellPL];
   __shared__ double XP[(kCellWaves + 2) * kCellHW];   // P1 rows j0 - 1 .. j0 + 8; the pinned entry read as 0
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
@@ -760,6 +758,25 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
   const int i = i0 + lane, j = j0 + w;
   const bool node = i <= n && j <= n;   // the cell's P1 vertex is in the lattice
   const int64_t q0 = (int64_t)j * (n + 1) + i;
+  // the step first: beta^2, and s, c and the slot as ms_step forms them, kept in LDS for the end (in
+  // registers they would be live over the products, which take all there are)
+  __shared__ double msc[3];   // s, c, beta^2
+  if constexpr (STEP) {
+    __shared__ double bred[1024 / kWave];
+    const double beta2 = ms_beta2<kWave * kCellWaves>(a.m.bpart.p + (int64_t)blockIdx.y * a.m.bpart.s, a.m.nb, bred);
+    if (threadIdx.x == 0) {
+      const MinresState &q = a.m.st[blockIdx.y];
+      double sc = q.s, cc = q.c_r1;
+      if (q.done == 0.0) {
+        const double beta = sqrt(beta2 > 0.0 ? beta2 : 0.0);
+        sc = beta > 0.0 ? 1.0 / beta : 0.0;
+        cc = beta > 0.0 ? -beta / q.beta : 0.0;
+      }
+      msc[0] = sc;
+      msc[1] = cc;
+      msc[2] = beta2;
+    }
+  }
   {   // the pressure tile
     constexpr int NE = (kCellWaves + 2) * kCellHW, NT = kWave * kCellWaves, IT = (NE + NT - 1) / NT;
     double v[IT];
@@ -790,7 +807,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
   V2<double> r1[4];
   double r1p = 0.0;
   if constexpr (MS) {   // after the staging, whose registers it takes over
-    load_cell(yg, N, L, n, i, j, r1);
+    load_cell((const double *)yg, N, L, n, i, j, r1);
     if (node) r1p = yg[o2 + q0];
   }
   __syncthreads();
@@ -820,17 +837,18 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
   double sp = -a.g * div;
   if (q0 == 0) xp = sp = xg[o2];   // the pinned entry
   if constexpr (MS) {
-    const double sc = a.ms_s[(int64_t)blockIdx.y * a.ls], cc = a.ms_c[(int64_t)blockIdx.y * a.ls];
-    int sl = (int)a.ms_slot[(int64_t)blockIdx.y * a.ls];
-    sl = sl < 0 ? 0 : sl >= a.nslot ? a.nslot - 1 : sl;
-    double *vg = a.vh + (int64_t)sl * a.vs + (int64_t)blockIdx.y * a.lv;
+    const MinresState &q = a.m.st[blockIdx.y];
+    const double sc = STEP ? msc[0] : q.s, cc = STEP ? msc[1] : q.c_r1;
+    int sl = (int)q.slot + (STEP ? 1 : 0);
+    sl = sl < 0 ? 0 : sl >= a.m.B ? a.m.B - 1 : sl;
+    double *vg = a.m.vh + (int64_t)sl * a.m.vs + (int64_t)blockIdx.y * a.lv;
     double acc = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       s[q] = V2<double>{sc * s[q].x, sc * s[q].y};
       if (cc != 0.0) s[q] = V2<double>{fma(cc, r1[q].x, s[q].x), fma(cc, r1[q].y, s[q].y)};
       x[q] = V2<double>{sc * x[q].x, sc * x[q].y};
-      acc += x[q].x * s[q].x + x[q].y * s[q].y;
+      acc = fma(x[q].y, s[q].y, fma(x[q].x, s[q].x, acc));
     }
     if (node) {
       store_cell<double, double>(yg, N, L, n, i, j, s);
@@ -840,7 +858,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
       xp *= sc;
       yg[o2 + q0] = sp;
       vg[o2 + q0] = xp;
-      acc += xp * sp;
+      acc = fma(xp, sp, acc);
     } else {
       acc = 0.0;
     }
@@ -852,7 +870,16 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
       double b = 0.0;
 #pragma unroll
       for (int k = 0; k < kCellWaves; ++k) b += red[k];
-      a.part[(int64_t)blockIdx.y * a.lp + t] = b;
+      a.m.part.p[(int64_t)blockIdx.y * a.m.part.s + t] = b;
+      if constexpr (STEP) {
+        if (blockIdx.x == 0) {
+          MinresState o = a.m.st[blockIdx.y];
+          o.beta2 = msc[2];
+          ms_step(&o, a.m.hist + (int64_t)blockIdx.y * kMsRec * a.m.B, a.m.B);
+          a.m.out[blockIdx.y] = o;
+          ms_tell(a.m.word ? a.m.word + blockIdx.y : nullptr, a.m.seq, o);
+        }
+      }
     }
   } else {
     if (a.cft_rp) {   // uniform: + C_f^T x_lam
@@ -972,13 +999,13 @@ void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s) {
   FSI_CHECK_LAUNCH();
 }
 
-template <bool MS>
+template <int MODE>
 static void launch_a11(A11Args a, hipStream_t s, int K) {
   cell_launch_checks(a.n, K);
   int tx;
   const int tiles = cell_tiles(a.n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
   a.g = 1.0 / (6.0 * a.n);
-  hipLaunchKernelGGL(k_a11<MS>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
+  hipLaunchKernelGGL(k_a11<MODE>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
                      tiles, band);
   FSI_CHECK_LAUNCH();
 }
@@ -995,29 +1022,22 @@ void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const
   a.cft_val = cft_val;
   a.xlx = xl;
   a.xly = xl ? xl + Ns : nullptr;
-  launch_a11<false>(a, s, 1);
+  launch_a11<A11_ROWS>(a, s, 1);
 }
 
-void a11_minres(int n, const AfCoef<double> &cf, LP<const double> x, LP<double> v, LP<double> r1y,
-                LP<const double> s_dev, LP<const double> c_dev, LP<const double> slot_dev, int64_t vs, int nslot,
-                LP<double> part, hipStream_t s, int K) {
-  FSI_REQUIRE(slot_dev.p && nslot >= 1, FSI_E_ARG, "the Lanczos block needs a slot index and at least one slot");
+void a11_minres(int n, const AfCoef<double> &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
+                int K) {
+  FSI_REQUIRE(m.st && m.B >= 1 && m.part.p && (m.nb == 0 || (m.out && m.out != m.st)), FSI_E_ARG,
+              "the A11 launch of an inner step needs its state, slots and parts");
   A11Args a{};
   a.n = n;
   a.cf = cf;
-  a.x = x.p;
-  a.y = r1y.p;
-  a.lv = common_stride({{x.p, x.s}, {v.p, v.s}, {r1y.p, r1y.s}}, K);
-  a.ms_s = s_dev.p;
-  a.ms_c = c_dev.p;
-  a.ms_slot = slot_dev.p;
-  a.ls = common_stride({{s_dev.p, s_dev.s}, {c_dev.p, c_dev.s}, {slot_dev.p, slot_dev.s}}, K);
-  a.vh = v.p;
-  a.vs = vs;
-  a.nslot = nslot;
-  a.part = part.p;
-  a.lp = part.s;
-  launch_a11<true>(a, s, K);
+  a.x = y.p;
+  a.y = r1.p;
+  a.lv = common_stride({{y.p, y.s}, {r1.p, r1.s}}, K);
+  a.m = m;
+  if (m.nb > 0) launch_a11<A11_MS_STEP>(a, s, K);
+  else launch_a11<A11_MS>(a, s, K);
 }
 
 int a11_tile_count(int n) {
