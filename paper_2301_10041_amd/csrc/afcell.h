@@ -172,13 +172,19 @@ __host__ __device__ constexpr double prolong_weight(int A, int B, int a, int b) 
   return 0.0;
 }
 
+// The interpolation weights that belong to a level's coefficients: here the triangle pair's
+template <typename C>
+struct TransferOf {
+  static constexpr double at(int A, int B, int a, int b) { return prolong_weight(A, B, a, b); }
+};
+
 // the coarse quadratic at fine node (A, B) of a coarse cell from its nine nodes c[3 b + a]
-template <int A, int B, typename T>
+template <typename C, int A, int B, typename T>
 __device__ __forceinline__ V2<T> prolong_node(const V2<T> (&c)[9]) {
   V2<T> s{T(0), T(0)};
   auto term = [&](auto q_tag) {
     constexpr int Q = decltype(q_tag)::value;
-    constexpr double w = prolong_weight(A, B, Q % 3, Q / 3);
+    constexpr double w = TransferOf<C>::at(A, B, Q % 3, Q / 3);
     if constexpr (w != 0.0) {
       s.x = fma(T(w), c[Q].x, s.x);
       s.y = fma(T(w), c[Q].y, s.y);
@@ -199,12 +205,16 @@ __device__ __forceinline__ V2<T> prolong_node(const V2<T> (&c)[9]) {
 // Weight of the fine node at offset (dI, dJ) of (2 Ic, 2 Jc) in the restriction R = P^T at a
 // coarse node of class (pa, pb) = (Ic mod 2, Jc mod 2): the coarse basis function there, from
 // the coarse cell holding the fine node
-__host__ __device__ constexpr double restrict_weight(int pa, int pb, int dI, int dJ) {
+template <typename Tr>
+__host__ __device__ constexpr double restrict_weight_of(int pa, int pb, int dI, int dJ) {
   // fine position relative to the coarse cell corner of (Ic - pa, Jc - pb): 2 pa + dI
   const int X = 2 * pa + dI + 8, Y = 2 * pb + dJ + 8;   // 8: two cells over, keeps them positive
   const int ci = X / 4 - 2, cj = Y / 4 - 2;
   const int a = pa - 2 * ci, b = pb - 2 * cj;           // the coarse node in that cell
-  return a < 0 || a > 2 || b < 0 || b > 2 ? 0.0 : prolong_weight(X % 4, Y % 4, a, b);
+  return a < 0 || a > 2 || b < 0 || b > 2 ? 0.0 : Tr::at(X % 4, Y % 4, a, b);
+}
+__host__ __device__ constexpr double restrict_weight(int pa, int pb, int dI, int dJ) {
+  return restrict_weight_of<TransferOf<void>>(pa, pb, dI, dJ);
 }
 
 // Host: the coefficients on an n x n grid (nu the viscosity, rdt = rho / dt), checked against

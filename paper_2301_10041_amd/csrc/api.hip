@@ -695,9 +695,8 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
         break;
       }
       case FSI_LAT_Q2AF: {
-        fsi::Q2Table<double> t;
-        fsi::Q2Table<float> tf;
-        fsi::q2_tables(n, nu, rdt, t, tf);
+        fsi::Q2Table t;
+        fsi::q2_tables(n, nu, rdt, t);
         for (int c = 0; c < 4; ++c) {
           counts[c] = t.count[c];
           for (int k = 0; k < t.count[c]; ++k) {
@@ -779,11 +778,9 @@ int fsi_profile_read(fsi_ctx *ctx, int prec, int64_t *launches, double *total_ms
     const double wy = (prec == FSI_FP32 && degree == 3) ? 8.0 : w;
     const double wd = degree > 3 ? w : 0.0;
     const double coarse = (degree >= 3 && c.mgu.lv.size() > 1) ? (double)c.mgu.lv[1].nodes * 2 * w : 0.0;
-    // the class-stencil step of the Q2 pair: x, b and d read, d and y written (two components)
     if (bytes_per_launch)
-      *bytes_per_launch = c.mgu.stencil ? (double)L.nodes * 2 * (2 * w + wd + wy) + coarse
-                          : L.q2tab64.p ? (double)L.nodes * 2 * 5 * w
-                                        : (double)L.A.nnz * (4 * w + 4) + (double)L.nodes * (4 + 14 * w) + 4.0;
+      *bytes_per_launch = c.mgu.stencil || L.q2 ? (double)L.nodes * 2 * (2 * w + wd + wy) + coarse
+                                                : (double)L.A.nnz * (4 * w + 4) + (double)L.nodes * (4 + 14 * w) + 4.0;
   });
 }
 

@@ -1250,8 +1250,7 @@ static void coarse_inverse_spd_device(Mg &mg, hipStream_t s) {
 size_t Mg::bytes() const {
   size_t b = cinv.bytes() + cinv32.bytes();
   for (auto &L : lv) {
-    b += L.A.bytes() + L.P.bytes() + L.R.bytes() + L.dinv.bytes() + L.dinv32.bytes() + L.q2tab64.bytes() +
-         L.q2tab32.bytes();
+    b += L.A.bytes() + L.P.bytes() + L.R.bytes() + L.dinv.bytes() + L.dinv32.bytes();
     for (int i = 0; i < 5; ++i) b += L.w64[i].bytes() + L.w32[i].bytes();
   }
   return b;
@@ -1694,80 +1693,9 @@ void build_fluid_q2(Ctx &c) {
 }
 
 
-// Coarse Q2 weights at fine lattice node (I, J) of an nf grid: the coarse cell's biquadratic
-// basis at the fine node (local coordinates multiples of 1/4: exact binary fractions), interior
-// coarse nodes only, in ascending coarse index.
-__device__ int q2_prolong_row(int I, int J, int nf, int *cidx, double *w) {
-  const int nc = nf / 2;
-  const int64_t Lc = 2 * nc + 1;
-  const int ci = min(I / 4, nc - 1), cj = min(J / 4, nc - 1);
-  const double xi = (I - 4 * ci) * 0.25, eta = (J - 4 * cj) * 0.25;
-  const double lx[3] = {2.0 * (xi - 0.5) * (xi - 1.0), 4.0 * xi * (1.0 - xi), 2.0 * xi * (xi - 0.5)};
-  const double ly[3] = {2.0 * (eta - 0.5) * (eta - 1.0), 4.0 * eta * (1.0 - eta), 2.0 * eta * (eta - 0.5)};
-  int cnt = 0;
-  for (int b = 0; b < 3; ++b)
-    for (int a = 0; a < 3; ++a) {
-      const double wt = lx[a] * ly[b];
-      if (wt == 0.0) continue;
-      const int Ic = 2 * ci + a, Jc = 2 * cj + b;
-      if (p2_boundary(Ic, Jc, nc)) continue;
-      cidx[cnt] = (int)(Jc * Lc + Ic);
-      w[cnt] = wt;
-      ++cnt;
-    }
-  return cnt;
-}
-
-__global__ void k_q2_prolong(int nf, int pass, int *cnt, const int *rowptr, int *col, double *V) {
-  const int64_t L = 2 * nf + 1;
-  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= L * L) return;
-  const int I = (int)(row % L), J = (int)(row / L);
-  int ci[9];
-  double w[9];
-  const int m = p2_boundary(I, J, nf) ? 0 : q2_prolong_row(I, J, nf, ci, w);
-  if (!pass) {
-    cnt[row] = m;
-    return;
-  }
-  const int k = rowptr[row];
-  for (int q = 0; q < m; ++q) {
-    col[k + q] = ci[q];
-    V[k + q] = w[q];
-  }
-}
-
-__global__ void k_q2_restrict(int nf, int pass, int *cnt, const int *rowptr, int *col, double *V) {
-  const int nc = nf / 2;
-  const int64_t Lc = 2 * nc + 1, L = 2 * nf + 1;
-  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= Lc * Lc) return;
-  const int Ic = (int)(row % Lc), Jc = (int)(row / Lc);
-  int k = pass ? rowptr[row] : 0, c = 0;
-  if (!p2_boundary(Ic, Jc, nc)) {
-    for (int J = 2 * Jc - 4; J <= 2 * Jc + 4; ++J)
-      for (int I = 2 * Ic - 4; I <= 2 * Ic + 4; ++I) {
-        if (I < 0 || J < 0 || I > 2 * nf || J > 2 * nf || p2_boundary(I, J, nf)) continue;
-        int ci[9];
-        double w[9];
-        const int m = q2_prolong_row(I, J, nf, ci, w);
-        for (int q = 0; q < m; ++q)
-          if (ci[q] == row) {
-            if (pass) {
-              col[k] = (int)((int64_t)J * L + I);
-              V[k] = w[q];
-              ++k;
-            }
-            ++c;
-          }
-      }
-  }
-  if (!pass) cnt[row] = c;
-}
-
-// The hierarchies of the Q2 pair, smoothed on the assembled operators (no matrix-free form):
-// velocity, A_f re-discretised on every level (the Galerkin operator of the nested Q2 spaces)
-// with the biquadratic prolongation and its transpose; pressure, L = B D^{-1} B^T of each level
+// The hierarchies of the Q2 pair: velocity, A_f re-discretised on every level (the Galerkin
+// operator of the nested Q2 spaces), smoothed and transferred cell by cell (biquadratic prolongation
+// and its transpose; the assembled A_f serves lmax and the coarsest inverse); pressure, L = B D^{-1} B^T of each level
 // (the Laplacian of the Cahouet-Chabard approximation for a discontinuous pressure) with the
 // P1-disc prolongation and its transpose; dense inverses at the coarsest level.
 void build_multigrid_q2(Ctx &c) {
@@ -1841,22 +1769,9 @@ void build_multigrid_q2(Ctx &c) {
                        U.A.col.p, U.A.val.p, U.dinv.p);
     FSI_CHECK_LAUNCH();
     U.lmax = 1.1 * power_lmax(U, 2, s);
-    if (m >= 2) {   // the class stencils of the smoothing steps and residuals
-      Q2Table<double> t64;
-      Q2Table<float> t32;
-      q2_tables(m, c.nu, c.rho / c.dt, t64, t32);
-      upload_bytes(U.q2tab64, &t64, sizeof(t64), s);
-      upload_bytes(U.q2tab32, &t32, sizeof(t32), s);
-    }
-    if (l + 1 < ns.size()) {
-      const int64_t nc2 = (int64_t)(m + 1) * (m + 1);
-      const unsigned gf2 = grid_for(U.nodes, 256), gc2 = grid_for(nc2, 256);
-      build_rows(U.P, U.nodes, nc2, 1, s, tmp, [&](int pass, int *cnt, const int *rp, int *col, double *v, double *) {
-        hipLaunchKernelGGL(k_q2_prolong, dim3(gf2), dim3(256), 0, s, m, pass, cnt, rp, col, v);
-      });
-      build_rows(U.R, nc2, U.nodes, 1, s, tmp, [&](int pass, int *cnt, const int *rp, int *col, double *v, double *) {
-        hipLaunchKernelGGL(k_q2_restrict, dim3(gc2), dim3(256), 0, s, m, pass, cnt, rp, col, v);
-      });
+    if (m >= 2) {   // the smoothing steps and residuals cell by cell
+      q2_coefs(m, c.nu, c.rho / c.dt, U.q64, U.q32);
+      U.q2 = true;
     }
     for (int i = 0; i < 5; ++i) U.w64[i].alloc(2 * U.nodes);
   }

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "afcell.h"
+#include "q2cell.h"
 #include "common.h"
 
 namespace fsi {
@@ -59,7 +60,9 @@ struct MgLevel {
   DevBuf<float> w32[5];
   AfCoef<double> af64{};                  // the level's A_f entries (velocity levels)
   AfCoef<float> af32{};
-  DevBuf<unsigned char> q2tab64, q2tab32; // Q2Table<double/float> (velocity levels of the Q2 pair)
+  bool q2 = false;         // a velocity level of the Q2 pair with its coefficients
+  Q2Coef<double> q64;
+  Q2Coef<float> q32;
 };
 
 struct Mg {

@@ -204,7 +204,7 @@ struct TailArgs {
 template <typename T>
 void mg_tail(const TailArgs<T> &a, hipStream_t s, int K = 1);
 // bc = R (b - A_f x) in one launch (stencil.hip): the residual lives only in LDS
-template <typename T>
-void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K = 1);
+template <typename T, typename C>
+void resid_restrict(int nf, const C &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K = 1);
 
 }  // namespace fsi

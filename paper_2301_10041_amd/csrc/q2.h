@@ -19,24 +19,13 @@ constexpr int kQ2Max = 25;
 constexpr int QE_M = 0, QE_K = 81, QE_B = QE_K + 324, QE_MP = QE_B + 54, QE_SIZE = QE_MP + 3;
 void q2_element_table(int n, double nu, std::vector<double> &out);
 
-template <typename T>
 struct Q2Table {
   int count[4];
-  int off[4][kQ2Max][2];   // (dI, dJ), dJ major
-  T coef[4][kQ2Max][4];    // 2 x 2 blocks: xx, xy, yx, yy
-  T dinv[4][4];            // inverse of the diagonal block
-  T dense[4][25][4];       // the same blocks on the full 5 x 5 window, entry (dI + 2) + 5 (dJ + 2) (zero
-                           // where the class has no neighbour)
+  int off[4][kQ2Max][2];        // (dI, dJ), dJ major
+  double coef[4][kQ2Max][4];    // 2 x 2 blocks: xx, xy, yx, yy
 };
 
-// One pass over the velocity lattice of an n x n grid (components at x and x + (2n+1)^2):
-//   resid: y = b - A x
-//   else:  d = c1 d + c2 D^{-1} (b - A x), y = x + d   (a Chebyshev step)
-template <typename T>
-void q2_stencil(int n, const Q2Table<T> *tab, const T *x, const T *b, T *d, T *y, T c1, T c2, bool resid,
-                hipStream_t s);
-
 // Host: the class stencils of A_f on an n x n grid (n >= 2) from the Q2 element matrices.
-void q2_tables(int n, double nu, double rdt, Q2Table<double> &t64, Q2Table<float> &t32);
+void q2_tables(int n, double nu, double rdt, Q2Table &t);
 
 }  // namespace fsi

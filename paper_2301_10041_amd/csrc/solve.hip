@@ -257,39 +257,13 @@ static T *chebyshev(int64_t nrows, const int *rp, const int *col, const T *val, 
   return x;
 }
 
-// The same iteration on the velocity levels of the Q2 pair with the class stencils
-// (q2_stencil) in place of the assembled rows; the first step from zero as chebyshev's.
-template <typename T>
-static T *chebyshev_q2(const MgLevel &L, const Q2Table<T> *tab, const T *dinv, double lmin, double lmax, int steps,
-                       const T *b, T *x, T *x2, T *d, bool zero_init, hipStream_t s, Prof *prof = nullptr) {
-  const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin);
-  const double sigma = theta / delta;
-  double rho = 1.0 / sigma;
-  if (zero_init) {
-    hipLaunchKernelGGL((k_dinv_first<T, 4, 2>), dim3(grid_for(L.nodes, 256)), dim3(256), 0, s, L.nodes, dinv, b,
-                       (T)(1.0 / theta), d, x);
-    FSI_CHECK_LAUNCH();
-  } else {
-    if (prof) prof->begin(s);
-    q2_stencil<T>(L.n, tab, x, b, d, x2, (T)0, (T)(1.0 / theta), false, s);
-    if (prof) prof->end(s);
-    std::swap(x, x2);
-  }
-  for (int k = 1; k < steps; ++k) {
-    const double rho1 = 1.0 / (2.0 * sigma - rho);
-    if (prof) prof->begin(s);
-    q2_stencil<T>(L.n, tab, x, b, d, x2, (T)(rho1 * rho), (T)(2.0 * rho1 / delta), false, s);
-    if (prof) prof->end(s);
-    std::swap(x, x2);
-    rho = rho1;
-  }
-  return x;
-}
-
 // The level's A_f entries in the arithmetic of the cycle
 template <typename T> static const AfCoef<T> &afc(const MgLevel &L);
 template <> const AfCoef<double> &afc<double>(const MgLevel &L) { return L.af64; }
 template <> const AfCoef<float> &afc<float>(const MgLevel &L) { return L.af32; }
+template <typename T> static const Q2Coef<T> &q2c(const MgLevel &L);
+template <> const Q2Coef<double> &q2c<double>(const MgLevel &L) { return L.q64; }
+template <> const Q2Coef<float> &q2c<float>(const MgLevel &L) { return L.q32; }
 
 // The Chebyshev coefficients of chebyshev for three steps: s = 1 / theta, then (c1, c2) of
 // the two later steps
@@ -454,15 +428,12 @@ static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullp
       return x;
     }
   }
-  if (mg.stencil) {   // matrix-free smoothing, residual and transfers
-    if constexpr (W == 4) {
-      // three launches per level: pre-smoothing; residual with the restriction (the residual stays
-      // in LDS); post-smoothing, which adds the coarse correction while it stages x (the profile
-      // brackets this one, the largest single kernel of a step)
+  if constexpr (W == 4) {   // matrix-free smoothing, residual and transfers
+    // three launches per level: pre-smoothing; residual with the restriction (the residual stays
+    // in LDS); post-smoothing, which adds the coarse correction while it stages x (the profile
+    // brackets this one, the largest single kernel of a step)
+    auto cycle = [&](const auto &cf) -> T * {
       FSI_REQUIRE(degree == 3, FSI_E_STATE, "the matrix-free velocity cycle takes three steps");
-      (void)r;
-      (void)d;
-      const AfCoef<T> &cf = afc<T>(L);
       const Cheb3Coef<T> cc = cheb3_coefs<T>(lmin, lmax);
       const LP<const T> lx(x, ls);
       pre3<T>(L.n, cf, LP<T>(const_cast<T *>(b.p), b.s), LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, fold);
@@ -477,26 +448,20 @@ static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullp
         post3<T, T>(L.n, cf, lx, b, LP<T>(x2, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, lxc, dot, b64);
       if (pl) pl->end(s);
       return out64.p ? nullptr : x2;
-    } else {
-      FSI_REQUIRE(false, FSI_E_STATE, "the matrix-free pressure cycle is p1_cycle");
-    }
+    };
+    if (mg.stencil) return cycle(afc<T>(L));
+    if (L.q2) return cycle(q2c<T>(L));
   }
-  // the Q2 pair's velocity levels: class stencils for the smoothing steps and the residual
-  const Q2Table<T> *q2 = nullptr;
-  if constexpr (W == 4)
-    q2 = (const Q2Table<T> *)(std::is_same<T, double>::value ? L.q2tab64.p : L.q2tab32.p);
-  T *xs = q2 ? chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b.p, x, x2, d, true, s, pl)
-             : chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b.p, x,
-                                   x2, d, true, s, pl);
+  FSI_REQUIRE(!mg.stencil, FSI_E_STATE, "the matrix-free pressure cycle is p1_cycle");
+  T *xs = chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b.p, x, x2, d, true, s,
+                              pl);
   T *xo = (xs == x) ? x2 : x;
-  if (q2) q2_stencil<T>(L.n, q2, xs, b.p, nullptr, r, (T)0, (T)0, true, s);
-  else spmv<T, W, NC, SP_RESID>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, xs, L.nodes, r, L.nodes, s, b.p);
+  spmv<T, W, NC, SP_RESID>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, xs, L.nodes, r, L.nodes, s, b.p);
   spmv<T, 1, NC, SP_APPLY>(L.R.nrows, L.R.rowptr.p, L.R.col.p, Pr<T>::val(L.R), r, L.nodes, bc,
                            C.nodes, s);
   T *xc = vcycle<T, W, NC>(mg, l + 1, LP<const T>(bc, lc), s);
   spmv<T, 1, NC, SP_ADD>(L.P.nrows, L.P.rowptr.p, L.P.col.p, Pr<T>::val(L.P), xc, C.nodes, xs,
                          L.nodes, s);
-  if (q2) return chebyshev_q2<T>(L, q2, dinv, lmin, lmax, degree, b.p, xs, xo, d, false, s, pl);
   return chebyshev<T, W, NC>(L.A.nrows, L.A.rowptr.p, L.A.col.p, val, dinv, lmin, lmax, degree, b.p,
                              xs, xo, d, false, s, pl);
 }
@@ -653,7 +618,7 @@ static void a11_precond(Ctx &c, LP<const T> ru, const double *r, double *z, int 
       convert_l(LP<T>(bu, 2 * N2), ru, 2 * N2, s, K);
       ru = LP<const T>(bu, 2 * N2);
     }
-    const bool direct = c.mgu.stencil && !one;   // the last smoothing launch writes z
+    const bool direct = (c.mgu.stencil || c.mgu.lv[0].q2) && !one;   // the last smoothing launch writes z
     T *xu = vcycle<T, 4, 2>(c.mgu, 0, ru, s, K == 1 && pf->on ? pf : nullptr, K,
                             direct ? LP<double>(z, nf) : LP<double>(), dot,
                             LP<const double>(dot.p && !std::is_same<T, double>::value ? r : nullptr, nf), fold,

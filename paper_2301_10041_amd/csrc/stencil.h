@@ -111,7 +111,8 @@ struct MsFold {
   int64_t ls = 0;
 };
 
-// Chebyshev smoothing of a velocity level, three steps per launch:
+// Chebyshev smoothing of a velocity level, three steps per launch (C: AfCoef<T> for the triangle pair,
+// Q2Coef<T> for the paper's, which takes no fold):
 // pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x.  With fold, b is the velocity
 //        part of q; q (all three parts) is written, and for T = float also the copy b.
 // post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and
@@ -119,11 +120,11 @@ struct MsFold {
 //        written).  With dot, tile t of lane k stores the sum over its nodes of b . y (FP64, y as
 //        stored) at dot.at(k)[t] (post3_dot_count(n) tiles); with b64 the sums take that FP64
 //        right-hand side in place of b (the FP32 cycle of the mixed form).
-template <typename T>
-void pre3(int n, const AfCoef<T> &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
+template <typename T, typename C>
+void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
           const MsFold *fold = nullptr);
-template <typename T, typename TY>
-void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
+template <typename T, typename TY, typename C>
+void post3(int n, const C &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
            hipStream_t st, int K, LP<const T> xc, LP<double> dot = LP<double>(),
            LP<const double> b64 = LP<const double>());
 int post3_dot_count(int n);

@@ -14,6 +14,7 @@
 #include "kernels.h"
 #include "lattice.h"
 #include "minres.h"
+#include "q2cell.h"
 #include "stencil.h"
 
 namespace fsi {
@@ -140,15 +141,15 @@ __device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int
   }
 }
 
-template <typename T>
+template <typename T, typename C>
 struct PreArgs {
   int n;
-  AfCoef<T> cf;
+  C cf;
   T *b;                      // read, or written with the update (FP32 only)
   T *y;
   T s, c1a, c2a, c1b, c2b;   // the first step's scale, the two stencil steps
   int64_t lb, ly;            // lane strides of b and y (lane = blockIdx.y)
-  MsFold f;                  // k_pre3<T, true>
+  MsFold f;                  // MS
   int64_t np;                // its pressure entries
 };
 
@@ -164,8 +165,8 @@ struct PreArgs {
 // here too.
 constexpr int kPreW = kWave - 2, kPreR = kCellWaves - 2;
 constexpr int kPrePres = 4 * kWave * kCellWaves;   // pressure entries per block
-template <typename T, bool MS>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T> a, int tiles_x, int tiles, int band) {
+template <typename T, typename C, bool MS>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, int tiles_x, int tiles, int band) {
   using TS = typename std::conditional<MS, double, T>::type;   // staged first
   __shared__ V2<TS> XS[2 * kCellPL];
   V2<T> *const X = reinterpret_cast<V2<T> *>(XS);
@@ -179,9 +180,9 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T> a, int
   const int i0 = (t % tiles_x) * kPreW - 1, j0 = (t / tiles_x) * kPreR - 1;   // first cell of the region
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
-  const AfCoef<T> &cf = a.cf;
+  const C &cf = a.cf;
   auto first = [&](int pj, int pi, V2<T> v) -> V2<T> {
-    const V2<T> z = cell_dinv(cf, pi | pj, v);
+    const V2<T> z = cell_dinv(cf, pi + 2 * pj, v);
     return V2<T>{a.s * z.x, a.s * z.y};
   };
   V2<T> b[4];
@@ -324,10 +325,10 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T> a, int
 constexpr int kPostW = kWave - 4, kPostR = kCellWaves - 4;
 static_assert(kPostW % 2 == 0 && kPostR % 2 == 0, "tile origins on coarse cell corners");
 
-template <typename T, typename TY>
+template <typename T, typename TY, typename C>
 struct PostArgs {
   int n;
-  AfCoef<T> cf;
+  C cf;
   const T *x, *b;
   TY *y;
   T c2a, c1b, c2b, c1c, c2c;
@@ -340,8 +341,8 @@ struct PostArgs {
   int64_t lb64;        // its lane stride
 };
 
-template <typename T, typename TY, bool DOT>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY> a, int tiles_x, int tiles, int band) {
+template <typename T, typename TY, typename C, bool DOT>
+__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, C> a, int tiles_x, int tiles, int band) {
   __shared__ V2<T> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
@@ -353,7 +354,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY> 
   const int i0 = (t % tiles_x) * kPostW - 2, j0 = (t / tiles_x) * kPostR - 2;   // first cell of the region
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
-  const AfCoef<T> &cf = a.cf;
+  const C &cf = a.cf;
   {   // stage x + P xc: coarse cell (ci, cj), its fine rows 0, 1 (first four waves) or 2, 3
     constexpr int CX = (kCellHW + 2) / 2, CY = (kCellH + 4) / 4 + 1;
     static_assert(CX * CY <= kWave * kCellWaves / 2, "two threads per coarse cell");
@@ -399,7 +400,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY> 
         constexpr int H = decltype(h_tag)::value;
         auto node = [&](auto a_tag, auto b_tag) {
           constexpr int A = decltype(a_tag)::value, B = decltype(b_tag)::value;
-          const V2<T> p = prolong_node<A, 2 * H + B, T>(k9);
+          const V2<T> p = prolong_node<C, A, 2 * H + B, T>(k9);
           v[B][A].x += p.x;
           v[B][A].y += p.y;
         };
@@ -524,36 +525,43 @@ static void cell_launch_checks(int n, int K) {
   FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
 }
 
-template <typename T>
-void pre3(int n, const AfCoef<T> &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
+template <typename T, typename C>
+void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
           const MsFold *fold) {
   cell_launch_checks(n, K);
   int tx;
   const int tiles = cell_tiles(n, kPreW, kPreR, tx), band = (tiles + kXcd - 1) / kXcd;
   FSI_REQUIRE(K == 1 || (x.s > 0 && (b.s > 0 || !b.p)), FSI_E_ARG, "lane views need a stride");
-  PreArgs<T> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
+  PreArgs<T, C> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
   const dim3 block(kWave * kCellWaves);
   if (fold) {
-    a.f = *fold;
-    a.np = (int64_t)(n + 1) * (n + 1);
-    a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
-    FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
-    const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
-    hipLaunchKernelGGL((k_pre3<T, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx, tiles,
-                       band);
+    if constexpr (std::is_same<C, AfCoef<T>>::value) {
+      a.f = *fold;
+      a.np = (int64_t)(n + 1) * (n + 1);
+      a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
+      FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
+      const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
+      hipLaunchKernelGGL((k_pre3<T, C, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx,
+                         tiles, band);
+    } else {
+      FSI_REQUIRE(false, FSI_E_STATE, "the update belongs to the triangle pair");
+    }
   } else {
-    hipLaunchKernelGGL((k_pre3<T, false>), dim3((unsigned)(band * kXcd), (unsigned)K), block, 0, st, a, tx, tiles,
+    hipLaunchKernelGGL((k_pre3<T, C, false>), dim3((unsigned)(band * kXcd), (unsigned)K), block, 0, st, a, tx, tiles,
                        band);
   }
   FSI_CHECK_LAUNCH();
 }
-template void pre3<double>(int, const AfCoef<double> &, LP<double>, LP<double>, double, double, double, double, double,
-                           hipStream_t, int, const MsFold *);
-template void pre3<float>(int, const AfCoef<float> &, LP<float>, LP<float>, float, float, float, float, float,
-                          hipStream_t, int, const MsFold *);
+#define FSI_PRE3_INST(T, C) \
+  template void pre3<T, C>(int, const C &, LP<T>, LP<T>, T, T, T, T, T, hipStream_t, int, const MsFold *);
+FSI_PRE3_INST(double, AfCoef<double>)
+FSI_PRE3_INST(float, AfCoef<float>)
+FSI_PRE3_INST(double, Q2Coef<double>)
+FSI_PRE3_INST(float, Q2Coef<float>)
+#undef FSI_PRE3_INST
 
-template <typename T, typename TY>
-void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
+template <typename T, typename TY, typename C>
+void post3(int n, const C &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
            hipStream_t st, int K, LP<const T> xc, LP<double> dot, LP<const double> b64) {
   cell_launch_checks(n, K);
   FSI_REQUIRE(xc.p && n % 2 == 0 && n >= 4, FSI_E_ARG, "a coarse correction needs an even fluid grid");
@@ -564,18 +572,21 @@ void post3(int n, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<TY> y, T
   FSI_REQUIRE(!dot.p || K == 1 || dot.s >= tiles, FSI_E_ARG, "lane stride of the tile sums too small");
   FSI_REQUIRE(!b64.p || (dot.p && (K == 1 || b64.s > 0) && !std::is_same<T, double>::value), FSI_E_ARG,
               "an FP64 right-hand side only for the sums of the FP32 form");
-  PostArgs<T, TY> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, x.s, b.s, y.s, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
+  PostArgs<T, TY, C> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, x.s, b.s, y.s, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
   const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(kWave * kCellWaves);
-  if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, true>), grid, block, 0, st, a, tx, tiles, band);
-  else hipLaunchKernelGGL((k_post3<T, TY, false>), grid, block, 0, st, a, tx, tiles, band);
+  if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, C, true>), grid, block, 0, st, a, tx, tiles, band);
+  else hipLaunchKernelGGL((k_post3<T, TY, C, false>), grid, block, 0, st, a, tx, tiles, band);
   FSI_CHECK_LAUNCH();
 }
-#define FSI_POST3_INST(T, TY)                                                                                    \
-  template void post3<T, TY>(int, const AfCoef<T> &, LP<const T>, LP<const T>, LP<TY>, T, T, T, T, T, hipStream_t, \
-                             int, LP<const T>, LP<double>, LP<const double>);
-FSI_POST3_INST(double, double)
-FSI_POST3_INST(float, float)
-FSI_POST3_INST(float, double)
+#define FSI_POST3_INST(T, TY, C)                                                                                 \
+  template void post3<T, TY, C>(int, const C &, LP<const T>, LP<const T>, LP<TY>, T, T, T, T, T, hipStream_t, int, \
+                                LP<const T>, LP<double>, LP<const double>);
+FSI_POST3_INST(double, double, AfCoef<double>)
+FSI_POST3_INST(float, float, AfCoef<float>)
+FSI_POST3_INST(float, double, AfCoef<float>)
+FSI_POST3_INST(double, double, Q2Coef<double>)
+FSI_POST3_INST(float, float, Q2Coef<float>)
+FSI_POST3_INST(float, double, Q2Coef<float>)
 #undef FSI_POST3_INST
 
 // ---------------------------------------------------------------- residual and restriction
@@ -589,18 +600,18 @@ FSI_POST3_INST(float, double)
 // The restriction runs by coarse classes, one per wave pass, with compile-time weights.
 constexpr int kRRc = (kWave - 3) / 2;
 
-template <typename T>
+template <typename T, typename C>
 struct ResidRestrArgs {
   int n;
-  AfCoef<T> cf;
+  C cf;
   const T *x, *b;
   T *bc;
   int64_t lx, lb, lc;   // lane strides of x, b and bc
 };
 
-template <typename T, int Q>
+template <typename T, typename C, int Q>
 __global__ void __launch_bounds__(kWave *kCellWaves, 4)
-    k_resid_restrict(ResidRestrArgs<T> a, int tiles_x, int tiles, int band) {
+    k_resid_restrict(ResidRestrArgs<T, C> a, int tiles_x, int tiles, int band) {
   constexpr int ROWS = 2 * kCellWaves * Q + 3, PL = ROWS * kCellHW;
   constexpr int CR = (kCellWaves * Q - 3) / 2;                      // coarse rows
   constexpr int RH = 2 * kCellWaves * Q, RPL = RH * kWave;          // residual planes
@@ -616,7 +627,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
   const int i0 = 2 * C0 - 2, j0 = 2 * R0 - 2;                       // first fine cell of the region
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane;
-  const AfCoef<T> &cf = a.cf;
+  const C &cf = a.cf;
   V2<T> b[Q][4];
   stage_pairs<T, ROWS>(X, xg, N, L, n, i0, j0, [](int, int, V2<T> v) -> V2<T> { return v; });
   load_cell(bg, N, L, n, i, j0 + w * Q, b[0]);   // after the staging, whose registers it takes over
@@ -655,7 +666,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
           constexpr int DJ = decltype(dj_tag)::value;
           auto term = [&](auto di_tag) {
             constexpr int DI = decltype(di_tag)::value;
-            constexpr double wt = restrict_weight(PA, PB, DI, DJ);
+            constexpr double wt = restrict_weight_of<TransferOf<C>>(PA, PB, DI, DJ);
             if constexpr (wt != 0.0) {
               constexpr int u0 = 2 * PA + DI, v0 = 2 * PB + DJ;
               const V2<T> v = r[(u0 & 1) * RPL + v0 * kWave + (u0 >> 1)];
@@ -695,27 +706,30 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
 
 constexpr int kRestrictWideN = 256;   // cells per side from which a block takes two rows per wave
 
-template <typename T>
-void resid_restrict(int nf, const AfCoef<T> &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K) {
+template <typename T, typename C>
+void resid_restrict(int nf, const C &cf, LP<const T> x, LP<const T> b, LP<T> bc, hipStream_t s, int K) {
   cell_launch_checks(nf, K);
   FSI_REQUIRE(nf % 2 == 0 && nf >= 4, FSI_E_ARG, "restriction needs an even fluid grid");
   FSI_REQUIRE(K == 1 || (x.s > 0 && b.s > 0 && bc.s > 0), FSI_E_ARG, "lane views need a stride");
-  ResidRestrArgs<T> a{nf, cf, x.p, b.p, bc.p, x.s, b.s, bc.s};
+  ResidRestrArgs<T, C> a{nf, cf, x.p, b.p, bc.p, x.s, b.s, bc.s};
   auto go = [&](auto q_tag) {
     constexpr int Q = decltype(q_tag)::value;
     int tx;
     const int tiles = cell_tiles(nf / 2, kRRc, (kCellWaves * Q - 3) / 2, tx), band = (tiles + kXcd - 1) / kXcd;
-    hipLaunchKernelGGL((k_resid_restrict<T, Q>), dim3((unsigned)(band * kXcd), (unsigned)K),
+    hipLaunchKernelGGL((k_resid_restrict<T, C, Q>), dim3((unsigned)(band * kXcd), (unsigned)K),
                        dim3(kWave * kCellWaves), 0, s, a, tx, tiles, band);
   };
   if (nf >= kRestrictWideN) go(std::integral_constant<int, 2>{});
   else go(std::integral_constant<int, 1>{});
   FSI_CHECK_LAUNCH();
 }
-template void resid_restrict<double>(int, const AfCoef<double> &, LP<const double>, LP<const double>, LP<double>,
-                                     hipStream_t, int);
-template void resid_restrict<float>(int, const AfCoef<float> &, LP<const float>, LP<const float>, LP<float>,
-                                    hipStream_t, int);
+#define FSI_RR_INST(T, C) \
+  template void resid_restrict<T, C>(int, const C &, LP<const T>, LP<const T>, LP<T>, hipStream_t, int);
+FSI_RR_INST(double, AfCoef<double>)
+FSI_RR_INST(float, AfCoef<float>)
+FSI_RR_INST(double, Q2Coef<double>)
+FSI_RR_INST(float, Q2Coef<float>)
+#undef FSI_RR_INST
 
 // ---------------------------------------------------------------- A11 rows
 // y = A11 x on [u_x | u_y | p] with one thread per cell: the cell's four velocity rows
