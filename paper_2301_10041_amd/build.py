@@ -17,7 +17,7 @@ OUT = os.path.join(HERE, "libfsi.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["api.hip", "assemble.hip", "coupling.hip", "hyper.hip", "lattice.hip", "mgtail.hip", "ops.hip",
-           "pressure.hip", "q2.hip", "solve.hip", "stencil.hip"]
+           "pressure.hip", "q2.hip", "qpressure.hip", "solve.hip", "stencil.hip"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I", INCLUDE,
           # no packed FP32 instructions (hardware notes)
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

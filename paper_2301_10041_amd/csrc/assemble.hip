@@ -1569,83 +1569,6 @@ __global__ void k_q_lp(int n, int pass, const int *__restrict__ brp, const int *
   if (r == 0) V[k0] = 1.0;   // the row's first column is unknown 0: B's row 0 left it zero
 }
 
-// Prolongation of the discontinuous P1 pressure from an nf / 2 grid into the nf grid: the coarse
-// cell's linear function on each of its four children (fine constant = the coarse function at
-// the child's centre, x_c +- h_c / 4; fine slopes = half the coarse ones); the pinned unknown 0
-// excluded on both grids.
-__device__ int pd_prolong_row(int64_t r, int nf, int *cidx, double *w) {
-  const int nc = nf / 2;
-  const int64_t cell = r / 3;
-  const int q = (int)(r % 3), i = (int)(cell % nf), j = (int)(cell / nf);
-  const int64_t cc = 3 * ((int64_t)(j >> 1) * nc + (i >> 1));
-  const double sx = (i & 1) ? 0.25 : -0.25, sy = (j & 1) ? 0.25 : -0.25;
-  int m = 0;
-  auto put = [&](int64_t c, double v) {
-    if (c == 0) return;
-    cidx[m] = (int)c;
-    w[m] = v;
-    ++m;
-  };
-  if (q == 0) {
-    put(cc, 1.0);
-    put(cc + 1, sx);
-    put(cc + 2, sy);
-  } else {
-    put(cc + q, 0.5);
-  }
-  return m;
-}
-
-__global__ void k_pd_prolong(int nf, int pass, int *cnt, const int *rowptr, int *col, double *V) {
-  const int64_t np = 3 * (int64_t)nf * nf;
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= np) return;
-  int ci[3];
-  double w[3];
-  const int m = r == 0 ? 0 : pd_prolong_row(r, nf, ci, w);
-  if (!pass) {
-    cnt[r] = m;
-    return;
-  }
-  const int k = rowptr[r];
-  for (int t = 0; t < m; ++t) {
-    col[k + t] = ci[t];
-    V[k + t] = w[t];
-  }
-}
-
-__global__ void k_pd_restrict(int nf, int pass, int *cnt, const int *rowptr, int *col, double *V) {
-  const int nc = nf / 2;
-  const int64_t npc = 3 * (int64_t)nc * nc;
-  const int64_t rc = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (rc >= npc) return;
-  const int64_t cell = rc / 3;
-  const int ic = (int)(cell % nc), jc = (int)(cell / nc);
-  int k = pass ? rowptr[rc] : 0, c = 0;
-  if (rc != 0)
-    for (int dj = 0; dj < 2; ++dj)
-      for (int di = 0; di < 2; ++di) {
-        const int64_t fcell = (int64_t)(2 * jc + dj) * nf + 2 * ic + di;
-        for (int q = 0; q < 3; ++q) {
-          const int64_t f = 3 * fcell + q;
-          if (f == 0) continue;
-          int ci[3];
-          double w[3];
-          const int m = pd_prolong_row(f, nf, ci, w);
-          for (int t = 0; t < m; ++t)
-            if (ci[t] == rc) {
-              if (pass) {
-                col[k] = (int)f;
-                V[k] = w[t];
-                ++k;
-              }
-              ++c;
-            }
-        }
-      }
-  if (!pass) cnt[rc] = c;
-}
-
 static void assemble_q2q2(Csr &A, DevBuf<double> *M, int n, const double *dE, double rdt, DevBuf<int> &tmp,
                           hipStream_t s) {
   const int64_t rows = (int64_t)(2 * n + 1) * (2 * n + 1);
@@ -1696,8 +1619,9 @@ void build_fluid_q2(Ctx &c) {
 // The hierarchies of the Q2 pair: velocity, A_f re-discretised on every level (the Galerkin
 // operator of the nested Q2 spaces), smoothed and transferred cell by cell (biquadratic prolongation
 // and its transpose; the assembled A_f serves lmax and the coarsest inverse); pressure, L = B D^{-1} B^T of each level
-// (the Laplacian of the Cahouet-Chabard approximation for a discontinuous pressure) with the
-// P1-disc prolongation and its transpose; dense inverses at the coarsest level.
+// (the Laplacian of the Cahouet-Chabard approximation for a discontinuous pressure), cell by cell too,
+// with the P1-disc prolongation (the coarse cell's linear function on its children) and its
+// transpose; dense inverses at the coarsest level.
 void build_multigrid_q2(Ctx &c) {
   hipStream_t s = c.stream;
   DevBuf<int> tmp;
@@ -1752,15 +1676,6 @@ void build_multigrid_q2(Ctx &c) {
                          P.dinv.p);
       FSI_CHECK_LAUNCH();
       P.lmax = 1.1 * power_lmax(P, 1, s);
-      if (l + 1 < ns.size()) {
-        const int64_t npc = 3 * (int64_t)(m / 2) * (m / 2);
-        build_rows(P.P, P.nodes, npc, 1, s, tmp, [&](int pass, int *cnt, const int *rp, int *col, double *v, double *) {
-          hipLaunchKernelGGL(k_pd_prolong, dim3(gp), dim3(256), 0, s, m, pass, cnt, rp, col, v);
-        });
-        build_rows(P.R, npc, P.nodes, 1, s, tmp, [&](int pass, int *cnt, const int *rp, int *col, double *v, double *) {
-          hipLaunchKernelGGL(k_pd_restrict, dim3(grid_for(npc, 256)), dim3(256), 0, s, m, pass, cnt, rp, col, v);
-        });
-      }
       for (int i = 0; i < 5; ++i) P.w64[i].alloc(P.nodes);
       FSI_HIP(hipStreamSynchronize(s));   // the level's B, B^T and D are freed below
     }

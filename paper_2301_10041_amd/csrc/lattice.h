@@ -173,6 +173,31 @@ template <typename T, typename TB, bool OUT>
 void p1_tail(const PTailArgs<T, TB> &a, hipStream_t s, int K);
 int p1_tail_lds_limit();
 
+// The paper's pair (qpressure.hip): descent and ascent of a level of its pressure cycle (n even).  down:
+// x = s D^{-1} b and the step (c1, c2), bc = P^T (b - L x).  up: x + P xc, a step with c1 = 0 (s) and the step
+// (c1, c2) into y, or with z the output z = nu mpinv b + rdt of that (z[0] = b[0] rounded through T).
+template <typename T, typename TB>
+struct QpDownArgs {
+  int n;
+  const TB *b;
+  T *x, *bc;
+  T s, c1, c2;
+};
+template <typename T, typename TB>
+void qp_down(const QpDownArgs<T, TB> &a, hipStream_t s);
+template <typename T, typename TB>
+struct QpUpArgs {
+  int n;
+  const TB *b;
+  const T *x, *xc;
+  T *y;
+  TB *z;
+  const T *mpinv;
+  T s, c1, c2, nu, rdt;
+};
+template <typename T, typename TB>
+void qp_up(const QpUpArgs<T, TB> &a, hipStream_t s);
+
 // The coarse end of a velocity V-cycle in one launch per system (mgtail.hip): levels
 // lv[0..nlev) (n <= kTailMaxN cells, each the next one's fine level) and the coarsest
 // level's dense inverse cinv (m x m, symmetric).  LDS: two buffers of kTailLevelV2 nodes per

@@ -583,6 +583,29 @@ static void p1_schur(Ctx &c, const double *r, double *z, int64_t lz, double *par
   p1_up<T, double, P1_Z>(a, s, K);
 }
 
+// The pressure V-cycle of the paper's pair from level l for right-hand side b; at level 0 the last launch
+// writes z = nu M_p^{-1} b + (rho/dt) (the result) and nullptr is returned, below it the level work
+// vector that holds the result.
+template <typename T, typename TB>
+static T *qp_cycle(Ctx &c, int l, const TB *b, TB *z, hipStream_t s) {
+  Mg &mg = c.mgp;
+  MgLevel &L = mg.lv[l], &C = mg.lv[l + 1];
+  FSI_REQUIRE((std::is_same<T, float>::value ? mg.degree32 : mg.degree) == 2, FSI_E_STATE,
+              "the pressure cycle takes two steps");
+  T c1[2], c2[2], *x = Pr<T>::w(L, 0), *bc = Pr<T>::w(C, 1), *xc;
+  p1_cheb_coefs<T>(L.lmax / 30.0, L.lmax, 2, c1, c2);
+  qp_down<T, TB>(QpDownArgs<T, TB>{L.n, b, x, bc, c2[0], c1[1], c2[1]}, s);
+  if (l + 2 == (int)mg.lv.size()) {
+    xc = Pr<T>::w(C, 0);
+    dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), bc, xc, 1, s);
+  } else {
+    xc = qp_cycle<T, T>(c, l + 1, bc, nullptr, s);
+  }
+  T *y = z ? nullptr : Pr<T>::w(L, 4);
+  qp_up<T, TB>(QpUpArgs<T, TB>{L.n, b, x, xc, y, z, mp_dinv<T>(c), c2[0], c1[1], c2[1], (T)c.nu, (T)(c.rho / c.dt)}, s);
+  return y;
+}
+
 // z = diag(V, S^{-1}) r on [u | p], for K systems at once (lane k of r and z at + k nf,
 // nf = 2 N2 + Np; K > 1 needs the matrix-free hierarchies), in arithmetic T on FP64 vectors.  ru is
 // the velocity part of r in T (lane stride ru.s): r itself, or its FP32 copy.  The two blocks share no
@@ -645,6 +668,11 @@ static void a11_precond(Ctx &c, LP<const T> ru, const double *r, double *z, int 
     return;
   }
   FSI_REQUIRE(!dot.p && K == 1, FSI_E_STATE, "the assembled form runs one system and forms no tile sums");
+  if (c.pair == FSI_PAIR_Q2P1DISC && c.mgp.lv.size() > 1) {
+    qp_cycle<T, double>(c, 0, r + 2 * N2, z + 2 * N2, sp);
+    join();
+    return;
+  }
   // r' = pressure residual with the pinned entry removed (keeps the operator symmetric)
   T *rp = Pr<T>::inner(c, 8).p;
   convert(rp, r + 2 * N2, Np, sp);
