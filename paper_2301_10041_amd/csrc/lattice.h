@@ -194,9 +194,11 @@ struct QpUpArgs {
   TB *z;
   const T *mpinv;
   T s, c1, c2, nu, rdt;
+  double *part;   // with z: per block (qp_up_tiles(n)) the part of sum b z, or null
 };
 template <typename T, typename TB>
 void qp_up(const QpUpArgs<T, TB> &a, hipStream_t s);
+int qp_up_tiles(int n);
 
 // The coarse end of a velocity V-cycle in one launch per system (mgtail.hip): levels
 // lv[0..nlev) (n <= kTailMaxN cells, each the next one's fine level) and the coarsest

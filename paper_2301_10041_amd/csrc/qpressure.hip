@@ -176,19 +176,39 @@ __global__ void __launch_bounds__(kQpT) k_qp_up(QpUpArgs<T, TB> a, int tiles_x) 
   x = qp_add(x, d);
   y = qp_product(s, x, q.i, q.j, q.n);
   x = pinned(qp_add(x, qp_step(z, a.c1, d, a.c2, b, y)));
-  if (!q.out) return;
+  double acc = 0.0;   // OUT: the thread's part of b . z
+  if (q.out) {
   if constexpr (OUT) {   // z = nu M_p^{-1} r + (rho/dt) x, the pinned unknown r rounded through T
     const T *m = a.mpinv + 3 * q.cell;
     const TB *r = a.b + 3 * q.cell;
     TB *zg = a.z + 3 * q.cell;
-    zg[0] = (TB)(q.cell == 0 ? (T)r[0] : a.nu * m[0] * (T)r[0] + a.rdt * x.c);
-    zg[1] = (TB)(a.nu * m[1] * (T)r[1] + a.rdt * x.x);
-    zg[2] = (TB)(a.nu * m[2] * (T)r[2] + a.rdt * x.y);
+    const TB v[3] = {(TB)(q.cell == 0 ? (T)r[0] : a.nu * m[0] * (T)r[0] + a.rdt * x.c),
+                     (TB)(a.nu * m[1] * (T)r[1] + a.rdt * x.x), (TB)(a.nu * m[2] * (T)r[2] + a.rdt * x.y)};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      zg[k] = v[k];
+      acc = fma((double)r[k], (double)v[k], acc);
+    }
   } else {
     T *yg = a.y + 3 * q.cell;
     yg[0] = x.c;
     yg[1] = x.x;
     yg[2] = x.y;
+  }
+  }
+  if constexpr (OUT) {
+    if (a.part) {   // uniform; the block's sum in a fixed order
+      __shared__ double red[kQpW];
+      acc = wave_sum(acc);
+      if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = acc;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < kQpW; ++k) t += red[k];
+        a.part[blockIdx.x] = t;
+      }
+    }
   }
 }
 
@@ -199,6 +219,11 @@ int qp_tiles(int n, int &tx) {
 }
 
 }  // namespace
+
+int qp_up_tiles(int n) {
+  int tx;
+  return qp_tiles(n, tx);
+}
 
 template <typename T, typename TB>
 void qp_down(const QpDownArgs<T, TB> &a, hipStream_t s) {

@@ -402,7 +402,7 @@ static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullp
   T *x = Pr<T>::w(L, 0), *x2 = Pr<T>::w(L, 4), *r = Pr<T>::w(L, 2), *d = Pr<T>::w(L, 3);
   // K systems (matrix-free hierarchy only): lane k of every level vector at + k comps nodes
   FSI_REQUIRE(K == 1 || mg.stencil, FSI_E_STATE, "several systems per V-cycle need the matrix-free smoother");
-  FSI_REQUIRE((!dot.p && !fold) || (l == 0 && W == 4 && mg.stencil && l + 1 < (int)mg.lv.size()), FSI_E_STATE,
+  FSI_REQUIRE((!dot.p && !fold) || (l == 0 && W == 4 && (mg.stencil || L.q2) && l + 1 < (int)mg.lv.size()), FSI_E_STATE,
               "tile sums and updates only at the finest velocity level of a matrix-free cycle");
   const int64_t ls = (int64_t)mg.comps * L.nodes;
   if (l + 1 == (int)mg.lv.size()) {
@@ -530,7 +530,10 @@ static bool p1_tail_all(const Ctx &c) {
   PTailArgs<double, double> a;   // the larger of the two precisions
   return p1_tail_args<double>(c.mgp, 0, true, a);
 }
-static int pres_dot_count(const Ctx &c) { return p1_tail_all(c) ? 1 : p1_up_tiles(c.n); }
+static bool q2_cells(const Ctx &c) { return c.pair == FSI_PAIR_Q2P1DISC && c.mgu.lv.size() > 1; }   // the Q2 pair's cycles by cells
+static int pres_dot_count(const Ctx &c) {
+  return q2_cells(c) ? qp_up_tiles(c.n) : p1_tail_all(c) ? 1 : p1_up_tiles(c.n);
+}
 
 // z = nu M_p^{-1} r + (rho/dt) L_p^{-1} r on the pressure unknowns of K systems (lane stride lz of r
 // and z), the pinned entry r[0], and with part the parts of sum r z
@@ -584,10 +587,10 @@ static void p1_schur(Ctx &c, const double *r, double *z, int64_t lz, double *par
 }
 
 // The pressure V-cycle of the paper's pair from level l for right-hand side b; at level 0 the last launch
-// writes z = nu M_p^{-1} b + (rho/dt) (the result) and nullptr is returned, below it the level work
+// writes z = nu M_p^{-1} b + (rho/dt) (the result), with part the parts of b . z, and nullptr is returned, below it the level work
 // vector that holds the result.
 template <typename T, typename TB>
-static T *qp_cycle(Ctx &c, int l, const TB *b, TB *z, hipStream_t s) {
+static T *qp_cycle(Ctx &c, int l, const TB *b, TB *z, double *part, hipStream_t s) {
   Mg &mg = c.mgp;
   MgLevel &L = mg.lv[l], &C = mg.lv[l + 1];
   FSI_REQUIRE((std::is_same<T, float>::value ? mg.degree32 : mg.degree) == 2, FSI_E_STATE,
@@ -599,10 +602,11 @@ static T *qp_cycle(Ctx &c, int l, const TB *b, TB *z, hipStream_t s) {
     xc = Pr<T>::w(C, 0);
     dense_mv<T>((int)mg.ncoarse, Pr<T>::cinv(mg), bc, xc, 1, s);
   } else {
-    xc = qp_cycle<T, T>(c, l + 1, bc, nullptr, s);
+    xc = qp_cycle<T, T>(c, l + 1, bc, nullptr, nullptr, s);
   }
   T *y = z ? nullptr : Pr<T>::w(L, 4);
-  qp_up<T, TB>(QpUpArgs<T, TB>{L.n, b, x, xc, y, z, mp_dinv<T>(c), c2[0], c1[1], c2[1], (T)c.nu, (T)(c.rho / c.dt)}, s);
+  qp_up<T, TB>(QpUpArgs<T, TB>{L.n, b, x, xc, y, z, mp_dinv<T>(c), c2[0], c1[1], c2[1], (T)c.nu, (T)(c.rho / c.dt), part},
+              s);
   return y;
 }
 
@@ -641,7 +645,7 @@ static void a11_precond(Ctx &c, LP<const T> ru, const double *r, double *z, int 
       convert_l(LP<T>(bu, 2 * N2), ru, 2 * N2, s, K);
       ru = LP<const T>(bu, 2 * N2);
     }
-    const bool direct = (c.mgu.stencil || c.mgu.lv[0].q2) && !one;   // the last smoothing launch writes z
+    const bool direct = (c.mgu.stencil || q2_cells(c)) && !one;   // the last smoothing launch writes z
     T *xu = vcycle<T, 4, 2>(c.mgu, 0, ru, s, K == 1 && pf->on ? pf : nullptr, K,
                             direct ? LP<double>(z, nf) : LP<double>(), dot,
                             LP<const double>(dot.p && !std::is_same<T, double>::value ? r : nullptr, nf), fold,
@@ -667,12 +671,13 @@ static void a11_precond(Ctx &c, LP<const T> ru, const double *r, double *z, int 
     join();
     return;
   }
-  FSI_REQUIRE(!dot.p && K == 1, FSI_E_STATE, "the assembled form runs one system and forms no tile sums");
-  if (c.pair == FSI_PAIR_Q2P1DISC && c.mgp.lv.size() > 1) {
-    qp_cycle<T, double>(c, 0, r + 2 * N2, z + 2 * N2, sp);
+  FSI_REQUIRE(K == 1, FSI_E_STATE, "several systems take the triangle pair's matrix-free form");
+  if (q2_cells(c)) {
+    qp_cycle<T, double>(c, 0, r + 2 * N2, z + 2 * N2, dot.p ? dot.p + post3_dot_count(c.n) : nullptr, sp);
     join();
     return;
   }
+  FSI_REQUIRE(!dot.p, FSI_E_STATE, "the assembled form forms no tile sums");
   // r' = pressure residual with the pinned entry removed (keeps the operator symmetric)
   T *rp = Pr<T>::inner(c, 8).p;
   convert(rp, r + 2 * N2, Np, sp);
@@ -1005,7 +1010,8 @@ constexpr int kMsFoldParts = 4096;
 // its precision ends with the fused three-step launch on a matrix-free hierarchy of two or
 // more levels (the FP32 form for one system, on FP64 vectors).
 static bool tile_dot_ok(const Ctx &c, bool fp32) {
-  return c.mgu.stencil && c.mgu.lv.size() > 1 && (fp32 ? c.mgu.degree32 : c.mgu.degree) == 3 && c.ms_dot.p;
+  return (c.mgu.stencil || q2_cells(c)) && c.mgu.lv.size() > 1 && (fp32 ? c.mgu.degree32 : c.mgu.degree) == 3 &&
+         c.ms_dot.p;
 }
 
 // A11 launches take the step of the recurrence at their head where beta^2 has at most this many parts
@@ -1042,7 +1048,9 @@ static void ms_head(Ctx &c, const MsBufs &b, const MinresState *prev, MinresStat
   m.part = LP<double>(c.ms_part.p, a11_tile_count(c.n));
   m.word = tell.word;
   m.seq = tell.seq;
-  a11_minres(c.n, c.mgu.lv[0].af64, LP<const double>(b.y, nf), LP<double>(b.r1, nf), m, c.stream, K);
+  const LP<const double> y(b.y, nf);
+  if (q2_cells(c)) a11_minres(c.n, c.mgu.lv[0].q64, y, LP<double>(b.r1, nf), m, c.stream, K);
+  else a11_minres(c.n, c.mgu.lv[0].af64, y, LP<double>(b.r1, nf), m, c.stream, K);
 }
 
 template <typename TA>
@@ -1110,10 +1118,10 @@ static void minres_a11(Ctx &c, const double *const *b, double *const *xout, int 
                        int *its) {
   hipStream_t s = c.stream;
   const int64_t nf = 2 * c.N2 + c.Np;
-  const bool fused = c.mgu.stencil;   // matrix-free FP64 A11
+  const bool fused = c.mgu.stencil || q2_cells(c);   // matrix-free FP64 A11
   const bool in_place = fused && !tile_dot_ok(c, std::is_same<TA, float>::value);
   FSI_REQUIRE(K >= 1 && K <= c.lanes, FSI_E_ARG, "more systems than inner lanes");
-  FSI_REQUIRE(K == 1 || fused, FSI_E_STATE, "several systems per inner solve need the matrix-free smoother");
+  FSI_REQUIRE(K == 1 || c.mgu.stencil, FSI_E_STATE, "several systems per inner solve need the matrix-free smoother");
   MinresState *st = (MinresState *)c.ms_state.p;
   double *dv = (double *)st;
   double *x = c.ms_x.p;

@@ -112,7 +112,7 @@ struct MsFold {
 };
 
 // Chebyshev smoothing of a velocity level, three steps per launch (C: AfCoef<T> for the triangle pair,
-// Q2Coef<T> for the paper's, which takes no fold):
+// Q2Coef<T> for the paper's):
 // pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x.  With fold, b is the velocity
 //        part of q; q (all three parts) is written, and for T = float also the copy b.
 // post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and
@@ -147,7 +147,8 @@ struct MsA11 {
   LP<double> part;
   unsigned long long *word = nullptr, seq = 0;
 };
-void a11_minres(int n, const AfCoef<double> &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
+template <typename C>
+void a11_minres(int n, const C &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
                 int K = 1);
 int a11_tile_count(int n);
 

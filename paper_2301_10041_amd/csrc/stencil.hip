@@ -535,17 +535,13 @@ void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b,
   PreArgs<T, C> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
   const dim3 block(kWave * kCellWaves);
   if (fold) {
-    if constexpr (std::is_same<C, AfCoef<T>>::value) {
-      a.f = *fold;
-      a.np = (int64_t)(n + 1) * (n + 1);
-      a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
-      FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
-      const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
-      hipLaunchKernelGGL((k_pre3<T, C, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx,
-                         tiles, band);
-    } else {
-      FSI_REQUIRE(false, FSI_E_STATE, "the update belongs to the triangle pair");
-    }
+    a.f = *fold;
+    a.np = std::is_same<C, AfCoef<T>>::value ? (int64_t)(n + 1) * (n + 1) : 3 * (int64_t)n * n;
+    a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
+    FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
+    const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
+    hipLaunchKernelGGL((k_pre3<T, C, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx,
+                       tiles, band);
   } else {
     hipLaunchKernelGGL((k_pre3<T, C, false>), dim3((unsigned)(band * kXcd), (unsigned)K), block, 0, st, a, tx, tiles,
                        band);
@@ -742,10 +738,11 @@ FSI_RR_INST(float, Q2Coef<float>)
 // 1024^2 in 59 us, more than a copy from device memory reaches, since part of them is still in the
 // last-level cache.  One thread per node with the coefficients of its class read through the scalar
 // cache took 84 us, and 8.0 against 6.6 at 32^2.
+template <typename C>
 struct A11Args {
   int n;
-  AfCoef<double> cf;
-  double g;             // h / 6, the unit of the entries of B
+  C cf;
+  double g;             // h / 6, the unit of the entries of B (Q2 pair: h)
   const double *x;
   double *y;            // in MINRES: r1, overwritten
   int64_t lv;           // lane stride of x, y and v (lane = blockIdx.y)
@@ -756,11 +753,20 @@ struct A11Args {
 
 // the operator's rows; a step's head; the head with the step before it
 enum { A11_ROWS = 0, A11_MS = 1, A11_MS_STEP = 2 };
-template <int MODE>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int tiles_x, int tiles, int band) {
+// waves per SIMD: the paper's pair spills within the registers of four (14 us a launch at 128^2 against 10.5)
+template <typename C>
+constexpr int kA11Waves = std::is_same<C, AfCoef<double>>::value ? 4 : 2;
+template <int MODE, typename C>
+__global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args<C> a, int tiles_x, int tiles, int band) {
   constexpr bool MS = MODE != A11_ROWS, STEP = MODE == A11_MS_STEP;
+  // the paper's pair: three pressure unknowns per cell (qpressure.hip has their tensor numbers), MINRES only
+  constexpr bool Q2 = !std::is_same<C, AfCoef<double>>::value;
+  static_assert(MS || !Q2, "the operator's rows of the paper's pair are assembled");
+  constexpr int NP = Q2 ? 3 : 1;
   __shared__ V2<double> X[2 * kCellPL];
-  __shared__ double XP[(kCellWaves + 2) * kCellHW];   // P1 rows j0 - 1 .. j0 + 8; the pinned entry read as 0
+  // P1 rows j0 - 1 .. j0 + 8 (Q2 pair: cells, three planes); the pinned entry read as 0
+  constexpr int XPN = (kCellWaves + 2) * kCellHW;
+  __shared__ double XP[NP * XPN];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
   const double *xg = a.x + (int64_t)blockIdx.y * a.lv;
@@ -770,8 +776,10 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
   const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellWaves;
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
-  const bool node = i <= n && j <= n;   // the cell's P1 vertex is in the lattice
-  const int64_t q0 = (int64_t)j * (n + 1) + i;
+  const bool node = i <= n && j <= n;                    // the cell's vertex is in the lattice
+  const int np1 = Q2 ? n : n + 1;                        // pressure places per row: cells, or vertices
+  const bool pres = i < np1 && j < np1;
+  const int64_t q0 = NP * ((int64_t)j * np1 + i);
   // the step first: beta^2, and s, c and the slot as ms_step forms them, kept in LDS for the end (in
   // registers they would be live over the products, which take all there are)
   __shared__ double msc[3];   // s, c, beta^2
@@ -792,17 +800,21 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     }
   }
   {   // the pressure tile
-    constexpr int NE = (kCellWaves + 2) * kCellHW, NT = kWave * kCellWaves, IT = (NE + NT - 1) / NT;
-    double v[IT];
+    constexpr int NT = kWave * kCellWaves, IT = (XPN + NT - 1) / NT;
+    double v[IT][NP];
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
       const int e = threadIdx.x + NT * k, pi = i0 - 1 + e % kCellHW, pj = j0 - 1 + e / kCellHW;
-      const int64_t q = (int64_t)pj * (n + 1) + pi;
-      v[k] = e < NE && pi >= 0 && pj >= 0 && pi <= n && pj <= n && q != 0 ? xg[o2 + q] : 0.0;
+      const bool in = e < XPN && pi >= 0 && pj >= 0 && pi < np1 && pj < np1;
+      const int64_t q = NP * ((int64_t)pj * np1 + pi);
+#pragma unroll
+      for (int u = 0; u < NP; ++u) v[k][u] = in && q + u != 0 ? xg[o2 + q + u] : 0.0;
     }
 #pragma unroll
     for (int k = 0; k < IT; ++k)
-      if (threadIdx.x + NT * k < NE) XP[threadIdx.x + NT * k] = v[k];
+#pragma unroll
+      for (int u = 0; u < NP; ++u)
+        if (threadIdx.x + NT * k < XPN) XP[u * XPN + threadIdx.x + NT * k] = v[k][u];
   }
   stage_pairs<double, kCellH>(X, xg, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
   int ct[2][3] = {};   // C_f^T rows of the cell's nodes: consecutive on each lattice row
@@ -819,18 +831,55 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     }
   }
   V2<double> r1[4];
-  double r1p = 0.0;
-  if constexpr (MS) {   // after the staging, whose registers it takes over
+  double r1p[NP] = {};
+  auto load_r1 = [&] {
     load_cell((const double *)yg, N, L, n, i, j, r1);
-    if (node) r1p = yg[o2 + q0];
-  }
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+      if (pres) r1p[u] = yg[o2 + q0 + u];
+  };
+  if constexpr (MS) load_r1();   // after the staging, whose registers it takes over
   __syncthreads();
   V2<double> x[4], s[4];
-  double div;
-  cell_products<double, kCellPL, kCellHW, CELL_ALL, true>(X + (2 * w + 2) * kCellHW + lane + 1, a.cf, x, s, &div);
+  double xp[NP], sp[NP];
+  const V2<double> *XV = X + (2 * w + 2) * kCellHW + lane + 1;
   const double *P = XP + (w + 1) * kCellHW + lane + 1;
-  double xp = P[0];
-  {   // - B^T x_p at the edge nodes
+  if constexpr (Q2) {
+    cell_products<double, kCellPL, kCellHW>(XV, a.cf, x, s);
+    const double k6 = a.g / 6.0, k18 = a.g / 18.0, k12 = a.g / 12.0, k9 = a.g / 9.0, k23 = a.g * (2.0 / 3.0),
+                 k29 = a.g * (2.0 / 9.0), k49 = a.g * (4.0 / 9.0);
+    {   // - B^T x_p from the cells that share the node: here, left, below, below left
+      const double *Px = P + XPN, *Py = Px + XPN;
+      constexpr int D = kCellHW;
+      s[0].x -= k6 * ((P[-1] + P[-D - 1]) - (P[0] + P[-D])) + k18 * ((Px[0] + Px[-1]) + (Px[-D] + Px[-D - 1])) +
+                k12 * ((Py[0] - Py[-1]) + (Py[-D - 1] - Py[-D]));
+      s[0].y -= k6 * ((P[-D] + P[-D - 1]) - (P[0] + P[-1])) + k12 * ((Px[0] - Px[-1]) + (Px[-D - 1] - Px[-D])) +
+                k18 * ((Py[0] + Py[-1]) + (Py[-D] + Py[-D - 1]));
+      s[1].x += k9 * (Px[0] + Px[-D]);
+      s[1].y -= k23 * (P[-D] - P[0]) + k29 * (Py[0] + Py[-D]);
+      s[2].x -= k23 * (P[-1] - P[0]) + k29 * (Px[0] + Px[-1]);
+      s[2].y += k9 * (Py[0] + Py[-1]);
+      s[3].x += k49 * Px[0];
+      s[3].y += k49 * Py[0];
+      xp[0] = P[0];
+      xp[1] = Px[0];
+      xp[2] = Py[0];
+    }
+    {   // - B x_u over the cell's nine nodes
+      auto W = [&](int dI, int dJ) -> V2<double> { return XV[(dI & 1) * kCellPL + dJ * kCellHW + (dI >> 1)]; };
+      const V2<double> v00 = W(0, 0), v20 = W(2, 0), v02 = W(0, 2), v22 = W(2, 2), bo = W(1, 0), up = W(1, 2),
+                       lf = W(0, 1), rt = W(2, 1), ce = W(1, 1);
+      sp[0] = -(k6 * (((v20.x + v22.x) - (v00.x + v02.x)) + ((v02.y + v22.y) - (v00.y + v20.y))) +
+                k23 * ((rt.x - lf.x) + (up.y - bo.y)));
+      sp[1] = -(k18 * ((v00.x + v20.x) + (v02.x + v22.x)) + k12 * ((v00.y - v20.y) + (v22.y - v02.y)) -
+                k9 * (bo.x + up.x) + k29 * (lf.x + rt.x) - k49 * ce.x);
+      sp[2] = -(k18 * ((v00.y + v20.y) + (v02.y + v22.y)) + k12 * ((v00.x - v20.x) + (v22.x - v02.x)) -
+                k9 * (lf.y + rt.y) + k29 * (bo.y + up.y) - k49 * ce.y);
+    }
+  } else {
+    double div;
+    cell_products<double, kCellPL, kCellHW, CELL_ALL, true>(XV, a.cf, x, s, &div);
+    // - B^T x_p at the edge nodes
     const double p00 = P[0], p10 = P[1], p01 = P[kCellHW], p11 = P[kCellHW + 1], pm = P[-1], p0m = P[-kCellHW];
     const double d1 = p10 - p00, d2 = p01 - p00, d3 = p11 - p01, d4 = p11 - p10;
     s[1].x = fma(2.0 * a.g, d1, s[1].x);
@@ -839,6 +888,8 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     s[2].y = fma(2.0 * a.g, d2, s[2].y);
     s[3].x = fma(a.g, d1 + d3, s[3].x);
     s[3].y = fma(a.g, d2 + d4, s[3].y);
+    xp[0] = p00;
+    sp[0] = -a.g * div;
   }
   const CellIn in = cell_inside(i, j, n);
   if (i == 0 || j == 0 || i >= n || j >= n) {   // Dirichlet rows: the identity; zero outside the lattice
@@ -848,8 +899,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     for (int q = 0; q < 4; ++q)
       if (!in.q[q]) x[q] = s[q] = xb[q];
   }
-  double sp = -a.g * div;
-  if (q0 == 0) xp = sp = xg[o2];   // the pinned entry
+  if (q0 == 0) xp[0] = sp[0] = xg[o2];   // the pinned entry
   if constexpr (MS) {
     const MinresState &q = a.m.st[blockIdx.y];
     const double sc = STEP ? msc[0] : q.s, cc = STEP ? msc[1] : q.c_r1;
@@ -867,12 +917,16 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     if (node) {
       store_cell<double, double>(yg, N, L, n, i, j, s);
       store_cell<double, double>(vg, N, L, n, i, j, x);
-      sp *= sc;
-      if (cc != 0.0) sp = fma(cc, r1p, sp);
-      xp *= sc;
-      yg[o2 + q0] = sp;
-      vg[o2 + q0] = xp;
-      acc = fma(xp, sp, acc);
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        if (!pres) continue;
+        sp[u] *= sc;
+        if (cc != 0.0) sp[u] = fma(cc, r1p[u], sp[u]);
+        xp[u] *= sc;
+        yg[o2 + q0 + u] = sp[u];
+        vg[o2 + q0 + u] = xp[u];
+        acc = fma(xp[u], sp[u], acc);
+      }
     } else {
       acc = 0.0;
     }
@@ -947,7 +1001,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_a11(A11Args a, int til
     }
     if (node) {
       store_cell<double, double>(yg, N, L, n, i, j, s);
-      yg[o2 + q0] = sp;
+      yg[o2 + q0] = sp[0];
     }
   }
 }
@@ -1013,20 +1067,20 @@ void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s) {
   FSI_CHECK_LAUNCH();
 }
 
-template <int MODE>
-static void launch_a11(A11Args a, hipStream_t s, int K) {
+template <int MODE, typename C>
+static void launch_a11(A11Args<C> a, hipStream_t s, int K) {
   cell_launch_checks(a.n, K);
   int tx;
   const int tiles = cell_tiles(a.n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
-  a.g = 1.0 / (6.0 * a.n);
-  hipLaunchKernelGGL(k_a11<MODE>, dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
+  a.g = std::is_same<C, AfCoef<double>>::value ? 1.0 / (6.0 * a.n) : 1.0 / a.n;
+  hipLaunchKernelGGL((k_a11<MODE, C>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
                      tiles, band);
   FSI_CHECK_LAUNCH();
 }
 
 void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
               const double *cft_val, const double *xl, int64_t Ns, hipStream_t s) {
-  A11Args a{};
+  A11Args<AfCoef<double>> a{};
   a.n = n;
   a.cf = cf;
   a.x = x;
@@ -1039,11 +1093,12 @@ void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const
   launch_a11<A11_ROWS>(a, s, 1);
 }
 
-void a11_minres(int n, const AfCoef<double> &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
+template <typename C>
+void a11_minres(int n, const C &cf, LP<const double> y, LP<double> r1, const MsA11 &m, hipStream_t s,
                 int K) {
   FSI_REQUIRE(m.st && m.B >= 1 && m.part.p && (m.nb == 0 || (m.out && m.out != m.st)), FSI_E_ARG,
               "the A11 launch of an inner step needs its state, slots and parts");
-  A11Args a{};
+  A11Args<C> a{};
   a.n = n;
   a.cf = cf;
   a.x = y.p;
@@ -1053,6 +1108,11 @@ void a11_minres(int n, const AfCoef<double> &cf, LP<const double> y, LP<double> 
   if (m.nb > 0) launch_a11<A11_MS_STEP>(a, s, K);
   else launch_a11<A11_MS>(a, s, K);
 }
+
+template void a11_minres<AfCoef<double>>(int, const AfCoef<double> &, LP<const double>, LP<double>, const MsA11 &,
+                                         hipStream_t, int);
+template void a11_minres<Q2Coef<double>>(int, const Q2Coef<double> &, LP<const double>, LP<double>, const MsA11 &,
+                                         hipStream_t, int);
 
 int a11_tile_count(int n) {
   int tx;
