@@ -1366,7 +1366,7 @@ static int cs_steps(const Ctx &c) { return c.cs_nsteps; }
 // A block is bound by the latency of its 72 dependent steps.  Measured per application (two solves of
 // 36 steps, FP64): 127 solid nodes 318 -> 22 us, 1,800 nodes 550 -> 68 us, 676 nodes with a tangent 290
 // (72 launches) -> 40 us, against one block for both components that read its rows from device
-// memory in every step; 6,211 nodes 1,260 -> 380 us with the launches over the whole chip.
+// memory in every step; 6,211 nodes 1,260 -> 350 us with the launches over the whole chip.
 constexpr int kA22Threads = 1024, kA22Rows = 7;
 constexpr int kA22RegRows = 3;   // rows per thread with the matrix in registers (4 spill)
 struct A22Lane {
@@ -1535,7 +1535,10 @@ __global__ void __launch_bounds__(kA22Threads) k_a22_block(A22Args a, int phase)
 
 // One Chebyshev step of every system (thread = row, both components): k = 0 the step from zero.  b is
 // r_lam (second = 0) or u.  x: the buffer the step reads (t or t2); the last step also scales the
-// result out: z_X = -dt x or z_lam = -x.
+// result out: z_X = -dt x or z_lam = -x.  A launch is a chain of latencies (row entries, gathers): the
+// entries come kCsUnroll at a time, then their gathers, then the sum in row order; one entry after
+// the other took 5.2 us a launch against 3.7 at 6,211 nodes, 6.5 against 5.0 at 75,938.
+constexpr int kCsUnroll = 8;
 __global__ void __launch_bounds__(256) k_cs_step(A22Args a, int second, int k, int flip, double c1, double c2) {
   const A22Lane &L = a.lane[blockIdx.y];
   const int ns = L.ns, r = blockIdx.x * 256 + threadIdx.x;
@@ -1549,17 +1552,32 @@ __global__ void __launch_bounds__(256) k_cs_step(A22Args a, int second, int k, i
     x1 = d1 = cs_first(a.theta, cd, b[ns + r]);
   } else {
     const double *x = flip ? L.t : L.t2;
+    const double p0 = L.d[r], p1 = L.d[ns + r], b0 = b[r], b1 = b[ns + r], y0 = x[r], y1 = x[ns + r];
     double s0 = 0.0, s1 = 0.0;
-    for (int u = 0; u < L.ew; ++u) {
-      const double v = L.ecs[(size_t)u * ns + r];
-      const int c = L.ecol[(size_t)u * ns + r];
-      s0 = fma(v, x[c], s0);
-      s1 = fma(v, x[ns + c], s1);
+    for (int u0 = 0; u0 < L.ew; u0 += kCsUnroll) {
+      double v[kCsUnroll], g0[kCsUnroll], g1[kCsUnroll];
+      int c[kCsUnroll];
+#pragma unroll
+      for (int u = 0; u < kCsUnroll; ++u) {   // past the row: value 0 at its own column
+        const bool in = u0 + u < L.ew;
+        v[u] = in ? L.ecs[(size_t)(u0 + u) * ns + r] : 0.0;
+        c[u] = in ? L.ecol[(size_t)(u0 + u) * ns + r] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kCsUnroll; ++u) {
+        g0[u] = c[u] >= 0 ? x[c[u]] : 0.0;
+        g1[u] = c[u] >= 0 ? x[ns + c[u]] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < kCsUnroll; ++u) {
+        s0 = fma(v[u], g0[u], s0);
+        s1 = fma(v[u], g1[u], s1);
+      }
     }
-    d0 = cs_next(c1, c2, L.d[r], cd, b[r], s0);
-    d1 = cs_next(c1, c2, L.d[ns + r], cd, b[ns + r], s1);
-    x0 = x[r] + d0;
-    x1 = x[ns + r] + d1;
+    d0 = cs_next(c1, c2, p0, cd, b0, s0);
+    d1 = cs_next(c1, c2, p1, cd, b1, s1);
+    x0 = y0 + d0;
+    x1 = y1 + d1;
   }
   if (k + 1 == a.steps) {
     double *z = second ? L.zl : L.zX;

@@ -21,7 +21,7 @@ from gpu_helpers import rel, to_dev, to_host, torch_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [5, 6, 8, 24, 36, 60, 64, 112, 120, 160, 256, 320, 512])
+@pytest.mark.parametrize("n", [5, 6, 8, 24, 36, 48, 60, 64, 80, 112, 120, 160, 256, 320, 512])
 def test_cell_launches_equal_assembled(n):
     print(f"[cell launches n={n}]", flush=True)
     torch = torch_dev()
