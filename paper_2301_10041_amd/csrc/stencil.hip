@@ -54,10 +54,32 @@ static int64_t common_stride(std::initializer_list<std::pair<const void *, int64
 //           139 -> 118 (beside the pressure part on the other stream)
 //   512^2   28.5 -> 15.2, 18.4 -> 11.5, 41.5 -> 24.4
 //   32^2    8.6 -> 6.2, 7.9 -> 4.8, 12.0 -> 8.1
-constexpr int kCellWaves = 8;
-constexpr int kCellHW = kWave + 2;                    // plane width: a halo of one cell
-constexpr int kCellH = 2 * kCellWaves + 3;            // staged rows of 8 cell rows
-constexpr int kCellPL = kCellH * kCellHW;             // plane stride
+constexpr int kCellRows = 8;                          // cell rows of a region
+constexpr int kCellH = 2 * kCellRows + 3;             // its staged rows: a halo of one cell
+// the names of a kernel on regions of LW cells per row
+#define FSI_CELL_REGION(LW)                                                                                    \
+  constexpr int kThreads = (LW) * kCellRows, kWaves = kThreads / kWave; /* one thread per cell */              \
+  constexpr int kCellHW = (LW) + 2, kCellPL = kCellH * kCellHW;         /* plane width and stride, with halo */ \
+  const int lane = threadIdx.x % (LW), w = region_row<LW>();            /* the thread's cell */                \
+  (void)kWaves, (void)kCellPL, (void)lane, (void)w
+template <int LW>
+__device__ __forceinline__ int region_row() {
+  static_assert(LW == kWave || 2 * LW == kWave, "one or two rows per wave");
+  return LW == kWave ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : threadIdx.x / LW;
+}
+constexpr int kPreTileR = kCellRows - 2, kPostTileR = kCellRows - 4;
+template <int LW> constexpr int kPreTile = LW - 2;     // tile widths in cells (restriction: coarse cells)
+template <int LW> constexpr int kPostTile = LW - 4;
+template <int LW> constexpr int kRRTile = (LW - 3) / 2;
+
+// Regions are 64 cells wide, or 32 on grids of at most this many cells per side, whose launches leave
+// most of the chip idle: NARROW_MEASURED
+constexpr int kNarrowN = 128;
+template <typename F>
+static void by_width(int n, F f) {
+  if (n <= kNarrowN) f(std::integral_constant<int, kWave / 2>{});
+  else f(std::integral_constant<int, kWave>{});
+}
 
 // device-memory nodes (2 i, J), (2 i + 1, J) of one component of a vector
 template <typename T>
@@ -116,13 +138,13 @@ __device__ __forceinline__ void put_cell(V2<T> *X, int r, int h, const V2<T> (&q
 // x (a pair of nodes of each staged row, interior nodes only) of the region whose first cell is
 // (i0, j0), with the halo of one cell; f maps a node's value before it is stored (row parity,
 // column parity, value)
-template <typename T, int ROWS, typename F>
+template <typename T, int ROWS, int LW, typename F>
 __device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int L, int n, int i0, int j0, F f) {
-  constexpr int NT = kWave * kCellWaves, NE = ROWS * kCellHW, IT = (NE + NT - 1) / NT, PL = ROWS * kCellHW;
+  constexpr int HW = LW + 2, NT = LW * kCellRows, NE = ROWS * HW, IT = (NE + NT - 1) / NT, PL = NE;
   NodePair<T> a[IT], b[IT];
 #pragma unroll
   for (int q = 0; q < IT; ++q) {
-    const int e = threadIdx.x + NT * q, lr = e / kCellHW, i = i0 - 1 + e % kCellHW, J = 2 * (j0 - 1) + lr;
+    const int e = threadIdx.x + NT * q, lr = e / HW, i = i0 - 1 + e % HW, J = 2 * (j0 - 1) + lr;
     a[q] = b[q] = NodePair<T>{T(0), T(0)};
     if (e < NE && i >= 0 && i < n && J > 0 && J < 2 * n) {
       const int64_t r = (int64_t)J * L + 2 * i;
@@ -133,7 +155,7 @@ __device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int
   }
 #pragma unroll
   for (int q = 0; q < IT; ++q) {
-    const int e = threadIdx.x + NT * q, lr = e / kCellHW;
+    const int e = threadIdx.x + NT * q, lr = e / HW;
     if (e < NE) {
       X[e] = f(lr & 1, 0, V2<T>{a[q].a, b[q].a});
       X[PL + e] = f(lr & 1, 1, V2<T>{a[q].b, b[q].b});
@@ -163,10 +185,11 @@ struct PreArgs {
 // less per inner step: 9 us against 6.2 + 2.6 + 1.9 and two gaps at 32^2, 83 against 37 + 38 + 4 and
 // two gaps at 1024^2 (FP64); 35 at 768^2 with FP32 arithmetic, where the FP32 copy of q is written
 // here too.
-constexpr int kPreW = kWave - 2, kPreR = kCellWaves - 2;
-constexpr int kPrePres = 4 * kWave * kCellWaves;   // pressure entries per block
-template <typename T, typename C, bool MS>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, int tiles_x, int tiles, int band) {
+constexpr int kPrePres = 2048;   // pressure entries per block
+template <typename T, typename C, int LW, bool MS>
+__global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a, int tiles_x, int tiles, int band) {
+  FSI_CELL_REGION(LW);
+  constexpr int kPreW = kPreTile<LW>, kPreR = kPreTileR;
   using TS = typename std::conditional<MS, double, T>::type;   // staged first
   __shared__ V2<TS> XS[2 * kCellPL];
   V2<T> *const X = reinterpret_cast<V2<T> *>(XS);
@@ -178,7 +201,6 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, 
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
   const int i0 = (t % tiles_x) * kPreW - 1, j0 = (t / tiles_x) * kPreR - 1;   // first cell of the region
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
   const C &cf = a.cf;
   auto first = [&](int pj, int pi, V2<T> v) -> V2<T> {
@@ -191,7 +213,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, 
     const double *y1 = a.f.y1.p + lane_v, *r2 = a.f.r2.p + lane_v;
     double *q = a.f.q.p + lane_v;
     // the staged nodes (as in stage_pairs), in flight over the sum of alfa
-    constexpr int NT = kWave * kCellWaves, NE = kCellH * kCellHW, IT = (NE + NT - 1) / NT;
+    constexpr int NT = kThreads, NE = kCellH * kCellHW, IT = (NE + NT - 1) / NT;
     NodePair<double> ya[IT], yb[IT], ra[IT], rb[IT];
     if (!pres) {
 #pragma unroll
@@ -208,18 +230,18 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, 
         }
       }
     }
-    __shared__ double red[kCellWaves];
+    __shared__ double red[kWaves];
     double *alfa = a.f.alfa + (int64_t)blockIdx.y * a.f.ls;
     double al = 0.0;
     if (a.f.nparts > 0) {
       const double *part = a.f.part + (int64_t)blockIdx.y * a.f.lp;
       for (int k = threadIdx.x; k < a.f.nparts; k += NT) al += part[k];
       al = wave_sum(al);
-      if (lane == 0) red[w] = al;
+      if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = al;
       __syncthreads();
       al = 0.0;
 #pragma unroll
-      for (int k = 0; k < kCellWaves; ++k) al += red[k];
+      for (int k = 0; k < kWaves; ++k) al += red[k];
       if (blockIdx.x == 0 && threadIdx.x == 0) *alfa = al;
     } else {
       al = *alfa;
@@ -279,7 +301,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, 
     }
   } else {
     load_cell((const T *)bg, N, L, n, i, j, b);
-    stage_pairs<T, kCellH>(X, (const T *)bg, N, L, n, i0, j0, first);
+    stage_pairs<T, kCellH, LW>(X, (const T *)bg, N, L, n, i0, j0, first);
   }
   const CellIn in = cell_inside(i, j, n);
   const int row = 2 * w + 2, h = lane + 1;
@@ -322,8 +344,6 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_pre3(PreArgs<T, C> a, 
 // step runs on 8 x 64 cells, the second on the inner 6 x 62, the third on 4 x 60, the tile.
 // x is staged by coarse cells (4 x 4 fine nodes; one thread takes two of its rows), so that the
 // interpolation weights are compile-time constants and no coarse value goes through LDS.
-constexpr int kPostW = kWave - 4, kPostR = kCellWaves - 4;
-static_assert(kPostW % 2 == 0 && kPostR % 2 == 0, "tile origins on coarse cell corners");
 
 template <typename T, typename TY, typename C>
 struct PostArgs {
@@ -341,8 +361,11 @@ struct PostArgs {
   int64_t lb64;        // its lane stride
 };
 
-template <typename T, typename TY, typename C, bool DOT>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, C> a, int tiles_x, int tiles, int band) {
+template <typename T, typename TY, typename C, int LW, bool DOT>
+__global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_post3(PostArgs<T, TY, C> a, int tiles_x, int tiles, int band) {
+  FSI_CELL_REGION(LW);
+  constexpr int kPostW = kPostTile<LW>, kPostR = kPostTileR;
+  static_assert(kPostW % 2 == 0 && kPostR % 2 == 0, "tile origins on coarse cell corners");
   __shared__ V2<T> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
@@ -352,13 +375,12 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, 
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
   const int i0 = (t % tiles_x) * kPostW - 2, j0 = (t / tiles_x) * kPostR - 2;   // first cell of the region
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane, j = j0 + w;
   const C &cf = a.cf;
   {   // stage x + P xc: coarse cell (ci, cj), its fine rows 0, 1 (first four waves) or 2, 3
     constexpr int CX = (kCellHW + 2) / 2, CY = (kCellH + 4) / 4 + 1;
-    static_assert(CX * CY <= kWave * kCellWaves / 2, "two threads per coarse cell");
-    const int c = threadIdx.x % (kWave * kCellWaves / 2), half = w / (kCellWaves / 2);
+    static_assert(CX * CY <= kThreads / 2, "two threads per coarse cell");
+    const int c = threadIdx.x % (kThreads / 2), half = w / (kCellRows / 2);
     const int kx = c % CX, ky = c / CX;
     const int ci = i0 / 2 - 1 + kx, cj = j0 / 2 - 1 + ky;   // i0 and j0 are even
     const int nc = n / 2, Lc = n + 1;
@@ -449,7 +471,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, 
   __syncthreads();
   put_cell<T, kCellPL, kCellHW>(X, row, h, x);
   __syncthreads();
-  const bool in2 = w >= 1 && w <= kCellWaves - 2;
+  const bool in2 = w >= 1 && w <= kCellRows - 2;
   if (in2) {
     cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
 #pragma unroll
@@ -460,7 +482,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, 
     }
   }
   __syncthreads();
-  if (in2 && lane >= 1 && lane <= kWave - 2) put_cell<T, kCellPL, kCellHW>(X, row, h, x);
+  if (in2 && lane >= 1 && lane <= LW - 2) put_cell<T, kCellPL, kCellHW>(X, row, h, x);
   __syncthreads();
   double by = 0.0;   // the thread's part of b . y
   if (w >= 2 && w < 2 + kPostR && j <= n) {
@@ -499,20 +521,27 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4) k_post3(PostArgs<T, TY, 
     }
   }
   if constexpr (DOT) {   // the tile's sum in a fixed order: lanes by shuffles, then waves
-    __shared__ double red[kPostR];
+    __shared__ double red[kWaves];
     by = wave_sum(by);
-    if (lane == 0 && w >= 2 && w < 2 + kPostR) red[w - 2] = by;
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = by;
     __syncthreads();
     if (threadIdx.x == 0) {
       double s0 = 0.0;
 #pragma unroll
-      for (int k = 0; k < kPostR; ++k) s0 += red[k];
+      for (int k = 0; k < kWaves; ++k) s0 += red[k];
       a.dot[(int64_t)blockIdx.y * a.ldot + t] = s0;
     }
   }
 }
 
-int post3_dot_count(int n) { return ((n + kPostW) / kPostW) * ((n + kPostR) / kPostR); }
+int post3_dot_count(int n) {
+  int c = 0;
+  by_width(n, [&](auto lw) {
+    constexpr int W = kPostTile<decltype(lw)::value>;
+    c = ((n + W) / W) * ((n + kPostTileR) / kPostTileR);
+  });
+  return c;
+}
 
 // tiles of W x R cells over the n + 1 cell columns and rows that hold nodes
 static int cell_tiles(int n, int W, int R, int &tx) {
@@ -529,23 +558,23 @@ template <typename T, typename C>
 void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
           const MsFold *fold) {
   cell_launch_checks(n, K);
-  int tx;
-  const int tiles = cell_tiles(n, kPreW, kPreR, tx), band = (tiles + kXcd - 1) / kXcd;
   FSI_REQUIRE(K == 1 || (x.s > 0 && (b.s > 0 || !b.p)), FSI_E_ARG, "lane views need a stride");
   PreArgs<T, C> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
-  const dim3 block(kWave * kCellWaves);
   if (fold) {
     a.f = *fold;
     a.np = std::is_same<C, AfCoef<T>>::value ? (int64_t)(n + 1) * (n + 1) : 3 * (int64_t)n * n;
     a.f.q.s = common_stride({{a.f.y1.p, a.f.y1.s}, {a.f.r2.p, a.f.r2.s}, {a.f.q.p, a.f.q.s}}, K);
     FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
-    const unsigned gp = (unsigned)((a.np + kPrePres - 1) / kPrePres);
-    hipLaunchKernelGGL((k_pre3<T, C, true>), dim3((unsigned)(band * kXcd) + gp, (unsigned)K), block, 0, st, a, tx,
-                       tiles, band);
-  } else {
-    hipLaunchKernelGGL((k_pre3<T, C, false>), dim3((unsigned)(band * kXcd), (unsigned)K), block, 0, st, a, tx, tiles,
-                       band);
   }
+  const unsigned gp = fold ? (unsigned)((a.np + kPrePres - 1) / kPrePres) : 0u;
+  by_width(n, [&](auto lw) {
+    constexpr int LW = decltype(lw)::value;
+    int tx;
+    const int tiles = cell_tiles(n, kPreTile<LW>, kPreTileR, tx), band = (tiles + kXcd - 1) / kXcd;
+    const dim3 grid((unsigned)(band * kXcd) + gp, (unsigned)K), block(LW * kCellRows);
+    if (fold) hipLaunchKernelGGL((k_pre3<T, C, LW, true>), grid, block, 0, st, a, tx, tiles, band);
+    else hipLaunchKernelGGL((k_pre3<T, C, LW, false>), grid, block, 0, st, a, tx, tiles, band);
+  });
   FSI_CHECK_LAUNCH();
 }
 #define FSI_PRE3_INST(T, C) \
@@ -562,16 +591,19 @@ void post3(int n, const C &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T 
   cell_launch_checks(n, K);
   FSI_REQUIRE(xc.p && n % 2 == 0 && n >= 4, FSI_E_ARG, "a coarse correction needs an even fluid grid");
   FSI_REQUIRE(K == 1 || xc.s > 0, FSI_E_ARG, "lane views of the coarse correction need a stride");
-  int tx;
-  const int tiles = cell_tiles(n, kPostW, kPostR, tx), band = (tiles + kXcd - 1) / kXcd;
   FSI_REQUIRE(K == 1 || (x.s > 0 && b.s > 0 && y.s > 0), FSI_E_ARG, "lane views need a stride");
-  FSI_REQUIRE(!dot.p || K == 1 || dot.s >= tiles, FSI_E_ARG, "lane stride of the tile sums too small");
+  FSI_REQUIRE(!dot.p || K == 1 || dot.s >= post3_dot_count(n), FSI_E_ARG, "lane stride of the tile sums too small");
   FSI_REQUIRE(!b64.p || (dot.p && (K == 1 || b64.s > 0) && !std::is_same<T, double>::value), FSI_E_ARG,
               "an FP64 right-hand side only for the sums of the FP32 form");
   PostArgs<T, TY, C> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, x.s, b.s, y.s, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
-  const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(kWave * kCellWaves);
-  if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, C, true>), grid, block, 0, st, a, tx, tiles, band);
-  else hipLaunchKernelGGL((k_post3<T, TY, C, false>), grid, block, 0, st, a, tx, tiles, band);
+  by_width(n, [&](auto lw) {
+    constexpr int LW = decltype(lw)::value;
+    int tx;
+    const int tiles = cell_tiles(n, kPostTile<LW>, kPostTileR, tx), band = (tiles + kXcd - 1) / kXcd;
+    const dim3 grid((unsigned)(band * kXcd), (unsigned)K), block(LW * kCellRows);
+    if (dot.p) hipLaunchKernelGGL((k_post3<T, TY, C, LW, true>), grid, block, 0, st, a, tx, tiles, band);
+    else hipLaunchKernelGGL((k_post3<T, TY, C, LW, false>), grid, block, 0, st, a, tx, tiles, band);
+  });
   FSI_CHECK_LAUNCH();
 }
 #define FSI_POST3_INST(T, TY, C)                                                                                 \
@@ -594,7 +626,6 @@ FSI_POST3_INST(float, double, Q2Coef<float>)
 // rows.  Q = 2 recomputes less (15 rows for 6 coarse rows, against 7 for 2) and is taken where
 // that leaves the chip enough blocks; Q = 1 shortens the two dependent passes of a block.
 // The restriction runs by coarse classes, one per wave pass, with compile-time weights.
-constexpr int kRRc = (kWave - 3) / 2;
 
 template <typename T, typename C>
 struct ResidRestrArgs {
@@ -605,12 +636,14 @@ struct ResidRestrArgs {
   int64_t lx, lb, lc;   // lane strides of x, b and bc
 };
 
-template <typename T, typename C, int Q>
-__global__ void __launch_bounds__(kWave *kCellWaves, 4)
+template <typename T, typename C, int LW, int Q>
+__global__ void __launch_bounds__(LW *kCellRows, LW / 16)
     k_resid_restrict(ResidRestrArgs<T, C> a, int tiles_x, int tiles, int band) {
-  constexpr int ROWS = 2 * kCellWaves * Q + 3, PL = ROWS * kCellHW;
-  constexpr int CR = (kCellWaves * Q - 3) / 2;                      // coarse rows
-  constexpr int RH = 2 * kCellWaves * Q, RPL = RH * kWave;          // residual planes
+  FSI_CELL_REGION(LW);
+  constexpr int kRRc = kRRTile<LW>;
+  constexpr int ROWS = 2 * kCellRows * Q + 3, PL = ROWS * kCellHW;
+  constexpr int CR = (kCellRows * Q - 3) / 2;                      // coarse rows
+  constexpr int RH = 2 * kCellRows * Q, RPL = RH * LW;          // residual planes
   static_assert(RPL <= PL, "the residual fits over the staged x");
   __shared__ V2<T> X[2 * PL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
@@ -621,11 +654,10 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
   const int64_t N = (int64_t)L * L, Nc = (int64_t)Lc * Lc;
   const int C0 = (t % tiles_x) * kRRc, R0 = (t / tiles_x) * CR;     // first coarse cell of the tile
   const int i0 = 2 * C0 - 2, j0 = 2 * R0 - 2;                       // first fine cell of the region
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int i = i0 + lane;
   const C &cf = a.cf;
   V2<T> b[Q][4];
-  stage_pairs<T, ROWS>(X, xg, N, L, n, i0, j0, [](int, int, V2<T> v) -> V2<T> { return v; });
+  stage_pairs<T, ROWS, LW>(X, xg, N, L, n, i0, j0, [](int, int, V2<T> v) -> V2<T> { return v; });
   load_cell(bg, N, L, n, i, j0 + w * Q, b[0]);   // after the staging, whose registers it takes over
   __syncthreads();
 #pragma unroll
@@ -642,12 +674,12 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
   __syncthreads();   // every wave has read x: r goes over it
   V2<T> *const R = X;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) put_cell<T, RPL, kWave>(R, 2 * (w * Q + q), lane, b[q]);
+  for (int q = 0; q < Q; ++q) put_cell<T, RPL, LW>(R, 2 * (w * Q + q), lane, b[q]);
   __syncthreads();
   // coarse classes (vertex, (1, 0), (0, 1), (1, 1)) of the kRRc x CR coarse cells, 64 cells a pass
   constexpr int NC = kRRc * CR, PASS = (NC + kWave - 1) / kWave;
-  for (int u = w; u < 4 * PASS; u += kCellWaves) {
-    const int c = (u >> 2) * kWave + lane;
+  for (int u = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); u < 4 * PASS; u += kWaves) {
+    const int c = (u >> 2) * kWave + threadIdx.x % kWave;
     if (c >= NC) continue;
     const int ck = c % kRRc, cr = c / kRRc;
     auto gather = [&](auto pa_tag, auto pb_tag) {
@@ -657,7 +689,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
       V2<T> sum{T(0), T(0)};
       if (Ic > 0 && Jc > 0 && Ic < n && Jc < n) {
         // fine node (2 Ic + dI, 2 Jc + dJ) relative to the region's first node (2 i0, 2 j0)
-        const V2<T> *r = R + (4 * cr + 4) * kWave + 2 * ck + 2;
+        const V2<T> *r = R + (4 * cr + 4) * LW + 2 * ck + 2;
         auto row = [&](auto dj_tag) {
           constexpr int DJ = decltype(dj_tag)::value;
           auto term = [&](auto di_tag) {
@@ -665,7 +697,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, 4)
             constexpr double wt = restrict_weight_of<TransferOf<C>>(PA, PB, DI, DJ);
             if constexpr (wt != 0.0) {
               constexpr int u0 = 2 * PA + DI, v0 = 2 * PB + DJ;
-              const V2<T> v = r[(u0 & 1) * RPL + v0 * kWave + (u0 >> 1)];
+              const V2<T> v = r[(u0 & 1) * RPL + v0 * LW + (u0 >> 1)];
               sum.x = fma(T(wt), v.x, sum.x);
               sum.y = fma(T(wt), v.y, sum.y);
             }
@@ -708,15 +740,16 @@ void resid_restrict(int nf, const C &cf, LP<const T> x, LP<const T> b, LP<T> bc,
   FSI_REQUIRE(nf % 2 == 0 && nf >= 4, FSI_E_ARG, "restriction needs an even fluid grid");
   FSI_REQUIRE(K == 1 || (x.s > 0 && b.s > 0 && bc.s > 0), FSI_E_ARG, "lane views need a stride");
   ResidRestrArgs<T, C> a{nf, cf, x.p, b.p, bc.p, x.s, b.s, bc.s};
-  auto go = [&](auto q_tag) {
-    constexpr int Q = decltype(q_tag)::value;
+  auto go = [&](auto lw, auto q_tag) {
+    constexpr int LW = decltype(lw)::value, Q = decltype(q_tag)::value;
     int tx;
-    const int tiles = cell_tiles(nf / 2, kRRc, (kCellWaves * Q - 3) / 2, tx), band = (tiles + kXcd - 1) / kXcd;
-    hipLaunchKernelGGL((k_resid_restrict<T, C, Q>), dim3((unsigned)(band * kXcd), (unsigned)K),
-                       dim3(kWave * kCellWaves), 0, s, a, tx, tiles, band);
+    const int tiles = cell_tiles(nf / 2, kRRTile<LW>, (kCellRows * Q - 3) / 2, tx), band = (tiles + kXcd - 1) / kXcd;
+    hipLaunchKernelGGL((k_resid_restrict<T, C, LW, Q>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(LW * kCellRows),
+                       0, s, a, tx, tiles, band);
   };
-  if (nf >= kRestrictWideN) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 1>{});
+  static_assert(kNarrowN < kRestrictWideN, "the larger tile is for wide regions");
+  if (nf >= kRestrictWideN) go(std::integral_constant<int, kWave>{}, std::integral_constant<int, 2>{});
+  else by_width(nf, [&](auto lw) { go(lw, std::integral_constant<int, 1>{}); });
   FSI_CHECK_LAUNCH();
 }
 #define FSI_RR_INST(T, C) \
@@ -756,16 +789,18 @@ enum { A11_ROWS = 0, A11_MS = 1, A11_MS_STEP = 2 };
 // waves per SIMD: the paper's pair spills within the registers of four (14 us a launch at 128^2 against 10.5)
 template <typename C>
 constexpr int kA11Waves = std::is_same<C, AfCoef<double>>::value ? 4 : 2;
-template <int MODE, typename C>
-__global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args<C> a, int tiles_x, int tiles, int band) {
+template <int MODE, typename C, int LW>
+__global__ void __launch_bounds__(LW *kCellRows, kA11Waves<C> * LW / kWave) k_a11(A11Args<C> a, int tiles_x, int tiles, int band) {
+  FSI_CELL_REGION(LW);
   constexpr bool MS = MODE != A11_ROWS, STEP = MODE == A11_MS_STEP;
   // the paper's pair: three pressure unknowns per cell (qpressure.hip has their tensor numbers), MINRES only
   constexpr bool Q2 = !std::is_same<C, AfCoef<double>>::value;
+  static_assert(MS || LW == kWave, "the C_f^T rows of a wave are one row of cells");
   static_assert(MS || !Q2, "the operator's rows of the paper's pair are assembled");
   constexpr int NP = Q2 ? 3 : 1;
   __shared__ V2<double> X[2 * kCellPL];
   // P1 rows j0 - 1 .. j0 + 8 (Q2 pair: cells, three planes); the pinned entry read as 0
-  constexpr int XPN = (kCellWaves + 2) * kCellHW;
+  constexpr int XPN = (kCellRows + 2) * kCellHW;
   __shared__ double XP[NP * XPN];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
@@ -773,8 +808,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
   double *yg = a.y + (int64_t)blockIdx.y * a.lv;
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L, o2 = 2 * N;
-  const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellWaves;
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int i0 = (t % tiles_x) * LW, j0 = (t / tiles_x) * kCellRows;
   const int i = i0 + lane, j = j0 + w;
   const bool node = i <= n && j <= n;                    // the cell's vertex is in the lattice
   const int np1 = Q2 ? n : n + 1;                        // pressure places per row: cells, or vertices
@@ -785,7 +819,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
   __shared__ double msc[3];   // s, c, beta^2
   if constexpr (STEP) {
     __shared__ double bred[1024 / kWave];
-    const double beta2 = ms_beta2<kWave * kCellWaves>(a.m.bpart.p + (int64_t)blockIdx.y * a.m.bpart.s, a.m.nb, bred);
+    const double beta2 = ms_beta2<kThreads>(a.m.bpart.p + (int64_t)blockIdx.y * a.m.bpart.s, a.m.nb, bred);
     if (threadIdx.x == 0) {
       const MinresState &q = a.m.st[blockIdx.y];
       double sc = q.s, cc = q.c_r1;
@@ -800,7 +834,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
     }
   }
   {   // the pressure tile
-    constexpr int NT = kWave * kCellWaves, IT = (XPN + NT - 1) / NT;
+    constexpr int NT = kThreads, IT = (XPN + NT - 1) / NT;
     double v[IT][NP];
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
@@ -816,7 +850,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
       for (int u = 0; u < NP; ++u)
         if (threadIdx.x + NT * k < XPN) XP[u * XPN + threadIdx.x + NT * k] = v[k][u];
   }
-  stage_pairs<double, kCellH>(X, xg, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
+  stage_pairs<double, kCellH, LW>(X, xg, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
   int ct[2][3] = {};   // C_f^T rows of the cell's nodes: consecutive on each lattice row
   if constexpr (!MS) {
     if (node && a.cft_rp) {
@@ -930,14 +964,14 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
     } else {
       acc = 0.0;
     }
-    __shared__ double red[kCellWaves];   // the tile's part of v . y in a fixed order
+    __shared__ double red[kWaves];   // the tile's part of v . y in a fixed order
     acc = wave_sum(acc);
-    if (lane == 0) red[w] = acc;
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
       double b = 0.0;
 #pragma unroll
-      for (int k = 0; k < kCellWaves; ++k) b += red[k];
+      for (int k = 0; k < kWaves; ++k) b += red[k];
       a.m.part.p[(int64_t)blockIdx.y * a.m.part.s + t] = b;
       if constexpr (STEP) {
         if (blockIdx.x == 0) {
@@ -956,7 +990,7 @@ __global__ void __launch_bounds__(kWave *kCellWaves, kA11Waves<C>) k_a11(A11Args
       // thread sums its own rows there in their order.  A thread that walks its rows in device
       // memory instead: 194 us at 1024^2 with 2.8 M entries, against
       // 98 (141 with one thread per node; 115 without fetching a segment ahead).
-      constexpr int CH = 2 * kCellPL / kCellWaves / kWave * kWave;
+      constexpr int CH = 2 * kCellPL / kCellRows / kWave * kWave;
       V2<double> *const buf = X + w * CH;
       const int last = min(n - i0, kWave - 1);   // the wave's last lane in the lattice
       __syncthreads();
@@ -1017,16 +1051,16 @@ struct MassArgs {
   double *b;
 };
 
-__global__ void __launch_bounds__(kWave *kCellWaves) k_mass(MassArgs a, int tiles_x, int tiles, int band) {
+__global__ void __launch_bounds__(kWave *kCellRows) k_mass(MassArgs a, int tiles_x, int tiles, int band) {
+  FSI_CELL_REGION(kWave);
   __shared__ V2<double> X[2 * kCellPL];
   const int t = (blockIdx.x % kXcd) * band + blockIdx.x / kXcd;
   if (t >= tiles) return;
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
-  const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellWaves;
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int i0 = (t % tiles_x) * kWave, j0 = (t / tiles_x) * kCellRows;
   const int i = i0 + lane, j = j0 + w;
-  stage_pairs<double, kCellH>(X, a.u, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
+  stage_pairs<double, kCellH, kWave>(X, a.u, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
   __syncthreads();
   if (i > n || j > n) return;
   const V2<double> *p = X + (2 * w + 2) * kCellHW + lane + 1;
@@ -1061,19 +1095,19 @@ __global__ void __launch_bounds__(kWave *kCellWaves) k_mass(MassArgs a, int tile
 void mass_rows(int n, double rdt, const double *u, double *b, hipStream_t s) {
   cell_launch_checks(n, 1);
   int tx;
-  const int tiles = cell_tiles(n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
-  hipLaunchKernelGGL(k_mass, dim3((unsigned)(band * kXcd)), dim3(kWave * kCellWaves), 0, s,
+  const int tiles = cell_tiles(n, kWave, kCellRows, tx), band = (tiles + kXcd - 1) / kXcd;
+  hipLaunchKernelGGL(k_mass, dim3((unsigned)(band * kXcd)), dim3(kWave * kCellRows), 0, s,
                      MassArgs{n, rdt / (720.0 * n * n), u, b}, tx, tiles, band);
   FSI_CHECK_LAUNCH();
 }
 
-template <int MODE, typename C>
+template <int MODE, int LW, typename C>
 static void launch_a11(A11Args<C> a, hipStream_t s, int K) {
   cell_launch_checks(a.n, K);
   int tx;
-  const int tiles = cell_tiles(a.n, kWave, kCellWaves, tx), band = (tiles + kXcd - 1) / kXcd;
+  const int tiles = cell_tiles(a.n, LW, kCellRows, tx), band = (tiles + kXcd - 1) / kXcd;
   a.g = std::is_same<C, AfCoef<double>>::value ? 1.0 / (6.0 * a.n) : 1.0 / a.n;
-  hipLaunchKernelGGL((k_a11<MODE, C>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(kWave * kCellWaves), 0, s, a, tx,
+  hipLaunchKernelGGL((k_a11<MODE, C, LW>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(LW * kCellRows), 0, s, a, tx,
                      tiles, band);
   FSI_CHECK_LAUNCH();
 }
@@ -1090,7 +1124,7 @@ void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const
   a.cft_val = cft_val;
   a.xlx = xl;
   a.xly = xl ? xl + Ns : nullptr;
-  launch_a11<A11_ROWS>(a, s, 1);
+  launch_a11<A11_ROWS, kWave>(a, s, 1);
 }
 
 template <typename C>
@@ -1105,8 +1139,11 @@ void a11_minres(int n, const C &cf, LP<const double> y, LP<double> r1, const MsA
   a.y = r1.p;
   a.lv = common_stride({{y.p, y.s}, {r1.p, r1.s}}, K);
   a.m = m;
-  if (m.nb > 0) launch_a11<A11_MS_STEP>(a, s, K);
-  else launch_a11<A11_MS>(a, s, K);
+  by_width(n, [&](auto lw) {
+    constexpr int LW = decltype(lw)::value;
+    if (m.nb > 0) launch_a11<A11_MS_STEP, LW>(a, s, K);
+    else launch_a11<A11_MS, LW>(a, s, K);
+  });
 }
 
 template void a11_minres<AfCoef<double>>(int, const AfCoef<double> &, LP<const double>, LP<double>, const MsA11 &,
@@ -1115,8 +1152,9 @@ template void a11_minres<Q2Coef<double>>(int, const Q2Coef<double> &, LP<const d
                                          hipStream_t, int);
 
 int a11_tile_count(int n) {
-  int tx;
-  return cell_tiles(n, kWave, kCellWaves, tx);
+  int c = 0, tx;
+  by_width(n, [&](auto lw) { c = cell_tiles(n, decltype(lw)::value, kCellRows, tx); });
+  return c;
 }
 
 }  // namespace fsi
