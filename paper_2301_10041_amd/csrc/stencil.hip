@@ -64,7 +64,7 @@ constexpr int kCellH = 2 * kCellRows + 3;             // its staged rows: a halo
   (void)kWaves, (void)kCellPL, (void)lane, (void)w
 template <int LW>
 __device__ __forceinline__ int region_row() {
-  static_assert(LW == kWave || 2 * LW == kWave, "one or two rows per wave");
+  static_assert(LW == kWave || 2 * LW == kWave || 4 * LW == kWave, "whole rows per wave");
   return LW == kWave ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : threadIdx.x / LW;
 }
 constexpr int kPreTileR = kCellRows - 2, kPostTileR = kCellRows - 4;
@@ -72,12 +72,23 @@ template <int LW> constexpr int kPreTile = LW - 2;     // tile widths in cells (
 template <int LW> constexpr int kPostTile = LW - 4;
 template <int LW> constexpr int kRRTile = (LW - 3) / 2;
 
-// Regions are 64 cells wide, or 32 on grids of at most this many cells per side, whose launches leave
-// most of the chip idle: NARROW_MEASURED
-constexpr int kNarrowN = 128;
+// Regions are 64 cells wide, narrower on grids whose launches leave most of the chip idle: a block's waves
+// queue for the LDS and the FP64 units of one CU, and twice the blocks of half as many waves queue
+// less.  Kernel times at 64 / 32 / 16 cells in us:
+//   smoothing      32^2 (FP64, in MINRES) 8.5 and 7.5 / 7.1 and 6.5 / 6.2 and 6.0; 64^2 level 6.1 and 8.2
+//                  / 5.8 and 6.2 / 5.1 and 5.9; 256^2 (FP32) 9.3 and 10.5 / 8.6 and 9.4, 512^2 in FP64 23
+//                  and 27 at 64, where the halo's recomputation begins to count
+//   restriction    32^2 4.8 / 4.2 / 4.5
+//   A11 rows       32^2 8.0 / 7.8 / 8.9 (two waves sum beta^2), 256^2 10.2 / 11.4
 template <typename F>
-static void by_width(int n, F f) {
-  if (n <= kNarrowN) f(std::integral_constant<int, kWave / 2>{});
+static void smooth_width(int n, F f) {
+  if (n <= 64) f(std::integral_constant<int, kWave / 4>{});
+  else if (n <= 256) f(std::integral_constant<int, kWave / 2>{});
+  else f(std::integral_constant<int, kWave>{});
+}
+template <typename F>
+static void rows_width(int n, F f) {   // restriction and A11
+  if (n <= 128) f(std::integral_constant<int, kWave / 2>{});
   else f(std::integral_constant<int, kWave>{});
 }
 
@@ -536,7 +547,7 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_post3(PostArgs<T, TY
 
 int post3_dot_count(int n) {
   int c = 0;
-  by_width(n, [&](auto lw) {
+  smooth_width(n, [&](auto lw) {
     constexpr int W = kPostTile<decltype(lw)::value>;
     c = ((n + W) / W) * ((n + kPostTileR) / kPostTileR);
   });
@@ -567,7 +578,7 @@ void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b,
     FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
   }
   const unsigned gp = fold ? (unsigned)((a.np + kPrePres - 1) / kPrePres) : 0u;
-  by_width(n, [&](auto lw) {
+  smooth_width(n, [&](auto lw) {
     constexpr int LW = decltype(lw)::value;
     int tx;
     const int tiles = cell_tiles(n, kPreTile<LW>, kPreTileR, tx), band = (tiles + kXcd - 1) / kXcd;
@@ -596,7 +607,7 @@ void post3(int n, const C &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T 
   FSI_REQUIRE(!b64.p || (dot.p && (K == 1 || b64.s > 0) && !std::is_same<T, double>::value), FSI_E_ARG,
               "an FP64 right-hand side only for the sums of the FP32 form");
   PostArgs<T, TY, C> a{n, cf, x.p, b.p, y.p, c2a, c1b, c2b, c1c, c2c, x.s, b.s, y.s, xc.p, xc.s, dot.p, dot.s, b64.p, b64.s};
-  by_width(n, [&](auto lw) {
+  smooth_width(n, [&](auto lw) {
     constexpr int LW = decltype(lw)::value;
     int tx;
     const int tiles = cell_tiles(n, kPostTile<LW>, kPostTileR, tx), band = (tiles + kXcd - 1) / kXcd;
@@ -747,9 +758,8 @@ void resid_restrict(int nf, const C &cf, LP<const T> x, LP<const T> b, LP<T> bc,
     hipLaunchKernelGGL((k_resid_restrict<T, C, LW, Q>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(LW * kCellRows),
                        0, s, a, tx, tiles, band);
   };
-  static_assert(kNarrowN < kRestrictWideN, "the larger tile is for wide regions");
   if (nf >= kRestrictWideN) go(std::integral_constant<int, kWave>{}, std::integral_constant<int, 2>{});
-  else by_width(nf, [&](auto lw) { go(lw, std::integral_constant<int, 1>{}); });
+  else rows_width(nf, [&](auto lw) { go(lw, std::integral_constant<int, 1>{}); });
   FSI_CHECK_LAUNCH();
 }
 #define FSI_RR_INST(T, C) \
@@ -790,7 +800,7 @@ enum { A11_ROWS = 0, A11_MS = 1, A11_MS_STEP = 2 };
 template <typename C>
 constexpr int kA11Waves = std::is_same<C, AfCoef<double>>::value ? 4 : 2;
 template <int MODE, typename C, int LW>
-__global__ void __launch_bounds__(LW *kCellRows, kA11Waves<C> * LW / kWave) k_a11(A11Args<C> a, int tiles_x, int tiles, int band) {
+__global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 ? kA11Waves<C> * LW / kWave : 1)) k_a11(A11Args<C> a, int tiles_x, int tiles, int band) {
   FSI_CELL_REGION(LW);
   constexpr bool MS = MODE != A11_ROWS, STEP = MODE == A11_MS_STEP;
   // the paper's pair: three pressure unknowns per cell (qpressure.hip has their tensor numbers), MINRES only
@@ -1139,7 +1149,7 @@ void a11_minres(int n, const C &cf, LP<const double> y, LP<double> r1, const MsA
   a.y = r1.p;
   a.lv = common_stride({{y.p, y.s}, {r1.p, r1.s}}, K);
   a.m = m;
-  by_width(n, [&](auto lw) {
+  rows_width(n, [&](auto lw) {
     constexpr int LW = decltype(lw)::value;
     if (m.nb > 0) launch_a11<A11_MS_STEP, LW>(a, s, K);
     else launch_a11<A11_MS, LW>(a, s, K);
@@ -1153,7 +1163,7 @@ template void a11_minres<Q2Coef<double>>(int, const Q2Coef<double> &, LP<const d
 
 int a11_tile_count(int n) {
   int c = 0, tx;
-  by_width(n, [&](auto lw) { c = cell_tiles(n, decltype(lw)::value, kCellRows, tx); });
+  rows_width(n, [&](auto lw) { c = cell_tiles(n, decltype(lw)::value, kCellRows, tx); });
   return c;
 }
 

@@ -1,14 +1,15 @@
-"""The velocity cycle's launches by cells (pre-smoothing tiles of 62 x 6 cells, post-smoothing 60 x 4,
-residual and restriction 30 x 2 coarse cells and, from 256^2 on, 30 x 6) at grids where their tiles
-end: one cell past a tile (60, 120), ragged last tiles (112, 160), and both sides of the rule that
-gives the restriction its larger tile; and the pressure part's (descent 29 x 5 coarse nodes, ascent
-60 x 12, from 512^2 on 29 x 13 and 60 x 28; the one-launch coarse end from 64^2 down, with the output
-where it starts on the finest level): a grid with one level (5), a coarse end alone (6 to 64, dense
-levels of 16 to 256 unknowns), one and more levels above it.  The matrix-free preconditioner equals the one on the
+"""The velocity cycle's launches by cells (regions of 64, 32 or 16 x 8 cells by the size of the grid:
+pre-smoothing tiles of 62, 30 or 14 x 6 cells, post-smoothing 60, 28 or 12 x 4, residual and restriction
+30 or 14 x 2 coarse cells and, from 256^2 on, 30 x 6) at grids where their tiles end: ragged last tiles
+(24, 36, 48, 80, 112, 160), one cell past a tile (60, 120) and both sides of the rules that choose the
+width; and the pressure part's (descent 29 x 5 coarse nodes, ascent 60 x 12, from 512^2 on 29 x 13 and
+60 x 28; the one-launch coarse end from 64^2 down, with the output where it starts on the finest
+level): a grid with one level (5), a coarse end alone (6 to 64, dense levels of 16 to 256 unknowns), one
+and more levels above it.  The matrix-free preconditioner equals the one on the
 assembled operators (fsi_set_smoother) up to the order of the sums, in velocity and pressure each (a
 few hundred roundings of a well conditioned cycle): one application in both precisions.
 
-The A11 rows by cells (tiles of 64 x 8 cells) are held against sums in extended precision: every
+The A11 rows by cells (tiles of 64 or 32 x 8 cells) are held against sums in extended precision: every
 row of A_f, B^T and B from its closed form, entry by entry within 64 roundings of |A| |x| (a row has
 at most 38 products, B^T 4 more, in sums of depth under 30)."""
 import numpy as np
