@@ -275,10 +275,12 @@ inline void lincomb(T *z, const T *x, const T *y, T a, T b, int64_t n, hipStream
 // ------------------------------------------------------------------ reductions
 // Multi-dot: out[i] = sum_e V_i[e] * w[e] for i < k, V_i = V + i * ldv.  Accumulates in
 // FP64.  Fixed partition into `nb` chunks (a function of n only) and fixed order.
+// A chunk of 1,024 entries is four per thread: with four times that the launches of a small system
+// had too few blocks (85 k entries: 21 blocks and 20 us for a Gram-Schmidt pass, against 8.6).
 constexpr int kRedBlock = 256;
 
 inline int red_blocks(int64_t n) {
-  int64_t nb = (n + 4095) / 4096;
+  int64_t nb = (n + 1023) / 1024;
   if (nb > 1024) nb = 1024;
   if (nb < 1) nb = 1;
   return (int)nb;
