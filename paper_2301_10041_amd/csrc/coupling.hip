@@ -1017,25 +1017,51 @@ __global__ void __launch_bounds__(kClipBlock)
 // inc[0] |= IF_PATTERN when a moved element's kept pieces, read in slot order, differ from
 // its previous ones.  A box that shifted with the same pieces keeps the piece list (and so
 // every row of C_f, with its sums in the same order).
-__global__ void k_inc_cmp(int64_t nt, const int *__restrict__ cand_off, const int *__restrict__ moved,
-                          const int *__restrict__ pair_T, const int *__restrict__ prevT, int *inc) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nt || !moved[e]) return;
-  const int64_t s1 = 2 * (int64_t)cand_off[e + 1];
-  int64_t a = 2 * (int64_t)cand_off[e], b = a;
+// One wavefront per element, 64 slots of either list at a time: the kept entries are numbered by
+// ballots, the previous ones put down by their number, the present ones compared with theirs (one
+// thread per element walked both lists: 34 us for 5,600 elements of 18 slots, now under 5).
+constexpr int kIncWaves = 4;
+__global__ void __launch_bounds__(kWave *kIncWaves)
+    k_inc_cmp(int64_t nt, const int *__restrict__ cand_off, const int *__restrict__ moved,
+              const int *__restrict__ pair_T, const int *__restrict__ prevT, int *inc) {
+  __shared__ int prev[kIncWaves][kWave];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int64_t e = (int64_t)blockIdx.x * kIncWaves + w;
+  if (e >= nt || !moved[e]) return;   // a wavefront is on its own: no block barrier below
+  const int64_t s0 = 2 * (int64_t)cand_off[e], s1 = 2 * (int64_t)cand_off[e + 1];
+  const uint64_t below = (1ull << lane) - 1;
+  // the k-th kept entry of either list, from position pos on, into v (lane k of a group of up to 64)
+  auto next = [&](const int *list, int64_t &pos, int &count) -> int {
+    int v = -1;
+    count = 0;
+    while (pos < s1 && count < kWave) {
+      const int64_t p = pos + lane;
+      const int t = p < s1 ? list[p] : -1;
+      uint64_t kept = __ballot(t >= 0);
+      const int n = __popcll(kept), take = min(n, kWave - count), r = __popcll(kept & below);
+      wave_fence();
+      if (t >= 0 && r < take) prev[w][count + r] = t;
+      wave_fence();
+      if (lane >= count && lane < count + take) v = prev[w][lane];
+      count += take;
+      if (take == n) {
+        pos += kWave;
+      } else {   // up to and with the last one taken
+        for (int k = 0; k + 1 < take; ++k) kept &= kept - 1;
+        pos += take > 0 ? __ffsll((unsigned long long)kept) : 0;
+      }
+    }
+    return v;
+  };
+  int64_t a = s0, b = s0;
   for (;;) {
-    while (a < s1 && pair_T[a] < 0) ++a;
-    while (b < s1 && prevT[b] < 0) ++b;
-    if (a == s1 || b == s1) {
-      if (a != s1 || b != s1) atomicOr(&inc[0], IF_PATTERN);
+    int na, nb;
+    const int va = next(pair_T, a, na), vb = next(prevT, b, nb);
+    if (__ballot(va != vb)) {   // also where one list has an entry more: -1 there
+      if (lane == 0) atomicOr(&inc[0], IF_PATTERN);
       return;
     }
-    if (pair_T[a] != prevT[b]) {
-      atomicOr(&inc[0], IF_PATTERN);
-      return;
-    }
-    ++a;
-    ++b;
+    if (na < kWave) return;   // both lists are at their ends
   }
 }
 
@@ -1086,7 +1112,7 @@ static void assemble_incremental(Ctx &c, const double *Xn) {
     hipLaunchKernelGGL(k_inc_emit, dim3(grid_for(c.n_cand, kClipBlock)), dim3(kClipBlock), 0, s, c.n_cand, nt, ns, n, Xn,
                        c.tri.p, c.ref_area.p, c.cand_off.p, c.inc_moved.p, c.pair_E.p, c.pair_T.p, c.inc_prevT.p,
                        c.piece_L.p, inc);
-    hipLaunchKernelGGL(k_inc_cmp, dim3(grid_for(nt, 256)), dim3(256), 0, s, nt, c.cand_off.p, c.inc_moved.p,
+    hipLaunchKernelGGL(k_inc_cmp, dim3(grid_for(nt, kIncWaves)), dim3(kWave * kIncWaves), 0, s, nt, c.cand_off.p, c.inc_moved.p,
                        c.pair_T.p, c.inc_prevT.p, inc);
     FSI_CHECK_LAUNCH();
     FSI_HIP(hipMemcpyAsync(c.inc_X.p, Xn, 2 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
