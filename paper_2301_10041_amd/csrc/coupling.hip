@@ -22,6 +22,7 @@
 // opposite signs, with the axis coordinate set to the line value; keep a piece iff its fan
 // area from vertex 0 exceeds 5e-11 h^2.  This file is compiled with -ffp-contract=off so
 // that no product is fused into an addition.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -192,6 +193,28 @@ __device__ __forceinline__ int find_owner(const int *off, int64_t nt, int64_t c)
   return (int)lo;
 }
 
+// The same for a whole wavefront with the consecutive candidates c0 + lane (c0 < off[nt]): the owner of
+// the first one by 64 probes at a time (three dependent loads for up to 262,144 elements against the 18
+// of a halving), the others' among the next 64 offsets.  Every lane takes part; a lane past the last
+// candidate gets some element.
+__device__ __forceinline__ int find_owner_wave(const int *off, int64_t nt, int64_t c0) {
+  const int lane = threadIdx.x % kWave;
+  int64_t lo = 0, hi = nt;
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave, p = lo + lane * step;
+    const int k = __popcll(__ballot(p < hi && off[p] <= c0)) - 1;   // lane 0's holds
+    lo += k * step;
+    hi = min(hi, lo + step);
+  }
+  const int64_t c = c0 + lane;
+  const int v = off[min(lo + 1 + lane, nt)], vlast = __shfl(v, kWave - 1);
+  int k = 0;
+  for (int step = kWave / 2; step > 0; step /= 2)
+    if (__shfl(v, k + step - 1) <= c) k += step;
+  if (k == kWave - 1 && vlast <= c) return min(find_owner(off, nt, c), (int)nt - 1);   // empty elements between
+  return min((int)lo + k, (int)nt - 1);
+}
+
 __device__ __forceinline__ void cand_cell(const Pt *P, int n, int q, int &i, int &j) {
   int i0, i1, j0, j1;
   cell_range(P, n, i0, i1, j0, j1);
@@ -207,15 +230,17 @@ __device__ __forceinline__ void cand_cell(const Pt *P, int n, int q, int &i, int
 
 // The clipping kernels are bound by the serial chain of cuts of a thread (five cuts of up to eight
 // vertices) and, in the emitting ones, by the FP64 work of the fan's points on lanes whose pieces have
-// different numbers of triangles.  At 1024^2 with 589 k candidate cells: count 137 -> 82 us with the
-// polygons in LDS, emit 224 -> 223; at 160^2 the time-coherent form's 48 -> 30.
+// different numbers of triangles.  A thread's element is found by the wavefront (at 1024^2 the whole
+// assembly 871 -> 829 us, the time-coherent form with nothing moved 102 -> 39).  At 1024^2 with 589 k
+// candidate cells: count 137 -> 82 us with the polygons in LDS, emit 224 -> 223; at 160^2 the time-coherent form's 48 -> 30.
 __global__ void __launch_bounds__(kClipBlock)
     k_clip_count(int64_t ncand, int64_t nt, int64_t ns, int n, const double *__restrict__ X,
                  const int *__restrict__ tri, const int *__restrict__ cand_off, int *piece_cnt) {
   FSI_CLIP_BUFFERS;
+  static_assert(kClipBlock == kWave, "a block is one wavefront");
   int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int e = find_owner_wave(cand_off, nt, c - threadIdx.x);
   if (c >= ncand) return;
-  int e = find_owner(cand_off, nt, c);
   Pt P[3];
   load_tri(X, ns, tri, e, P);
   int i, j;
@@ -274,10 +299,10 @@ __global__ void __launch_bounds__(kClipBlock)
                 const int *__restrict__ piece_off, int *pair_E, int *pair_T, double *piece_L) {
   FSI_CLIP_BUFFERS;
   int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int e = find_owner_wave(cand_off, nt, c - threadIdx.x);
   if (c >= ncand) return;
   int p = piece_off[c];
   if (piece_off[c + 1] == p) return;   // no kept piece
-  int e = find_owner(cand_off, nt, c);
   Pt P[3];
   load_tri(X, ns, tri, e, P);
   int i, j;
@@ -925,6 +950,7 @@ __global__ void k_inc_box(int64_t nt, int64_t ns, int n, const double *__restric
                           int *box, int *cnt, int *moved, int *flag) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= nt) return;
+  if (e == 0) flag[1] = 1;   // every element counts as moved
   Pt P[3];
   load_tri(X, ns, tri, (int)e, P);
   bool ok = tri_area(P) > 0.0;
@@ -982,10 +1008,10 @@ __global__ void __launch_bounds__(kClipBlock)
                const int *__restrict__ tri, const double *__restrict__ ref_area, const int *__restrict__ cand_off,
                const int *__restrict__ moved, int *pair_E, int *pair_T, int *prevT, double *piece_L, int *inc) {
   FSI_CLIP_BUFFERS;
+  if (inc[1] == 0) return;   // no element moved
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nslot) return;
-  const int e = find_owner(cand_off, nt, c);
-  if (!moved[e]) return;
+  const int e = find_owner_wave(cand_off, nt, c - threadIdx.x);
+  if (c >= nslot || !moved[e]) return;
   Pt P[3];
   load_tri(X, ns, tri, e, P);
   int i0, i1, j0, j1;
@@ -1019,17 +1045,19 @@ __global__ void __launch_bounds__(kClipBlock)
 // every row of C_f, with its sums in the same order).
 // One wavefront per element, 64 slots of either list at a time: the kept entries are numbered by
 // ballots, the previous ones put down by their number, the present ones compared with theirs (one
-// thread per element walked both lists: 34 us for 5,600 elements of 18 slots, now under 5).
+// thread per element walked both lists: 34 us for 5,600 elements of 18 slots, now under 5).  Above
+// kIncBlocks blocks a wavefront takes several elements, up to its first difference, and a block
+// reports once: with one report per element of 150,528 changed ones, the flag's atomics alone
+// took 1,240 us.
 constexpr int kIncWaves = 4;
+constexpr int kIncBlocks = 2048;   // 8 blocks of 4 wavefronts on each of 256 CUs
 __global__ void __launch_bounds__(kWave *kIncWaves)
     k_inc_cmp(int64_t nt, const int *__restrict__ cand_off, const int *__restrict__ moved,
               const int *__restrict__ pair_T, const int *__restrict__ prevT, int *inc) {
   __shared__ int prev[kIncWaves][kWave];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-  const int64_t e = (int64_t)blockIdx.x * kIncWaves + w;
-  if (e >= nt || !moved[e]) return;   // a wavefront is on its own: no block barrier below
-  const int64_t s0 = 2 * (int64_t)cand_off[e], s1 = 2 * (int64_t)cand_off[e + 1];
   const uint64_t below = (1ull << lane) - 1;
+  int64_t s1 = 0;
   // the k-th kept entry of either list, from position pos on, into v (lane k of a group of up to 64)
   auto next = [&](const int *list, int64_t &pos, int &count) -> int {
     int v = -1;
@@ -1053,16 +1081,19 @@ __global__ void __launch_bounds__(kWave *kIncWaves)
     }
     return v;
   };
-  int64_t a = s0, b = s0;
-  for (;;) {
-    int na, nb;
-    const int va = next(pair_T, a, na), vb = next(prevT, b, nb);
-    if (__ballot(va != vb)) {   // also where one list has an entry more: -1 there
-      if (lane == 0) atomicOr(&inc[0], IF_PATTERN);
-      return;
+  bool differs = false;
+  if (inc[1] == 0) return;   // no element moved
+  for (int64_t e = (int64_t)blockIdx.x * kIncWaves + w; e < nt && !differs; e += (int64_t)gridDim.x * kIncWaves) {
+    if (!moved[e]) continue;
+    int64_t a = 2 * (int64_t)cand_off[e], b = a;
+    s1 = 2 * (int64_t)cand_off[e + 1];
+    int na = kWave, nb;
+    while (na == kWave && !differs) {   // until both lists are at their ends
+      const int va = next(pair_T, a, na), vb = next(prevT, b, nb);
+      differs = __ballot(va != vb) != 0;   // also where one list has an entry more: -1 there
     }
-    if (na < kWave) return;   // both lists are at their ends
   }
+  if (__syncthreads_or(differs) && threadIdx.x == 0) atomicOr(&inc[0], IF_PATTERN);
 }
 
 __global__ void k_inc_slot_off(int64_t nt, const int *cand_off, int *e_piece) {
@@ -1112,8 +1143,8 @@ static void assemble_incremental(Ctx &c, const double *Xn) {
     hipLaunchKernelGGL(k_inc_emit, dim3(grid_for(c.n_cand, kClipBlock)), dim3(kClipBlock), 0, s, c.n_cand, nt, ns, n, Xn,
                        c.tri.p, c.ref_area.p, c.cand_off.p, c.inc_moved.p, c.pair_E.p, c.pair_T.p, c.inc_prevT.p,
                        c.piece_L.p, inc);
-    hipLaunchKernelGGL(k_inc_cmp, dim3(grid_for(nt, kIncWaves)), dim3(kWave * kIncWaves), 0, s, nt, c.cand_off.p, c.inc_moved.p,
-                       c.pair_T.p, c.inc_prevT.p, inc);
+    hipLaunchKernelGGL(k_inc_cmp, dim3(std::min<unsigned>(grid_for(nt, kIncWaves), kIncBlocks)), dim3(kWave * kIncWaves), 0,
+                       s, nt, c.cand_off.p, c.inc_moved.p, c.pair_T.p, c.inc_prevT.p, inc);
     FSI_CHECK_LAUNCH();
     FSI_HIP(hipMemcpyAsync(c.inc_X.p, Xn, 2 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
     int h[3] = {0, 0, 0};

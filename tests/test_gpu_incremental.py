@@ -146,6 +146,37 @@ def test_incremental_coupling_equals_full(case):
     inc.close()
 
 
+@pytest.mark.parametrize("e", [0, 8191, 8192, -1])
+def test_one_changed_element_of_many(e):
+    """More elements than one pass of the comparing wavefronts takes (8,192): a change of pieces
+    around one element, at either end of a pass, is seen, and C_f is that of the full assembly."""
+    wl = inputs.Workload("many128", 128, [inputs.Solid(38, (0.4987, 0.5071), 0.31)])
+    xy, tri = wl.solid_mesh()
+    assert tri.shape[0] > 8192
+    full, inc = fsi.Context.from_workload(wl), fsi.Context.from_workload(wl)
+    inc.set_coupling_mode(fsi.COUPLING_INCREMENTAL)
+    for c in (full, inc):
+        c.assemble_coupling(to_dev(soa(xy)))
+    E0, T0 = full.export_pairs()
+    node = tri[e][0]
+    for k in range(1, 9):   # towards the element's other nodes until a piece appears or goes
+        X = xy.copy()
+        X[node] += 0.05 * k * (xy[tri[e][1]] - xy[node])
+        full.assemble_coupling(to_dev(soa(X)))
+        E, T = full.export_pairs()
+        if not (np.array_equal(E, E0) and np.array_equal(T, T0)):
+            break
+    else:
+        pytest.fail("no position with other pieces")
+    before = inc.coupling_counts()
+    inc.assemble_coupling(to_dev(soa(X)))
+    after = inc.coupling_counts()
+    assert after["pattern_builds"] == before["pattern_builds"] + 1, (before, after)
+    _same(full, inc, e)
+    full.close()
+    inc.close()
+
+
 @pytest.mark.parametrize("prec", [fsi.FP64, fsi.FP32])
 def test_incremental_time_loop(prec):
     """The prescribed rotation of the time-loop workload at 16^2 (0.1 rad per step) and at 64^2
