@@ -82,21 +82,21 @@ def inner_step_bytes(n, prec):
     """Bytes one inner MINRES step must move (one A11 product with the Lanczos and update
     vectors, one application of diag(V, S^{-1})), per kernel of the matrix-free path, with
     w = 8 (FP64) or 4 (FP32 preconditioner):
+      A11 product with the MINRES scaling and first update (FP64): 64 N2 + 32 Np;
       velocity V-cycle, per level above the one-launch tail (cells > 16): pre-smoothing 4w N2_l
         (b read, x written, two components), residual + restriction 4w N2_l + 2w N2_{l+1},
-        post-smoothing with the coarse correction 6w N2_l + 2w N2_{l+1};
+        post-smoothing with the coarse correction 6w N2_l + 2w N2_{l+1}; the finest
+        pre-smoothing makes its right-hand side (two FP64 vectors read, one written: 48 N2 + 24 Np)
+        in place of reading it;
       tail: 4w N2 of its first level + the dense coarsest inverse (162^2 w);
-      pressure V-cycle (P1), per level above the 4^2 dense level: first step 3w, one more
-        Chebyshev step 5w, residual 3w, restriction w + w coarse, prolongation 2w + w coarse,
-        two post steps 10w per node; dense 25^2 w;
-      pressure mass solve 13w Np, pressure residual copy (8 + w) Np, output (2w + 16) Np;
-      A11 product with the fused MINRES updates (FP64): 64 N2 + 32 Np;
-      remaining MINRES vector work: 4 vectors of nf = 2 N2 + Np doubles (the second
-        three-term update, 3; the directions and the iterate are formed once per block of
-        stored Lanczos vectors, counted in step_bytes);
-      FP32 form: the velocity residual converted (24 N2), the finest post-smoothing writes the
-        FP64 output ((4w + 16) N2 instead of 6w N2) and reads the FP64 residual for the sums of
-        r . z (16 N2)."""
+      pressure V-cycle (P1), per level above the 4^2 dense level: descent 2w + w coarse (b read, x and
+        the restricted residual written), ascent 3w + w coarse (x and b read, the result written;
+        the finest also takes the mass solve and writes the FP64 output); dense 25^2 w;
+      FP32 form: the copy of the velocity right-hand side written (8 N2), the finest post-smoothing
+        writes the FP64 output ((4w + 16) N2 instead of 6w N2) and reads the FP64 residual for the
+        sums of r . z (16 N2).
+    The directions and the iterate are formed once per block of stored Lanczos vectors, counted in
+    step_bytes."""
     w = 8 if prec == "fp64" else 4
     N2 = lambda m: (2 * m + 1) ** 2
     Np = lambda m: (m + 1) ** 2
@@ -107,16 +107,16 @@ def inner_step_bytes(n, prec):
         if k == 0 and prec != "fp64":
             post = (4 * w + 16) * N2(m) + 16 * N2(m)
         b += 4 * w * N2(m) + (4 * w * N2(m) + 2 * w * N2(m // 2)) + post + 2 * w * N2(m // 2)
+    b += 48 * N2(n) + 24 * Np(n) - 2 * w * N2(n)
     b += 4 * w * N2(tail) + 162 * 162 * w
     pfull, _ = _levels(n, 4)
     for m in pfull:
-        b += 24 * w * Np(m) + 2 * w * Np(m // 2)
+        b += 5 * w * Np(m) + 2 * w * Np(m // 2)
+    b += 3 * (8 - w) * Np(n)   # the finest right-hand side (read twice) and output are FP64
     b += 25 * 25 * w
-    b += 13 * w * Np(n) + (8 + w) * Np(n) + (2 * w + 16) * Np(n)
     b += 64 * N2(n) + 32 * Np(n)
-    b += 4 * 8 * (2 * N2(n) + Np(n))
     if prec != "fp64":
-        b += 24 * N2(n)
+        b += 8 * N2(n)
     return b
 
 
@@ -125,7 +125,7 @@ def step_bytes(n, Ns, nnz_s, nnz_cf, n_pairs, its, inner_its, restarts, prec, pc
     inner solves), w = 8 for every outer vector:
       C_f: the piece list and 3 x 6 matrices written and read (2 x 152 B per piece), C_f and
         C_f^T written, ranked and read (4 x 12 B per entry);
-      g1 = (rho/dt) M_f u^n: the P2 pattern (46 n^2 entries, 12 B) and two components in and out;
+      g1 = (rho/dt) M_f u^n, cell by cell: two components in and out, zeros for the pressure;
       per outer step j: the operator (matrix-free fluid rows 32 N2 + 16 Np, C_f^T and C_f
         entries 12 B each twice, the solid rows 20 B per entry of the solid pattern and 8
         vectors of Ns), A22 by two C_s Chebyshev solves of cs_steps steps (12 B per entry and
@@ -138,7 +138,7 @@ def step_bytes(n, Ns, nnz_s, nnz_cf, n_pairs, its, inner_its, restarts, prec, pc
     N2, Np = (2 * n + 1) ** 2, (n + 1) ** 2
     N = 2 * N2 + Np + 4 * Ns
     b = 2 * 152 * n_pairs + 4 * 12 * nnz_cf
-    b += (46 * n * n) * 12 + 4 * 8 * N2
+    b += 4 * 8 * N2 + 8 * Np
     op = 32 * N2 + 16 * Np + 2 * 12 * nnz_cf + 20 * nnz_s + 8 * 8 * Ns
     a22 = 2 * cs_steps * (12 * nnz_s + 6 * 8 * Ns) + 12 * nnz_s + 6 * 8 * Ns
     cf = 12 * nnz_cf + 2 * 8 * Ns if pc == "tri" else 0
@@ -147,7 +147,7 @@ def step_bytes(n, Ns, nnz_s, nnz_cf, n_pairs, its, inner_its, restarts, prec, pc
         jj = j % m
         b += op + a22 + cf + 16 * (jj + 1) * N + 24 * N + 16 * N
     b += inner_its * inner_step_bytes(n, prec)
-    b += its * (inner_step_bytes(n, prec) - 64 * N2 - 32 * Np - 4 * 8 * (2 * N2 + Np))
+    b += its * (inner_step_bytes(n, prec) - 64 * N2 - 32 * Np - 32 * N2 - 16 * Np)
     b += (inner_its + its) * 8 * (2 * N2 + Np)
     b += restarts * ((min(its, m) + 1) * N * 8 + op + 3 * N * 8)
     return b
@@ -643,13 +643,13 @@ def qpair_leg(args, fsi, inputs, torch, dev, save):
                         t_sol_ms=r["t_solve_ms"], its_mean=sum(r["its"]) / steps, its_max=max(r["its"]),
                         inner_its_mean=sum(r["inner_its"]) / steps, relres_true_max=r["relres_true"])
         k = r.get("kernel")
-        if k and k["launches"]:   # the finest velocity level's class-stencil Chebyshev step (HIP events)
+        if k and k["launches"]:   # the finest velocity level's post-smoothing launch (HIP events)
             rec[tag]["roofline"] = dict(
-                bound="hbm", kernel="k_q2_stencil (finest velocity level, one Chebyshev step: x, b, d read, d, y "
-                                    "written)", launches=k["launches"], avg_us=k["avg_us"],
+                bound="hbm", kernel="k_post3 (finest velocity level, the coarse correction and three Chebyshev steps: "
+                                    "x, b and the coarse correction read, y written)", launches=k["launches"], avg_us=k["avg_us"],
                 bytes_per_launch=k["bytes_per_launch"], achieved=k["achieved_gbs"], peak=HBM_PEAK_GBS,
                 unit="GB/s", frac=k["achieved_gbs"] / HBM_PEAK_GBS,
-                traffic=recorded_traffic("qbar256", "k_q2_stencil<double>") if prec == fsi.FP64 else None)
+                traffic=recorded_traffic("qbar256", "k_post3<double, Q2>") if prec == fsi.FP64 else None)
     sz = ctx.refresh_sizes()
     rec["pieces"] = sz["n_pairs"]
     rec["nnz_Cf"] = sz["nnz_Cf"]
@@ -842,8 +842,8 @@ def main():
     k = m["kernel"]
     roofline = {"bound": "hbm", "achieved": round(k["achieved_gbs"], 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(k["achieved_gbs"] / HBM_PEAK_GBS, 4),
-                "traffic": recorded_traffic(args.workload, "k_cheb3<double>"),
-                "kernel": "k_cheb3<double> (finest-level matrix-free A_f smoothing: the coarse correction added "
+                "traffic": recorded_traffic(args.workload, "k_post3<double>"),
+                "kernel": "k_post3<double> (finest-level matrix-free A_f smoothing: the coarse correction added "
                           "while staging x, then the three post-smoothing Chebyshev steps, in one launch)",
                 "bytes_per_launch": k["bytes_per_launch"], "avg_us": round(k["avg_us"], 2),
                 "launches": k["launches"]}
