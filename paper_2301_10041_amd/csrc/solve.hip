@@ -430,15 +430,17 @@ static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullp
   }
   if constexpr (W == 4) {   // matrix-free smoothing, residual and transfers
     // three launches per level: pre-smoothing; residual with the restriction (the residual stays
-    // in LDS); post-smoothing, which adds the coarse correction while it stages x (the profile
+    // in LDS), on small levels in the first one; post-smoothing, which adds the coarse correction while it stages x (the profile
     // brackets this one, the largest single kernel of a step)
     auto cycle = [&](const auto &cf) -> T * {
       FSI_REQUIRE(degree == 3, FSI_E_STATE, "the matrix-free velocity cycle takes three steps");
       const Cheb3Coef<T> cc = cheb3_coefs<T>(lmin, lmax);
       const LP<const T> lx(x, ls);
-      pre3<T>(L.n, cf, LP<T>(const_cast<T *>(b.p), b.s), LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, fold);
+      const bool rr = pre3_restricts(L.n, K);
+      pre3<T>(L.n, cf, LP<T>(const_cast<T *>(b.p), b.s), LP<T>(x, ls), cc.s, cc.c1a, cc.c2a, cc.c1b, cc.c2b, s, K, fold,
+              rr ? LP<T>(bc, lc) : LP<T>());
       if (ev) FSI_HIP(hipEventRecord(ev, s));
-      resid_restrict<T>(L.n, cf, lx, b, LP<T>(bc, lc), s, K);
+      if (!rr) resid_restrict<T>(L.n, cf, lx, b, LP<T>(bc, lc), s, K);
       T *xc = vcycle<T, W, NC>(mg, l + 1, LP<const T>(bc, lc), s, nullptr, K);
       const LP<const T> lxc(xc, lc);
       if (pl) pl->begin(s);

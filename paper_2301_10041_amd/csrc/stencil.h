@@ -115,6 +115,7 @@ struct MsFold {
 // Q2Coef<T> for the paper's):
 // pre3 : x = s D^{-1} b, then the steps (c1a, c2a), (c1b, c2b); writes x.  With fold, b is the velocity
 //        part of q; q (all three parts) is written, and for T = float also the copy b.
+//        With bc (where pre3_restricts(n, K)) also bc = R (b - A_f x), as resid_restrict.
 // post3: from x + P xc (xc the coarse correction of lattice n / 2) a step with c1 = 0 (c2a) and
 //        the steps (c1b, c2b), (c1c, c2c); writes y (stored as TY: double or T; x is not
 //        written).  With dot, tile t of lane k stores the sum over its nodes of b . y (FP64, y as
@@ -122,7 +123,8 @@ struct MsFold {
 //        right-hand side in place of b (the FP32 cycle of the mixed form).
 template <typename T, typename C>
 void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
-          const MsFold *fold = nullptr);
+          const MsFold *fold = nullptr, LP<T> bc = LP<T>());
+bool pre3_restricts(int n, int K);
 template <typename T, typename TY, typename C>
 void post3(int n, const C &cf, LP<const T> x, LP<const T> b, LP<TY> y, T c2a, T c1b, T c2b, T c1c, T c2c,
            hipStream_t st, int K, LP<const T> xc, LP<double> dot = LP<double>(),

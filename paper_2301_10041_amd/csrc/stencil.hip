@@ -57,9 +57,10 @@ static int64_t common_stride(std::initializer_list<std::pair<const void *, int64
 constexpr int kCellRows = 8;                          // cell rows of a region
 constexpr int kCellH = 2 * kCellRows + 3;             // its staged rows: a halo of one cell
 // the names of a kernel on regions of LW cells per row
-#define FSI_CELL_REGION(LW)                                                                                    \
-  constexpr int kThreads = (LW) * kCellRows, kWaves = kThreads / kWave; /* one thread per cell */              \
-  constexpr int kCellHW = (LW) + 2, kCellPL = kCellH * kCellHW;         /* plane width and stride, with halo */ \
+#define FSI_CELL_REGION(LW) FSI_CELL_REGION_R(LW, kCellRows)
+#define FSI_CELL_REGION_R(LW, R)                                                                               \
+  constexpr int kThreads = (LW) * (R), kWaves = kThreads / kWave;       /* one thread per cell */              \
+  constexpr int kCellHW = (LW) + 2, kCellPL = (2 * (R) + 3) * kCellHW;  /* plane width and stride, with halo */ \
   const int lane = threadIdx.x % (LW), w = region_row<LW>();            /* the thread's cell */                \
   (void)kWaves, (void)kCellPL, (void)lane, (void)w
 template <int LW>
@@ -78,10 +79,10 @@ template <int LW> constexpr int kRRTile = (LW - 3) / 2;
 //   smoothing      32^2 (FP64, in MINRES) 8.5 and 7.5 / 7.1 and 6.5 / 6.2 and 6.0; 64^2 level 6.1 and 8.2
 //                  / 5.8 and 6.2 / 5.1 and 5.9; 256^2 (FP32) 9.3 and 10.5 / 8.6 and 9.4, 512^2 in FP64 23
 //                  and 27 at 64, where the halo's recomputation begins to count
-//   restriction    32^2 4.8 / 4.2 / 4.5
+//   restriction    32^2 4.8 / 4.2 / 4.5 (as its own launch: batches, by pre3_restricts)
 //   A11 rows       32^2 8.0 / 7.8 / 8.9 (two waves sum beta^2), 256^2 10.2 / 11.4
 template <typename F>
-static void smooth_width(int n, F f) {
+static void smooth_width(int n, F f) {   // post-smoothing
   if (n <= 64) f(std::integral_constant<int, kWave / 4>{});
   else if (n <= 256) f(std::integral_constant<int, kWave / 2>{});
   else f(std::integral_constant<int, kWave>{});
@@ -149,9 +150,9 @@ __device__ __forceinline__ void put_cell(V2<T> *X, int r, int h, const V2<T> (&q
 // x (a pair of nodes of each staged row, interior nodes only) of the region whose first cell is
 // (i0, j0), with the halo of one cell; f maps a node's value before it is stored (row parity,
 // column parity, value)
-template <typename T, int ROWS, int LW, typename F>
+template <typename T, int ROWS, int LW, int NT = LW *kCellRows, typename F>
 __device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int L, int n, int i0, int j0, F f) {
-  constexpr int HW = LW + 2, NT = LW * kCellRows, NE = ROWS * HW, IT = (NE + NT - 1) / NT, PL = NE;
+  constexpr int HW = LW + 2, NE = ROWS * HW, IT = (NE + NT - 1) / NT, PL = NE;
   NodePair<T> a[IT], b[IT];
 #pragma unroll
   for (int q = 0; q < IT; ++q) {
@@ -174,6 +175,68 @@ __device__ __forceinline__ void stage_pairs(V2<T> *X, const T *v, int64_t N, int
   }
 }
 
+// The restriction sums of the CW x CR coarse cells from (C0, R0) on: R is the place of the first one's fine
+// vertex in the staged residual (column-parity planes of stride PL, rows of HW).
+template <typename T, typename C, int HW, int PL, int CW, int CR, int WAVES>
+__device__ __forceinline__ void restrict_cells(const V2<T> *R, int n, int C0, int R0, T *bcg) {
+  const int Lc = n + 1;
+  const int64_t Nc = (int64_t)Lc * Lc;
+  // coarse classes (vertex, (1, 0), (0, 1), (1, 1)) of the CW x CR coarse cells, 64 cells a pass
+  constexpr int NC = CW * CR, PASS = (NC + kWave - 1) / kWave;
+  for (int u = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); u < 4 * PASS; u += WAVES) {
+    const int c = (u >> 2) * kWave + threadIdx.x % kWave;
+    if (c >= NC) continue;
+    const int ck = c % CW, cr = c / CW;
+    auto gather = [&](auto pa_tag, auto pb_tag) {
+      constexpr int PA = decltype(pa_tag)::value, PB = decltype(pb_tag)::value;
+      const int Ic = 2 * (C0 + ck) + PA, Jc = 2 * (R0 + cr) + PB;
+      if (Ic >= Lc || Jc >= Lc) return;
+      V2<T> sum{T(0), T(0)};
+      if (Ic > 0 && Jc > 0 && Ic < n && Jc < n) {
+        // fine node (2 Ic + dI, 2 Jc + dJ) relative to the tile's first node
+        const V2<T> *r = R + 4 * cr * HW + 2 * ck;
+        auto row = [&](auto dj_tag) {
+          constexpr int DJ = decltype(dj_tag)::value;
+          auto term = [&](auto di_tag) {
+            constexpr int DI = decltype(di_tag)::value;
+            constexpr double wt = restrict_weight_of<TransferOf<C>>(PA, PB, DI, DJ);
+            if constexpr (wt != 0.0) {
+              constexpr int u0 = 2 * PA + DI, v0 = 2 * PB + DJ;
+              const V2<T> v = r[(u0 & 1) * PL + v0 * HW + (u0 >> 1)];
+              sum.x = fma(T(wt), v.x, sum.x);
+              sum.y = fma(T(wt), v.y, sum.y);
+            }
+          };
+          term(std::integral_constant<int, -3>{});
+          term(std::integral_constant<int, -2>{});
+          term(std::integral_constant<int, -1>{});
+          term(std::integral_constant<int, 0>{});
+          term(std::integral_constant<int, 1>{});
+          term(std::integral_constant<int, 2>{});
+          term(std::integral_constant<int, 3>{});
+        };
+        row(std::integral_constant<int, -3>{});
+        row(std::integral_constant<int, -2>{});
+        row(std::integral_constant<int, -1>{});
+        row(std::integral_constant<int, 0>{});
+        row(std::integral_constant<int, 1>{});
+        row(std::integral_constant<int, 2>{});
+        row(std::integral_constant<int, 3>{});
+      }
+      const int64_t k = (int64_t)Jc * Lc + Ic;
+      bcg[k] = sum.x;
+      bcg[Nc + k] = sum.y;
+    };
+    using std::integral_constant;
+    switch (u & 3) {
+      case 0: gather(integral_constant<int, 0>{}, integral_constant<int, 0>{}); break;
+      case 1: gather(integral_constant<int, 1>{}, integral_constant<int, 0>{}); break;
+      case 2: gather(integral_constant<int, 0>{}, integral_constant<int, 1>{}); break;
+      default: gather(integral_constant<int, 1>{}, integral_constant<int, 1>{}); break;
+    }
+  }
+}
+
 template <typename T, typename C>
 struct PreArgs {
   int n;
@@ -184,6 +247,8 @@ struct PreArgs {
   int64_t lb, ly;            // lane strides of b and y (lane = blockIdx.y)
   MsFold f;                  // MS
   int64_t np;                // its pressure entries
+  T *bc;                     // RR: the coarse right-hand side
+  int64_t lc;                // its lane stride
 };
 
 // The pre-smoothing of a degree-3 smoother: x = d = s D^{-1} b, then two steps; reads b, writes x
@@ -196,11 +261,21 @@ struct PreArgs {
 // less per inner step: 9 us against 6.2 + 2.6 + 1.9 and two gaps at 32^2, 83 against 37 + 38 + 4 and
 // two gaps at 1024^2 (FP64); 35 at 768^2 with FP32 arithmetic, where the FP32 copy of q is written
 // here too.
+//
+// RR: the residual and its restriction too, in regions of 16 x 16 cells: x2 is right on the inner 14 x 14,
+// the residual on 12 x 12, which gives 4 x 4 coarse cells, so 8 x 8 of the region's cells are the tile's.
+// Four times the tile's work against a launch, its gap and two passes over memory less: small levels are
+// bound by launches.  The values are those of k_pre3 and k_resid_restrict bit for bit.
 constexpr int kPrePres = 2048;   // pressure entries per block
-template <typename T, typename C, int LW, bool MS>
-__global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a, int tiles_x, int tiles, int band) {
-  FSI_CELL_REGION(LW);
-  constexpr int kPreW = kPreTile<LW>, kPreR = kPreTileR;
+constexpr int kPreRRRows = 16, kPreRRc = (16 + 2 - 6 - 3) / 2;   // region rows; coarse cells per tile and side
+template <typename T, typename C, int LW, bool MS, bool RR>
+__global__ void __launch_bounds__(LW *(RR ? kPreRRRows : kCellRows), RR ? 1 : LW / 16)
+    k_pre3(PreArgs<T, C> a, int tiles_x, int tiles, int band) {
+  constexpr int kRows = RR ? kPreRRRows : kCellRows;
+  static_assert(!RR || LW == kPreRRRows, "square regions");
+  FSI_CELL_REGION_R(LW, kRows);
+  // the first cell of the tile in the region, and its cells (a region's outermost cells are halo)
+  constexpr int kOff = RR ? 4 : 1, kPreW = RR ? 2 * kPreRRc : kPreTile<LW>, kPreR = RR ? 2 * kPreRRc : kPreTileR;
   using TS = typename std::conditional<MS, double, T>::type;   // staged first
   __shared__ V2<TS> XS[2 * kCellPL];
   V2<T> *const X = reinterpret_cast<V2<T> *>(XS);
@@ -211,7 +286,7 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a
   T *yg = a.y + (int64_t)blockIdx.y * a.ly;
   const int n = a.n, L = 2 * n + 1;
   const int64_t N = (int64_t)L * L;
-  const int i0 = (t % tiles_x) * kPreW - 1, j0 = (t / tiles_x) * kPreR - 1;   // first cell of the region
+  const int i0 = (t % tiles_x) * kPreW - kOff, j0 = (t / tiles_x) * kPreR - kOff;   // first cell of the region
   const int i = i0 + lane, j = j0 + w;
   const C &cf = a.cf;
   auto first = [&](int pj, int pi, V2<T> v) -> V2<T> {
@@ -224,7 +299,7 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a
     const double *y1 = a.f.y1.p + lane_v, *r2 = a.f.r2.p + lane_v;
     double *q = a.f.q.p + lane_v;
     // the staged nodes (as in stage_pairs), in flight over the sum of alfa
-    constexpr int NT = kThreads, NE = kCellH * kCellHW, IT = (NE + NT - 1) / NT;
+    constexpr int NT = kThreads, NE = kCellPL, IT = (NE + NT - 1) / NT;
     NodePair<double> ya[IT], yb[IT], ra[IT], rb[IT];
     if (!pres) {
 #pragma unroll
@@ -306,13 +381,13 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a
         X[kCellPL + e] = first(lr & 1, 1, V2<T>{(T)qb[k].x, (T)qb[k].y});
       }
     }
-    if (w >= 1 && w <= kPreR && j <= n && lane >= 1 && lane <= kPreW && i <= n) {
+    if (w >= kOff && w < kOff + kPreR && j <= n && lane >= kOff && lane < kOff + kPreW && i <= n) {
       store_cell<double, double>(q, N, L, n, i, j, by);
       if constexpr (!std::is_same<T, double>::value) store_cell<T, T>(bg, N, L, n, i, j, b);
     }
   } else {
     load_cell((const T *)bg, N, L, n, i, j, b);
-    stage_pairs<T, kCellH, LW>(X, (const T *)bg, N, L, n, i0, j0, first);
+    stage_pairs<T, 2 * kRows + 3, LW, kThreads>(X, (const T *)bg, N, L, n, i0, j0, first);
   }
   const CellIn in = cell_inside(i, j, n);
   const int row = 2 * w + 2, h = lane + 1;
@@ -329,9 +404,10 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a
   __syncthreads();
   put_cell<T, kCellPL, kCellHW>(X, row, h, x);
   __syncthreads();
-  if (w < 1 || w > kPreR || j > n) return;
+  const bool mine = w >= kOff && w < kOff + kPreR && j <= n && lane >= kOff && lane < kOff + kPreW && i <= n;
+  if (!RR && (w < 1 || w > kPreR || j > n)) return;
   cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
-  if (lane < 1 || lane > kPreW || i > n) return;
+  if (!RR && !mine) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     if (in.q[q]) {
@@ -346,7 +422,25 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16) k_pre3(PreArgs<T, C> a
       x[q] = V2<T>{steps(b[q].x), steps(b[q].y)};
     }
   }
-  store_cell<T, T>(yg, N, L, n, i, j, x);
+  if (!RR || mine) store_cell<T, T>(yg, N, L, n, i, j, x);
+  if constexpr (RR) {
+    // x is right on the region without its outermost cells, r on one cell less at each side
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = in.q[q] ? x[q] : V2<T>{T(0), T(0)};
+    __syncthreads();
+    put_cell<T, kCellPL, kCellHW>(X, row, h, x);
+    __syncthreads();
+    cell_products<T, kCellPL, kCellHW>(p, cf, x, s);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      b[q] = in.q[q] ? V2<T>{b[q].x - s[q].x, b[q].y - s[q].y} : V2<T>{T(0), T(0)};
+    __syncthreads();   // every wave has read x: r goes over it
+    put_cell<T, kCellPL, kCellHW>(X, row, h, b);
+    __syncthreads();
+    const int C0 = (t % tiles_x) * kPreRRc, R0 = (t / tiles_x) * kPreRRc;
+    restrict_cells<T, C, kCellHW, kCellPL, kPreRRc, kPreRRc, kWaves>(
+        X + (2 * kOff + 2) * kCellHW + kOff + 1, n, C0, R0, a.bc + (int64_t)blockIdx.y * a.lc);
+  }
 }
 
 // The coarse correction and the whole post-smoothing of a degree-3 smoother: x + P xc staged,
@@ -565,12 +659,22 @@ static void cell_launch_checks(int n, int K) {
   FSI_REQUIRE(K >= 1 && K <= 65535, FSI_E_ARG, "lane count out of range");
 }
 
+// RR up to 256^2 cells in all lanes together, where its recomputation still fits beside the idle part of
+// the chip.  Whole steps with / without it: 32^2 12.6 / 13.9 ms, 96^2 (block-diagonal) 62.7 / 69.0, 256^2
+// mixed 33.3 / 36.2, 4 x 128^2 30.6 / 30.3, 8 x 64^2 mixed 23.9 / 26.1; beyond the line 2 x 256^2 47.7 /
+// 46.6, 5 x 192^2 63.6 / 61.3, 512^2 32.8 / 31.2.  Up to 64^2 with any number of lanes: there the first
+// launch without it had other block sizes, and a system's sum of alfa may not depend on its company.
+bool pre3_restricts(int n, int K) {
+  return n % 2 == 0 && n >= 4 && (n <= 64 || (n <= 256 && (int64_t)K * n * n <= 256 * 256));
+}
+
 template <typename T, typename C>
 void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
-          const MsFold *fold) {
+          const MsFold *fold, LP<T> bc) {
   cell_launch_checks(n, K);
+  FSI_REQUIRE(!bc.p || (pre3_restricts(n, K) && (K == 1 || bc.s > 0)), FSI_E_ARG, "no restriction in this launch");
   FSI_REQUIRE(K == 1 || (x.s > 0 && (b.s > 0 || !b.p)), FSI_E_ARG, "lane views need a stride");
-  PreArgs<T, C> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0};
+  PreArgs<T, C> a{n, cf, b.p, x.p, s, c1a, c2a, c1b, c2b, b.s, x.s, MsFold(), 0, bc.p, bc.s};
   if (fold) {
     a.f = *fold;
     a.np = std::is_same<C, AfCoef<T>>::value ? (int64_t)(n + 1) * (n + 1) : 3 * (int64_t)n * n;
@@ -578,18 +682,30 @@ void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b,
     FSI_REQUIRE(a.f.q.p != a.f.y1.p && a.f.q.p != a.f.r2.p, FSI_E_ARG, "the update reads its neighbours' operands");
   }
   const unsigned gp = fold ? (unsigned)((a.np + kPrePres - 1) / kPrePres) : 0u;
-  smooth_width(n, [&](auto lw) {
+  if (bc.p) {
+    constexpr int LW = kPreRRRows;
+    int tx;
+    const int tiles = cell_tiles(n / 2, kPreRRc, kPreRRc, tx), band = (tiles + kXcd - 1) / kXcd;
+    const dim3 grid((unsigned)(band * kXcd) + gp, (unsigned)K), block(LW * kPreRRRows);
+    if (fold) hipLaunchKernelGGL((k_pre3<T, C, LW, true, true>), grid, block, 0, st, a, tx, tiles, band);
+    else hipLaunchKernelGGL((k_pre3<T, C, LW, false, true>), grid, block, 0, st, a, tx, tiles, band);
+    FSI_CHECK_LAUNCH();
+    return;
+  }
+  auto go = [&](auto lw) {
     constexpr int LW = decltype(lw)::value;
     int tx;
     const int tiles = cell_tiles(n, kPreTile<LW>, kPreTileR, tx), band = (tiles + kXcd - 1) / kXcd;
     const dim3 grid((unsigned)(band * kXcd) + gp, (unsigned)K), block(LW * kCellRows);
-    if (fold) hipLaunchKernelGGL((k_pre3<T, C, LW, true>), grid, block, 0, st, a, tx, tiles, band);
-    else hipLaunchKernelGGL((k_pre3<T, C, LW, false>), grid, block, 0, st, a, tx, tiles, band);
-  });
+    if (fold) hipLaunchKernelGGL((k_pre3<T, C, LW, true, false>), grid, block, 0, st, a, tx, tiles, band);
+    else hipLaunchKernelGGL((k_pre3<T, C, LW, false, false>), grid, block, 0, st, a, tx, tiles, band);
+  };
+  if (n <= 256) go(std::integral_constant<int, kWave / 2>{});
+  else go(std::integral_constant<int, kWave>{});
   FSI_CHECK_LAUNCH();
 }
 #define FSI_PRE3_INST(T, C) \
-  template void pre3<T, C>(int, const C &, LP<T>, LP<T>, T, T, T, T, T, hipStream_t, int, const MsFold *);
+  template void pre3<T, C>(int, const C &, LP<T>, LP<T>, T, T, T, T, T, hipStream_t, int, const MsFold *, LP<T>);
 FSI_PRE3_INST(double, AfCoef<double>)
 FSI_PRE3_INST(float, AfCoef<float>)
 FSI_PRE3_INST(double, Q2Coef<double>)
@@ -661,8 +777,8 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16)
   if (t >= tiles) return;
   const T *xg = a.x + (int64_t)blockIdx.y * a.lx, *bg = a.b + (int64_t)blockIdx.y * a.lb;
   T *bcg = a.bc + (int64_t)blockIdx.y * a.lc;
-  const int n = a.n, L = 2 * n + 1, Lc = n + 1;
-  const int64_t N = (int64_t)L * L, Nc = (int64_t)Lc * Lc;
+  const int n = a.n, L = 2 * n + 1;
+  const int64_t N = (int64_t)L * L;
   const int C0 = (t % tiles_x) * kRRc, R0 = (t / tiles_x) * CR;     // first coarse cell of the tile
   const int i0 = 2 * C0 - 2, j0 = 2 * R0 - 2;                       // first fine cell of the region
   const int i = i0 + lane;
@@ -687,60 +803,7 @@ __global__ void __launch_bounds__(LW *kCellRows, LW / 16)
 #pragma unroll
   for (int q = 0; q < Q; ++q) put_cell<T, RPL, LW>(R, 2 * (w * Q + q), lane, b[q]);
   __syncthreads();
-  // coarse classes (vertex, (1, 0), (0, 1), (1, 1)) of the kRRc x CR coarse cells, 64 cells a pass
-  constexpr int NC = kRRc * CR, PASS = (NC + kWave - 1) / kWave;
-  for (int u = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); u < 4 * PASS; u += kWaves) {
-    const int c = (u >> 2) * kWave + threadIdx.x % kWave;
-    if (c >= NC) continue;
-    const int ck = c % kRRc, cr = c / kRRc;
-    auto gather = [&](auto pa_tag, auto pb_tag) {
-      constexpr int PA = decltype(pa_tag)::value, PB = decltype(pb_tag)::value;
-      const int Ic = 2 * (C0 + ck) + PA, Jc = 2 * (R0 + cr) + PB;
-      if (Ic >= Lc || Jc >= Lc) return;
-      V2<T> sum{T(0), T(0)};
-      if (Ic > 0 && Jc > 0 && Ic < n && Jc < n) {
-        // fine node (2 Ic + dI, 2 Jc + dJ) relative to the region's first node (2 i0, 2 j0)
-        const V2<T> *r = R + (4 * cr + 4) * LW + 2 * ck + 2;
-        auto row = [&](auto dj_tag) {
-          constexpr int DJ = decltype(dj_tag)::value;
-          auto term = [&](auto di_tag) {
-            constexpr int DI = decltype(di_tag)::value;
-            constexpr double wt = restrict_weight_of<TransferOf<C>>(PA, PB, DI, DJ);
-            if constexpr (wt != 0.0) {
-              constexpr int u0 = 2 * PA + DI, v0 = 2 * PB + DJ;
-              const V2<T> v = r[(u0 & 1) * RPL + v0 * LW + (u0 >> 1)];
-              sum.x = fma(T(wt), v.x, sum.x);
-              sum.y = fma(T(wt), v.y, sum.y);
-            }
-          };
-          term(std::integral_constant<int, -3>{});
-          term(std::integral_constant<int, -2>{});
-          term(std::integral_constant<int, -1>{});
-          term(std::integral_constant<int, 0>{});
-          term(std::integral_constant<int, 1>{});
-          term(std::integral_constant<int, 2>{});
-          term(std::integral_constant<int, 3>{});
-        };
-        row(std::integral_constant<int, -3>{});
-        row(std::integral_constant<int, -2>{});
-        row(std::integral_constant<int, -1>{});
-        row(std::integral_constant<int, 0>{});
-        row(std::integral_constant<int, 1>{});
-        row(std::integral_constant<int, 2>{});
-        row(std::integral_constant<int, 3>{});
-      }
-      const int64_t k = (int64_t)Jc * Lc + Ic;
-      bcg[k] = sum.x;
-      bcg[Nc + k] = sum.y;
-    };
-    using std::integral_constant;
-    switch (u & 3) {
-      case 0: gather(integral_constant<int, 0>{}, integral_constant<int, 0>{}); break;
-      case 1: gather(integral_constant<int, 1>{}, integral_constant<int, 0>{}); break;
-      case 2: gather(integral_constant<int, 0>{}, integral_constant<int, 1>{}); break;
-      default: gather(integral_constant<int, 1>{}, integral_constant<int, 1>{}); break;
-    }
-  }
+  restrict_cells<T, C, LW, RPL, kRRc, CR, kWaves>(R + 4 * LW + 2, n, C0, R0, bcg);
 }
 
 constexpr int kRestrictWideN = 256;   // cells per side from which a block takes two rows per wave

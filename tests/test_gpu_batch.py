@@ -125,6 +125,26 @@ def test_inner_check_modes_bitwise(prec):
             ctx.close()
 
 
+@pytest.mark.parametrize("n, K", [(128, 5), (96, 8), (64, 17)])
+@pytest.mark.parametrize("prec", [fsi.FP64, fsi.FP32])
+def test_batch_across_the_restriction_rule(n, K, prec):
+    """Alone, the levels of up to 256^2 cells restrict in their first smoothing launch; in a batch of more
+    than 65,536 cells the finest level (not at 64^2) takes the two launches: the same bits."""
+    torch_dev()
+    assert K * n * n > 256 * 256
+    print(f"[batch rule n={n} K={K} prec={prec}]", flush=True)
+    opts = fsi.Opts(prec=prec, pc=fsi.PC_TRI, rtol=1e-8)
+    wls = workloads(n, K, seed=31)
+    ctxs = [fsi.Context.from_workload(wl) for wl in wls]
+    states, stats, rcs = batch(ctxs, wls, opts)
+    assert rcs == [fsi.FSI_OK] * K
+    for k in (0, K - 1):
+        a, sa = alone(wls[k], opts, False)
+        assert np.array_equal(states[k], a) and stats[k]["inner_its"] == sa["inner_its"], k
+    for c in ctxs:
+        c.close()
+
+
 def test_batch_matches_oracle():
     torch_dev()
     print("[batch oracle]", flush=True)
