@@ -84,7 +84,8 @@ def inner_step_bytes(n, prec):
     w = 8 (FP64) or 4 (FP32 preconditioner):
       A11 product with the MINRES scaling and first update (FP64): 64 N2 + 32 Np;
       velocity V-cycle, per level above the one-launch tail (cells > 16): pre-smoothing 4w N2_l
-        (b read, x written, two components), residual + restriction 4w N2_l + 2w N2_{l+1},
+        (b read, x written, two components), residual + restriction 4w N2_l + 2w N2_{l+1}
+        (2w N2_{l+1} up to 256^2 cells, where the pre-smoothing launch does it),
         post-smoothing with the coarse correction 6w N2_l + 2w N2_{l+1}; the finest
         pre-smoothing makes its right-hand side (two FP64 vectors read, one written: 48 N2 + 24 Np)
         in place of reading it;
@@ -106,7 +107,8 @@ def inner_step_bytes(n, prec):
         post = 6 * w * N2(m)
         if k == 0 and prec != "fp64":
             post = (4 * w + 16) * N2(m) + 16 * N2(m)
-        b += 4 * w * N2(m) + (4 * w * N2(m) + 2 * w * N2(m // 2)) + post + 2 * w * N2(m // 2)
+        resid = (0 if m <= 256 else 4 * w * N2(m)) + 2 * w * N2(m // 2)
+        b += 4 * w * N2(m) + resid + post + 2 * w * N2(m // 2)
     b += 48 * N2(n) + 24 * Np(n) - 2 * w * N2(n)
     b += 4 * w * N2(tail) + 162 * 162 * w
     pfull, _ = _levels(n, 4)
