@@ -168,9 +168,9 @@ void stencil_tables(int n, double nu, double rdt, StencilTable &t) {
   }
 }
 
-// The values of AfCoef from nu and M = (rho/dt) h^2 / 720; every entry of the stencil table above,
-// summed from the element matrices, has to be the value cell_products takes for it.
-void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f) {
+// The values of AfCoef from nu and M = (rho/dt) h^2 / 720
+static AfCoef<double> af_closed_form(int n, double nu, double rdt) {
+  AfCoef<double> c;
   const double h = 1.0 / n, k = nu / 24.0, m = rdt * h * h / 720.0;
   c.cv = 72 * k + 72 * m;
   c.ce = 96 * k + 128 * m;
@@ -191,46 +191,62 @@ void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f)
   c.dvo = c.k12 / dv;
   c.ded = c.ce / de;
   c.deo = c.k16 / de;
+  return c;
+}
+
+// Every entry of the stencil table above, summed from the element matrices, has to be the value that
+// cell_products and cell_dinv take for it.  A_f is linear in nu and rho/dt: each part at a unit value,
+// so that a caller's parameters, of any size (dt = inf included), decide nothing here.
+static void check_af_closed_form(int n) {
+  for (int part = 0; part < 2; ++part) {
+    const double nu = part == 0 ? 1.0 : 0.0, rdt = 1.0 - nu;
+    const AfCoef<double> c = af_closed_form(n, nu, rdt);
+    StencilTable t;
+    stencil_tables(n, nu, rdt, t);
+    // entry (class, offset): along and across the x component, and the cross coupling
+    struct E { double xx, yy, xy; };
+    auto entry = [&](int cls, int I, int J) -> E {
+      if (I < 0 || (I == 0 && J < 0)) { I = -I; J = -J; }   // opposite neighbours are alike
+      const int key = 10 * I + J;
+      if (key == 0) return cls == 0 ? E{c.cv, c.cv, -c.k12} : E{c.ce, c.ce, -c.k16};
+      if (cls == 0) switch (key) {
+        case 10: return E{-c.k32, -c.k16, c.k8};
+        case 1: return E{-c.k16, -c.k32, c.k8};
+        case 20: return E{c.v2p, c.v2n, -c.k2};
+        case 2: return E{c.v2n, c.v2p, -c.k2};
+        case 11: return E{0, 0, -c.k8};
+        case 22: return E{c.m4, c.m4, c.k2};
+        default: return E{c.m8, c.m8, 0};                   // (1, 2), (2, 1), (1, -1)
+      }
+      if (key == 10) return cls == 1 ? E{-c.k32, -c.k16, c.k8} : E{c.e1p, c.e1n, c.k8};
+      if (key == 1) return cls == 2 ? E{-c.k16, -c.k32, c.k8} : E{c.e1n, c.e1p, c.k8};
+      if (key == 11) return cls == 3 ? E{0, 0, -c.k8} : E{c.m32, c.m32, -c.k8};
+      return E{c.m8, c.m8, 0};
+    };
+    for (int cls = 0; cls < 4; ++cls) {
+      for (int q = 0; q < t.count[cls]; ++q) {
+        const E e = entry(cls, t.off[cls][q][0], t.off[cls][q][1]);
+        const double *v = t.coef[cls][q], tol = 1e-13 * c.ce;
+        FSI_REQUIRE(std::abs(v[0] - e.xx) <= tol && std::abs(v[3] - e.yy) <= tol && std::abs(v[1] - e.xy) <= tol &&
+                        std::abs(v[2] - e.xy) <= tol,
+                    FSI_E_STATE, "an entry of A_f differs from its closed form");
+      }
+      const double *d = t.dinv[cls], dd = cls ? c.ded : c.dvd, od = cls ? c.deo : c.dvo;
+      FSI_REQUIRE(std::abs(d[0] - dd) <= 1e-12 * dd && std::abs(d[3] - dd) <= 1e-12 * dd &&
+                      std::abs(d[1] - od) <= 1e-12 * dd && std::abs(d[2] - od) <= 1e-12 * dd,
+                  FSI_E_STATE, "an inverse diagonal block of A_f differs from its closed form");
+    }
+  }
+}
+
+void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f) {
+  check_af_closed_form(n);
+  c = af_closed_form(n, nu, rdt);
   const double *p = &c.cv;
   float *q = &f.cv;
   static_assert(sizeof(AfCoef<double>) == 18 * sizeof(double) && sizeof(AfCoef<float>) == 18 * sizeof(float),
                 "coefficients only");
   for (int i = 0; i < 18; ++i) q[i] = (float)p[i];
-  StencilTable t;
-  stencil_tables(n, nu, rdt, t);
-  // entry (class, offset): along and across the x component, and the cross coupling
-  struct E { double xx, yy, xy; };
-  auto entry = [&](int cls, int I, int J) -> E {
-    if (I < 0 || (I == 0 && J < 0)) { I = -I; J = -J; }   // opposite neighbours are alike
-    const int key = 10 * I + J;
-    if (key == 0) return cls == 0 ? E{c.cv, c.cv, -c.k12} : E{c.ce, c.ce, -c.k16};
-    if (cls == 0) switch (key) {
-      case 10: return E{-c.k32, -c.k16, c.k8};
-      case 1: return E{-c.k16, -c.k32, c.k8};
-      case 20: return E{c.v2p, c.v2n, -c.k2};
-      case 2: return E{c.v2n, c.v2p, -c.k2};
-      case 11: return E{0, 0, -c.k8};
-      case 22: return E{c.m4, c.m4, c.k2};
-      default: return E{c.m8, c.m8, 0};                   // (1, 2), (2, 1), (1, -1)
-    }
-    if (key == 10) return cls == 1 ? E{-c.k32, -c.k16, c.k8} : E{c.e1p, c.e1n, c.k8};
-    if (key == 1) return cls == 2 ? E{-c.k16, -c.k32, c.k8} : E{c.e1n, c.e1p, c.k8};
-    if (key == 11) return cls == 3 ? E{0, 0, -c.k8} : E{c.m32, c.m32, -c.k8};
-    return E{c.m8, c.m8, 0};
-  };
-  for (int cls = 0; cls < 4; ++cls) {
-    for (int q2 = 0; q2 < t.count[cls]; ++q2) {
-      const E e = entry(cls, t.off[cls][q2][0], t.off[cls][q2][1]);
-      const double *v = t.coef[cls][q2], tol = 1e-13 * c.ce;
-      FSI_REQUIRE(std::abs(v[0] - e.xx) <= tol && std::abs(v[3] - e.yy) <= tol && std::abs(v[1] - e.xy) <= tol &&
-                      std::abs(v[2] - e.xy) <= tol,
-                  FSI_E_STATE, "an entry of A_f differs from its closed form");
-    }
-    const double *d = t.dinv[cls], dd = cls ? c.ded : c.dvd, od = cls ? c.deo : c.dvo;
-    FSI_REQUIRE(std::abs(d[0] - dd) <= 1e-12 * dd && std::abs(d[3] - dd) <= 1e-12 * dd &&
-                    std::abs(d[1] - od) <= 1e-12 * dd && std::abs(d[2] - od) <= 1e-12 * dd,
-                FSI_E_STATE, "an inverse diagonal block of A_f differs from its closed form");
-  }
 }
 
 // Host: B^T rows of the four interior P2 node classes and the B row of an interior P1
@@ -665,12 +681,7 @@ void build_fluid(Ctx &c) {
   c.Mp_dinv.alloc(np);
   hipLaunchKernelGGL(k_diag_inv, dim3(gp), dim3(256), 0, s, np, c.Mp.rowptr.p, c.Mp.col.p, c.Mp.val.p,
                      c.Mp_dinv.p);
-  check_div_closed_form(n);
-  {   // the entries of (rho/dt) M_f alone, as mass_rows takes them
-    AfCoef<double> m64;
-    AfCoef<float> m32;
-    af_coefs(n, 0.0, c.rho / c.dt, m64, m32);
-  }
+  check_div_closed_form(n);   // (af_coefs checks the entries of M_f, which mass_rows takes too)
   c.bnd.alloc(n2);
   hipLaunchKernelGGL(k_p2_boundary_flags, dim3(g2), dim3(256), 0, s, n, c.bnd.p);
   FSI_CHECK_LAUNCH();

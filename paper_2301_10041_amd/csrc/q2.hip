@@ -47,10 +47,9 @@ void q2_tables(int n, double nu, double rdt, Q2Table &t) {
   }
 }
 
-// The values of Q2Coef; every entry of the class stencils, summed from the element matrices, has to be
-// the one that cell_products takes for it.
-void q2_coefs(int n, double nu, double rdt, Q2Coef<double> &c, Q2Coef<float> &f) {
+static Q2Coef<double> q2_closed_form(int n, double nu, double rdt) {
   const double h = 1.0 / n;
+  Q2Coef<double> c;
   c.a = nu / 90.0;
   c.b = nu / 180.0;
   c.g = rdt * h * h / 900.0;
@@ -59,31 +58,47 @@ void q2_coefs(int n, double nu, double rdt, Q2Coef<double> &c, Q2Coef<float> &f)
   c.d1 = 1.0 / (128 * c.a + 224 * c.b + 128 * c.g);
   c.d2 = 1.0 / (224 * c.a + 128 * c.b + 128 * c.g);
   c.dc = 1.0 / (256 * (c.a + c.b) + 256 * c.g);
+  return c;
+}
+
+// Every entry of the class stencils, summed from the element matrices, has to be the one that
+// cell_products takes for it: the parts of nu and of rho/dt each at a unit value (A_f is linear in them),
+// so that a caller's parameters decide nothing here.
+static void check_q2_closed_form(int n) {
+  static const double M[2][5] = {{-1, 2, 8, 2, -1}, {0, 2, 16, 2, 0}}, K[2][5] = {{1, -8, 14, -8, 1}, {0, -8, 16, -8, 0}},
+                      G[2][5] = {{-1, 4, 0, -4, 1}, {0, 4, 0, -4, 0}};
+  for (int part = 0; part < 2; ++part) {
+    const double nu = part == 0 ? 1.0 : 0.0, rdt = 1.0 - nu;
+    const Q2Coef<double> c = q2_closed_form(n, nu, rdt);
+    Q2Table t;
+    q2_tables(n, nu, rdt, t);
+    const double tol = 1e-13 * 256 * (c.a + c.b + c.g);
+    for (int cls = 0; cls < 4; ++cls)
+      for (int e = 0; e < t.count[cls]; ++e) {
+        const int u = cls & 1, v = cls >> 1, i = t.off[cls][e][0] + 2, j = t.off[cls][e][1] + 2;
+        const double km = K[u][i] * M[v][j], mk = M[u][i] * K[v][j], mm = M[u][i] * M[v][j], gg = G[u][i] * G[v][j];
+        const double want[4] = {c.a * km + c.b * mk + c.g * mm, -c.k * gg, -c.k * gg, c.b * km + c.a * mk + c.g * mm};
+        for (int k = 0; k < 4; ++k)
+          FSI_REQUIRE(std::abs(t.coef[cls][e][k] - want[k]) <= tol, FSI_E_STATE,
+                      "an entry of the Q2 A_f differs from its closed form");
+        if (i == 2 && j == 2) {
+          const double d[2] = {cls == 0 ? c.dv : cls == 1 ? c.d1 : cls == 2 ? c.d2 : c.dc,
+                               cls == 0 ? c.dv : cls == 1 ? c.d2 : cls == 2 ? c.d1 : c.dc};
+          FSI_REQUIRE(std::abs(d[0] * want[0] - 1.0) <= 1e-12 && std::abs(d[1] * want[3] - 1.0) <= 1e-12, FSI_E_STATE,
+                      "an inverse diagonal of the Q2 A_f differs from its closed form");
+        }
+      }
+  }
+}
+
+void q2_coefs(int n, double nu, double rdt, Q2Coef<double> &c, Q2Coef<float> &f) {
+  check_q2_closed_form(n);
+  c = q2_closed_form(n, nu, rdt);
   const double *p = &c.a;
   float *q = &f.a;
   static_assert(sizeof(Q2Coef<double>) == 8 * sizeof(double) && sizeof(Q2Coef<float>) == 8 * sizeof(float),
                 "coefficients only");
   for (int i = 0; i < 8; ++i) q[i] = (float)p[i];
-  static const double M[2][5] = {{-1, 2, 8, 2, -1}, {0, 2, 16, 2, 0}}, K[2][5] = {{1, -8, 14, -8, 1}, {0, -8, 16, -8, 0}},
-                      G[2][5] = {{-1, 4, 0, -4, 1}, {0, 4, 0, -4, 0}};
-  Q2Table t;
-  q2_tables(n, nu, rdt, t);
-  const double tol = 1e-13 * 256 * (c.a + c.b + c.g);
-  for (int cls = 0; cls < 4; ++cls)
-    for (int e = 0; e < t.count[cls]; ++e) {
-      const int u = cls & 1, v = cls >> 1, i = t.off[cls][e][0] + 2, j = t.off[cls][e][1] + 2;
-      const double km = K[u][i] * M[v][j], mk = M[u][i] * K[v][j], mm = M[u][i] * M[v][j], gg = G[u][i] * G[v][j];
-      const double want[4] = {c.a * km + c.b * mk + c.g * mm, -c.k * gg, -c.k * gg, c.b * km + c.a * mk + c.g * mm};
-      for (int k = 0; k < 4; ++k)
-        FSI_REQUIRE(std::abs(t.coef[cls][e][k] - want[k]) <= tol, FSI_E_STATE,
-                    "an entry of the Q2 A_f differs from its closed form");
-      if (i == 2 && j == 2) {
-        const double d[2] = {cls == 0 ? c.dv : cls == 1 ? c.d1 : cls == 2 ? c.d2 : c.dc,
-                             cls == 0 ? c.dv : cls == 1 ? c.d2 : cls == 2 ? c.d1 : c.dc};
-        FSI_REQUIRE(std::abs(d[0] * want[0] - 1.0) <= 1e-12 && std::abs(d[1] * want[3] - 1.0) <= 1e-12, FSI_E_STATE,
-                    "an inverse diagonal of the Q2 A_f differs from its closed form");
-      }
-    }
 }
 
 }  // namespace fsi

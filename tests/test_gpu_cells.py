@@ -193,3 +193,26 @@ def test_mass_rows_by_cells(n):
         assert np.all(err <= 64 * 2.0**-53 * mag)
     assert np.all(got[sz["off_p"] : sz["off_Xx"]] == 0)
     ctx.close()
+
+
+@pytest.mark.parametrize("dt", [1e200, np.inf])
+def test_time_steps_without_inertia(dt):
+    """(rho/dt) M_f below every rounding (its squares below the smallest number), or exactly 0: the
+    context is made and its A11 is the one of dt = 1e30, entry by entry within the 64 roundings above."""
+    torch = torch_dev()
+    n, wl = 24, inputs.small_workload(24, 4, (0.5, 0.5), 0.2)
+    xy, tri = wl.solid_mesh()
+    X = to_dev(np.concatenate([xy[:, 0], xy[:, 1]]))
+    out = []
+    for d in (1e30, dt):
+        ctx = fsi.Context(n, xy, tri, nu=wl.nu, rho=wl.rho, dt=d)
+        ctx.assemble_coupling(X)
+        nf = ctx.sizes["off_Xx"]
+        x = np.zeros(ctx.sizes["N"])
+        x[:nf] = np.random.default_rng(8).uniform(-1, 1, nf)
+        y = torch.zeros(ctx.sizes["N"], dtype=torch.float64, device="cuda")
+        ctx.apply_operator(to_dev(x), y)
+        out.append(to_host(y)[:nf])
+        ctx.close()
+    _, mag = a11_rows(n, wl.nu, 0.0, x[:nf])
+    assert np.all(np.abs(out[1] - out[0]) <= 2 * 64 * 2.0**-53 * mag.astype(np.float64))
