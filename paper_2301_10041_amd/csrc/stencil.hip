@@ -1058,13 +1058,16 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
     }
   } else {
     if (a.cft_rp) {   // uniform: + C_f^T x_lam
-      // The rows of a wave's nodes on one lattice row are consecutive in C_f^T: the wave forms their
-      // products entry by entry (coalesced) into LDS, over the x nobody needs any more, and each
-      // thread sums its own rows there in their order.  A thread that walks its rows in device
-      // memory instead: 194 us at 1024^2 with 2.8 M entries, against
-      // 98 (141 with one thread per node; 115 without fetching a segment ahead).
+      // The rows of a wave's nodes on one lattice row are consecutive in C_f^T: the wave brings their
+      // values and the x_lam that they meet (coalesced entry by entry) into LDS, the latter over the x
+      // nobody needs any more, and each thread sums its own rows there in their order, every product
+      // fused into its sum.  A thread that walks its rows in device memory instead: 194 us at 1024^2 with
+      // 2.8 M entries, against 89 (97 with the products rounded before they go through LDS; 141 with one thread
+      // per node).
       constexpr int CH = 2 * kCellPL / kCellRows / kWave * kWave;
+      __shared__ double values[kCellRows * CH];
       V2<double> *const buf = X + w * CH;
+      double *const cbuf = values + w * CH;
       const int last = min(n - i0, kWave - 1);   // the wave's last lane in the lattice
       __syncthreads();
 #pragma unroll
@@ -1085,10 +1088,13 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
           V2<double> xl[CH / kWave];
 #pragma unroll
           for (int u = 0; u < CH / kWave; ++u)
-            if (cc[u] >= 0) xl[u] = V2<double>{cv[u] * a.xlx[cc[u]], cv[u] * a.xly[cc[u]]};
+            if (cc[u] >= 0) xl[u] = V2<double>{a.xlx[cc[u]], a.xly[cc[u]]};
 #pragma unroll
           for (int u = 0; u < CH / kWave; ++u)
-            if (cc[u] >= 0) buf[kWave * u + lane] = xl[u];
+            if (cc[u] >= 0) {
+              buf[kWave * u + lane] = xl[u];
+              cbuf[kWave * u + lane] = cv[u];
+            }
           fetch(c0 + CH);
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
@@ -1097,8 +1103,9 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
             const int e = min(ct[h][q + 1], c0 + CH);
             for (int k = max(ct[h][q], c0); k < e; ++k) {
               const V2<double> v = buf[k - c0];
-              s[2 * h + q].x += v.x;
-              s[2 * h + q].y += v.y;
+              const double c = cbuf[k - c0];
+              s[2 * h + q].x = fma(c, v.x, s[2 * h + q].x);
+              s[2 * h + q].y = fma(c, v.y, s[2 * h + q].y);
             }
           }
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

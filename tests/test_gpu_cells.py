@@ -216,3 +216,35 @@ def test_time_steps_without_inertia(dt):
         ctx.close()
     _, mag = a11_rows(n, wl.nu, 0.0, x[:nf])
     assert np.all(np.abs(out[1] - out[0]) <= 2 * 64 * 2.0**-53 * mag.astype(np.float64))
+
+
+@pytest.mark.parametrize("n, m", [(16, 4), (24, 9), (24, 40)])
+def test_cft_term_rounds_once_per_product(n, m):
+    """The C_f^T x_lam term of a velocity row with nothing else in it: its products in the row's order,
+    each fused into the sum (one rounding), bit for bit.  At m = 40 the rows of a lattice row hold more
+    entries than one segment (256)."""
+    from fractions import Fraction
+
+    torch = torch_dev()
+    wl = inputs.small_workload(n, m, (0.5, 0.5), 0.2)
+    ctx = fsi.Context.from_workload(wl)
+    xy, _ = wl.solid_mesh()
+    ctx.assemble_coupling(to_dev(np.concatenate([xy[:, 0], xy[:, 1]])))
+    sz = ctx.sizes
+    ns, N2 = sz["Ns"], sz["N2"]
+    x = np.zeros(sz["N"])
+    lam = x[sz["off_lx"] :]
+    lam[:] = np.random.default_rng(m).uniform(-1, 1, 2 * ns)
+    y = torch.zeros(sz["N"], dtype=torch.float64, device="cuda")
+    ctx.apply_operator(to_dev(x), y)
+    y = to_host(y)
+    rp, col, val = ctx.export_csr("CFT")
+    ctx.close()
+    rows = np.flatnonzero(np.diff(rp) > 1)
+    assert rows.size
+    for r in rows[:: max(1, rows.size // 200)]:
+        for k in range(2):
+            s = 0.0
+            for e in range(rp[r], rp[r + 1]):
+                s = float(Fraction(val[e, 0]) * Fraction(lam[k * ns + col[e]]) + Fraction(s))
+            assert y[k * N2 + r] == s, (r, k)
