@@ -169,8 +169,8 @@ static void launch_operator(Ctx &c, const Tx *x, Ty *y, bool fluid_only, bool so
   FSI_CHECK_LAUNCH();
 }
 
-// Fluid rows matrix-free (structured-grid products enabled, FP64): one launch for
-// the velocity and pressure rows, then the solid row group of the fused kernel.
+// Fluid rows matrix-free (structured-grid products enabled, FP64): a launch for the velocity and
+// pressure rows, one for C_f^T x_lam, then the solid row group of the fused kernel.
 static void fluid_rows_stencil(Ctx &c, const double *x, double *y, bool fluid_only) {
   const bool cft = !fluid_only && c.CfT.rowptr.p != nullptr;
   const double *xl = x + 2 * c.N2 + c.Np + 2 * c.Ns;

@@ -88,8 +88,9 @@ struct DivTable {
 // Launchers run K independent systems (lane = blockIdx.y) over per-lane views (LP); the
 // vector views of one launch share one lane stride.  K = 1: one system.
 
-// Fluid rows of the operator on [u_x | u_y | p] in one launch:
-//   y_u = A_f x_u - B^T x_p (+ C_f^T x_lam when cft_rp is given; lam_x at xl, lam_y at xl + Ns)
+// Fluid rows of the operator on [u_x | u_y | p]:
+//   y_u = A_f x_u - B^T x_p (+ C_f^T x_lam, a launch of its own, when cft_rp is given; lam_x at xl, lam_y
+//   at xl + Ns)
 //   y_p = -B x_u, and y_p[0] = x_p[0] (pinned node)
 void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
               const double *cft_val, const double *xl, int64_t Ns, hipStream_t s);

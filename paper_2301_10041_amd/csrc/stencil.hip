@@ -852,8 +852,6 @@ struct A11Args {
   const double *x;
   double *y;            // in MINRES: r1, overwritten
   int64_t lv;           // lane stride of x, y and v (lane = blockIdx.y)
-  const int *cft_rp, *cft_col;   // C_f^T of one system (K = 1), or null
-  const double *cft_val, *xlx, *xly;
   MsA11 m;              // in MINRES
 };
 
@@ -868,7 +866,6 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
   constexpr bool MS = MODE != A11_ROWS, STEP = MODE == A11_MS_STEP;
   // the paper's pair: three pressure unknowns per cell (qpressure.hip has their tensor numbers), MINRES only
   constexpr bool Q2 = !std::is_same<C, AfCoef<double>>::value;
-  static_assert(MS || LW == kWave, "the C_f^T rows of a wave are one row of cells");
   static_assert(MS || !Q2, "the operator's rows of the paper's pair are assembled");
   constexpr int NP = Q2 ? 3 : 1;
   __shared__ V2<double> X[2 * kCellPL];
@@ -924,19 +921,6 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
         if (threadIdx.x + NT * k < XPN) XP[u * XPN + threadIdx.x + NT * k] = v[k][u];
   }
   stage_pairs<double, kCellH, LW>(X, xg, N, L, n, i0, j0, [](int, int, V2<double> v) -> V2<double> { return v; });
-  int ct[2][3] = {};   // C_f^T rows of the cell's nodes: consecutive on each lattice row
-  if constexpr (!MS) {
-    if (node && a.cft_rp) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (h == 1 && j == n) continue;
-        const int *rp = a.cft_rp + (int64_t)(2 * j + h) * L + 2 * i;
-        ct[h][0] = rp[0];
-        ct[h][1] = rp[1];
-        ct[h][2] = i < n ? rp[2] : ct[h][1];
-      }
-    }
-  }
   V2<double> r1[4];
   double r1p[NP] = {};
   auto load_r1 = [&] {
@@ -1057,62 +1041,6 @@ __global__ void __launch_bounds__(LW *kCellRows, (kA11Waves<C> * LW / kWave > 1 
       }
     }
   } else {
-    if (a.cft_rp) {   // uniform: + C_f^T x_lam
-      // The rows of a wave's nodes on one lattice row are consecutive in C_f^T: the wave brings their
-      // values and the x_lam that they meet (coalesced entry by entry) into LDS, the latter over the x
-      // nobody needs any more, and each thread sums its own rows there in their order, every product
-      // fused into its sum.  A thread that walks its rows in device memory instead: 194 us at 1024^2 with
-      // 2.8 M entries, against 89 (97 with the products rounded before they go through LDS; 141 with one thread
-      // per node).
-      constexpr int CH = 2 * kCellPL / kCellRows / kWave * kWave;
-      __shared__ double values[kCellRows * CH];
-      V2<double> *const buf = X + w * CH;
-      double *const cbuf = values + w * CH;
-      const int last = min(n - i0, kWave - 1);   // the wave's last lane in the lattice
-      __syncthreads();
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k0 = __shfl(ct[h][0], 0), k1 = __shfl(ct[h][2], last);
-        double cv[CH / kWave];
-        int cc[CH / kWave];
-        auto fetch = [&](int c0) {   // the entries of a segment, one segment ahead of their products
-#pragma unroll
-          for (int u = 0; u < CH / kWave; ++u) {
-            const int k = c0 + kWave * u + lane;
-            cv[u] = k < k1 ? a.cft_val[k] : 0.0;
-            cc[u] = k < k1 ? a.cft_col[k] : -1;
-          }
-        };
-        fetch(k0);
-        for (int c0 = k0; c0 < k1; c0 += CH) {
-          V2<double> xl[CH / kWave];
-#pragma unroll
-          for (int u = 0; u < CH / kWave; ++u)
-            if (cc[u] >= 0) xl[u] = V2<double>{a.xlx[cc[u]], a.xly[cc[u]]};
-#pragma unroll
-          for (int u = 0; u < CH / kWave; ++u)
-            if (cc[u] >= 0) {
-              buf[kWave * u + lane] = xl[u];
-              cbuf[kWave * u + lane] = cv[u];
-            }
-          fetch(c0 + CH);
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int e = min(ct[h][q + 1], c0 + CH);
-            for (int k = max(ct[h][q], c0); k < e; ++k) {
-              const V2<double> v = buf[k - c0];
-              const double c = cbuf[k - c0];
-              s[2 * h + q].x = fma(c, v.x, s[2 * h + q].x);
-              s[2 * h + q].y = fma(c, v.y, s[2 * h + q].y);
-            }
-          }
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-        }
-      }
-    }
     if (node) {
       store_cell<double, double>(yg, N, L, n, i, j, s);
       yg[o2 + q0] = sp[0];
@@ -1192,6 +1120,88 @@ static void launch_a11(A11Args<C> a, hipStream_t s, int K) {
   FSI_CHECK_LAUNCH();
 }
 
+// y_u += C_f^T x_lam: one lane per row, which sums its entries in their order, every product fused into
+// the sum.  The entries of the 64 rows of a wavefront come kCftSlice per row and round, a row's by
+// neighbouring lanes, with the x_lam that they meet, through LDS, one round ahead; rows without entries
+// (most of them) end after their pointers.
+//
+// Bound by the latency of a round where the solid is fine (rows of 40 to 1,000 entries), by the memory
+// path of the scattered x_lam beyond 256^2.  As a part of the A11 launch, a wavefront summing two lattice
+// rows of cells from segments of 256 entries, it left all lanes but one idle on long rows.  Whole operator in us,
+// [one thread per node inside the row kernel] / [segments in the A11 launch] / now, at r = 0.2: 32^2 with
+// rows of 7.8 entries 16.5 / 15.7 / 15.9, of 141 137 / 428 / 70; 128^2, 9.3 17.9 / 20.8 / 17.2, 124 203 / 713 / 84; 256^2,
+// 9.4 24.1 / 31.8 / 19.6; 512^2, 9.5 61 / 55 / 44; 1024^2, 6.3 151 / 112 / 106, 18.6 624 / 288 / 298.
+// Slices of 8 (twice the LDS): 141 at 1024^2, 165 against 228 at 512^2 with 45 entries.
+struct CftArgs {
+  int64_t N;   // rows
+  const int *rp, *col;
+  const double *val, *lx, *ly;
+  double *y;   // two components
+};
+constexpr int kCftThreads = 256, kCftSlice = 4;
+
+__global__ void __launch_bounds__(kCftThreads) k_cft_rows(CftArgs a) {
+  constexpr int S = kCftSlice, G = kWave / S, ROW = kWave + 8;   // 8: the writes of a slice over all banks
+  __shared__ V2<double> xs[kCftThreads / kWave][S * ROW];
+  __shared__ double vs[kCftThreads / kWave][S * ROW];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int64_t r = (int64_t)blockIdx.x * kCftThreads + threadIdx.x;
+  int k = a.rp[min(r, a.N)];
+  const int k1 = a.rp[min(r + 1, a.N)];
+  if (!__ballot(k < k1)) return;   // no barrier follows: a wavefront is on its own
+  const bool any = k < k1;
+  double sx = 0.0, sy = 0.0;
+  if (any) {
+    sx = a.y[r];
+    sy = a.y[a.N + r];
+  }
+  // slice entry u of this lane: entry lane % S of the row of lane u G + lane / S
+  double v[S];
+  int c[S];
+  auto fetch = [&](int pos) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int o = u * G + lane / S, p = __shfl(pos, o) + lane % S;
+      const bool in = p < __shfl(k1, o);
+      v[u] = in ? a.val[p] : 0.0;
+      c[u] = in ? a.col[p] : -1;
+    }
+  };
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  fetch(k);
+  for (; __ballot(k < k1); k += S) {
+    V2<double> x[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if (c[u] >= 0) x[u] = V2<double>{a.lx[c[u]], a.ly[c[u]]};
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if (c[u] >= 0) {
+        const int q = lane % S * ROW + u * G + lane / S;
+        xs[w][q] = x[u];
+        vs[w][q] = v[u];
+      }
+    fetch(k + S);
+    fence();
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+      if (k + t < k1) {
+        const V2<double> g = xs[w][t * ROW + lane];
+        const double cv = vs[w][t * ROW + lane];
+        sx = fma(cv, g.x, sx);
+        sy = fma(cv, g.y, sy);
+      }
+    fence();
+  }
+  if (any) {
+    a.y[r] = sx;
+    a.y[a.N + r] = sy;
+  }
+}
+
 void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const int *cft_rp, const int *cft_col,
               const double *cft_val, const double *xl, int64_t Ns, hipStream_t s) {
   A11Args<AfCoef<double>> a{};
@@ -1199,12 +1209,12 @@ void a11_rows(int n, const AfCoef<double> &cf, const double *x, double *y, const
   a.cf = cf;
   a.x = x;
   a.y = y;
-  a.cft_rp = cft_rp;
-  a.cft_col = cft_col;
-  a.cft_val = cft_val;
-  a.xlx = xl;
-  a.xly = xl ? xl + Ns : nullptr;
   launch_a11<A11_ROWS, kWave>(a, s, 1);
+  if (!cft_rp) return;
+  const int64_t N = (int64_t)(2 * n + 1) * (2 * n + 1);
+  hipLaunchKernelGGL(k_cft_rows, dim3((unsigned)((N + kCftThreads - 1) / kCftThreads)), dim3(kCftThreads), 0, s,
+                     CftArgs{N, cft_rp, cft_col, cft_val, xl, xl + Ns, y});
+  FSI_CHECK_LAUNCH();
 }
 
 template <typename C>

@@ -221,8 +221,8 @@ def test_time_steps_without_inertia(dt):
 @pytest.mark.parametrize("n, m", [(16, 4), (24, 9), (24, 40)])
 def test_cft_term_rounds_once_per_product(n, m):
     """The C_f^T x_lam term of a velocity row with nothing else in it: its products in the row's order,
-    each fused into the sum (one rounding), bit for bit.  At m = 40 the rows of a lattice row hold more
-    entries than one segment (256)."""
+    each fused into the sum (one rounding), bit for bit: rows shorter and longer than a round's slice (4
+    entries), up to hundreds of entries at m = 40, and wavefronts of 64 rows without any."""
     from fractions import Fraction
 
     torch = torch_dev()
