@@ -241,6 +241,8 @@ static void check_af_closed_form(int n) {
 
 void af_coefs(int n, double nu, double rdt, AfCoef<double> &c, AfCoef<float> &f) {
   check_af_closed_form(n);
+  StencilTable t;
+  stencil_tables(n, nu, rdt, t);   // refuses a viscosity whose cross couplings are not finite
   c = af_closed_form(n, nu, rdt);
   const double *p = &c.cv;
   float *q = &f.cv;

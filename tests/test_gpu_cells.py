@@ -248,3 +248,12 @@ def test_cft_term_rounds_once_per_product(n, m):
             for e in range(rp[r], rp[r + 1]):
                 s = float(Fraction(val[e, 0]) * Fraction(lam[k * ns + col[e]]) + Fraction(s))
             assert y[k * N2 + r] == s, (r, k)
+
+
+def test_infinite_viscosity_is_refused():
+    torch_dev()
+    wl = inputs.small_workload(8, 3, (0.5, 0.5), 0.2)
+    xy, tri = wl.solid_mesh()
+    with pytest.raises(fsi.FsiError) as e:
+        fsi.Context(8, xy, tri, nu=np.inf)
+    assert e.value.code == fsi.FSI_E_ARG
