@@ -262,7 +262,7 @@ int fsi_set_smoother(fsi_ctx *ctx, int kind) {
   if (kind != FSI_SMOOTH_CSR && kind != FSI_SMOOTH_STENCIL) return FSI_E_ARG;
   return guarded(ctx, [&] {
     FSI_REQUIRE(ctx->c.pair == FSI_PAIR_P2P1 || kind == FSI_SMOOTH_CSR, FSI_E_STATE,
-                "the matrix-free smoother takes the triangle pair only");
+                "the Q2 pair has no such choice: its cycles are matrix-free (FSI_SMOOTH_CSR is taken and changes nothing)");
     FSI_HIP(hipStreamSynchronize(ctx->c.stream));   // captured graphs may still be running
     ctx->c.drop_graphs();
     ctx->c.mgu.stencil = ctx->c.mgp.stencil = kind == FSI_SMOOTH_STENCIL;
@@ -641,9 +641,8 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
       }
       case FSI_LAT_LP:
       case FSI_LAT_MP: {
-        fsi::P1Table<double> t;
-        fsi::P1Table<float> tf;
-        fsi::p1_tables(n, table == FSI_LAT_LP ? fsi::kTableLp : fsi::kTableMp, table == FSI_LAT_LP ? 1 : 0, t, tf);
+        fsi::P1Table t;
+        fsi::p1_tables(n, table == FSI_LAT_LP ? fsi::kTableLp : fsi::kTableMp, table == FSI_LAT_LP ? 1 : 0, t);
         static const int nb[fsi::kP1Nbr][2] = {{0, 0}, {-1, 0}, {1, 0}, {0, -1}, {0, 1}, {-1, -1}, {1, 1}};
         for (int c = 0; c < 9; ++c) {
           counts[c] = fsi::kP1Nbr;
@@ -681,9 +680,8 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
         break;
       }
       case FSI_LAT_R: {
-        fsi::P2RestrTable<double> t;
-        fsi::P2RestrTable<float> tf;
-        fsi::p2_restrict_tables(t, tf);
+        fsi::P2RestrTable t;
+        fsi::p2_restrict_tables(t);
         for (int c = 0; c < 4; ++c) {
           counts[c] = t.count[c];
           for (int k = 0; k < t.count[c]; ++k) {
@@ -771,15 +769,10 @@ int fsi_profile_read(fsi_ctx *ctx, int prec, int64_t *launches, double *total_ms
     const fsi::MgLevel &L = c.mgu.lv[0];
     if (launches) *launches = cnt;
     if (total_ms) *total_ms = t;
-    // FP32 form with three post-smoothing steps: the launch stores y into the FP64 output;
-    // the direction is stored only for the single steps after the fused launch, which with
-    // three or more steps also reads the coarse correction (two components, next level)
-    const int degree = prec == FSI_FP64 ? c.mgu.degree : c.mgu.degree32;
-    const double wy = (prec == FSI_FP32 && degree == 3) ? 8.0 : w;
-    const double wd = degree > 3 ? w : 0.0;
-    const double coarse = (degree >= 3 && c.mgu.lv.size() > 1) ? (double)c.mgu.lv[1].nodes * 2 * w : 0.0;
+    // the launch reads x, b and the coarse correction (next level) and, in FP32 too, stores y in FP64
+    const double coarse = c.mgu.lv.size() > 1 ? (double)c.mgu.lv[1].nodes * 2 * w : 0.0;
     if (bytes_per_launch)
-      *bytes_per_launch = c.mgu.stencil || L.q2 ? (double)L.nodes * 2 * (2 * w + wd + wy) + coarse
+      *bytes_per_launch = c.mgu.stencil || L.q2 ? (double)L.nodes * 2 * (2 * w + 8.0) + coarse
                                                 : (double)L.A.nnz * (4 * w + 4) + (double)L.nodes * (4 + 14 * w) + 4.0;
   });
 }

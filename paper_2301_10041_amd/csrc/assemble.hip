@@ -19,13 +19,6 @@
 
 namespace fsi {
 
-// Copy of a host table into a device buffer (synchronous: the host object is a local).
-static void upload_bytes(DevBuf<unsigned char> &dst, const void *src, size_t bytes, hipStream_t s) {
-  dst.alloc(bytes);
-  FSI_HIP(hipMemcpyAsync(dst.p, src, bytes, hipMemcpyHostToDevice, s));
-  FSI_HIP(hipStreamSynchronize(s));
-}
-
 // ---------------------------------------------------------------- element matrices
 // Degree-4 six-point rule on a triangle (Dunavant, 1985): positive weights, exact for
 // polynomials of degree <= 4, which covers every integrand below (P2 x P2 mass).
@@ -372,12 +365,11 @@ void check_div_closed_form(int n) {
 
 // Host: rows of a P1 x P1 matrix (EM_MP: mass, EM_LP: Laplacian) at one node of each of
 // the nine position classes of an n x n grid, summed over the triangles around the node.
-void p1_tables(int n, int which, int pin, P1Table<double> &t64, P1Table<float> &t32) {
+void p1_tables(int n, int which, int pin, P1Table &t) {
   FSI_REQUIRE(n >= 2, FSI_E_ARG, "P1 tables need n >= 2");
   std::vector<double> E;
   element_tables(n, 1.0, E);
-  std::memset(&t64, 0, sizeof(t64));
-  std::memset(&t32, 0, sizeof(t32));
+  std::memset(&t, 0, sizeof(t));
   static const int nb[kP1Nbr][2] = {{0, 0}, {-1, 0}, {1, 0}, {0, -1}, {0, 1}, {-1, -1}, {1, 1}};
   const int rep[3] = {0, 1, n};
   for (int cls = 0; cls < 9; ++cls) {
@@ -387,23 +379,20 @@ void p1_tables(int n, int which, int pin, P1Table<double> &t64, P1Table<float> &
       double v = 0.0;
       for (int cj = std::max(0, j - 1); cj <= std::min(n - 1, j); ++cj)
         for (int ci = std::max(0, i - 1); ci <= std::min(n - 1, i); ++ci)
-          for (int t = 0; t < 2; ++t) {
+          for (int tr = 0; tr < 2; ++tr) {
             int a = -1, b = -1;
             for (int q = 0; q < 3; ++q) {
-              if (2 * ci + hOff[t][q][0] == 2 * i && 2 * cj + hOff[t][q][1] == 2 * j) a = q;
-              if (2 * ci + hOff[t][q][0] == 2 * i2 && 2 * cj + hOff[t][q][1] == 2 * j2) b = q;
+              if (2 * ci + hOff[tr][q][0] == 2 * i && 2 * cj + hOff[tr][q][1] == 2 * j) a = q;
+              if (2 * ci + hOff[tr][q][0] == 2 * i2 && 2 * cj + hOff[tr][q][1] == 2 * j2) b = q;
             }
-            if (a >= 0 && b >= 0) v += E[t * EM_SIZE + which + a * 3 + b];
+            if (a >= 0 && b >= 0) v += E[tr * EM_SIZE + which + a * 3 + b];
           }
       if (pin && cls == 0) v = (k == 0) ? 1.0 : 0.0;   // identity row of the pinned node 0
-      t64.coef[cls][k] = v;
-      t32.coef[cls][k] = (float)v;
+      t.coef[cls][k] = v;
     }
-    FSI_REQUIRE(t64.coef[cls][0] > 0.0, FSI_E_ARG, "P1 table: non-positive diagonal");
-    t64.dinv[cls] = 1.0 / t64.coef[cls][0];
-    t32.dinv[cls] = (float)t64.dinv[cls];
+    FSI_REQUIRE(t.coef[cls][0] > 0.0, FSI_E_ARG, "P1 table: non-positive diagonal");
+    t.dinv[cls] = 1.0 / t.coef[cls][0];
   }
-  t64.pin = t32.pin = pin;
 }
 
 // ---------------------------------------------------------------- structured adjacency
@@ -1344,9 +1333,8 @@ void build_multigrid(Ctx &c) {
     }
   }
   {   // (checks the compiled transfer weights)
-    P2RestrTable<double> t64;
-    P2RestrTable<float> t32;
-    p2_restrict_tables(t64, t32);
+    P2RestrTable t;
+    p2_restrict_tables(t);
   }
   if (nu < ns.size()) coarse_inverse_spd_device(c.mgu, s);
   else coarse_inverse(c.mgu, s);

@@ -355,17 +355,6 @@ inline void dot_l(LP<const TV> V, LP<const TW> w, int64_t n, LP<double> out, dou
   FSI_CHECK_LAUNCH();
 }
 
-// w -= sum_{i<k} h[i] V_i (h on the device), all FP64
-__global__ void k_multiaxpy_sub(double *w, const double *V, int64_t ldv, int k, const double *h,
-                                int64_t n) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    double s = w[e];
-    for (int i = 0; i < k; ++i) s -= h[i] * V[(int64_t)i * ldv + e];
-    w[e] = s;
-  }
-}
-
 // x += sum_{i<k} y[i] Z_i (y on the device)
 __global__ void k_multiaxpy_add(double *x, const double *Z, int64_t ldz, int k, const double *y,
                                 int64_t n) {

@@ -1,6 +1,6 @@
-// Matrix-free pieces of the two multigrid hierarchies on the structured grid (see
-// lattice.hip): P1 pressure operators (L_p with the pinned node, M_p), the first Chebyshev
-// step with class-wise diagonal inverses, and the P2 / P1 grid transfers.
+// Matrix-free pieces of the two multigrid hierarchies on the structured grid: the launches of the
+// pressure parts and of the velocity cycle's coarse end, and host tables of the P1 operators and of the P2
+// restriction (exported to tests; the kernels hold these numbers in closed form).
 #pragma once
 
 #include "common.h"
@@ -15,43 +15,22 @@ constexpr int kP1Nbr = 7;
 
 // Node classes by position: ci = 0 (i = 0), 1 (interior), 2 (i = n); the same for j;
 // class = 3 cj + ci.  coef[c][k] couples a node of class c with the node at offset k
-// (zero where that node is outside the lattice).  pin = 1: the row of node 0 is the
+// (zero where that node is outside the lattice).  With the pin the row of node 0 is the
 // identity and its column is zero (the pressure level is fixed at node 0).
-template <typename T>
 struct P1Table {
-  T coef[9][kP1Nbr];
-  T dinv[9];
-  int pin;
+  double coef[9][kP1Nbr];
+  double dinv[9];
 };
 
 // P2 restriction R = P^T: for each class of coarse node (bit 0 = Ic odd, bit 1 = Jc odd),
 // the fine nodes (offsets from the fine node 2 Ic, 2 Jc) whose interpolated value uses the
 // coarse node, with the coarse basis function's value there as weight.
 constexpr int kRestrMax = 81;
-template <typename T>
 struct P2RestrTable {
   int count[4];
   int off[4][kRestrMax][2];
-  T w[4][kRestrMax];
+  double w[4][kRestrMax];
 };
-
-// The fine-node offsets of the restriction classes in table order (dJ, then dI); they
-// follow from the nested triangulation alone (the table builder checks them).  Kernels
-// index them with compile-time class and entry.
-constexpr int kRestrCount[4] = {25, 9, 9, 9};
-struct RestrOffsets {
-  int d[4][25][2];
-};
-__host__ __device__ constexpr RestrOffsets restrict_offsets() {
-  return RestrOffsets{{
-      {{-3, -3}, {-2, -3}, {-1, -3}, {0, -3}, {-3, -2}, {1, -2}, {-3, -1}, {-1, -1}, {0, -1},
-       {2, -1}, {-3, 0}, {-1, 0}, {0, 0}, {1, 0}, {3, 0}, {-2, 1}, {0, 1}, {1, 1},
-       {3, 1}, {-1, 2}, {3, 2}, {0, 3}, {1, 3}, {2, 3}, {3, 3}},
-      {{-1, -2}, {-1, -1}, {0, -1}, {-1, 0}, {0, 0}, {1, 0}, {0, 1}, {1, 1}, {1, 2}},
-      {{-2, -1}, {-1, -1}, {0, -1}, {-1, 0}, {0, 0}, {1, 0}, {0, 1}, {1, 1}, {2, 1}},
-      {{-1, -1}, {0, -1}, {1, -1}, {-1, 0}, {0, 0}, {1, 0}, {-1, 1}, {0, 1}, {1, 1}},
-  }};
-}
 
 // Lattice offsets (units h/2 from the cell's lower-left node) of the six P2 nodes of
 // triangle t of a cell: T0 = (v00, v10, v11), T1 = (v00, v11, v01); vertices a, b, c
@@ -103,8 +82,8 @@ __host__ __device__ inline int p2_prolong_weights(int I, int J, int nf, int *Ic,
 
 // Host table builders (which: kTableMp = pressure mass, kTableLp = pressure Laplacian)
 constexpr int kTableMp = 216, kTableLp = 225;   // offsets of the P1 blocks in the element tables
-void p1_tables(int n, int which, int pin, P1Table<double> &t64, P1Table<float> &t32);   // assemble.hip
-void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32);          // lattice.hip
+void p1_tables(int n, int which, int pin, P1Table &t);   // assemble.hip
+void p2_restrict_tables(P2RestrTable &t);                // lattice.hip
 
 // Launchers (stream-ordered, no synchronisation) over K independent systems (lane =
 // blockIdx.y; each vector is a per-lane view, K = 1 for one system).
@@ -206,7 +185,7 @@ int qp_up_tiles(int n);
 // level, the right-hand sides (two nodes per thread and level), the coarsest b and x (m each)
 // and, at byte offp, the partial sums of the dense solve in FP64; lds = the total in bytes.  b and x
 // in device memory: the first level's right-hand side and result (lane stride lb).
-constexpr int kTailMax = 3, kTailDeg = 8, kTailMaxN = 16, kTailDenseMax = 6 * 64;
+constexpr int kTailMax = 3, kTailSteps = 3, kTailMaxN = 16, kTailDenseMax = 6 * 64;
 constexpr int kTailDenseReg = 54;   // entries of the dense inverse that a thread keeps in registers
 constexpr int kTailLevelV2 = 2 * (2 * kTailMaxN + 5) * (kTailMaxN + 3);
 // Largest LDS block of the tail launch on the current device (queried once, at most 160 KiB).
@@ -216,11 +195,11 @@ struct TailLevel {
   int n;
   AfCoef<T> cf;
   T s;                                     // 1 / theta: the first step of both smoothings
-  T c1[kTailDeg - 1], c2[kTailDeg - 1];    // the later Chebyshev steps
+  T c1[kTailSteps - 1], c2[kTailSteps - 1];   // the later Chebyshev steps
 };
 template <typename T>
 struct TailArgs {
-  int nlev, degree;
+  int nlev;
   TailLevel<T> lv[kTailMax];
   int offp, m, lds;
   const T *cinv;

@@ -11,9 +11,8 @@ namespace fsi {
 // ---------------------------------------------------------------- P2 restriction weights
 // Host: the restriction weights do not depend on the level (nested uniform refinement),
 // so they are read off at interior coarse nodes of a 16 x 16 fine grid.
-void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32) {
-  std::memset(&t64, 0, sizeof(t64));
-  std::memset(&t32, 0, sizeof(t32));
+void p2_restrict_tables(P2RestrTable &t) {
+  std::memset(&t, 0, sizeof(t));
   const int nf = 16;
   for (int cls = 0; cls < 4; ++cls) {
     const int Ic = 4 + (cls & 1), Jc = 4 + (cls >> 1);
@@ -26,19 +25,13 @@ void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32) {
         for (int q = 0; q < m; ++q)
           if (ic[q] == Ic && jc[q] == Jc) {
             FSI_REQUIRE(cnt < kRestrMax, FSI_E_ARG, "restriction table overflow");
-            t64.off[cls][cnt][0] = t32.off[cls][cnt][0] = dI;
-            t64.off[cls][cnt][1] = t32.off[cls][cnt][1] = dJ;
-            t64.w[cls][cnt] = w[q];
-            t32.w[cls][cnt] = (float)w[q];
+            t.off[cls][cnt][0] = dI;
+            t.off[cls][cnt][1] = dJ;
+            t.w[cls][cnt] = w[q];
             ++cnt;
           }
       }
-    t64.count[cls] = t32.count[cls] = cnt;
-    constexpr RestrOffsets ro = restrict_offsets();
-    FSI_REQUIRE(cnt == kRestrCount[cls], FSI_E_ARG, "unexpected restriction width");
-    for (int k = 0; k < cnt; ++k)
-      FSI_REQUIRE(t64.off[cls][k][0] == ro.d[cls][k][0] && t64.off[cls][k][1] == ro.d[cls][k][1], FSI_E_ARG,
-                  "restriction offsets differ from the compiled pattern");
+    t.count[cls] = cnt;
   }
   // the compiled transfer weights (afcell.h) against the interpolation they stand for
   for (int B = 0; B < 4; ++B)
@@ -53,11 +46,11 @@ void p2_restrict_tables(P2RestrTable<double> &t64, P2RestrTable<float> &t32) {
     }
   for (int cls = 0; cls < 4; ++cls) {
     double sum = 0.0;
-    for (int k = 0; k < t64.count[cls]; ++k) {
-      const int *o = t64.off[cls][k];
-      sum += t64.w[cls][k];
+    for (int k = 0; k < t.count[cls]; ++k) {
+      const int *o = t.off[cls][k];
+      sum += t.w[cls][k];
       FSI_REQUIRE(std::abs(o[0]) <= 3 && std::abs(o[1]) <= 3 &&
-                      t64.w[cls][k] == restrict_weight(cls & 1, cls >> 1, o[0], o[1]),
+                      t.w[cls][k] == restrict_weight(cls & 1, cls >> 1, o[0], o[1]),
                   FSI_E_ARG, "the compiled restriction weights differ from the transposed interpolation");
     }
     for (int dJ = -3; dJ <= 3; ++dJ)

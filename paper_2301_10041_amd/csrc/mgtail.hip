@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
     put(buf(l, k), pl, x);
     __syncthreads();
 #pragma unroll 1
-    for (int j = 0; j + 1 < a.degree; ++j, k ^= 1) {
+    for (int j = 0; j + 1 < kTailSteps; ++j, k ^= 1) {
       cheb_step(cf, pl, buf(l, k), lv.c1[j], lv.c2[j], x);
       put(buf(l, k ^ 1), pl, x);
       __syncthreads();
@@ -276,7 +276,7 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
   }
   __syncthreads();
   // ascent: coarse correction, post-smoothing
-  const int kend = (a.degree - 1) & 1;   // buffer that the pre-smoothing left the iterate in
+  constexpr int kend = (kTailSteps - 1) & 1;   // buffer that the pre-smoothing left the iterate in
 #pragma unroll 1
   for (int l = a.nlev - 1; l >= 0; --l) {
     const TailLevel<T> &lv = a.lv[l];
@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
           return V2<T>{dx[q], dx[Lc * Lc + q]};
         });
       } else {   // the next level's iterate: the buffer that its post-smoothing ended on
-        const V2<T> *xc = buf(l + 1, kend ^ (a.degree & 1));
+        const V2<T> *xc = buf(l + 1, kend ^ (kTailSteps & 1));
         add([&](int ai, int bj) -> V2<T> { return xc[tail_at(Ib + ai, Jb + bj)]; });
       }
     }
@@ -310,10 +310,10 @@ __global__ void __launch_bounds__(kTailThreads, 2) k_mg_tail(TailArgs<T> a) {
     __syncthreads();
     int k = kend;
 #pragma unroll 1
-    for (int j = 0; j < a.degree; ++j, k ^= 1) {
+    for (int j = 0; j < kTailSteps; ++j, k ^= 1) {
       if (j == 0) d[0] = d[1] = V2<T>{T(0), T(0)};
       cheb_step(cf, pl, buf(l, k), j == 0 ? T(0) : lv.c1[j - 1], j == 0 ? lv.s : lv.c2[j - 1], x);
-      if (l == 0 && j + 1 == a.degree) break;   // the result goes to device memory
+      if (l == 0 && j + 1 == kTailSteps) break;   // the result goes to device memory
       put(buf(l, k ^ 1), pl, x);
       __syncthreads();
     }
@@ -352,8 +352,7 @@ int tail_lds_limit() {
 
 template <typename T>
 void mg_tail(const TailArgs<T> &a, hipStream_t s, int K) {
-  FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kTailMax && a.degree >= 2 && a.degree <= kTailDeg, FSI_E_ARG,
-              "coarse tail shape out of range");
+  FSI_REQUIRE(a.nlev >= 1 && a.nlev <= kTailMax, FSI_E_ARG, "coarse tail shape out of range");
   FSI_REQUIRE(a.lv[0].n <= kTailMaxN, FSI_E_ARG, "coarse tail level too fine");
   for (int l = 0; l + 1 < a.nlev; ++l)
     FSI_REQUIRE(a.lv[l + 1].n * 2 == a.lv[l].n, FSI_E_ARG, "coarse tail levels not nested");

@@ -134,35 +134,6 @@ static void dense_mv(int m, const T *A, const T *x, T *y, int K, hipStream_t s) 
   FSI_CHECK_LAUNCH();
 }
 
-// y = a x + b y + c z
-template <typename T>
-__global__ void k_axpbypcz(T *y, const T *x, const T *z, T a, T b, T c, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    y[i] = a * x[i] + b * y[i] + c * z[i];
-}
-
-// y -= (alpha[0] * s) r   (alpha on the device)
-template <typename T>
-__global__ void k_sub_dev(T *y, const T *r, const double *alpha, double s, int64_t n) {
-  T c = (T)(alpha[0] * s);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    y[i] -= c * r[i];
-}
-
-// MINRES direction and iterate: wn = (v - e w1 - d w2) / g;  x += phi wn
-template <typename T>
-__global__ void k_minres_update(T *wn, const T *v, const T *w1, const T *w2, T *x, T e, T d, T ginv,
-                                T phi, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    T w = (v[i] - e * w1[i] - d * w2[i]) * ginv;
-    wn[i] = w;
-    x[i] += phi * w;
-  }
-}
-
 // The Schur approximation of the discontinuous pair on the pressure unknowns:
 // z = nu M_p^{-1} r + (rho/dt) x_L (M_p diagonal, x_L the V-cycle on L = B D^{-1} B^T) in T, stored
 // as TZ, except z[0] = r[0] rounded through T (the pinned unknown)
@@ -297,33 +268,25 @@ static void p1_cheb_coefs(double lmin, double lmax, int steps, T *c1, T *c2) {
 
 // The arguments of the one-launch coarse end of the velocity V-cycle from level l (l >= 1,
 // where the restricted right-hand side vanishes at Dirichlet nodes), or false when the
-// remaining levels do not fit it (too fine, too many, smoothing degree or LDS).
+// remaining levels do not fit it (too fine, too many or LDS).
 template <typename T>
-static bool tail_args(Mg &mg, int l, int degree, const T *b, T *x, int64_t ls, TailArgs<T> &a) {
+static bool tail_args(Mg &mg, int l, const T *b, T *x, int64_t ls, TailArgs<T> &a) {
   const int last = (int)mg.lv.size() - 1;   // the dense coarsest level
   const int nlev = last - l;
-  if (!mg.stencil || mg.comps != 2 || l < 1 || nlev < 1 || nlev > kTailMax || degree < 2 || degree > kTailDeg ||
-      mg.lv[l].n > kTailMaxN)
-    return false;
+  if (!mg.stencil || mg.comps != 2 || l < 1 || nlev < 1 || nlev > kTailMax || mg.lv[l].n > kTailMaxN) return false;
   a = TailArgs<T>{};
   a.nlev = nlev;
-  a.degree = degree;
   for (int k = 0; k < nlev; ++k) {
     const MgLevel &L = mg.lv[l + k];
     TailLevel<T> &t = a.lv[k];
     t.n = L.n;
     t.cf = afc<T>(L);
-    // the coefficients of cheb3_coefs on [lmax / 15, lmax]
-    const double lmax = L.lmax, lmin = L.lmax / 15.0;
-    const double theta = 0.5 * (lmax + lmin), delta = 0.5 * (lmax - lmin), sigma = theta / delta;
-    double rho = 1.0 / sigma;
-    t.s = (T)(1.0 / theta);
-    for (int j = 0; j + 1 < degree; ++j) {
-      const double rho1 = 1.0 / (2.0 * sigma - rho);
-      t.c1[j] = (T)(rho1 * rho);
-      t.c2[j] = (T)(2.0 * rho1 / delta);
-      rho = rho1;
-    }
+    const Cheb3Coef<T> cc = cheb3_coefs<T>(L.lmax / 15.0, L.lmax);
+    t.s = cc.s;
+    t.c1[0] = cc.c1a;
+    t.c2[0] = cc.c2a;
+    t.c1[1] = cc.c1b;
+    t.c2[1] = cc.c2b;
   }
   a.m = (int)mg.ncoarse;
   FSI_REQUIRE(a.m == 2 * (int)mg.lv[last].nodes, FSI_E_STATE, "coarsest level size");
@@ -423,7 +386,7 @@ static T *vcycle(Mg &mg, int l, LP<const T> b, hipStream_t s, Prof *prof = nullp
   const int64_t lc = (int64_t)mg.comps * C.nodes;
   if constexpr (W == 4) {   // the coarse end of the velocity cycle in one launch
     TailArgs<T> ta;
-    if (mg.tail && tail_args<T>(mg, l, degree, b.p, x, ls, ta)) {   // l >= 1: b has the level's stride
+    if (mg.tail && tail_args<T>(mg, l, b.p, x, ls, ta)) {   // l >= 1: b has the level's stride
       mg_tail<T>(ta, s, K);
       return x;
     }
@@ -1008,12 +971,10 @@ static MsBufs ms_bufs_fused(Ctx &c, double *x, int it) {
 // 4 us; beyond that the sum is a launch of its own.
 constexpr int kMsFoldParts = 4096;
 
-// The preconditioner can take the update and hand over r . z as tile and block sums when the velocity cycle of
-// its precision ends with the fused three-step launch on a matrix-free hierarchy of two or
-// more levels (the FP32 form for one system, on FP64 vectors).
-static bool tile_dot_ok(const Ctx &c, bool fp32) {
-  return (c.mgu.stencil || q2_cells(c)) && c.mgu.lv.size() > 1 && (fp32 ? c.mgu.degree32 : c.mgu.degree) == 3 &&
-         c.ms_dot.p;
+// The preconditioner can take the update and hand over r . z as tile and block sums when the velocity
+// cycle is matrix-free and has two or more levels.
+static bool tile_dot_ok(const Ctx &c) {
+  return (c.mgu.stencil || q2_cells(c)) && c.mgu.lv.size() > 1;
 }
 
 // A11 launches take the step of the recurrence at their head where beta^2 has at most this many parts
@@ -1063,7 +1024,7 @@ static void ms_tail(Ctx &c, const MsBufs &b, MinresState *st, int K, bool fold, 
   const int tiles = a11_tile_count(c.n);
   const bool fold_sum = tiles <= kMsFoldParts;
   constexpr bool f32 = std::is_same<TA, float>::value;
-  const bool dot_ok = tile_dot_ok(c, f32);
+  const bool dot_ok = tile_dot_ok(c);
   if (!dot_ok || !fold_sum) hipLaunchKernelGGL(k_ms_alfa, dim3(1, K), dim3(1024), 0, s, c.ms_part.p, tiles, st);
   if (dot_ok) {
     const int nb = post3_dot_count(c.n) + pres_dot_count(c);
@@ -1121,7 +1082,7 @@ static void minres_a11(Ctx &c, const double *const *b, double *const *xout, int 
   hipStream_t s = c.stream;
   const int64_t nf = 2 * c.N2 + c.Np;
   const bool fused = c.mgu.stencil || q2_cells(c);   // matrix-free FP64 A11
-  const bool in_place = fused && !tile_dot_ok(c, std::is_same<TA, float>::value);
+  const bool in_place = fused && !tile_dot_ok(c);
   FSI_REQUIRE(K >= 1 && K <= c.lanes, FSI_E_ARG, "more systems than inner lanes");
   FSI_REQUIRE(K == 1 || c.mgu.stencil, FSI_E_STATE, "several systems per inner solve need the matrix-free smoother");
   MinresState *st = (MinresState *)c.ms_state.p;
@@ -1811,10 +1772,9 @@ double inner_pressure_weight(Ctx &c) {
     const double det = d[0] * d[3] - d[1] * d[2];
     au += 0.25 * 0.5 * (d[0] + d[3]) / det;
   }
-  P1Table<double> mp, lp;
-  P1Table<float> f;
-  p1_tables(c.n, kTableMp, 0, mp, f);
-  p1_tables(c.n, kTableLp, 0, lp, f);
+  P1Table mp, lp;
+  p1_tables(c.n, kTableMp, 0, mp);
+  p1_tables(c.n, kTableLp, 0, lp);
   const double sp = c.nu * mp.dinv[4] + (c.rho / c.dt) * lp.dinv[4];
   FSI_REQUIRE(au > 0 && sp > 0, FSI_E_STATE, "non-positive diagonal scales");
   c.gi_wp = std::sqrt(au * sp);
@@ -1913,9 +1873,8 @@ static void residual64(Ctx &c, const double *b, const double *x, double *r) {
 }
 
 // The Gram-Schmidt reductions of one Arnoldi step for every system of a batch in one launch
-// each (lane = blockIdx.y): the same partition, order and arithmetic as multidot and
-// k_multiaxpy_sub on one system (red_blocks(n) chunks of the lane's own length), so each
-// system's numbers do not depend on the batch.
+// each (lane = blockIdx.y): the same partition, order and arithmetic as multidot on one system
+// (red_blocks(n) chunks of the lane's own length), so each system's numbers do not depend on the batch.
 struct ArnLane {
   const double *V;   // Krylov basis (k vectors at stride ldv, n when ldv is 0)
   const double *w;   // current vector (w for the dots, updated in place by the axpy)

@@ -668,6 +668,11 @@ bool pre3_restricts(int n, int K) {
   return n % 2 == 0 && n >= 4 && (n <= 64 || (n <= 256 && (int64_t)K * n * n <= 256 * 256));
 }
 
+// Several systems at once: the triangle pair only.  A single one takes the launch with the restriction on
+// every level of up to 256^2 cells, so the paper's pair never reaches the other forms of those sizes.
+template <typename C>
+constexpr bool kBatched = std::is_same<C, AfCoef<double>>::value || std::is_same<C, AfCoef<float>>::value;
+
 template <typename T, typename C>
 void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b, hipStream_t st, int K,
           const MsFold *fold, LP<T> bc) {
@@ -700,8 +705,14 @@ void pre3(int n, const C &cf, LP<T> b, LP<T> x, T s, T c1a, T c2a, T c1b, T c2b,
     if (fold) hipLaunchKernelGGL((k_pre3<T, C, LW, true, false>), grid, block, 0, st, a, tx, tiles, band);
     else hipLaunchKernelGGL((k_pre3<T, C, LW, false, false>), grid, block, 0, st, a, tx, tiles, band);
   };
-  if (n <= 256) go(std::integral_constant<int, kWave / 2>{});
-  else go(std::integral_constant<int, kWave>{});
+  if constexpr (kBatched<C>) {
+    if (n <= 256) {
+      go(std::integral_constant<int, kWave / 2>{});
+      FSI_CHECK_LAUNCH();
+      return;
+    }
+  }
+  go(std::integral_constant<int, kWave>{});
   FSI_CHECK_LAUNCH();
 }
 #define FSI_PRE3_INST(T, C) \
@@ -821,8 +832,14 @@ void resid_restrict(int nf, const C &cf, LP<const T> x, LP<const T> b, LP<T> bc,
     hipLaunchKernelGGL((k_resid_restrict<T, C, LW, Q>), dim3((unsigned)(band * kXcd), (unsigned)K), dim3(LW * kCellRows),
                        0, s, a, tx, tiles, band);
   };
-  if (nf >= kRestrictWideN) go(std::integral_constant<int, kWave>{}, std::integral_constant<int, 2>{});
-  else rows_width(nf, [&](auto lw) { go(lw, std::integral_constant<int, 1>{}); });
+  if constexpr (kBatched<C>) {
+    if (nf < kRestrictWideN) {
+      rows_width(nf, [&](auto lw) { go(lw, std::integral_constant<int, 1>{}); });
+      FSI_CHECK_LAUNCH();
+      return;
+    }
+  }
+  go(std::integral_constant<int, kWave>{}, std::integral_constant<int, 2>{});
   FSI_CHECK_LAUNCH();
 }
 #define FSI_RR_INST(T, C) \

@@ -184,7 +184,7 @@ class Workload:
         return dict(N2=n2, Np=np_, Ns=ns, Nt=tri.shape[0], N=2 * n2 + np_ + 4 * ns)
 
 
-# The five workloads (sizes and seeds) of the evaluation; see the design doc for the recipe.
+# The five workloads (sizes and seeds) of the evaluation.
 WORKLOADS = {
     # 32^2 fluid, disk R=0.2 at the centre with 216 triangles, block-diagonal, seed 0
     "disk32": Workload("disk32", 32, [Solid(6, (0.5, 0.5), 0.2)], dt=0.01, seed=0),
