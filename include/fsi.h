@@ -434,14 +434,15 @@ int fsi_export_lattice(int32_t n, double nu, double rdt, int32_t table, int32_t 
 
 /* Products inside the A11 preconditioner (both multigrid hierarchies and the pressure
  * mass solve): FSI_SMOOTH_STENCIL (default) applies them matrix-free on the structured
- * grid: A_f from four translation-invariant 2x2-block stencils (boundary rows identity,
- * boundary columns zero), L_p and M_p from 7-point stencils in nine position classes
+ * grid: A_f cell by cell from closed forms of its distinct entries (boundary rows identity,
+ * boundary columns zero), L_p and M_p from weights that follow from a node's position
  * (L_p: pinned node identity row, zero column), and the P2 / P1 prolongations and
- * restrictions from the nested refinement, all with the same element matrices and
- * interpolation weights as the assembled operators.  FSI_SMOOTH_CSR reads the assembled
- * matrices.  The same switch selects the matrix-free fluid rows of the FP64 operator
+ * restrictions from the nested refinement; the closed forms of A_f, B and the P2 weights are
+ * checked against the element matrices when a context is made.  FSI_SMOOTH_CSR reads the
+ * assembled matrices.  The same switch selects the matrix-free fluid rows of the FP64 operator
  * (A11 in the inner solves and fsi_apply_operator).  Both settings give the same results
- * up to the order of the sums. */
+ * up to the order of the sums.  The Q2 pair (fsi_create_q2) has one form of its cycles, matrix-free:
+ * it takes FSI_SMOOTH_CSR, which changes nothing, and refuses FSI_SMOOTH_STENCIL (FSI_E_STATE). */
 enum fsi_smoother { FSI_SMOOTH_CSR = 0, FSI_SMOOTH_STENCIL = 1 };
 int fsi_set_smoother(fsi_ctx *ctx, int kind);
 
@@ -449,9 +450,8 @@ int fsi_set_smoother(fsi_ctx *ctx, int kind);
  * inner MINRES steps as captured HIP graphs.  Default: off.  A graph keeps the pressure part
  * on the context's stream (without it, that part runs on a second stream beside the velocity
  * cycle) and the inner solve checks convergence every 2 steps (frozen steps past
- * convergence); with the coarse ends of both multigrid cycles in one launch each, the two
- * streams measured faster at every grid size.  The graph holds kernel nodes only; results
- * are the same as without it. */
+ * convergence); the two streams measured faster (FP64 step at 32^2 9.9 against 12.0 ms, at 128^2
+ * 17.9 against 22.6).  The graph holds kernel nodes only; results are the same as without it. */
 int fsi_set_graphs(fsi_ctx *ctx, int enable);
 
 /* When the inner MINRES solve learns that it has converged (without graphs).
@@ -462,9 +462,10 @@ int fsi_set_graphs(fsi_ctx *ctx, int enable);
  *  FSI_CHECK_LAGGED: the state of step k - 1 is looked at after step k has been enqueued, so the
  *    device does not wait for the host; the step enqueued past convergence is frozen by the
  *    device-side done flag (the same results, bitwise; one extra step of work per solve).
- *    Faster for one solve on an idle device (32^2-256^2: 4-15% per step), slower where other
- *    streams keep the device busy (the request loop of serve.py measured 141-147 against 151
- *    requests/s), where the extra step takes time from the other work.
+ *    Faster for one solve on an idle device (per step at 32^2, 64^2, 128^2 and 256^2: 4, 1, 5 and 2% in
+ *    FP64, 11, 2, 10 and 9% mixed; at 512^2 4 and 2% slower), not where other streams keep the device
+ *    busy and the extra step takes time from the other work (the request loop of serve.py: 175-186
+ *    against 179-186 requests/s, p99 411-546 against 346-460 ms).
  * Errors: FSI_E_ARG (unknown mode). */
 enum fsi_check_mode { FSI_CHECK_AUTO = 0, FSI_CHECK_EVERY_STEP = 1, FSI_CHECK_LAGGED = 2 };
 int fsi_set_inner_check(fsi_ctx *ctx, int mode);
@@ -472,18 +473,14 @@ int fsi_set_inner_check(fsi_ctx *ctx, int mode);
 /* Measurement of the dominant kernel, the finest-level Chebyshev smoothing on A_f
  * (d = c1 d + c2 D^{-1}(b - A_f x), y = x + d on the 2x2-block system): with the
  * structured-grid products (default) the launch that takes the post-smoothing steps at
- * once (three for the default degree 3, temporal blocking); with FSI_SMOOTH_CSR every
- * single-step launch.
+ * once (three, temporal blocking); with FSI_SMOOTH_CSR every single-step launch.
  * fsi_profile(ctx, 1) starts (and resets) timing every such launch with a pair of HIP
  * events on the context's stream; fsi_profile(ctx, 0) stops.  fsi_profile_read
  * synchronises and returns, for precision prec, the number of timed launches, their summed
  * duration in milliseconds and the algorithmic bytes one launch must move, with w = 8
- * (FP64) or 4 (FP32) bytes: structured form 6 w N2 for the default degrees 2 and 3 (x and
- * b read, y written, two components each: the first step has c1 = 0 and reads no d, and
- * the last direction is not stored when no single step follows; 8 w N2 when one does),
- * in FP32 with three steps (4 w + 16) N2 (y is stored straight into the FP64
- * preconditioner output); with three or more steps the launch also reads the coarse
- * correction, 2 w N2c (N2c = (n + 1)^2 nodes of the next level).  Inside the inner MINRES
+ * (FP64) or 4 (FP32) bytes: structured form (4 w + 16) N2 + 2 w N2c (x and b read, y written
+ * in FP64, in FP32 too straight into the FP64 preconditioner output, two components each; the
+ * coarse correction read, N2c = (n + 1)^2 nodes of the next level).  Inside the inner MINRES
  * the FP32 launch also reads the FP64 residual for its tile sums of r . z (16 N2 bytes,
  * not counted here: the figure is that of the smoothing itself); CSR form
  * nnz (4 w + 4) + N2 (4 + 14 w) + 4 (values and column indices once; per node the row

@@ -178,7 +178,7 @@ static int create_ctx(const fsi_fluid_desc *fluid, const fsi_solid_desc *solid, 
     std::fill(c.ms_word, c.ms_word + FSI_MAX_LANES, 0ull);
     FSI_HIP(hipHostGetDevicePointer((void **)&c.ms_word_dev, c.ms_word, 0));
     fsi::build_solid(c);
-    if (quads) {   // the assembled operators only: the matrix-free kernels are the triangle pair's
+    if (quads) {   // its operator rows are assembled, its cycles and inner products by cells
       fsi::build_fluid_q2(c);
       fsi::build_multigrid_q2(c);
     } else {
@@ -187,10 +187,9 @@ static int create_ctx(const fsi_fluid_desc *fluid, const fsi_solid_desc *solid, 
       c.mgu.stencil = c.mgp.stencil = true;
     }
     // graphs keep the preconditioner on one stream (the pressure chain no longer beside the
-    // velocity cycle) and check convergence every second MINRES step: with the coarse ends of
-    // both cycles in one launch each they measured slower than the two streams at every size
-    // (32^2 27.1 / 23.3 ms, 128^2 54.6 / 43.8 ms per FP64 step, batches of 8 likewise), so
-    // they are off unless fsi_set_graphs asks for them
+    // velocity cycle), take the scalar step in a launch of its own and check convergence every second
+    // MINRES step: slower than the two streams (32^2 12.0 / 9.9 ms, 128^2 22.6 / 17.9 ms per FP64 step),
+    // so they are off unless fsi_set_graphs asks for them
     c.use_graphs = false;
     fsi::make_shadow(c.Af, c.stream);
     fsi::make_shadow(c.B, c.stream);

@@ -37,9 +37,10 @@ static int64_t common_stride(std::initializer_list<std::pair<const void *, int64
 
 // ---------------------------------------------------------------- smoothing, cell by cell
 // The Chebyshev steps of a velocity level and its residual with one thread per cell
-// (cell_products, afcell.h).  A block of 8 waves owns 8 rows of 64 cells: wave w is cell row w of
-// the region, lane l cell column l, in every pass, so a thread's right-hand side, directions and
-// values stay in its registers from one step to the next.  x is staged in LDS as two planes of
+// (cell_products, afcell.h).  A block owns a region of 8 rows of 64, 32 or 16 cells (16 x 16 with the
+// restriction in the first launch): a thread is the same cell, row w and column lane of the region, in
+// every pass, so its right-hand side, directions and values stay in its registers from one step to the
+// next.  x is staged in LDS as two planes of
 // even and odd lattice columns, [parity][row][column / 2], with both components of a node side
 // by side, so that the lanes of a wave read consecutive 16-byte (FP32: 8-byte) words; each step
 // writes its values over the ones before it between two barriers.  Dirichlet and out-of-lattice
@@ -47,13 +48,13 @@ static int64_t common_stride(std::initializer_list<std::pair<const void *, int64
 // device memory.
 //
 // On coarse levels a launch is bound by the latency of its dependent passes, on fine ones by
-// memory (pre3: 134 MB at 1024^2, 3.6 TB/s of the 4.3 that a copy reaches) and, in post3, by the
-// FP64 issue of the steps it recomputes on the halo.  Against one thread per node with the
-// coefficients loaded through the scalar cache in every pass (kernel times in a step, FP64):
-//   1024^2  pre-smoothing 79.7 -> 37.6 us, residual and restriction 51.2 -> 32.7, post-smoothing
-//           139 -> 118 (beside the pressure part on the other stream)
-//   512^2   28.5 -> 15.2, 18.4 -> 11.5, 41.5 -> 24.4
-//   32^2    8.6 -> 6.2, 7.9 -> 4.8, 12.0 -> 8.1
+// memory (pre3 with the MINRES update: 294 MB at 1024^2, 3.5 TB/s of the 4.3 that a copy reaches) and,
+// in post3, by the FP64 issue of the steps it recomputes on the halo.  Against one thread per node with
+// the coefficients loaded through the scalar cache in every pass (kernel times in a step in us, FP64):
+//   1024^2, finest level  pre-smoothing 79.7 -> 37.6 (84 with the update, launches of 75 before),
+//                         residual and restriction 51.2 -> 36.0, post-smoothing 139 -> 92.7
+//   512^2 level           28.5 -> 15.4, 18.4 -> 11.8, 41.5 -> 25.0
+//   32^2, finest level    8.6 and 7.9 -> 8.0 in one launch with the update, 12.0 -> 6.2
 constexpr int kCellRows = 8;                          // cell rows of a region
 constexpr int kCellH = 2 * kCellRows + 3;             // its staged rows: a halo of one cell
 // the names of a kernel on regions of LW cells per row
@@ -79,7 +80,8 @@ template <int LW> constexpr int kRRTile = (LW - 3) / 2;
 //   smoothing      32^2 (FP64, in MINRES) 8.5 and 7.5 / 7.1 and 6.5 / 6.2 and 6.0; 64^2 level 6.1 and 8.2
 //                  / 5.8 and 6.2 / 5.1 and 5.9; 256^2 (FP32) 9.3 and 10.5 / 8.6 and 9.4, 512^2 in FP64 23
 //                  and 27 at 64, where the halo's recomputation begins to count
-//   restriction    32^2 4.8 / 4.2 / 4.5 (as its own launch: batches, by pre3_restricts)
+//   restriction    4.8 / 4.2 / 4.5 on 32^2 cells (where it is a launch of its own, by pre3_restricts, a
+//                  level has 65^2 cells or more)
 //   A11 rows       32^2 8.0 / 7.8 / 8.9 (two waves sum beta^2), 256^2 10.2 / 11.4
 template <typename F>
 static void smooth_width(int n, F f) {   // post-smoothing
@@ -258,9 +260,9 @@ struct PreArgs {
 // MS: in MINRES b is made here, q = y1 - alfa s r2, from the parts of alfa that the A11 launch
 // left: every block sums them (in the same order) while its loads of y1 and r2 are in flight, and
 // blocks past the tiles update the pressure part.  Two launches and one pass over three vectors
-// less per inner step: 9 us against 6.2 + 2.6 + 1.9 and two gaps at 32^2, 83 against 37 + 38 + 4 and
-// two gaps at 1024^2 (FP64); 35 at 768^2 with FP32 arithmetic, where the FP32 copy of q is written
-// here too.
+// less per inner step, without the restriction: 9 us against 6.2 + 2.6 + 1.9 and two gaps at 32^2, 84
+// against 37 + 38 + 4 and two gaps at 1024^2 (FP64); 72 at 1024^2 with FP32 arithmetic, where the FP32
+// copy of q is written here too.
 //
 // RR: the residual and its restriction too, in regions of 16 x 16 cells: x2 is right on the inner 14 x 14,
 // the residual on 12 x 12, which gives 4 x 4 coarse cells, so 8 x 8 of the region's cells are the tile's.
@@ -661,9 +663,11 @@ static void cell_launch_checks(int n, int K) {
 
 // RR up to 256^2 cells in all lanes together, where its recomputation still fits beside the idle part of
 // the chip.  Whole steps with / without it: 32^2 12.6 / 13.9 ms, 96^2 (block-diagonal) 62.7 / 69.0, 256^2
-// mixed 33.3 / 36.2, 4 x 128^2 30.6 / 30.3, 8 x 64^2 mixed 23.9 / 26.1; beyond the line 2 x 256^2 47.7 /
-// 46.6, 5 x 192^2 63.6 / 61.3, 512^2 32.8 / 31.2.  Up to 64^2 with any number of lanes: there the first
-// launch without it had other block sizes, and a system's sum of alfa may not depend on its company.
+// mixed 33.3 / 36.2, 8 x 64^2 mixed 23.9 / 26.1; on the line 4 x 128^2 25.0 / 24.7 in FP64 and 21.7 / 22.4
+// mixed; beyond it 2 x 256^2 47.7 / 46.6, 5 x 192^2 63.6 / 61.3, 512^2 32.8 / 31.2.  Up to 64^2 with any
+// number of lanes, where the two are alike (17 x 64^2 30.1-31.2 / 31.3 ms, 32 x 64^2 46.0-47.9 / 47.0, mixed
+// 40.1-41.5 / 41.7) and one form is enough.  A system's sums do not depend on the choice: both forms have
+// blocks of 256 threads up to 256^2.
 bool pre3_restricts(int n, int K) {
   return n % 2 == 0 && n >= 4 && (n <= 64 || (n <= 256 && (int64_t)K * n * n <= 256 * 256));
 }
@@ -760,8 +764,8 @@ FSI_POST3_INST(float, double, Q2Coef<float>)
 // under a coarse tile is computed as in the smoothing launches and kept in LDS for the
 // restriction sums, so r never goes to HBM (reads x and b, writes bc).  A coarse node gathers the
 // interior fine nodes within 3 of its place, so C coarse cells need the residual of 2 C + 3 fine
-// cells: a block takes Q rows of fine cells per wave, 30 coarse columns and (8 Q - 3) / 2 coarse
-// rows.  Q = 2 recomputes less (15 rows for 6 coarse rows, against 7 for 2) and is taken where
+// cells: a block takes Q rows of fine cells per row of its region, 30 coarse columns (14 where it is 32
+// cells wide) and (8 Q - 3) / 2 coarse rows.  Q = 2 recomputes less (15 rows for 6 coarse rows, against 7 for 2) and is taken where
 // that leaves the chip enough blocks; Q = 1 shortens the two dependent passes of a block.
 // The restriction runs by coarse classes, one per wave pass, with compile-time weights.
 
@@ -857,10 +861,9 @@ FSI_RR_INST(float, Q2Coef<float>)
 // thread reads anyway.  No row is computed twice: a block of 8 waves owns 8 x 64 cells.
 //
 // Bound by memory where the vectors leave the caches: the form in MINRES reads x and r1 and writes
-// y and v, 302 MB at
-// 1024^2 in 59 us, more than a copy from device memory reaches, since part of them is still in the
-// last-level cache.  One thread per node with the coefficients of its class read through the scalar
-// cache took 84 us, and 8.0 against 6.6 at 32^2.
+// y and v, 302 MB at 1024^2 in 59 us, more than a copy from device memory reaches, since part of them is
+// still in the last-level cache.  One thread per node with the coefficients of its class read through the
+// scalar cache took 84 us, and 8.0 at 32^2 against 6.2 (7.9 with the step before it at the head).
 template <typename C>
 struct A11Args {
   int n;
