@@ -1,8 +1,9 @@
-"""The velocity cycle's launches by cells (regions of 64, 32 or 16 x 8 cells by the size of the grid:
-pre-smoothing tiles of 62, 30 or 14 x 6 cells, post-smoothing 60, 28 or 12 x 4, residual and restriction
-30 or 14 x 2 coarse cells and, from 256^2 on, 30 x 6) at grids where their tiles end: ragged last tiles
-(24, 36, 48, 80, 112, 160), one cell past a tile (60, 120) and both sides of the rules that choose the
-width; and the pressure part's (descent 29 x 5 coarse nodes, ascent 60 x 12, from 512^2 on 29 x 13 and
+"""The velocity cycle's launches by cells at grids where their tiles end.  A single system takes, on levels of
+up to 256^2 cells, the first launch with the restriction (regions of 16 x 16 cells, tiles of 8 x 8 cells
+and 4 x 4 coarse ones) and post-smoothing tiles of 60, 28 or 12 x 4 cells by the size of the grid; above
+(320, 512) pre-smoothing tiles of 62 x 6 and a restriction launch of 30 x 6 coarse cells.  Ragged last tiles
+(24, 36, 48, 80, 112, 160, 320), one cell past a tile (60, 120) and both sides of the rules that choose
+the width; and the pressure part's (descent 29 x 5 coarse nodes, ascent 60 x 12, from 512^2 on 29 x 13 and
 60 x 28; the one-launch coarse end from 64^2 down, with the output where it starts on the finest
 level): a grid with one level (5), a coarse end alone (6 to 64, dense levels of 16 to 256 unknowns), one
 and more levels above it.  The matrix-free preconditioner equals the one on the

@@ -1,6 +1,7 @@
-"""The paper's pair cell by cell: velocity cycle (tiles of 62, 30 or 14 x 6, 60, 28 or 12 x 4 and 30 or
-14 x 2 coarse cells, by the size of the grid) and pressure cycle (60 x 4) at grids whose last tiles
-are ragged or one cell past a tile (120, 72, 24), with one and several levels above the dense one.
+"""The paper's pair cell by cell: velocity cycle (first launch with the restriction, tiles of 8 x 8 cells,
+and post-smoothing tiles of 28 or 12 x 4 by the size of the grid; the forms above 256^2 cells are
+test_gpu_width_rules.py's) and pressure cycle (60 x 4) at grids whose last tiles are ragged or one cell
+past a tile (120, 72, 24), with one and several levels above the dense one.
 
  * The preconditioner M = diag(V, S~^{-1}) is linear and symmetric: a cycle with equal smoothing on both
    sides and the transposed transfer is, and one with a wrong entry, weight or tile edge is not.  One
